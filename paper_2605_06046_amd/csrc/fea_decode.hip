@@ -1,5 +1,5 @@
 // fea_decode_attention: argument checks, workspace carving and the three launches
-// (plan, KV sweep, merge), or the one launch that small batches take.  No device memory is allocated here and nothing
+// (plan, KV sweep, merge), or the one or two (sweep, merge) of batches that need no plan.  No device memory is allocated here and nothing
 // synchronises except fea_decode_plan_info.
 #include <hip/hip_runtime.h>
 
@@ -29,19 +29,19 @@ static int env_int(const char* name, int dflt) {
 // second thread sets) cannot switch kernels or move the workspace layout between the
 // sizing call and the attention call.  What tests need to steer is in fea_attn_params.
 struct Knobs {
-    int force_generic, sweep_grid, spare_waves, min_piece, min_run, w32, w64, no_fast_shared, w_team, w_team2, team_fixed;
+    int force_generic, sweep_grid, spare_waves, min_piece, min_run, w32, w64, no_fast_shared, w_team, w_team2, team_fixed, direct_pieces;
 };
 static const Knobs& knobs() {
     static const Knobs k = {env_int("FEA_FORCE_GENERIC", 0), env_int("FEA_SWEEP_GRID", 0), env_int("FEA_SPARE_WAVES", 16),
                             env_int("FEA_MIN_PIECE", 4),     env_int("FEA_MIN_RUN", 2),    env_int("FEA_W32", 20),
                             env_int("FEA_W64", 24), env_int("FEA_NO_FAST_SHARED", 0), env_int("FEA_WTEAM", 12),
-                            env_int("FEA_WTEAM2", 12), env_int("FEA_TEAM_FIXED", 40)};
+                            env_int("FEA_WTEAM2", 12), env_int("FEA_TEAM_FIXED", 40), env_int("FEA_DIRECT_PIECES", 0)};
     return k;
 }
 
 struct Resolved {
     int variant;      // 0 generic, 1 MFMA
-    int fused;        // the batch is small enough for the one-launch kernel (no plan, sweep and merge)
+    int direct;       // pieces per history of the kernel that needs no plan (1: it writes the output, more: they are merged); 0: plan, sweep and merge
     int G, mpt, grouping, split_user, grid;
     int pre, pre_grid;   // leaders and common runs on many workgroups first (large tables)
     int merge_by_rows;   // very many output rows: the merge takes several rows per wave
@@ -70,38 +70,48 @@ static int cu_count() {
     return n;
 }
 
-// Whether the one-launch kernel is expected to beat plan + sweep + merge.  Both sides are estimates in
-// microseconds fitted to measurements (1 to 128 requests, 128 to 4096 tokens, bf16 and float32, head dims 64 to
-// 256, query groups of 4 to 65).  The one launch pays, per round of workgroups on the chip and per pass of four
-// query heads, a fixed part (the chain of dependent loads, the folds, the barrier) plus vector-unit work per
-// token in proportion to the head dim.  The three launches cost their start-up and the planner's one workgroup,
-// then the KV bytes of the requests' own columns on the matrix-core path; the vector-unit sweep costs far more
-// to start with, and from some hundred thousand (query row, token) pairs on in proportion to them.  The one
-// launch is taken where it wins by a tenth (more where its workgroups need several rounds on the chip).
-static bool fused_pays(const fea_attn_params* p, int64_t B, int64_t stride, int variant) {
+// The kernel that needs no plan (fea_direct.hip) reads every request's whole history: how many workgroups it has
+// without cutting histories, and how many tiles a wave of it sweeps one after the other.
+static int64_t direct_groups(const fea_attn_params* p, int64_t B) {
+    return B * p->num_kv_heads * ((p->num_q_heads / p->num_kv_heads + 15) / 16);
+}
+static int64_t direct_rounds(const fea_attn_params* p, int64_t stride) {
+    const int64_t tile_blocks = p->dtype == FEA_DTYPE_F32 && p->head_dim >= 128 ? 1 : 2, waves = p->head_dim == 256 ? 4 : 8;
+    return ((stride + tile_blocks - 1) / tile_blocks + waves - 1) / waves;
+}
+
+// Pieces a history is cut into there.  Workgroups that leave most of the chip idle are worth cutting, up to one per
+// compute unit; the merge of the pieces is a launch of its own (3.5 to 4 us), a round of a wave's tiles takes 1 us
+// (bf16, head_dim 64) to 2.7 us (float32, head_dim 128 and 256), so it has to save three rounds.  Measured: float32
+// 32/8/128, 4 requests of 2048 tokens 51.6 us whole, 33.0 / 22.1 / 18.6 / 20.3 in 2 / 4 / 8 / 16 pieces; bf16 32/8/128,
+// 16 requests (128 workgroups) of 512 tokens 10.0 whole, 12.3 in 2 (2 rounds: not cut).
+static int64_t direct_pieces(const fea_attn_params* p, int64_t B, int64_t stride) {
+    const int64_t groups = direct_groups(p, B), rounds = direct_rounds(p, stride);
+    if (groups <= 0 || 2 * groups > cu_count()) return 1;
+    const int64_t n = std::min<int64_t>(cu_count() / groups, rounds);
+    return rounds - (rounds + n - 1) / n >= 3 ? n : 1;
+}
+
+// Whether it is expected to beat plan + sweep + merge.  It reads what requests share once per request (at 5 to 5.6 TB/s
+// whether from L2 or HBM), which the host cannot know; so it is taken where even a batch that shares everything would
+// lose more to the three launches than to the reading: on the matrix-core path up to 64 MB of KV histories (measured,
+// nothing shared: 8 requests of 1024 tokens 13.5 against 24.8 us, 32 of 1024 (134 MB) 27.0 against 44.5).  The
+// vector-unit sweep costs 26 to 120 us to start with, and from some hundred thousand (query row, token) pairs on time
+// in proportion to them (fitted to 1 to 128 requests, 128 to 4096 tokens, head dims 64 to 256, query groups of 4 to 65).
+static bool direct_pays(const fea_attn_params* p, int64_t B, int64_t stride, int variant) {
     const bool f32 = p->dtype == FEA_DTYPE_F32;
-    const int64_t rounds = (B * p->num_kv_heads + cu_count() - 1) / cu_count();
-    const int per_pass = f32 && p->num_q_heads / p->num_kv_heads > 4 ? 8 : 4;   // query heads the kernel takes per pass
-    const int64_t passes = (p->num_q_heads / p->num_kv_heads + per_pass - 1) / per_pass;
+    const int64_t row_tiles = (p->num_q_heads / p->num_kv_heads + 15) / 16;
     const double tokens = (double)stride * kBlock, dd = p->head_dim / 64.0;
-    // (passes of one query group run side by side on 2, 4 or 8 sets of the workgroup's waves: their fixed part is
-    // paid once per round of passes, their work per token adds up as if they ran one after the other)
-    int64_t sets = 1;
-    while (sets < 8 && sets < passes) sets <<= 1;
-    const int64_t seq = (passes + sets - 1) / sets;
-    const double fused_us = 2.4 + (double)rounds * ((double)seq * 6.0 + (double)(seq * sets) * (f32 ? 0.0165 : 0.0096) *
-                                                                         (per_pass == 8 ? 1.7 : 1.0) * dd * tokens);
-    double planned_us;
-    if (variant == 1) {
-        planned_us = (B < 2 ? 22.0 : B < 16 ? 27.0 : B <= 64 ? 31.0 : 35.0) + (p->head_dim == 256 ? 4.0 : 0.0) +
-                     (0.03 + 0.003 * (double)B) * (double)stride * (p->num_kv_heads * p->head_dim / 1024.0);
-    } else {
-        const double G = (double)(p->num_q_heads / p->num_kv_heads);   // (the vector sweep passes over its tokens once per 4 or 16 stacked rows)
-        const double base = B < 4 ? 20.0 + 1.5 * G : std::min(30.0 + 4.0 * G, 120.0);
-        planned_us = (B < 16 ? base : std::max(94.0, base)) * (p->head_dim >= 128 ? 1.4 : 1.0) +
-                     (f32 ? 0.027e-3 : 0.0175e-3) * std::pow(dd, 1.6) * (double)(B * p->num_q_heads) * tokens;
-    }
-    return (1.1 + 0.05 * (double)(rounds - 1)) * fused_us < planned_us;   // (several rounds of workgroups take longer than their sum)
+    const double bytes = (double)B * tokens * p->num_kv_heads * p->head_dim * (f32 ? 8.0 : 4.0) * (double)row_tiles;
+    if (variant == 1) return bytes <= 64e6;
+    const int64_t pieces = direct_pieces(p, B, stride);
+    const double serial_us = 2.7 * (double)((direct_rounds(p, stride) + pieces - 1) / pieces);   // one workgroup's tiles, a round after the other
+    const double direct_us = 7.0 + (pieces > 1 ? 4.0 : 0.0) + std::max(serial_us, bytes / 5.0e6);
+    const double G = (double)(p->num_q_heads / p->num_kv_heads);   // (the vector sweep passes over its tokens once per 4 or 16 stacked rows)
+    const double base = B < 4 ? 20.0 + 1.5 * G : std::min(30.0 + 4.0 * G, 120.0);
+    const double planned_us = (B < 16 ? base : std::max(94.0, base)) * (p->head_dim >= 128 ? 1.4 : 1.0) +
+                              (f32 ? 0.027e-3 : 0.0175e-3) * std::pow(dd, 1.6) * (double)(B * p->num_q_heads) * tokens;
+    return 1.1 * direct_us < planned_us;
 }
 
 static int32_t check_params(const fea_attn_params* p, const char* who) {
@@ -136,8 +146,8 @@ static int32_t resolve(const fea_attn_params* p, int32_t B, int32_t stride, Reso
     const bool mfma_ok = p->dtype == FEA_DTYPE_BF16 && (p->head_dim == 128 || p->head_dim == 64 || p->head_dim == 256) &&
                          r.G <= (p->head_dim == 256 ? 32 : 64);
     r.variant = (mfma_ok && !kn.force_generic) ? 1 : 0;
-    // One launch instead of three where that is estimated to be faster; an explicit bound on the row length stands alone.
-    r.fused = p->fused_max < 0 ? 0 : p->fused_max > 0 ? (stride <= p->fused_max) : fused_pays(p, B, stride, r.variant);
+    // No plan where that is estimated to be faster; an explicit bound on the row length stands alone.
+    const bool direct = p->fused_max < 0 ? false : p->fused_max > 0 ? (stride <= p->fused_max) : direct_pays(p, B, stride, r.variant);
     // requests per row tile of a shared run: 64 query rows per work item, 32 on the matrix-core path at head_dim 256
     // (a wave's accumulation registers hold O for 32 rows of 256 dims)
     const int tile_rows = (r.variant == 1 && p->head_dim == 256) ? 32 : kTileRows;
@@ -195,6 +205,7 @@ static int32_t resolve(const fea_attn_params* p, int32_t B, int32_t stride, Reso
     l.total = off;
     l.max_items = (int32_t)max_items;
     l.max_rows = (int32_t)max_rows;
+    r.direct = direct ? (int)std::max<int64_t>(1, std::min<int64_t>(kn.direct_pieces > 0 ? kn.direct_pieces : direct_pieces(p, B, stride), max_rows / std::max<int64_t>(1, rows))) : 0;
     return FEA_OK;
 }
 
@@ -251,9 +262,9 @@ int32_t decode_impl(const fea_attn_params* p, const void* q, const void* k_cache
         unsigned char mask = 0;
         for (int k = 0; k < 3; ++k) {
             if (g_prof_which >= 0 && g_prof_which != k) continue;
-            if (k == 0 && ((p->flags & FEA_FLAG_REUSE_PLAN) || (r.fused && !plan_only))) continue;
+            if (k == 0 && ((p->flags & FEA_FLAG_REUSE_PLAN) || (r.direct && !plan_only))) continue;
             if (k > 0 && plan_only) continue;
-            if (k == 2 && r.fused) continue;
+            if (k == 2 && r.direct == 1) continue;
             where[k].ev_start = ev[2 * k];
             where[k].ev_stop = ev[2 * k + 1];
             if (k == 0) { where[0].ev_mid[0] = ev[6]; where[0].ev_mid[1] = ev[7]; }
@@ -263,7 +274,7 @@ int32_t decode_impl(const fea_attn_params* p, const void* q, const void* k_cache
         ++g_prof_calls;
     }
     if (prof_lock.owns_lock()) prof_lock.unlock();
-    if (!(p->flags & FEA_FLAG_REUSE_PLAN) && (plan_only || !r.fused)) {   // a new plan, or the one in the workspace stretched to the lengths of now
+    if (!(p->flags & FEA_FLAG_REUSE_PLAN) && (plan_only || !r.direct)) {   // a new plan, or the one in the workspace stretched to the lengths of now
         PlanArgs pa;
         std::memset(&pa, 0, sizeof pa);
         pa.bt = block_tables;
@@ -309,8 +320,9 @@ int32_t decode_impl(const fea_attn_params* p, const void* q, const void* k_cache
     sa.G = r.G;
     sa.mpt = r.mpt;
     sa.fast_shared = (p->head_dim == 128 && (int64_t)B * p->num_q_heads < (1 << 23) && !knobs().no_fast_shared) ? 1 : 0;
-    if (r.fused) {
-        launch_decode_small(sa, p->dtype, p->head_dim, where[1]);
+    if (r.direct) {
+        launch_decode_direct(sa, p->dtype, p->head_dim, r.direct, where[1]);
+        if (r.direct > 1) launch_merge(sa, p->dtype, p->head_dim, r.merge_by_rows != 0, where[2]);
     } else {
         if (r.variant == 1) launch_sweep_mfma(sa, p->head_dim, r.grid, where[1]);
         else launch_sweep_generic(sa, p->dtype, p->head_dim, r.grid, where[1]);

@@ -1,0 +1,422 @@
+// Decode attention without a plan: out[i,h,:] = softmax(q K^T * scale) V (Section 2.1) for batches whose
+// histories are so short, or so few, that detecting aliases, cutting the work and merging pieces would cost
+// more than it saves.  A block that several requests alias is read once per request, out of L2 after the
+// first (workgroups are numbered so that, with 8 KV heads, those of one KV head share an XCD).
+//
+// One workgroup per (request, row tile of 16 query heads, KV head) and, where these are too few to fill the
+// chip, per piece of the history: the pieces take the request's tiles in turn and leave partial rows for
+// merge_kernel.  A wave takes every (waves x pieces)-th tile of 32 tokens (16 for float32 at head_dim 256),
+// each on the matrix cores, straight from global memory into the operand registers:
+//     S^T = K Q^T     lane (n, kg) = (lane % 16, lane / 16) holds K rows as 16-byte chunks 4 j + kg of token
+//                     row n, and q's chunks alike: any order of the head dims serves, as long as both agree
+//     O^T += V^T P^T  the scores' accumulator layout (head n, tokens 4 kg + r) is the B operand as it stands;
+//                     V is read as whole token rows 4 kg + r.  float32 (16x16x4 products, one k-slot per lane
+//                     group): row element 4 n + i of the A operand of product i, no data movement; bfloat16
+//                     (16x16x32): an 8x8 transpose in registers.
+// Everything is float32 on the way: float32 caches use the float32 matrix instructions, and with bfloat16
+// caches the softmax weights enter the second product as the sum of two bfloat16 numbers (the weight rounded,
+// and what that left over: 2^-17 of the weight), the denominator as unrounded float32.
+//
+// Bound: latency (the chain length, table row and q -> K -> V -> fold over the waves) for short histories, 7 to 8 us
+// in all; then memory, at 5.0 to 5.9 TB/s where the chip is full; with float32 and few workgroups the matrix cores'
+// float32 rate (a block of 16 tokens is 64 instructions of 32 cycles at head_dim 128, whatever part of the 16 query
+// rows is real).  Measured against the vector-unit kernel it replaces: float32 8/2/64, 4 requests of 320 tokens
+// 11.6 -> 9.1 us a call; float32 32/8/128, 16 requests of 1152 to 2048 tokens 78.7 -> 35.0; against plan, sweep
+// and merge: bf16 28/4/128, 8 requests of 90 to 700 tokens 23.6 -> 9.1.
+#include <hip/hip_runtime.h>
+#include <hip/hip_ext.h>
+
+#include "../../include/fea.h"
+#include "fea_plan.h"
+
+namespace fea {
+namespace {
+
+typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+struct bf16_t { uint16_t bits; };
+
+__device__ __forceinline__ u32x4 ld16(const void* p) { return *reinterpret_cast<const u32x4*>(p); }
+__device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
+
+__device__ __forceinline__ uint32_t bf16_rne(float v) {
+    uint32_t u = __float_as_uint(v);
+    if ((u & 0x7FFFFFFFu) > 0x7F800000u) return 0x7FC0u;
+    return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
+}
+
+// 16 bytes of a cache row hold EPC elements; a lane's registers of one tile, and the two products.
+template <typename T, int D> struct Tile;
+
+template <int D> struct Tile<float, D> {
+    static constexpr int TB = D >= 128 ? 1 : 2;            // blocks per tile
+    static constexpr int KC = D / 16;                      // chunks of a K row per lane
+    static constexpr int VH = D >= 64 ? D / 64 : 1;        // chunks of a V row per lane
+    static constexpr int NI = 4 * VH;                      // output products (head_dim 32: half of their rows count)
+    static constexpr int ES = 4;
+    f32x4 k[TB][KC], v[TB][4][VH], q[KC];
+
+    __device__ __forceinline__ void load_q(const char* row, int kg, bool live) {
+#pragma unroll
+        for (int j = 0; j < KC; ++j) q[j] = live ? *reinterpret_cast<const f32x4*>(row + (4 * j + kg) * 16) : f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    __device__ __forceinline__ void load_k(int b, const char* blk, int n, int kg) {
+#pragma unroll
+        for (int j = 0; j < KC; ++j) k[b][j] = *reinterpret_cast<const f32x4*>(blk + (uint32_t)(n * (D * 4) + kg * 16 + j * 64));
+    }
+    __device__ __forceinline__ void load_v(int b, const char* blk, int n, int kg) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int h = 0; h < VH; ++h)
+                v[b][r][h] = *reinterpret_cast<const f32x4*>(blk + (uint32_t)((4 * kg + r) * (D * 4) + (D >= 64 ? n : n & 7) * 16 + h * 256));
+    }
+    __device__ __forceinline__ void zero_v(int b, int r) {
+#pragma unroll
+        for (int h = 0; h < VH; ++h) v[b][r][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    __device__ __forceinline__ void scores(f32x4 (&s)[TB]) {
+        // Partial sums of 8 products, added up in pairs: a single chain over the head dims would be one rounding after
+        // another, which doubles the error of the scores.
+        constexpr int GC = KC < 4 ? KC : 4, Y = D == 256 ? 1 : GC / 2;    // chunks taken together, partial sums over them (head_dim 256: 16 products each, 8 spill registers)
+#pragma unroll
+        for (int b = 0; b < TB; ++b)
+#pragma unroll
+            for (int j0 = 0; j0 < KC; j0 += GC) {
+                f32x4 c[Y][4];
+#pragma unroll
+                for (int x = 0; x < GC / Y; ++x)
+#pragma unroll
+                    for (int y = 0; y < Y; ++y)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            c[y][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(k[b][j0 + x * Y + y][e], q[j0 + x * Y + y][e],
+                                                                           x == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : c[y][e], 0, 0, 0);
+                if constexpr (Y == 2) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) c[0][e] += c[1][e];
+                }
+                const f32x4 part = (c[0][0] + c[0][1]) + (c[0][2] + c[0][3]);
+                s[b] = j0 == 0 ? part : s[b] + part;
+            }
+    }
+    __device__ __forceinline__ void accumulate(const float (&p)[TB * 4], f32x4 (&o)[NI]) {
+        // The sums over a block start at zero and are added to the running ones: a short chain of products, and a chain
+        // of one addition per block (the error grows with the length of a chain).
+#pragma unroll
+        for (int b = 0; b < TB; ++b)
+#pragma unroll
+            for (int h = 0; h < VH; ++h) {
+                f32x4 c[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        c[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[b][r][h][e], p[4 * b + r], r == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : c[e], 0, 0, 0);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[4 * h + e] += c[e];
+            }
+    }
+    // product i = 4 h + e, output row m = 4 kg + r: dim 64 h + 4 m + e
+    __device__ __forceinline__ static void to_lds(float* row, const f32x4 (&o)[NI], int kg) {
+#pragma unroll
+        for (int h = 0; h < VH; ++h)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (D >= 64 || kg < 2)
+                    *reinterpret_cast<f32x4*>(row + 64 * h + 4 * (4 * kg + r)) = f32x4{o[4 * h][r], o[4 * h + 1][r], o[4 * h + 2][r], o[4 * h + 3][r]};
+    }
+};
+
+template <int D> struct Tile<bf16_t, D> {
+    static constexpr int TB = 2;
+    static constexpr int KC = D / 32;
+    static constexpr int VH = D == 256 ? 2 : 1;
+    static constexpr int NI = D / 16;
+    static constexpr int ES = 2;
+    u32x4 k[TB][KC], v[TB][4][VH], q[KC];
+
+    __device__ __forceinline__ void load_q(const char* row, int kg, bool live) {
+#pragma unroll
+        for (int j = 0; j < KC; ++j) q[j] = live ? ld16(row + (4 * j + kg) * 16) : u32x4{0u, 0u, 0u, 0u};
+    }
+    __device__ __forceinline__ void load_k(int b, const char* blk, int n, int kg) {
+#pragma unroll
+        for (int j = 0; j < KC; ++j) k[b][j] = ld16(blk + (uint32_t)(n * (D * 2) + kg * 16 + j * 64));
+    }
+    __device__ __forceinline__ void load_v(int b, const char* blk, int n, int kg) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int h = 0; h < VH; ++h) v[b][r][h] = ld16(blk + (uint32_t)((4 * kg + r) * (D * 2) + (D >= 128 ? n : n & 7) * 16 + h * 256));
+    }
+    __device__ __forceinline__ void zero_v(int b, int r) {
+#pragma unroll
+        for (int h = 0; h < VH; ++h) v[b][r][h] = u32x4{0u, 0u, 0u, 0u};
+    }
+    __device__ __forceinline__ void scores(f32x4 (&s)[TB]) {
+#pragma unroll
+        for (int b = 0; b < TB; ++b) s[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < KC; ++j)
+#pragma unroll
+            for (int b = 0; b < TB; ++b)
+                s[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, k[b][j]), __builtin_bit_cast(bf16x8, q[j]), s[b], 0, 0, 0);
+    }
+    __device__ __forceinline__ void accumulate(const float (&p)[TB * 4], f32x4 (&o)[NI], int n) {
+        bf16x8 hi, lo;
+#pragma unroll
+        for (int x = 0; x < 8; ++x) {
+            hi[x] = (__bf16)p[x];
+            lo[x] = (__bf16)(p[x] - (float)hi[x]);
+        }
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            u32x4 t;
+            if constexpr (D >= 128) {
+                const int h = i >> 3, e = i & 7;
+                const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    const int j0 = 2 * w, j1 = 2 * w + 1;
+                    t[w] = __builtin_amdgcn_perm(v[j1 >> 2][j1 & 3][h][e >> 1], v[j0 >> 2][j0 & 3][h][e >> 1], sel);
+                }
+            } else {
+                // lanes n and n + 8 hold the same chunk: lane n < 8 hands over its elements 0..3, lane n >= 8 elements 4..7
+                const uint32_t sel = (i & 1) ? 0x07060302u : 0x05040100u;
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    const int j0 = 2 * w, j1 = 2 * w + 1;
+                    const uint32_t a1 = n < 8 ? v[j1 >> 2][j1 & 3][0][i >> 1] : v[j1 >> 2][j1 & 3][0][2 + (i >> 1)];
+                    const uint32_t a0 = n < 8 ? v[j0 >> 2][j0 & 3][0][i >> 1] : v[j0 >> 2][j0 & 3][0][2 + (i >> 1)];
+                    t[w] = __builtin_amdgcn_perm(a1, a0, sel);
+                }
+            }
+            const bf16x8 a = __builtin_bit_cast(bf16x8, t);
+            o[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, hi, o[i], 0, 0, 0);
+            o[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, lo, o[i], 0, 0, 0);
+        }
+    }
+    // product i, output row m = 4 kg + r: dim 128 (i / 8) + 8 m + i % 8; head_dim 64: 8 m + i, or 8 (m - 8) + 4 + i
+    __device__ __forceinline__ static void to_lds(float* row, const f32x4 (&o)[NI], int kg) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int m = 4 * kg + r;
+            if constexpr (D >= 128) {
+#pragma unroll
+                for (int h = 0; h < VH; ++h)
+#pragma unroll
+                    for (int e = 0; e < 8; e += 4)
+                        *reinterpret_cast<f32x4*>(row + 128 * h + 8 * m + e) =
+                            f32x4{o[8 * h + e][r], o[8 * h + e + 1][r], o[8 * h + e + 2][r], o[8 * h + e + 3][r]};
+            } else {
+                *reinterpret_cast<f32x4*>(row + (m < 8 ? 8 * m : 8 * (m - 8) + 4)) = f32x4{o[0][r], o[1][r], o[2][r], o[3][r]};
+            }
+        }
+    }
+};
+
+// Waves of a workgroup: eight, two to a SIMD (a lane holds a whole tile: up to 256 registers); at head_dim 256 four.
+template <int D> constexpr int direct_waves() { return D == 256 ? 4 : 8; }
+// log2 of the largest softmax weight before a row's reference exponent is raised.  float32: any score above it raises it
+// (the rounding of score - reference grows with its size, so the largest weights want theirs near zero).
+template <typename T> constexpr float direct_slack() { return sizeof(T) == 4 ? 0.f : 24.f; }
+
+template <typename T, int D>
+__global__ __launch_bounds__(64 * direct_waves<D>()) void decode_direct_kernel(SweepArgs a, int row_tiles, int pieces) {
+    using TileT = Tile<T, D>;
+    constexpr int W = direct_waves<D>(), TB = TileT::TB, NI = TileT::NI, ES = TileT::ES;
+    constexpr int BLK = kBlock * D * ES;           // bytes of one (block, KV head)
+    constexpr int PAD = D + 4;                     // floats between the rows of the fold buffer (16 rows written side by side)
+    __shared__ __attribute__((aligned(16))) float s_acc[W][16][PAD];
+    __shared__ float2 s_ml[W][16];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane & 15, kg = lane >> 4;
+    int x = blockIdx.x;
+    const int g = x % a.Hkv; x /= a.Hkv;
+    const int rt = x % row_tiles; x /= row_tiles;
+    const int pc = x % pieces;
+    const int i = x / pieces;
+    const int nh = min(16, a.G - 16 * rt);         // query heads of this row tile
+
+    // The length, the ids of this wave's blocks and the query rows are requested together (the ids without
+    // knowing the length: every address is inside the request's table row; entries past the length are not used).
+    const int32_t* row = a.bt + (size_t)i * a.stride;
+    const int first = pc * W + wave, step = W * pieces;   // tiles of this wave: first, first + step, ...
+    auto ids_from = [&](int t0) {                         // lane TB x + b: block b of the x-th tile from t0 on
+        const int col = TB * (t0 + (lane / TB) * step) + lane % TB;
+        return row[min(max(col, 0), a.stride - 1)];
+    };
+    const int raw_len = a.seq_lens[i];
+    int ids = a.stride > 0 ? ids_from(first) : 0;
+    TileT tile;
+    tile.load_q(static_cast<const char*>(a.q) + ((size_t)i * a.Hq + g * a.G + 16 * rt + min(n, nh - 1)) * (D * ES), kg, n < nh);
+    const int L = __builtin_amdgcn_readfirstlane(min(max(raw_len, 0), a.stride * kBlock));
+    const int nb = (L + kBlock - 1) / kBlock, ntiles = (nb + TB - 1) / TB;
+
+    f32x4 o[NI];
+#pragma unroll
+    for (int j = 0; j < NI; ++j) o[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float m = -INFINITY, l = 0.f;                  // of head n: reference exponent (alike in its four lanes), this lane's part of the denominator
+    const char* kb[TB];
+    const char* vb[TB];
+    auto locate = [&](int t, int at) {             // the blocks of tile t, whose ids sit in lanes TB at + b
+#pragma unroll
+        for (int b = 0; b < TB; ++b) {
+            // (a negative entry inside a request's length - the caller's error - must not become a read before the cache)
+            const int blk = max(__builtin_amdgcn_readlane(ids, TB * at + (TB * t + b < nb ? b : 0)), 0);
+            const size_t off = ((size_t)blk * a.Hkv + g) * BLK;
+            kb[b] = static_cast<const char*>(a.k_cache) + off;
+            vb[b] = static_cast<const char*>(a.v_cache) + off;
+        }
+    };
+    if (first < ntiles) {
+        locate(first, 0);
+#pragma unroll
+        for (int b = 0; b < TB; ++b) tile.load_k(b, kb[b], n, kg);
+#pragma unroll
+        for (int b = 0; b < TB; ++b) tile.load_v(b, vb[b], n, kg);
+        int at = 0;
+        for (int t = first; t < ntiles; t += step) {
+            f32x4 s[TB];
+            tile.scores(s);
+            const bool more = t + step < ntiles;
+            if (more) {                            // K of the next tile while this one's weights and second product are worked out
+                if (++at == 64 / TB) { ids = ids_from(t + step); at = 0; }
+                locate(t + step, at);
+#pragma unroll
+                for (int b = 0; b < TB; ++b) tile.load_k(b, kb[b], n, kg);
+            }
+            float p[TB * 4];
+            const int pos = t * (TB * kBlock);
+            const bool ragged = pos + TB * kBlock > L;
+#pragma unroll
+            for (int b = 0; b < TB; ++b)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) p[4 * b + r] = s[b][r];
+            if (ragged) {                          // tokens past the end: weight 0, and whatever their V rows hold is left out
+#pragma unroll
+                for (int b = 0; b < TB; ++b)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (pos + 16 * b + 4 * kg + r >= L) { p[4 * b + r] = -INFINITY; tile.zero_v(b, r); }
+            }
+            float mx = p[0];
+#pragma unroll
+            for (int y = 1; y < TB * 4; ++y) mx = fmaxf(mx, p[y]);
+            mx *= a.scale_log2;
+            // (bfloat16: raised to the row maximum only when a score outgrows it by 2^24, which the float32 sums absorb
+            // without loss; on the first tile it is -inf, so that always happens there)
+            if (__any(mx > m + direct_slack<T>())) {
+                mx = fmaxf(mx, __shfl_xor(mx, 16));
+                mx = fmaxf(mx, __shfl_xor(mx, 32));
+                const float mn = fmaxf(m, mx);
+                const float al = m == -INFINITY ? 0.f : exp2_fast(m - mn);
+                l *= al;
+#pragma unroll
+                for (int j = 0; j < NI; ++j) o[j] *= al;
+                m = mn;
+            }
+#pragma unroll
+            for (int y = 0; y < TB * 4; ++y) {
+                p[y] = exp2_fast(fmaf(p[y], a.scale_log2, -m));
+                l += p[y];
+            }
+            if constexpr (ES == 4) tile.accumulate(p, o);
+            else tile.accumulate(p, o, n);
+            if (more) {
+#pragma unroll
+                for (int b = 0; b < TB; ++b) tile.load_v(b, vb[b], n, kg);
+            }
+        }
+    }
+    l += __shfl_xor(l, 16);
+    l += __shfl_xor(l, 32);
+    if (n < nh) {
+        TileT::to_lds(&s_acc[wave][n][0], o, kg);
+        if (kg == 0) s_ml[wave][n] = make_float2(m, l);
+    }
+    __syncthreads();
+
+    // fold the waves (fixed order) at the common reference exponent
+    const int rows0 = ((i * a.Hkv + g) * pieces + pc) * a.G + 16 * rt;   // partial row of the tile's first head
+    for (int y = tid; y < nh * (D / 8); y += 64 * W) {
+        const int h = y / (D / 8), c = y - h * (D / 8);
+        float M = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < W; ++w) M = fmaxf(M, s_ml[w][h].x);
+        float den = 0.f, num[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) num[e] = 0.f;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const float2 ml = s_ml[w][h];
+            const float f = ml.x == -INFINITY && ml.y == 0.f ? 0.f : exp2_fast(ml.x - M);   // (a wave that had no tile)
+            den = fmaf(f, ml.y, den);
+            const f32x4 a0 = *reinterpret_cast<const f32x4*>(&s_acc[w][h][8 * c]), a1 = *reinterpret_cast<const f32x4*>(&s_acc[w][h][8 * c + 4]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { num[e] = fmaf(f, a0[e], num[e]); num[4 + e] = fmaf(f, a1[e], num[4 + e]); }
+        }
+        if (pieces > 1) {
+            float* dst = reinterpret_cast<float*>(a.ws + a.lay.acc) + (size_t)(rows0 + h) * D + 8 * c;
+            *reinterpret_cast<f32x4*>(dst) = f32x4{num[0], num[1], num[2], num[3]};
+            *reinterpret_cast<f32x4*>(dst + 4) = f32x4{num[4], num[5], num[6], num[7]};
+            if (c == 0) reinterpret_cast<float2*>(a.ws + a.lay.ml)[rows0 + h] = make_float2(M, den);
+        } else {
+            const float inv = den == 0.f ? 0.f : 1.f / den;   // an empty history gives a zero row
+            char* dst = static_cast<char*>(a.out) + ((size_t)i * a.Hq + g * a.G + 16 * rt + h) * (D * ES) + 8 * c * ES;
+            if constexpr (ES == 4) {
+                *reinterpret_cast<f32x4*>(dst) = f32x4{num[0] * inv, num[1] * inv, num[2] * inv, num[3] * inv};
+                *reinterpret_cast<f32x4*>(dst + 16) = f32x4{num[4] * inv, num[5] * inv, num[6] * inv, num[7] * inv};
+            } else {
+                u32x4 w;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w[e] = bf16_rne(num[2 * e] * inv) | (bf16_rne(num[2 * e + 1] * inv) << 16);
+                *reinterpret_cast<u32x4*>(dst) = w;
+            }
+        }
+    }
+    // What the merge reads about a request, and what a later look at the workspace finds: no plan, this kernel.
+    if (pieces > 1 && pc == 0 && rt == 0 && tid == 0) {
+        SegDesc sd;
+        sd.pbase = (i * a.Hkv + g) * pieces * a.G;
+        sd.npieces = pieces;
+        reinterpret_cast<SegDesc*>(a.ws + a.lay.segs)[(size_t)i * a.Hkv + g] = sd;
+        if (g == 0) *reinterpret_cast<int4*>(a.ws + a.lay.req + (size_t)i * sizeof(ReqDesc)) = make_int4(0, 0, 0, 0);
+    }
+    if (blockIdx.x == 0 && tid < H_WORDS)
+        reinterpret_cast<int*>(a.ws)[tid] = tid == H_VARIANT ? 2 : tid == H_WAVES ? (int)gridDim.x * W : 0;
+}
+
+template <typename T, int D>
+void launch(const SweepArgs& a, int pieces, const Launch& L) {
+    const int row_tiles = (a.G + 15) / 16;
+    hipExtLaunchKernelGGL((decode_direct_kernel<T, D>), dim3((unsigned)(a.B * a.Hkv * row_tiles * pieces)), dim3(64 * direct_waves<D>()), 0,
+                          static_cast<hipStream_t>(L.stream), static_cast<hipEvent_t>(L.ev_start), static_cast<hipEvent_t>(L.ev_stop), 0,
+                          a, row_tiles, pieces);
+}
+
+}  // namespace
+
+void launch_decode_direct(const SweepArgs& a, int dtype, int head_dim, int pieces, const Launch& L) {
+    if (dtype == FEA_DTYPE_F32) {
+        switch (head_dim) {
+            case 32: launch<float, 32>(a, pieces, L); break;
+            case 64: launch<float, 64>(a, pieces, L); break;
+            case 128: launch<float, 128>(a, pieces, L); break;
+            case 256: launch<float, 256>(a, pieces, L); break;
+            default: break;
+        }
+    } else {
+        switch (head_dim) {
+            case 64: launch<bf16_t, 64>(a, pieces, L); break;
+            case 128: launch<bf16_t, 128>(a, pieces, L); break;
+            case 256: launch<bf16_t, 256>(a, pieces, L); break;
+            default: break;
+        }
+    }
+}
+
+}  // namespace fea

@@ -17,6 +17,7 @@
 #include <hip/hip_ext.h>
 
 #include <climits>
+#include <type_traits>
 
 #include "fea_plan.h"
 
@@ -65,33 +66,68 @@ __device__ __forceinline__ long long ddiv(long long x, int d) {
     return q;
 }
 
-// Exclusive prefix sum of one int per thread over the 1024-thread block.
-__device__ int block_scan_excl(int v, int* s_tmp, int& total) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int x = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(x, o);
-        if (lane >= o) x += y;
-    }
-    if (lane == 63) s_tmp[wave] = x;
+// Sums and minima over the lanes of a wave in the vector unit's own lane shifts (a shift within a row of 16 lanes, then
+// the last lane of a row, and of the lower half, handed on): a handful of instructions, where a shuffle through LDS would
+// be a round trip per step.
+template <int CTRL, int ROWS> __device__ __forceinline__ int lane_shift(int v, int other) {
+    return __builtin_amdgcn_update_dpp(other, v, CTRL, ROWS, 0xF, false);   // lanes without a source: `other`
+}
+__device__ __forceinline__ int wave_scan_incl(int v) {
+    v += lane_shift<0x111, 0xF>(v, 0);
+    v += lane_shift<0x112, 0xF>(v, 0);
+    v += lane_shift<0x114, 0xF>(v, 0);
+    v += lane_shift<0x118, 0xF>(v, 0);
+    v += lane_shift<0x142, 0xA>(v, 0);
+    v += lane_shift<0x143, 0xC>(v, 0);
+    return v;
+}
+__device__ __forceinline__ float wave_sum(float x) {
+    auto shifted = [](float v, auto ctrl, auto rows) {
+        return __int_as_float(lane_shift<decltype(ctrl)::value, decltype(rows)::value>(__float_as_int(v), 0));
+    };
+    using std::integral_constant;
+    x += shifted(x, integral_constant<int, 0x111>{}, integral_constant<int, 0xF>{});
+    x += shifted(x, integral_constant<int, 0x112>{}, integral_constant<int, 0xF>{});
+    x += shifted(x, integral_constant<int, 0x114>{}, integral_constant<int, 0xF>{});
+    x += shifted(x, integral_constant<int, 0x118>{}, integral_constant<int, 0xF>{});
+    x += shifted(x, integral_constant<int, 0x142>{}, integral_constant<int, 0xA>{});
+    x += shifted(x, integral_constant<int, 0x143>{}, integral_constant<int, 0xC>{});
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
+}
+__device__ __forceinline__ int wave_sum(int v) { return __builtin_amdgcn_readlane(wave_scan_incl(v), 63); }
+__device__ __forceinline__ uint32_t wave_min(uint32_t x) {
+    constexpr int kNone = -1;   // the largest value
+    int v = (int)x;
+    auto least = [](int p, int q) { return (int)min((uint32_t)p, (uint32_t)q); };
+    v = least(v, lane_shift<0x111, 0xF>(v, kNone));
+    v = least(v, lane_shift<0x112, 0xF>(v, kNone));
+    v = least(v, lane_shift<0x114, 0xF>(v, kNone));
+    v = least(v, lane_shift<0x118, 0xF>(v, kNone));
+    v = least(v, lane_shift<0x142, 0xA>(v, kNone));
+    v = least(v, lane_shift<0x143, 0xC>(v, kNone));
+    return (uint32_t)__builtin_amdgcn_readlane(v, 63);
+}
+
+// Exclusive prefix sum of one int per thread over the block.  One barrier: every thread adds up the waves before its own.
+// `s_sums` (16-byte aligned, one int per wave) must not be in use by another scan.
+__device__ __forceinline__ int block_scan_excl(int v, int* s_sums, int& total) {
+    constexpr int kWaves = kPlanThreads / 64;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int x = wave_scan_incl(v);
+    if (lane == 63) s_sums[wave] = x;
     __syncthreads();
-    if (wave == 0) {
-        constexpr int kWaves = kPlanThreads / 64;
-        const int w = lane < kWaves ? s_tmp[lane] : 0;
-        int xs = w;
+    int base = 0, all = 0;
 #pragma unroll
-        for (int o = 1; o < kWaves; o <<= 1) {
-            const int y = __shfl_up(xs, o);
-            if (lane >= o) xs += y;
+    for (int w = 0; w < kWaves; w += 4) {
+        const int4 q = *reinterpret_cast<const int4*>(s_sums + w);
+        const int part[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            base += w + k < wave ? part[k] : 0;
+            all += part[k];
         }
-        if (lane < kWaves) s_tmp[32 + lane] = xs - w;
-        if (lane == kWaves - 1) s_tmp[31] = xs;
     }
-    __syncthreads();
-    const int base = s_tmp[32 + wave];
-    total = s_tmp[31];
-    __syncthreads();
+    total = all;
     return base + x - v;
 }
 
@@ -235,7 +271,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
         unsigned short flw[kGroupReqMax];       // followers (grouped, not leader), for the run detection
         unsigned short glist[kGroupMax];        // then the list of viable leaders
     } w;
-    __shared__ int s_tmp[64];
+    __shared__ __attribute__((aligned(16))) int s_sums[3][kPlanThreads / 64];
     __shared__ int s_ngroups, s_ngrouped, s_shared_blocks, s_nflw, s_nest, s_adopt;
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -584,15 +620,44 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
     }
     auto viable = [&](int i) { return s_lead[i] == i && u.c.cnt[i] >= 2 && u.c.run[i] >= a.tune.min_run; };
 
-    // ---- member-list offsets (exclusive scan over leaders) and the list of groups
+    // ---- member-list offsets (exclusive scan over leaders) and the list of groups; and, for the cost model below, the
+    // private stream: request i owns Hkv * priv_tiles(i) consecutive tiles, KV head by KV head.  Its segments (request,
+    // KV head) are the entries the threads share out, so that a batch of few requests still spreads over many lanes.
+    auto run_of = [&](int i) {   // shared columns of request i (0 if ungrouped)
+        if (i >= nG) return 0;
+        const int lead = s_lead[i];
+        return (lead >= 0 && viable(lead)) ? u.c.run[lead] : 0;
+    };
+    auto len_of = [&](int i) { return i < nG ? s_len[i] : clampL(a.seq_lens[i]); };
+    auto priv_tiles = [&](int i) { return ((((len_of(i) + kBlock - 1) / kBlock) - run_of(i)) + 1) >> 1; };   // per KV head
+    const int NE = B * Hkv;
+    const int per = (NE + kPlanThreads - 1) / kPlanThreads;
+    const int e0 = tid * per, e1 = min(NE, e0 + per);
+    const FastDiv by_hkv(Hkv);
+    int T_pr, tbase;
     {
-        const int per = (nG + kPlanThreads - 1) / kPlanThreads;   // 0, 1 or 2
-        const int i0 = tid * per, i1 = min(nG, i0 + per);
-        int local = 0;
+        const int per_lead = (nG + kPlanThreads - 1) / kPlanThreads;   // 0, 1 or 2
+        const int i0 = tid * per_lead, i1 = min(nG, i0 + per_lead);
+        int local = 0, lt = 0;
         for (int i = i0; i < i1; ++i)
             if (viable(i)) local += u.c.cnt[i];
+        for (int e = e0, seen = -1, t = 0; e < e1; ++e) {     // (neighbouring segments mostly are one request's)
+            const int i = by_hkv.div(e);
+            if (i != seen) { seen = i; t = priv_tiles(i); }
+            lt += t;
+        }
+        const int tiles_in_wave = wave_scan_incl(lt);        // (both scans share the one barrier)
+        if (lane == 63) s_sums[1][wave] = tiles_in_wave;
         int total;
-        int base = block_scan_excl(local, s_tmp, total);
+        int base = block_scan_excl(local, s_sums[0], total);
+        tbase = tiles_in_wave - lt;
+        T_pr = 0;
+#pragma unroll
+        for (int w = 0; w < kPlanThreads / 64; ++w) {
+            const int part = s_sums[1][w];
+            tbase += w < wave ? part : 0;
+            T_pr += part;
+        }
         for (int i = i0; i < i1; ++i)
             if (viable(i)) {
                 u.c.moff[i] = base;
@@ -609,54 +674,24 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
     // equal pieces per segment, one piece per wave (a "share"); the private columns of
     // all requests form one stream of tiles that is cut into equal shares for the
     // remaining waves.  Both kinds of share are sized to the same cost.
-    auto run_of = [&](int i) {   // shared columns of request i (0 if ungrouped)
-        if (i >= nG) return 0;
-        const int lead = s_lead[i];
-        return (lead >= 0 && viable(lead)) ? u.c.run[lead] : 0;
-    };
-    auto len_of = [&](int i) { return i < nG ? s_len[i] : clampL(a.seq_lens[i]); };
-    auto priv_tiles = [&](int i) { return ((((len_of(i) + kBlock - 1) / kBlock) - run_of(i)) + 1) >> 1; };   // per KV head
-
-    // private stream: request i owns Hkv * priv_tiles(i) consecutive tiles, KV head by KV
-    // head.  Its segments (request, KV head) are the entries the threads share out, so
-    // that a batch of few requests still spreads over many lanes.
-    const int NE = B * Hkv;
-    const int per = (NE + kPlanThreads - 1) / kPlanThreads;
-    const int e0 = tid * per, e1 = min(NE, e0 + per);
-    const FastDiv by_hkv(Hkv);
-    int lt = 0;
-    for (int e = e0; e < e1; ++e) lt += priv_tiles(by_hkv.div(e));
-    int T_pr;
-    const int tbase = block_scan_excl(lt, s_tmp, T_pr);
-    // shared side: wave 0 sizes the shares, lanes over the groups (float reciprocals are
-    // exact here: every dividend is a tile or share count far below 2^24)
+    //
+    // shared side: wave 0 sizes the shares, lanes over the groups
     __shared__ int s_plan[8];
-    auto idiv = [](int x, int d) {
-        int qq = (int)((float)x * (1.0f / (float)d));
-        const int r = x - qq * d;
-        if (r >= d) ++qq;
-        if (r < 0) --qq;
-        return qq;
+    // Quotients from the hardware's reciprocal (this stretch is serial, a true division a dozen dependent steps): exact up to
+    // quotients of 2^22, where the product is less than one off; idiv takes a second step and is exact for every x >= 0.
+    auto near_div = [](int x, int d, float rcp) {
+        const int qq = (int)((float)x * rcp), r = x - qq * d;
+        return qq + (r >= d ? 1 : 0) - (r < 0 ? 1 : 0);
+    };
+    auto idiv = [&](int x, int d) {
+        const float rcp = __builtin_amdgcn_rcpf((float)d);
+        const int qq = (int)((float)x * rcp), r = x - qq * d, q2 = (int)((float)r * rcp), r2 = r - q2 * d;
+        return qq + q2 + (r2 >= d ? 1 : 0) - (r2 < 0 ? 1 : 0);
     };
     if (wave == 0) {
-        // Sums and scans over the groups, one group per lane.  Cross-lane moves cost an LDS
-        // round trip each and this stretch is serial, so only as many butterfly steps are
-        // taken as the lanes that hold a group need (none for a single group).
-        int span = 1;
-        while (span < min(n_groups, 64)) span <<= 1;
-        auto wsum = [&](long long x) {   // lanes >= n_groups pass 0 (and are handed the total too)
-            for (int o = 1; o < span; o <<= 1) x += __shfl_xor(x, o);
-            const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
-            const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((unsigned long long)x >> 32));
-            return (long long)(((unsigned long long)hi << 32) | lo);
-        };
-        auto scan_excl = [&](int v, int& total) {   // the same for an exclusive prefix sum
-            int x = v;
-            for (int o = 1; o < span; o <<= 1) {
-                const int y = __shfl_up(x, o);
-                if (lane >= o) x += y;
-            }
-            total = span > 1 ? __shfl(x, span - 1) : __builtin_amdgcn_readfirstlane(x);
+        auto scan_excl = [&](int v, int& total) {
+            const int x = wave_scan_incl(v);
+            total = __builtin_amdgcn_readlane(x, 63);
             return x - v;
         };
         const int fixed_tiles = a.split_user > 0 ? a.split_user >> 1 : 0;   // split_user is even
@@ -668,16 +703,17 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
             if (gi == lane) { ld = my_ld; cnt = my_cnt; run = my_run; }
             else { ld = w.glist[gi]; cnt = u.c.cnt[ld]; run = u.c.run[ld]; }
         };
-        long long u_loc = 0, t_loc = 0;
+        // (sums in float: they only say where the search below starts, and how few waves a small batch gets)
+        float u_loc = 0.f, t_loc = 0.f;
         for (int gi = lane; gi < n_groups; gi += 64) {
             int ld, cnt, run;
             group(gi, ld, cnt, run);
-            const long long t = (long long)Hkv * by_mpt.cdiv(cnt) * ((run + 1) >> 1);
-            u_loc += t * group_weight(cnt);
+            const float t = (float)(Hkv * by_mpt.cdiv(cnt)) * (float)((run + 1) >> 1);
+            u_loc += t * (float)group_weight(cnt);
             t_loc += t;
         }
-        const long long U = wsum(u_loc) + 16ll * T_pr, total_tiles = wsum(t_loc) + T_pr;
-        const int n_act = (int)max(1ll, min((long long)a.tune.n_waves, ddiv(total_tiles, max(a.tune.min_piece, 1))));
+        const float U = 16.f * (float)T_pr + wave_sum(u_loc), total_tiles = (float)T_pr + wave_sum(t_loc);
+        const int n_act = max(1, (int)fminf((float)a.tune.n_waves, total_tiles * __builtin_amdgcn_rcpf((float)max(a.tune.min_piece, 1))));
         // Pieces of a group's run of T_seg tiles when a share may cost Q.
         auto pieces = [&](int cnt, int T_seg, int Q) {
             const int want = fixed_tiles > 0 ? fixed_tiles : max(1, idiv(max(Q - group_fixed(cnt), 0), group_weight(cnt)));
@@ -685,11 +721,11 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
         };
         // shares of the private stream at cost Q per share, and their tiles
         auto own_shares = [&](int Q, int& q) {
-            const int n_pr = max(1, (int)ddiv(16ll * T_pr + Q - 1, Q));
+            const int n_pr = max(1, (int)ddiv(16ll * T_pr + Q - 1, Q));   // (only where nothing fitted the waves, below)
             q = max(1, idiv(T_pr + n_pr - 1, n_pr));
             return idiv(T_pr + q - 1, q);
         };
-        int Q = (int)min(1ll << 25, max(16ll, ddiv(U + n_act - 1, n_act)));   // the even split
+        int Q = max(16, (int)fminf(U * __builtin_amdgcn_rcpf((float)n_act) + 1.f, 33554432.f));   // the even split
         int q = 1, n_sh = 0;
         bool searched = false;
         if (fixed_tiles == 0 && n_groups > 0 && n_groups <= 32) {
@@ -698,29 +734,32 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
             // pieces, from 3/4 of the even split to 7/4 of it; the waves the pieces leave over share the private
             // stream; the lane whose longest share (shared piece or private share) costs least wins.
             const int Qc = Q - (Q >> 2) + (int)(((long long)Q * lane) >> 6);
+            // (What a group brings to it is worked out by the lane that holds the group.  The tiles a share may hold are
+            // exact, and the pieces wherever they fit the waves, so what is chosen here is what is laid out below.)
+            const int my_slots = Hkv * tiles_padded(by_mpt.cdiv(my_cnt)), my_w = group_weight(max(my_cnt, 1)), my_fixed = group_fixed(my_cnt);
             int slots = 0, longest = 0;
             for (int gi = 0; gi < n_groups; ++gi) {
-                const int ld = w.glist[gi], cnt = u.c.cnt[ld], T_seg = (u.c.run[ld] + 1) >> 1;
-                const int n_pc = pieces(cnt, T_seg, Qc);
-                slots += items_padded(Hkv * tiles_padded(by_mpt.cdiv(cnt)) * n_pc);
-                longest = max(longest, ((T_seg + n_pc - 1) / n_pc) * group_weight(cnt) + group_fixed(cnt));
+                const int T_seg = (__builtin_amdgcn_readlane(my_run, gi) + 1) >> 1, wt = __builtin_amdgcn_readlane(my_w, gi);
+                const int fixed = __builtin_amdgcn_readlane(my_fixed, gi);
+                const int want = max(1, idiv(max(Qc - fixed, 0), wt));
+                const int n_pc = near_div(T_seg + want - 1, want, __builtin_amdgcn_rcpf((float)want));
+                slots += items_padded(__builtin_amdgcn_readlane(my_slots, gi) * n_pc);
+                longest = max(longest, near_div(T_seg + n_pc - 1, n_pc, __builtin_amdgcn_rcpf((float)n_pc)) * wt + fixed);
             }
             int qq = 0;
             if (T_pr > 0) {
-                const int n_own = min(n_act - slots, (T_pr + a.tune.min_piece - 1) / max(a.tune.min_piece, 1));
-                qq = n_own >= 1 ? (T_pr + n_own - 1) / n_own : -1;
+                const int n_own = min(n_act - slots, idiv(T_pr + a.tune.min_piece - 1, max(a.tune.min_piece, 1)));
+                qq = n_own >= 1 ? idiv(T_pr + n_own - 1, n_own) : -1;
                 if (qq > (1 << 26)) qq = -1;
             }
             const bool fits = slots <= n_act && qq >= 0;
-            int cost = fits ? max(longest, 16 * qq) : 0x7FFFFFFF;
-            int who = lane;
-            for (int o = 1; o < 64; o <<= 1) {     // least cost; among equals the largest Qc (fewest pieces)
-                const int c2 = __shfl_xor(cost, o), w2 = __shfl_xor(who, o);
-                if (c2 < cost || (c2 == cost && w2 > who)) { cost = c2; who = w2; }
-            }
-            if (cost != 0x7FFFFFFF) {
-                Q = __shfl(Qc, who);
-                q = max(1, __shfl(qq, who));
+            // least cost; among equals the largest Qc (fewest pieces), which the lane number in the low bits says
+            const uint32_t cost = fits ? min((uint32_t)max(longest, 16 * qq), (1u << 25) - 2u) : (1u << 25) - 1u;
+            const uint32_t best = wave_min((cost << 6) | (uint32_t)(63 - lane));
+            if (best >> 6 != (1u << 25) - 1u) {
+                const int who = 63 - (int)(best & 63u);
+                Q = __builtin_amdgcn_readlane(Qc, who);
+                q = max(1, __builtin_amdgcn_readlane(qq, who));
                 searched = true;
             }
         }
@@ -735,7 +774,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
                 v.g.npc[gi] = n_pc;
                 loc += items_padded(Hkv * tiles_padded(by_mpt.cdiv(cnt)) * n_pc);
             }
-            n_sh = (int)wsum(loc);
+            n_sh = wave_sum(loc);
             if (fixed_tiles > 0 || searched) break;
             const int shares = n_sh + own_shares(Q, q);
             if (shares <= n_act) break;
@@ -801,11 +840,14 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
     int li = 0;
     {
         int k = k_start, rem = rem_start;
-        for (int e = e0; e < e1; ++e)
-            for_pieces(priv_tiles(by_hkv.div(e)), k, rem, [&](int, int, bool, int) { ++li; });
+        for (int e = e0, seen = -1, t = 0; e < e1; ++e) {
+            const int i = by_hkv.div(e);
+            if (i != seen) { seen = i; t = priv_tiles(i); }
+            for_pieces(t, k, rem, [&](int, int, bool, int) { ++li; });
+        }
     }
     int priv_items;
-    const int ibase = n_sh + block_scan_excl(li, s_tmp, priv_items);
+    const int ibase = n_sh + block_scan_excl(li, s_sums[2], priv_items);
     const int total_items = n_sh + priv_items, total_rows = rows_sh + priv_items * a.G;
     const bool overflow = total_items > a.lay.max_items || total_rows > a.lay.max_rows;
 
@@ -825,9 +867,10 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
     // ---- descriptors and items of the requests' own columns
     {
         int k = k_start, rem = rem_start, idx = ibase;
+        int seen = -1, L = 0, nb = 0, c0 = 0;
         for (int e = e0; e < e1; ++e) {
             const int i = by_hkv.div(e), g = e - i * Hkv;
-            const int L = len_of(i), nb = (L + kBlock - 1) / kBlock, c0 = run_of(i);
+            if (i != seen) { seen = i; L = len_of(i); nb = (L + kBlock - 1) / kBlock; c0 = run_of(i); }
             if (g == 0) {
                 ReqDesc rd;
                 rd.ns_sh = rd.sh_base0 = rd.sh_gstride = rd.sh_pstride = 0;   // a group fills these in below

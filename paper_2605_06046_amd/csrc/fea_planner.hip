@@ -272,7 +272,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
         unsigned short glist[kGroupMax];        // then the list of viable leaders
     } w;
     __shared__ __attribute__((aligned(16))) int s_sums[3][kPlanThreads / 64];
-    __shared__ int s_ngroups, s_ngrouped, s_shared_blocks, s_nflw, s_nest, s_adopt;
+    __shared__ int s_ngroups, s_ngrouped, s_shared_blocks, s_nflw, s_nest, s_adopt, s_longest[kPlanThreads / 64];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -289,7 +289,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
     const int maxL = a.stride * kBlock;
     auto clampL = [&](int L) { return max(0, min(L, maxL)); };
 
-    int my_key[kGroupReqMax / kPlanThreads];
+    int my_key[kGroupReqMax / kPlanThreads], my_longest = 0;
     for (int s = tid; s < kHashSlots; s += kPlanThreads) { h2.keys[s] = -1; h2.vals[s] = INT_MAX; }
     if (tid == 0) { s_ngroups = 0; s_ngrouped = 0; s_shared_blocks = 0; s_nflw = 0; }
     if (a.pre) {
@@ -313,6 +313,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
             if (i < nG) {
                 const int L = clampL(a.seq_lens[i]);
                 s_len[i] = L;
+                my_longest = max(my_longest, L);
                 if (L >= kBlock) {
                     const int key = a.bt[(size_t)i * a.stride];
                     my_key[k] = key;
@@ -327,6 +328,8 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
                 }
             }
         }
+        my_longest = ~(int)wave_min(~(uint32_t)my_longest);
+        if (lane == 0) s_longest[wave] = my_longest;
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < kGroupReqMax / kPlanThreads; ++k) {
@@ -355,10 +358,18 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
     // ---- longest common run of block ids with the leader's row.  All (follower,
     // column group) pairs are spread flat over the threads, six at a time so that
     // their loads are in flight together; a mismatch lowers the follower's run with
-    // an LDS atomic.  Columns below from(i) are known to agree and are not read.
+    // an LDS atomic.  Columns below from(i) are known to agree and are not read, and columns past the
+    // longest history are not looked at (a table is often as wide as the longest history that is allowed).
+    int columns = a.stride;
+    if (!a.pre) {
+        int longest = 0;
+#pragma unroll
+        for (int w = 0; w < kPlanThreads / 64; ++w) longest = max(longest, s_longest[w]);
+        columns = longest / kBlock;
+    }
     auto lcp_pass = [&](int nflw, const short* lead_of, auto&& from, auto&& hit) {
         constexpr int cpe = 4;                             // columns per element
-        const int epr = cdiv(a.stride, cpe);               // elements per row (the last one may be short)
+        const int epr = cdiv(columns, cpe);                // elements per row (the last one may be short)
         const FastDiv by_epr(max(epr, 1));
         const int total = nflw * epr;
         constexpr int kBatch = 6;

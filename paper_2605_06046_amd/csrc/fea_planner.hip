@@ -249,6 +249,7 @@ __global__ __launch_bounds__(kRunThreads) void run_kernel(PlanArgs a) {
     }
 }
 
+constexpr int kSegmentTiles = 1;              // tiles that a further segment of a share costs
 constexpr int kGroupMax = kGroupReqMax / 2;   // a group has at least two members
 
 __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
@@ -632,7 +633,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
     auto viable = [&](int i) { return s_lead[i] == i && u.c.cnt[i] >= 2 && u.c.run[i] >= a.tune.min_run; };
 
     // ---- member-list offsets (exclusive scan over leaders) and the list of groups; and, for the cost model below, the
-    // private stream: request i owns Hkv * priv_tiles(i) consecutive tiles, KV head by KV head.  Its segments (request,
+    // private stream: request i owns Hkv * priv_units(i) consecutive units, KV head by KV head.  Its segments (request,
     // KV head) are the entries the threads share out, so that a batch of few requests still spreads over many lanes.
     auto run_of = [&](int i) {   // shared columns of request i (0 if ungrouped)
         if (i >= nG) return 0;
@@ -640,7 +641,18 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
         return (lead >= 0 && viable(lead)) ? u.c.run[lead] : 0;
     };
     auto len_of = [&](int i) { return i < nG ? s_len[i] : clampL(a.seq_lens[i]); };
-    auto priv_tiles = [&](int i) { return ((((len_of(i) + kBlock - 1) / kBlock) - run_of(i)) + 1) >> 1; };   // per KV head
+    // What a segment is to the wave that sweeps it, in tiles (per KV head): its tiles, and the change to another request
+    // (query rows, the first tile's way through the pipeline, the partial rows).  Measured, per segment more in a share:
+    // 1.2 us at head_dim 64 and 128, 2.4 at 256, where a tile takes 0.9, 1.5 to 1.9 and 1.65.  Shares cut by tiles alone
+    // ended that much apart (22 to 32 us in a batch of head_dim 64, 22 to 27 since), and the batch ends with the last.
+    // Whole calls, 0, 1 and 2 tiles charged: head_dim 64 56.8, 54.6 and 57.8 us; 256 56.5, 52.5 and 51.9; four layers
+    // under a refreshed plan 149.8, 135.9 and 134.9, under a new one 176, 168 and 173; 256 requests in 8 groups 174, 170
+    // and 173.
+    const int per_seg = a.variant == 1 && a.split_user == 0 ? kSegmentTiles : 0;
+    auto priv_units = [&](int i) {
+        const int t = ((((len_of(i) + kBlock - 1) / kBlock) - run_of(i)) + 1) >> 1;
+        return t > 0 ? t + per_seg : 0;
+    };
     const int NE = B * Hkv;
     const int per = (NE + kPlanThreads - 1) / kPlanThreads;
     const int e0 = tid * per, e1 = min(NE, e0 + per);
@@ -654,7 +666,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
             if (viable(i)) local += u.c.cnt[i];
         for (int e = e0, seen = -1, t = 0; e < e1; ++e) {     // (neighbouring segments mostly are one request's)
             const int i = by_hkv.div(e);
-            if (i != seen) { seen = i; t = priv_tiles(i); }
+            if (i != seen) { seen = i; t = priv_units(i); }
             lt += t;
         }
         const int tiles_in_wave = wave_scan_incl(lt);        // (both scans share the one barrier)
@@ -814,7 +826,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
         }
         if (lane == 0) {
             s_plan[0] = fixed_tiles;
-            s_plan[1] = q;
+            s_plan[1] = q = max(q, 1 + per_seg);
             s_plan[2] = n_sh;
             s_plan[3] = rb;
         }
@@ -822,22 +834,24 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
     __syncthreads();
     const int fixed_tiles = s_plan[0], q = s_plan[1], n_sh = s_plan[2], rows_sh = s_plan[3];
 
-    // Cutting one segment of T_seg tiles into pieces, walking along the stream: `rem`
-    // tiles of share `k` are used up at the segment's start.  Calls f(jb, je,
-    // starts_share, k) for every piece, in order, and moves (k, rem) to the segment's end.
-    auto for_pieces = [&](int T_seg, int& k, int& rem, auto&& f) {
-        int jb = 0;
-        while (jb < T_seg) {
+    // Cutting one segment of `units` into pieces, walking along the stream: `rem` units of share `k` are used up
+    // at the segment's start.  Calls f(jb, je, starts_share, k) for every piece of tiles, in order, and moves (k, rem)
+    // to the segment's end.  (The units before the first tile may be all a share has left: that makes no piece.  A
+    // share holds more than those, so its first units always make one.)
+    auto for_pieces = [&](int units, int& k, int& rem, auto&& f) {
+        int u = 0;
+        while (u < units) {
             int take;
             bool starts = false;
             if (fixed_tiles > 0) {
-                take = min(T_seg - jb, fixed_tiles);
+                take = min(units - u, fixed_tiles);
             } else {
-                take = min(T_seg - jb, q - rem);
+                take = min(units - u, q - rem);
                 starts = rem == 0;
             }
-            f(jb, jb + take, starts, k);
-            jb += take;
+            const int jb = max(u - per_seg, 0), je = u + take - per_seg;
+            if (je > jb) f(jb, je, starts, k);
+            u += take;
             if (fixed_tiles == 0) {
                 rem += take;
                 if (rem == q) { rem = 0; ++k; }
@@ -853,7 +867,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
         int k = k_start, rem = rem_start;
         for (int e = e0, seen = -1, t = 0; e < e1; ++e) {
             const int i = by_hkv.div(e);
-            if (i != seen) { seen = i; t = priv_tiles(i); }
+            if (i != seen) { seen = i; t = priv_units(i); }
             for_pieces(t, k, rem, [&](int, int, bool, int) { ++li; });
         }
     }
@@ -878,10 +892,10 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
     // ---- descriptors and items of the requests' own columns
     {
         int k = k_start, rem = rem_start, idx = ibase;
-        int seen = -1, L = 0, nb = 0, c0 = 0;
+        int seen = -1, L = 0, nb = 0, c0 = 0, units = 0;
         for (int e = e0; e < e1; ++e) {
             const int i = by_hkv.div(e), g = e - i * Hkv;
-            if (i != seen) { seen = i; L = len_of(i); nb = (L + kBlock - 1) / kBlock; c0 = run_of(i); }
+            if (i != seen) { seen = i; L = len_of(i); nb = (L + kBlock - 1) / kBlock; c0 = run_of(i); units = priv_units(i); }
             if (g == 0) {
                 ReqDesc rd;
                 rd.ns_sh = rd.sh_base0 = rd.sh_gstride = rd.sh_pstride = 0;   // a group fills these in below
@@ -893,7 +907,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
             }
             const int seg_first = idx;
             if (!overflow) {
-                for_pieces(((nb - c0) + 1) >> 1, k, rem, [&](int jb, int je, bool starts, int kk) {
+                for_pieces(units, k, rem, [&](int jb, int je, bool starts, int kk) {
                     const int cs = c0 + 2 * jb, ce = min(nb, c0 + 2 * je);
                     // (the piece that ends at the request's last column is marked: it grows with the request, see refresh_kernel)
                     write_item(&items[idx], i, g, a.G, ce == nb ? kOpenEnded : -1, cs, ce, rows_sh + (idx - n_sh) * a.G, min(L, ce * kBlock));

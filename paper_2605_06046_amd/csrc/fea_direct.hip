@@ -222,6 +222,9 @@ template <int D> constexpr int direct_waves() { return D == 256 ? 4 : 8; }
 // log2 of the largest softmax weight before a row's reference exponent is raised.  float32: any score above it raises it
 // (the rounding of score - reference grows with its size, so the largest weights want theirs near zero).
 template <typename T> constexpr float direct_slack() { return sizeof(T) == 4 ? 0.f : 24.f; }
+// The reference exponent before any score: the lowest finite number and not -inf, so that a tile whose scores are all
+// -inf (which raise nothing) gets weights 2^(-inf - m) = 0 and leaves (m, l, o) as they were; -inf - -inf would be NaN.
+constexpr float kLowest = -3.402823466e38f;
 
 template <typename T, int D>
 __global__ __launch_bounds__(64 * direct_waves<D>()) void decode_direct_kernel(SweepArgs a, int row_tiles, int pieces) {
@@ -259,7 +262,7 @@ __global__ __launch_bounds__(64 * direct_waves<D>()) void decode_direct_kernel(S
     f32x4 o[NI];
 #pragma unroll
     for (int j = 0; j < NI; ++j) o[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float m = -INFINITY, l = 0.f;                  // of head n: reference exponent (alike in its four lanes), this lane's part of the denominator
+    float m = kLowest, l = 0.f;                    // of head n: reference exponent (alike in its four lanes), this lane's part of the denominator
     const char* kb[TB];
     const char* vb[TB];
     auto locate = [&](int t, int at) {             // the blocks of tile t, whose ids sit in lanes TB at + b
@@ -308,12 +311,12 @@ __global__ __launch_bounds__(64 * direct_waves<D>()) void decode_direct_kernel(S
             for (int y = 1; y < TB * 4; ++y) mx = fmaxf(mx, p[y]);
             mx *= a.scale_log2;
             // (bfloat16: raised to the row maximum only when a score outgrows it by 2^24, which the float32 sums absorb
-            // without loss; on the first tile it is -inf, so that always happens there)
+            // without loss; the first score above -inf always does)
             if (__any(mx > m + direct_slack<T>())) {
                 mx = fmaxf(mx, __shfl_xor(mx, 16));
                 mx = fmaxf(mx, __shfl_xor(mx, 32));
                 const float mn = fmaxf(m, mx);
-                const float al = m == -INFINITY ? 0.f : exp2_fast(m - mn);
+                const float al = exp2_fast(m - mn);   // (0 where the reference was the lowest number)
                 l *= al;
 #pragma unroll
                 for (int j = 0; j < NI; ++j) o[j] *= al;
@@ -344,7 +347,7 @@ __global__ __launch_bounds__(64 * direct_waves<D>()) void decode_direct_kernel(S
     const int rows0 = ((i * a.Hkv + g) * pieces + pc) * a.G + 16 * rt;   // partial row of the tile's first head
     for (int y = tid; y < nh * (D / 8); y += 64 * W) {
         const int h = y / (D / 8), c = y - h * (D / 8);
-        float M = -INFINITY;
+        float M = kLowest;
 #pragma unroll
         for (int w = 0; w < W; ++w) M = fmaxf(M, s_ml[w][h].x);
         float den = 0.f, num[8];
@@ -353,7 +356,7 @@ __global__ __launch_bounds__(64 * direct_waves<D>()) void decode_direct_kernel(S
 #pragma unroll
         for (int w = 0; w < W; ++w) {
             const float2 ml = s_ml[w][h];
-            const float f = ml.x == -INFINITY && ml.y == 0.f ? 0.f : exp2_fast(ml.x - M);   // (a wave that had no tile)
+            const float f = exp2_fast(ml.x - M);   // (a wave that had no tile, or no score above -inf, has sums of 0)
             den = fmaf(f, ml.y, den);
             const f32x4 a0 = *reinterpret_cast<const f32x4*>(&s_acc[w][h][8 * c]), a1 = *reinterpret_cast<const f32x4*>(&s_acc[w][h][8 * c + 4]);
 #pragma unroll
@@ -365,7 +368,7 @@ __global__ __launch_bounds__(64 * direct_waves<D>()) void decode_direct_kernel(S
             *reinterpret_cast<f32x4*>(dst + 4) = f32x4{num[4], num[5], num[6], num[7]};
             if (c == 0) reinterpret_cast<float2*>(a.ws + a.lay.ml)[rows0 + h] = make_float2(M, den);
         } else {
-            const float inv = den == 0.f ? 0.f : 1.f / den;   // an empty history gives a zero row
+            const float inv = L == 0 ? 0.f : 1.f / den;   // an empty history gives a zero row, one of scores of -inf alone 0/0
             char* dst = static_cast<char*>(a.out) + ((size_t)i * a.Hq + g * a.G + 16 * rt + h) * (D * ES) + 8 * c * ES;
             if constexpr (ES == 4) {
                 *reinterpret_cast<f32x4*>(dst) = f32x4{num[0] * inv, num[1] * inv, num[2] * inv, num[3] * inv};
@@ -382,7 +385,7 @@ __global__ __launch_bounds__(64 * direct_waves<D>()) void decode_direct_kernel(S
     if (pieces > 1 && pc == 0 && rt == 0 && tid == 0) {
         SegDesc sd;
         sd.pbase = (i * a.Hkv + g) * pieces * a.G;
-        sd.npieces = pieces;
+        sd.npieces = L == 0 ? 0 : pieces;
         reinterpret_cast<SegDesc*>(a.ws + a.lay.segs)[(size_t)i * a.Hkv + g] = sd;
         if (g == 0) *reinterpret_cast<int4*>(a.ws + a.lay.req + (size_t)i * sizeof(ReqDesc)) = make_int4(0, 0, 0, 0);
     }

@@ -339,7 +339,7 @@ __global__ __launch_bounds__(256) void merge_kernel(SweepArgs a) {
         for (int k = 0; k < 8; ++k) num[k] += __shfl_xor(num[k], o);
     }
     if (slot == 0) {
-        const float inv = den > 0.f ? 1.f / den : 0.f;
+        const float inv = ns > 0 ? 1.f / den : 0.f;     // an empty history gives a zero row, one of scores of -inf alone 0/0
 #pragma unroll
         for (int k = 0; k < 8; ++k) num[k] *= inv;
         Elem<T>::store8(out + c * 8, num);
@@ -416,7 +416,7 @@ __global__ __launch_bounds__(256) void merge_rows_kernel(SweepArgs a) {
             num[6] = fmaf(w, x[q][1].z, num[6]); num[7] = fmaf(w, x[q][1].w, num[7]);
         }
     }
-    const float inv = den > 0.f ? 1.f / den : 0.f;
+    const float inv = ns > 0 ? 1.f / den : 0.f;          // an empty history gives a zero row, one of scores of -inf alone 0/0
 #pragma unroll
     for (int k = 0; k < 8; ++k) num[k] *= inv;
     Elem<T>::store8(out + c * 8, num);

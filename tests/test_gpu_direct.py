@@ -55,13 +55,13 @@ def test_edges_of_tiles_waves_and_pieces(dtype, Hq, Hkv, d, lens):
 @pytest.mark.parametrize("dtype,Hq,Hkv,d", [("f32", 8, 2, 64), ("bf16", 14, 2, 128)])
 @pytest.mark.parametrize("lens", [[40, 300, 33], [1600, 900]])
 def test_nan_and_infinity_of_a_live_token_stay_with_their_request(dtype, Hq, Hkv, d, lens):
-    """A NaN in one live K or V row, or an infinite score, reaches every query head that attends to it - also where that token's
-    wave or piece holds nothing else - and no other request; scores of -inf next to finite ones have weight 0."""
+    """A NaN in one live K or V row, or an infinite score, reaches every query head that attends to it and no other request;
+    scores of -inf next to finite ones of the same tile have weight 0 (for tiles of nothing else: test_gpu_minus_infinity)."""
     nan = W.BF16_NAN if dtype == "bf16" else np.float32(np.nan)
     inf = (lambda s: np.uint16(0x7F80 if s > 0 else 0xFF80)) if dtype == "bf16" else (lambda s: np.float32(s * np.inf))
     for where in ("k", "v", "+inf", "-inf"):
         q, k, v, bt, L = _batch(dtype, Hq, Hkv, d, lens, 5)
-        t = lens[0] - 1                                    # the last token: alone in its block's tile in the first batch
+        t = lens[0] - 1                                    # the last token, in a tile that ends short
         blk = bt[0, t // 16]
         if where in ("k", "v"):
             (k if where == "k" else v)[blk, 0, t % 16, 3] = nan

@@ -222,9 +222,6 @@ template <int D> constexpr int direct_waves() { return D == 256 ? 4 : 8; }
 // log2 of the largest softmax weight before a row's reference exponent is raised.  float32: any score above it raises it
 // (the rounding of score - reference grows with its size, so the largest weights want theirs near zero).
 template <typename T> constexpr float direct_slack() { return sizeof(T) == 4 ? 0.f : 24.f; }
-// The reference exponent before any score: the lowest finite number and not -inf, so that a tile whose scores are all
-// -inf (which raise nothing) gets weights 2^(-inf - m) = 0 and leaves (m, l, o) as they were; -inf - -inf would be NaN.
-constexpr float kLowest = -3.402823466e38f;
 
 template <typename T, int D>
 __global__ __launch_bounds__(64 * direct_waves<D>()) void decode_direct_kernel(SweepArgs a, int row_tiles, int pieces) {

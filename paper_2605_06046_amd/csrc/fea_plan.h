@@ -13,6 +13,9 @@ constexpr int kPlanThreads = 1024;    // the planner is one workgroup
 constexpr int kGroupReqMax = 2048;    // requests with index >= this are never grouped
 constexpr int kHashSlots = 4096;      // LDS hash slots for leader finding (2x kGroupReqMax)
 constexpr int kTileRows = 64;         // query rows one MFMA work item carries at most
+// A row's reference exponent is never below the lowest finite number: scores of -inf then get weights 2^(-inf - m) = 0,
+// also where a wave's first tile holds nothing else; -inf - -inf would be NaN.
+constexpr float kLowest = -3.402823466e38f;
 constexpr int kOpenEnded = -2;        // Item::mlist_off of a request's last piece of its own columns
 
 // header words (int32) at the start of the workspace

@@ -135,7 +135,7 @@ __global__ __launch_bounds__(kGenThreads) void sweep_generic_kernel(SweepArgs a)
             constexpr int RPW = (RB + kGenWaves - 1) / kGenWaves;   // rows whose softmax state one wave keeps
             float m_run[RPW], l_run[RPW];   // of rows wave, wave + kGenWaves, ...
 #pragma unroll
-            for (int k = 0; k < RPW; ++k) { m_run[k] = -INFINITY; l_run[k] = 0.f; }
+            for (int k = 0; k < RPW; ++k) { m_run[k] = kLowest; l_run[k] = 0.f; }
 
             for (int p0 = t_begin; p0 < t_end; p0 += kPiece) {
                 const int np = min(kPiece, t_end - p0);

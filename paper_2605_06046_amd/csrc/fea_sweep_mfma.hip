@@ -524,8 +524,7 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const Item& item,
     // Online softmax.  The running "maximum" is a reference exponent m_ref per row:
     // weights are 2^(s - m_ref).  It is raised to the true row maximum (and l, O
     // rescaled) only when some score exceeds it by more than kSlack, which float32
-    // sums absorb without loss; on the first tile it is -inf, so that always happens
-    // there.  Softmax is shift-invariant, so the result is the same, and the common
+    // sums absorb without loss; the first tile sets it.  Softmax is shift-invariant, so the result is the same, and the common
     // case costs no cross-lane traffic and no rescale of O.
     auto raise_refs = [&]() {
 #pragma unroll
@@ -562,7 +561,7 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const Item& item,
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
         float rmax = fmaxf(tmax[nt], __shfl_xor(tmax[nt], 16));
-        m_run[nt] = fmaxf(rmax, __shfl_xor(rmax, 32));
+        m_run[nt] = fmaxf(fmaxf(rmax, __shfl_xor(rmax, 32)), kLowest);
     }
     back();
     // Fast loop: no reference is ever raised in here, the accumulators are only touched

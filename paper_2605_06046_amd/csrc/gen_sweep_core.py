@@ -452,6 +452,7 @@ class Gen:
             e("s_waitcnt lgkmcnt(0)")
             e(f"v_max_f32 {T(8)}, {T(8)}, {T(10)}")
             e(f"v_mul_f32 {T(8)}, %[scale], {T(8)}")
+            e(f"v_max_f32 {T(8)}, 0xff7fffff, {T(8)}")   # (scores of -inf alone: the lowest finite number, see kLowest)
             e(f"v_xor_b32 {NEGM(nt)}, 0x80000000, {T(8)}")
         e(f"s_mov_b32 {ST}, 0")
         self.set_addresses(1, 0, True)             # the reads of iteration 0: K(1) and V(0)

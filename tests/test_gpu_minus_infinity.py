@@ -55,3 +55,38 @@ def test_nothing_but_minus_infinity(dtype, Hq, Hkv, d, lens):
     G = Hq // Hkv
     assert np.isnan(out[0, :G]).all() and np.isfinite(out[0, G:]).all()
     assert (out[1] == 0).all() and np.isfinite(out[2:]).all()
+
+
+@pytest.mark.parametrize("dtype,Hq,Hkv,d", SHAPES)
+@pytest.mark.parametrize("lens,tokens", [([33, 300, 33], [32]), ([290, 33], list(range(288))), ([1601, 900], list(range(0, 1568)))])
+@pytest.mark.parametrize("split", [0, 2])
+def test_own_columns_under_a_plan(dtype, Hq, Hkv, d, lens, tokens, split):
+    """Pieces of a request's own columns whose first tile, or every tile, scores -inf."""
+    q, k, v, bt, L = _batch(dtype, Hq, Hkv, d, lens, 13)
+    finite = _forbid(k, q, bt, tokens, dtype)
+    out, info = run_hip(q, k, v, bt, L, Hq, Hkv, d, dtype, fused_max=-1, split_blocks=split)
+    assert info["variant"] == (1 if dtype == "bf16" else 0)
+    assert_close(out, decode_attention(values(q), finite, values(v), bt, L), dtype, what=f"{dtype} {Hq}/{Hkv}/{d} {lens} split {split}")
+
+
+@pytest.mark.parametrize("dtype,Hq,Hkv,d,members", [("f32", 8, 2, 64, 5), ("bf16", 8, 2, 64, 20), ("bf16", 4, 2, 256, 20),
+                                                  ("bf16", 8, 2, 128, 9), ("bf16", 8, 2, 128, 20), ("bf16", 8, 2, 128, 40)])
+@pytest.mark.parametrize("spared", [[], [511], [200]])
+def test_a_shared_run_under_a_plan(dtype, Hq, Hkv, d, members, spared):
+    """A run of 512 tokens that scores -inf for every member, but for the tokens spared (head_dim 128, bf16: one row tile,
+    teams of two waves, teams of four); the members' own tokens are finite."""
+    lens = [512 + 3 + 5 * j for j in range(members)]
+    q, k, v, bt, L = _batch(dtype, Hq, Hkv, d, lens, 14)
+    for i in range(1, members):
+        bt[i, :32] = bt[0, :32]
+    finite = _forbid(k, q, bt, [t for t in range(512) if t not in spared], dtype, requests=tuple(range(members)))
+    out, info = run_hip(q, k, v, bt, L, Hq, Hkv, d, dtype, fused_max=-1)
+    assert info["groups"] == 1 and info["grouped_requests"] == members
+    assert_close(out, decode_attention(values(q), finite, values(v), bt, L), dtype, what=f"{dtype} {Hq}/{Hkv}/{d} x{members}")
+    q, k, v, bt, L = _batch(dtype, Hq, Hkv, d, [512] * members, 15)       # and nothing else: undefined rows of KV head 0 alone
+    for i in range(1, members):
+        bt[i, :32] = bt[0, :32]
+    _forbid(k, q, bt, range(512), dtype, requests=tuple(range(members)))
+    out, _ = run_hip(q, k, v, bt, L, Hq, Hkv, d, dtype, fused_max=-1)
+    G = Hq // Hkv
+    assert np.isnan(out[:, :G]).all() and np.isfinite(out[:, G:]).all()

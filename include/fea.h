@@ -65,7 +65,10 @@ extern "C" {
                                   when the plan was made (empty, or every block shared) and
                                   has grown since has no piece to stretch: the call then
                                   fills every output row with NaN and
-                                  fea_decode_plan_info reports overflow flag 2            */
+                                  fea_decode_plan_info reports overflow flag 2.  Where the
+                                  earlier calls needed no plan (fused_max) and the table has
+                                  grown past that, every history is cut evenly and shared
+                                  runs are not looked for, until a call plans anew        */
 
 typedef struct fea_kv_pool fea_kv_pool;
 
@@ -266,7 +269,8 @@ int32_t fea_validate_block_tables(const int32_t* block_tables, int32_t table_str
  * vector unit, several times slower (fea_decode_plan_info: kernel
  * variant).  A batch within fea_attn_params.fused_max goes through the matrix
  * cores with either cache type and makes no plan: FEA_FLAG_REUSE_PLAN and
- * FEA_FLAG_REFRESH_PLAN change nothing for it, FEA_FLAG_PLAN_ONLY still makes the plan (for
+ * FEA_FLAG_REFRESH_PLAN change nothing for it (what a refresh does once the table has
+ * grown past that bound is said at the flag), FEA_FLAG_PLAN_ONLY still makes the plan (for
  * fea_decode_plan_info), and after an attention call fea_decode_plan_info
  * reports variant 2 and no groups.
  *

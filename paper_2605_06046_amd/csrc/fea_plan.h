@@ -21,7 +21,7 @@ constexpr int kOpenEnded = -2;        // Item::mlist_off of a request's last pie
 // header words (int32) at the start of the workspace
 enum Hdr {
     H_ITEMS = 0,       // number of work items
-    H_QUEUE = 1,       // unused (kept zero)
+    H_QUEUE = 1,       // zero but while plain_split runs: its workgroups that have read the header
     H_GROUPS = 2,      // prefix groups found
     H_GROUPED = 3,     // requests that belong to a group
     H_SPLIT = 4,       // KV blocks per wave (balanced mode) or per item (fixed split)

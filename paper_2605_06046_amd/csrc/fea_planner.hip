@@ -1016,12 +1016,65 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
     }
 }
 
+// What a refresh does where the workspace holds no plan (the calls before it needed none, and the table has since grown
+// past what is done without one): every (request, KV head) history cut evenly into pieces of its own, nothing looked for
+// that requests share.  Every piece is a share: (slots past a short history's pieces hold none, which only a share of its
+// own may).  The header is written by the workgroup that comes last, when all have seen that there is no plan.
+__device__ __forceinline__ void plain_split(const PlanArgs& a) {
+    int* hdr = reinterpret_cast<int*>(a.ws);
+    ReqDesc* req = reinterpret_cast<ReqDesc*>(a.ws + a.lay.req);
+    SegDesc* segs = reinterpret_cast<SegDesc*>(a.ws + a.lay.segs);
+    int* wave_first = reinterpret_cast<int*>(a.ws + a.lay.wave_first);
+    Item* items = reinterpret_cast<Item*>(a.ws + a.lay.items);
+    const int NE = a.B * a.Hkv, min_piece = max(a.tune.min_piece, 1);
+    const int pieces = max(1, min(a.tune.n_waves / NE, min(a.lay.max_items / NE, a.lay.max_rows / (NE * a.G))));
+    const int n_items = NE * pieces;
+    for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < n_items; x += gridDim.x * blockDim.x) {
+        const int e = x / pieces, p = x - e * pieces, i = e / a.Hkv, g = e - i * a.Hkv;
+        const int L = max(0, min(a.seq_lens[i], a.stride * kBlock)), nb = cdiv(L, kBlock), tiles = (nb + 1) >> 1;
+        const int np = min(pieces, cdiv(tiles, min_piece));
+        if (p < np) {
+            const int each = tiles / np, extra = tiles - each * np, jb = p * each + min(p, extra), je = jb + each + (p < extra ? 1 : 0);
+            const int ce = min(nb, 2 * je);
+            write_item(&items[x], i, g, a.G, ce == nb ? kOpenEnded : -1, 2 * jb, ce, x * a.G, min(L, ce * kBlock));
+        } else {
+            write_item(&items[x], 0, 0, 0, -1, 0, 0, 0, 0);
+        }
+        wave_first[x] = x;
+        if (p == 0) {
+            SegDesc sd;
+            sd.pbase = x * a.G;
+            sd.npieces = np;
+            segs[e] = sd;
+            if (g == 0) {
+                ReqDesc rd;
+                rd.ns_sh = rd.sh_base0 = rd.sh_gstride = rd.sh_pstride = 0;
+                rd.nb = nb;
+                rd.L = L;
+                rd.group = -1;
+                rd.priv_c0 = 0;
+                req[i] = rd;
+            }
+        }
+        if (x == n_items - 1) wave_first[n_items] = wave_first[a.lay.max_items] = n_items;
+    }
+    __syncthreads();   // (the whole workgroup has read the header)
+    if (threadIdx.x == 0 && atomicAdd(&hdr[H_QUEUE], 1) == (int)gridDim.x - 1) {
+        hdr[H_QUEUE] = hdr[H_GROUPS] = hdr[H_GROUPED] = hdr[H_SHARED_BLOCKS] = hdr[H_OVERFLOW] = 0;
+        hdr[H_ITEMS] = hdr[H_WAVES] = n_items;
+        hdr[H_SPLIT] = 2 * cdiv((a.stride + 1) >> 1, pieces);
+        hdr[H_ROWS] = n_items * a.G;
+        hdr[H_VARIANT] = a.variant;
+    }
+}
+
 // A plan made for shorter histories: the requests have grown since (decode steps append tokens, tables got
 // new columns at their ends), nothing else changed.  The split of the work stays; the last piece of every
 // request's own columns is stretched to the request's length now.  (Lengths that shrank would leave the plan
 // wrong - attention over rows that no longer count - but never out of bounds: a piece keeps at least one tile.)
 __global__ __launch_bounds__(256) void refresh_kernel(PlanArgs a) {
     const int* hdr = reinterpret_cast<const int*>(a.ws);
+    if (hdr[H_VARIANT] == 2) { plain_split(a); return; }
     Item* items = reinterpret_cast<Item*>(a.ws + a.lay.items);
     const int n_items = min(hdr[H_ITEMS], a.lay.max_items);
     const int maxL = a.stride * kBlock;

@@ -320,7 +320,8 @@ int32_t fea_decode_attention_static(const fea_attn_params* p,
  * info: HOST int32[9] = { work items, prefix groups, requests in groups,
  * blocks per work item, partial rows, shared-run blocks (sum over groups),
  * kernel variant (0 generic, 1 MFMA, 2 no plan needed, see fused_max), overflow flag (1: the plan did not fit
- * its buffers, 2: FEA_FLAG_REFRESH_PLAN met a request it cannot stretch), sweep waves that
+ * its buffers, 2: FEA_FLAG_REFRESH_PLAN met a request it cannot stretch, or
+ * FEA_FLAG_REUSE_PLAN a workspace whose last call needed no plan), sweep waves that
  * were given a share }. */
 int32_t fea_decode_plan_info(const void* workspace /* DEVICE */, void* hip_stream,
                              int32_t* info /* HOST [9] */);

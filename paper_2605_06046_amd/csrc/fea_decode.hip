@@ -319,6 +319,7 @@ int32_t decode_impl(const fea_attn_params* p, const void* q, const void* k_cache
     sa.Hkv = p->num_kv_heads;
     sa.G = r.G;
     sa.mpt = r.mpt;
+    sa.direct = r.direct;
     sa.fast_shared = (p->head_dim == 128 && (int64_t)B * p->num_q_heads < (1 << 23) && !knobs().no_fast_shared) ? 1 : 0;
     if (r.direct) {
         launch_decode_direct(sa, p->dtype, p->head_dim, r.direct, where[1]);

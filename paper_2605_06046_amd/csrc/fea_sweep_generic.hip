@@ -268,7 +268,9 @@ __global__ __launch_bounds__(256) void merge_kernel(SweepArgs a) {
     T* out = static_cast<T*>(a.out) + (size_t)rowid * D;
     const int c = lane % LPR, slot = lane / LPR;
 
-    if (hdr[H_OVERFLOW]) {   // the plan did not fit its buffers: make it loud
+    const bool no_plan = hdr[H_VARIANT] == 2 && !a.direct;   // a reused plan that is none
+    if (no_plan && rowid == 0 && lane == 0) hdr[H_OVERFLOW] = 2;
+    if (no_plan || hdr[H_OVERFLOW]) {   // that, or the plan did not fit its buffers: make it loud
         for (int e = lane; e < D; e += 64) Elem<T>::store(out + e, __uint_as_float(0x7FC00000u));
         return;
     }
@@ -356,7 +358,7 @@ __global__ __launch_bounds__(256) void merge_rows_kernel(SweepArgs a) {
     constexpr int SLOTS = 64 / LPR;      // rows per wave
     const int lane = threadIdx.x & 63, c = lane % LPR;
     const int rowid = (blockIdx.x * 4 + (threadIdx.x >> 6)) * SLOTS + lane / LPR;
-    const int* hdr = reinterpret_cast<const int*>(a.ws);
+    int* hdr = reinterpret_cast<int*>(a.ws);
     if (rowid >= a.B * a.Hq) return;     // nothing below crosses lane groups
     const int i = rowid / a.Hq, h = rowid - i * a.Hq;
     const int g = h / a.G, hh = h - g * a.G;
@@ -367,7 +369,9 @@ __global__ __launch_bounds__(256) void merge_rows_kernel(SweepArgs a) {
     const float2* ml = reinterpret_cast<const float2*>(a.ws + a.lay.ml);
     const float* pacc = reinterpret_cast<const float*>(a.ws + a.lay.acc);
     T* out = static_cast<T*>(a.out) + (size_t)rowid * D;
-    if (hdr[H_OVERFLOW]) {   // the plan did not fit its buffers: make it loud
+    const bool no_plan = hdr[H_VARIANT] == 2 && !a.direct;   // a reused plan that is none
+    if (no_plan && rowid == 0 && c == 0) hdr[H_OVERFLOW] = 2;
+    if (no_plan || hdr[H_OVERFLOW]) {   // that, or the plan did not fit its buffers: make it loud
         for (int e = c; e < D; e += LPR) Elem<T>::store(out + e, __uint_as_float(0x7FC00000u));
         return;
     }

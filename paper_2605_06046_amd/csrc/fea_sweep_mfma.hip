@@ -788,7 +788,7 @@ __global__ __launch_bounds__(64 * waves_per_group<D>()) void sweep_mfma_kernel(S
     }
     int share = WPG * group + wv;
     const int n_waves = WPG * (int)gridDim.x;
-    const int n_shares = hdr[H_WAVES];
+    const int n_shares = hdr[H_VARIANT] == 2 ? 0 : hdr[H_WAVES];   // (a reused plan that is none: nothing is swept, the merge reports it)
     const int* wave_first = reinterpret_cast<const int*>(a.ws + a.lay.wave_first);
     for (; share < n_shares; share += n_waves) {
         int it = __builtin_amdgcn_readfirstlane(wave_first[share]);

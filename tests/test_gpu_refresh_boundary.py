@@ -62,3 +62,15 @@ def test_a_table_that_outgrows_the_plan_free_kernel(dtype, Hq, Hkv, d, lens):
         assert info["variant"] == (1 if dtype == "bf16" and Hq < 65 else 0) and info["groups"] == 0
     s.step(later, s.bt.shape[1], FEA_FLAG_REFRESH_PLAN)
     s.step(grown, s.bt.shape[1], 0)                    # a plan of its own after all
+
+
+@pytest.mark.parametrize("dtype,Hq,Hkv,d", [("f32", 8, 2, 64), ("bf16", 14, 2, 128)])
+@pytest.mark.parametrize("lens,merge_rows_min", [([640, 33], 0), ([1600], -1)])
+def test_a_reused_plan_that_is_none_is_reported(dtype, Hq, Hkv, d, lens, merge_rows_min):
+    """(Outside the contract: nothing may have changed since the plan.  The rows must be NaN, not what is left in the workspace.)"""
+    width = -(-max(lens) // 16)
+    s = Steps(dtype, Hq, Hkv, d, [n + 32 for n in lens], 4, fused_max=width, merge_rows_min=merge_rows_min)
+    s.step(lens, width, 0)
+    got, info = s.step(lens, width + 1, FEA_FLAG_REUSE_PLAN, check=False)
+    assert np.isnan(got).all() and info["overflow"] == 2 and info["variant"] == 2
+    s.step(lens, width + 2, 0)

@@ -67,8 +67,9 @@ extern "C" {
                                   fills every output row with NaN and
                                   fea_decode_plan_info reports overflow flag 2.  Where the
                                   earlier calls needed no plan (fused_max) and the table has
-                                  grown past that, every history is cut evenly and shared
-                                  runs are not looked for, until a call plans anew        */
+                                  grown past that, or split_blocks > 0 and the table has
+                                  grown by a piece or more, every history is cut evenly and
+                                  shared runs are not looked for, until a call plans anew */
 
 typedef struct fea_kv_pool fea_kv_pool;
 

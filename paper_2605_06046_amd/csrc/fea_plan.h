@@ -30,6 +30,7 @@ enum Hdr {
     H_VARIANT = 7,     // 0 generic, 1 MFMA, 2 no plan (fea_direct.hip)
     H_OVERFLOW = 8,    // planner ran out of item/partial capacity (never by construction)
     H_WAVES = 9,       // sweep waves that received work
+    H_CAPACITY = 10,   // items the workspace it was made in has room for (its sections lie by that); 0: no plan (fea_direct.hip)
     H_WORDS = 64
 };
 

@@ -1013,11 +1013,13 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
         hdr[H_VARIANT] = a.variant;
         hdr[H_OVERFLOW] = overflow ? 1 : 0;
         hdr[H_WAVES] = n_shares;
+        hdr[H_CAPACITY] = a.lay.max_items;
     }
 }
 
 // What a refresh does where the workspace holds no plan (the calls before it needed none, and the table has since grown
-// past what is done without one): every (request, KV head) history cut evenly into pieces of its own, nothing looked for
+// past what is done without one), or one whose sections lie elsewhere (with a fixed split they follow from the table's
+// width, and the table has grown): every (request, KV head) history cut evenly into pieces of its own, nothing looked for
 // that requests share.  Every piece is a share: (slots past a short history's pieces hold none, which only a share of its
 // own may).  The header is written by the workgroup that comes last, when all have seen that there is no plan.
 __device__ __forceinline__ void plain_split(const PlanArgs& a) {
@@ -1065,6 +1067,7 @@ __device__ __forceinline__ void plain_split(const PlanArgs& a) {
         hdr[H_SPLIT] = 2 * cdiv((a.stride + 1) >> 1, pieces);
         hdr[H_ROWS] = n_items * a.G;
         hdr[H_VARIANT] = a.variant;
+        hdr[H_CAPACITY] = a.lay.max_items;
     }
 }
 
@@ -1074,7 +1077,7 @@ __device__ __forceinline__ void plain_split(const PlanArgs& a) {
 // wrong - attention over rows that no longer count - but never out of bounds: a piece keeps at least one tile.)
 __global__ __launch_bounds__(256) void refresh_kernel(PlanArgs a) {
     const int* hdr = reinterpret_cast<const int*>(a.ws);
-    if (hdr[H_VARIANT] == 2) { plain_split(a); return; }
+    if (hdr[H_CAPACITY] != a.lay.max_items) { plain_split(a); return; }
     Item* items = reinterpret_cast<Item*>(a.ws + a.lay.items);
     const int n_items = min(hdr[H_ITEMS], a.lay.max_items);
     const int maxL = a.stride * kBlock;

@@ -74,3 +74,19 @@ def test_a_reused_plan_that_is_none_is_reported(dtype, Hq, Hkv, d, lens, merge_r
     got, info = s.step(lens, width + 1, FEA_FLAG_REUSE_PLAN, check=False)
     assert np.isnan(got).all() and info["overflow"] == 2 and info["variant"] == 2
     s.step(lens, width + 2, 0)
+
+
+@pytest.mark.parametrize("dtype,Hq,Hkv,d", [("f32", 8, 2, 64), ("bf16", 14, 2, 128), ("bf16", 10, 2, 256)])
+@pytest.mark.parametrize("split", [2, 7, 64])
+def test_a_plan_of_fixed_pieces_under_a_wider_table(dtype, Hq, Hkv, d, split):
+    """With a fixed split the workspace's sections follow from the table's width: a refresh under a wider table cannot stretch
+    the plan where it lies.  (Fewer new columns than make a piece: it can, and does.)"""
+    lens = np.array([640, 1000, 33, 7, 500])
+    width = -(-int(lens.max()) // 16)
+    steps = [lens + grown for grown in (0, 17, 400)]
+    s = Steps(dtype, Hq, Hkv, d, [int(x) for x in steps[-1]], 5, fused_max=-1, split_blocks=split)
+    s.step(steps[0], width, 0)
+    s.step(steps[1], width + 2, FEA_FLAG_REFRESH_PLAN)
+    s.step(steps[1], width + 2, FEA_FLAG_REUSE_PLAN)
+    s.step(steps[2], s.bt.shape[1], FEA_FLAG_REFRESH_PLAN)
+    s.step(steps[2], s.bt.shape[1], FEA_FLAG_REFRESH_PLAN)

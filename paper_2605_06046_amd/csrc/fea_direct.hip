@@ -217,16 +217,19 @@ template <int D> struct Tile<bf16_t, D> {
     }
 };
 
-// Waves of a workgroup: eight, two to a SIMD (a lane holds a whole tile: up to 256 registers); at head_dim 256 four.
+// Waves of a workgroup: eight, two to a SIMD (a lane holds a whole tile: up to 256 registers); at head_dim 256 four.  Two
+// where the table has no more than two tiles: the others would only hold registers, of which a workgroup of eight takes
+// all that a compute unit has (bf16 32/8/128, 2000 requests of one block 185 -> 61 us; float32 64/1/64, 250 of one block
+// 18.9 -> 6.9, the vector-unit kernel before 13.2; four requests of one block 4.98 -> 4.68).
 template <int D> constexpr int direct_waves() { return D == 256 ? 4 : 8; }
 // log2 of the largest softmax weight before a row's reference exponent is raised.  float32: any score above it raises it
 // (the rounding of score - reference grows with its size, so the largest weights want theirs near zero).
 template <typename T> constexpr float direct_slack() { return sizeof(T) == 4 ? 0.f : 24.f; }
 
-template <typename T, int D>
-__global__ __launch_bounds__(64 * direct_waves<D>()) void decode_direct_kernel(SweepArgs a, int row_tiles, int pieces) {
+template <typename T, int D, int W>
+__global__ __launch_bounds__(64 * W) void decode_direct_kernel(SweepArgs a, int row_tiles, int pieces) {
     using TileT = Tile<T, D>;
-    constexpr int W = direct_waves<D>(), TB = TileT::TB, NI = TileT::NI, ES = TileT::ES;
+    constexpr int TB = TileT::TB, NI = TileT::NI, ES = TileT::ES;
     constexpr int BLK = kBlock * D * ES;           // bytes of one (block, KV head)
     constexpr int PAD = D + 4;                     // floats between the rows of the fold buffer (16 rows written side by side)
     __shared__ __attribute__((aligned(16))) float s_acc[W][16][PAD];
@@ -390,12 +393,18 @@ __global__ __launch_bounds__(64 * direct_waves<D>()) void decode_direct_kernel(S
         reinterpret_cast<int*>(a.ws)[tid] = tid == H_VARIANT ? 2 : tid == H_WAVES ? (int)gridDim.x * W : 0;
 }
 
-template <typename T, int D>
-void launch(const SweepArgs& a, int pieces, const Launch& L) {
+template <typename T, int D, int W>
+void launch_waves(const SweepArgs& a, int pieces, const Launch& L) {
     const int row_tiles = (a.G + 15) / 16;
-    hipExtLaunchKernelGGL((decode_direct_kernel<T, D>), dim3((unsigned)(a.B * a.Hkv * row_tiles * pieces)), dim3(64 * direct_waves<D>()), 0,
+    hipExtLaunchKernelGGL((decode_direct_kernel<T, D, W>), dim3((unsigned)(a.B * a.Hkv * row_tiles * pieces)), dim3(64 * W), 0,
                           static_cast<hipStream_t>(L.stream), static_cast<hipEvent_t>(L.ev_start), static_cast<hipEvent_t>(L.ev_stop), 0,
                           a, row_tiles, pieces);
+}
+
+template <typename T, int D>
+void launch(const SweepArgs& a, int pieces, const Launch& L) {
+    if (a.stride <= 2 * Tile<T, D>::TB) launch_waves<T, D, 2>(a, pieces, L);
+    else launch_waves<T, D, direct_waves<D>()>(a, pieces, L);
 }
 
 }  // namespace

@@ -52,6 +52,21 @@ def test_edges_of_tiles_waves_and_pieces(dtype, Hq, Hkv, d, lens):
     assert np.array_equal(out, again)
 
 
+@pytest.mark.parametrize("dtype,Hq,Hkv,d", SHAPES)
+@pytest.mark.parametrize("blocks", [1, 2, 3, 4, 5])
+def test_tables_of_up_to_two_tiles_and_just_more(dtype, Hq, Hkv, d, blocks):
+    """Workgroups of two waves up to two tiles of the table's width (a tile: two blocks; one for float32 from head_dim 128 on)."""
+    lens = sorted({0, 1, 15, 16, 17, 16 * blocks - 15, 16 * blocks - 1, 16 * blocks} & set(range(16 * blocks + 1)))
+    q, k, v, bt, L = _batch(dtype, Hq, Hkv, d, lens, 3 * Hq + d + blocks, stride_extra=0)
+    assert bt.shape[1] == blocks
+    out, info = run_hip(q, k, v, bt, L, Hq, Hkv, d, dtype, fused_max=blocks)
+    assert info["variant"] == 2
+    waves = 2 if blocks <= (2 if dtype == "f32" and d >= 128 else 4) else 4 if d == 256 else 8
+    assert info["shares"] == waves * len(lens) * Hkv * -(-Hq // Hkv // 16)
+    assert_close(out, decode_attention(values(q), values(k), values(v), bt, L), dtype, what=f"direct {dtype} {Hq}/{Hkv}/{d} {lens}")
+    assert (out[L == 0] == 0).all()
+
+
 @pytest.mark.parametrize("dtype,Hq,Hkv,d", [("f32", 8, 2, 64), ("bf16", 14, 2, 128)])
 @pytest.mark.parametrize("lens", [[40, 300, 33], [1600, 900]])
 def test_nan_and_infinity_of_a_live_token_stay_with_their_request(dtype, Hq, Hkv, d, lens):

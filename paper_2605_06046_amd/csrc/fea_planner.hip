@@ -726,7 +726,9 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
             if (gi == lane) { ld = my_ld; cnt = my_cnt; run = my_run; }
             else { ld = w.glist[gi]; cnt = u.c.cnt[ld]; run = u.c.run[ld]; }
         };
-        // (sums in float: they only say where the search below starts, and how few waves a small batch gets)
+        // (sums over the groups in float, exact up to 2^24: they only say where the search below starts, and how few waves a small
+        // batch gets.  The quotient of the two is rounded up exactly: one more than that is a tile more in every share of a
+        // batch whose shares are as short as they may be.)
         float u_loc = 0.f, t_loc = 0.f;
         for (int gi = lane; gi < n_groups; gi += 64) {
             int ld, cnt, run;
@@ -735,7 +737,8 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
             u_loc += t * (float)group_weight(cnt);
             t_loc += t;
         }
-        const float U = 16.f * (float)T_pr + wave_sum(u_loc), total_tiles = (float)T_pr + wave_sum(t_loc);
+        const long long U = 16ll * T_pr + (long long)wave_sum(u_loc);
+        const float total_tiles = (float)T_pr + wave_sum(t_loc);
         const int n_act = max(1, (int)fminf((float)a.tune.n_waves, total_tiles * __builtin_amdgcn_rcpf((float)max(a.tune.min_piece, 1))));
         // Pieces of a group's run of T_seg tiles when a share may cost Q.
         auto pieces = [&](int cnt, int T_seg, int Q) {
@@ -748,7 +751,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
             q = max(1, idiv(T_pr + n_pr - 1, n_pr));
             return idiv(T_pr + q - 1, q);
         };
-        int Q = max(16, (int)fminf(U * __builtin_amdgcn_rcpf((float)n_act) + 1.f, 33554432.f));   // the even split
+        int Q = (int)min(1ll << 25, max(16ll, ddiv(U + n_act - 1, n_act)));   // the even split
         int q = 1, n_sh = 0;
         bool searched = false;
         if (fixed_tiles == 0 && n_groups > 0 && n_groups <= 32) {

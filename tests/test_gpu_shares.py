@@ -40,3 +40,22 @@ def test_a_prefix_in_a_table_wider_than_its_histories(extra):
     out, info = run_hip(q, kb, vb, bt, L, 8, 2, 128, "bf16", fused_max=-1)
     assert info["variant"] == 1 and info["groups"] == 2 and info["grouped_requests"] == 7
     assert_close(out, decode_attention(values(q), values(kb), values(vb), bt, L), "bf16", what=f"{extra} columns more")
+
+
+def _shared(dtype, Hq, Hkv, d, members, run, own, seed):
+    """`members` requests on a common run of `run` columns, each with own[i] tokens after it (no dead slots: _batch's are refilled)."""
+    lens = [16 * run + n for n in own]
+    q, k, v, bt, L = _batch(dtype, Hq, Hkv, d, lens, seed)
+    for i in range(1, members):
+        bt[i, :run] = bt[0, :run]
+    return q, k, v, bt, L
+
+
+@pytest.mark.parametrize("dtype,Hq,Hkv,d", [("f32", 8, 2, 64), ("f32", 4, 2, 256), ("bf16", 65, 1, 64)])
+@pytest.mark.parametrize("tokens", [2048, 16384])
+def test_the_even_split_is_rounded_up_and_not_past_that(dtype, Hq, Hkv, d, tokens):
+    """A batch whose shares are as short as they may be (four tiles of two blocks), and come out even."""
+    q, k, v, bt, L = _batch(dtype, Hq, Hkv, d, [tokens], 51)
+    out, info = run_hip(q, k, v, bt, L, Hq, Hkv, d, dtype, fused_max=-1)
+    assert info["split_blocks"] == 8 and info["shares"] == Hkv * tokens // (8 * 16) and info["items"] == info["shares"]
+    assert_close(out, decode_attention(values(q), values(k), values(v), bt, L), dtype, what=f"{dtype} {Hq}/{Hkv}/{d} {tokens}")

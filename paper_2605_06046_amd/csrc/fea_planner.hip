@@ -272,7 +272,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
         unsigned short flw[kGroupReqMax];       // followers (grouped, not leader), for the run detection
         unsigned short glist[kGroupMax];        // then the list of viable leaders
     } w;
-    __shared__ __attribute__((aligned(16))) int s_sums[3][kPlanThreads / 64];
+    __shared__ __attribute__((aligned(16))) int s_sums[4][kPlanThreads / 64];
     __shared__ int s_ngroups, s_ngrouped, s_shared_blocks, s_nflw, s_nest, s_adopt, s_longest[kPlanThreads / 64];
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -657,29 +657,31 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
     const int per = (NE + kPlanThreads - 1) / kPlanThreads;
     const int e0 = tid * per, e1 = min(NE, e0 + per);
     const FastDiv by_hkv(Hkv);
-    int T_pr, tbase;
+    int T_pr, tbase, segs_pr;    // units of the private stream, those before the thread's first segment, segments that have any
     {
         const int per_lead = (nG + kPlanThreads - 1) / kPlanThreads;   // 0, 1 or 2
         const int i0 = tid * per_lead, i1 = min(nG, i0 + per_lead);
-        int local = 0, lt = 0;
+        int local = 0, lt = 0, ls = 0;
         for (int i = i0; i < i1; ++i)
             if (viable(i)) local += u.c.cnt[i];
         for (int e = e0, seen = -1, t = 0; e < e1; ++e) {     // (neighbouring segments mostly are one request's)
             const int i = by_hkv.div(e);
             if (i != seen) { seen = i; t = priv_units(i); }
             lt += t;
+            ls += t > 0 ? 1 : 0;
         }
-        const int tiles_in_wave = wave_scan_incl(lt);        // (both scans share the one barrier)
-        if (lane == 63) s_sums[1][wave] = tiles_in_wave;
+        const int tiles_in_wave = wave_scan_incl(lt), segs_in_wave = wave_scan_incl(ls);   // (the scans share the one barrier)
+        if (lane == 63) { s_sums[1][wave] = tiles_in_wave; s_sums[3][wave] = segs_in_wave; }
         int total;
         int base = block_scan_excl(local, s_sums[0], total);
         tbase = tiles_in_wave - lt;
-        T_pr = 0;
+        T_pr = segs_pr = 0;
 #pragma unroll
         for (int w = 0; w < kPlanThreads / 64; ++w) {
             const int part = s_sums[1][w];
             tbase += w < wave ? part : 0;
             T_pr += part;
+            segs_pr += s_sums[3][w];
         }
         for (int i = i0; i < i1; ++i)
             if (viable(i)) {
@@ -738,7 +740,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
             t_loc += t;
         }
         const long long U = 16ll * T_pr + (long long)wave_sum(u_loc);
-        const float total_tiles = (float)T_pr + wave_sum(t_loc);
+        const float total_tiles = (float)(T_pr - per_seg * segs_pr) + wave_sum(t_loc);   // (tiles to sweep: what a segment is charged is none)
         const int n_act = max(1, (int)fminf((float)a.tune.n_waves, total_tiles * __builtin_amdgcn_rcpf((float)max(a.tune.min_piece, 1))));
         // Pieces of a group's run of T_seg tiles when a share may cost Q.
         auto pieces = [&](int cnt, int T_seg, int Q) {

@@ -59,3 +59,13 @@ def test_the_even_split_is_rounded_up_and_not_past_that(dtype, Hq, Hkv, d, token
     out, info = run_hip(q, k, v, bt, L, Hq, Hkv, d, dtype, fused_max=-1)
     assert info["split_blocks"] == 8 and info["shares"] == Hkv * tokens // (8 * 16) and info["items"] == info["shares"]
     assert_close(out, decode_attention(values(q), values(k), values(v), bt, L), dtype, what=f"{dtype} {Hq}/{Hkv}/{d} {tokens}")
+
+
+@pytest.mark.parametrize("Hq,Hkv,d", [(8, 8, 64), (8, 8, 128), (8, 8, 256)])
+def test_no_more_shares_than_the_tiles_are_worth(Hq, Hkv, d):
+    """A share holds four tiles or more on average, of tiles that are swept: what a segment is charged is none."""
+    q, k, v, bt, L = _shared("bf16", Hq, Hkv, d, 24, 8, [20] * 24, 61)
+    out, info = run_hip(q, k, v, bt, L, Hq, Hkv, d, "bf16", fused_max=-1)
+    assert info["groups"] == 1 and info["grouped_requests"] == 24
+    assert info["shares"] <= Hkv * (4 + 24) // 4         # one row tile of the run's four tiles, and each request's own one
+    assert_close(out, decode_attention(values(q), values(k), values(v), bt, L), "bf16", what=f"{Hq}/{Hkv}/{d}")

@@ -99,8 +99,10 @@ typedef struct fea_attn_params {
                                launch merges (a shared block is then read once per request, which
                                at this size the L2 serves).  0: the library decides, from an
                                estimate of both ways' durations (about: up to 64 MB of KV
-                               histories at full table rows; far more for float32 caches and
-                               query groups the matrix-core sweep does not take); < 0: never;
+                               histories at full table rows, up to 300 MB with few query heads
+                               per KV head and one workgroup to a compute unit; nearly always
+                               for float32 caches and query groups the matrix-core sweep does
+                               not take); < 0: never;
                                > 0: every batch whose table rows have at most this many entries */
 } fea_attn_params;
 

@@ -71,13 +71,18 @@ static int cu_count() {
 }
 
 // The kernel that needs no plan (fea_direct.hip) reads every request's whole history: how many workgroups it has
-// without cutting histories, and how many tiles a wave of it sweeps one after the other.
+// without cutting histories, how many tiles a history is at the table's width, and how many of them a wave sweeps one
+// after the other (two waves where there are no more than two tiles).
 static int64_t direct_groups(const fea_attn_params* p, int64_t B) {
     return B * p->num_kv_heads * ((p->num_q_heads / p->num_kv_heads + 15) / 16);
 }
+static int64_t direct_tiles(const fea_attn_params* p, int64_t stride) {
+    const int64_t tile_blocks = p->dtype == FEA_DTYPE_F32 && p->head_dim >= 128 ? 1 : 2;
+    return (stride + tile_blocks - 1) / tile_blocks;
+}
 static int64_t direct_rounds(const fea_attn_params* p, int64_t stride) {
-    const int64_t tile_blocks = p->dtype == FEA_DTYPE_F32 && p->head_dim >= 128 ? 1 : 2, waves = p->head_dim == 256 ? 4 : 8;
-    return ((stride + tile_blocks - 1) / tile_blocks + waves - 1) / waves;
+    const int64_t tiles = direct_tiles(p, stride), waves = tiles <= 2 ? 2 : p->head_dim == 256 ? 4 : 8;
+    return (tiles + waves - 1) / waves;
 }
 
 // Pieces a history is cut into there.  Workgroups that leave most of the chip idle are worth cutting, up to one per
@@ -92,24 +97,36 @@ static int64_t direct_pieces(const fea_attn_params* p, int64_t B, int64_t stride
     return rounds - (rounds + n - 1) / n >= 3 ? n : 1;
 }
 
-// Whether it is expected to beat plan + sweep + merge.  It reads what requests share once per request (at 5 to 5.6 TB/s
-// whether from L2 or HBM), which the host cannot know; so it is taken where even a batch that shares everything would
-// lose more to the three launches than to the reading: on the matrix-core path up to 64 MB of KV histories (measured,
-// nothing shared: 8 requests of 1024 tokens 13.5 against 24.8 us, 32 of 1024 (134 MB) 27.0 against 44.5).  The
-// vector-unit sweep costs 26 to 120 us to start with, and from some hundred thousand (query row, token) pairs on time
-// in proportion to them (fitted to 1 to 128 requests, 128 to 4096 tokens, head dims 64 to 256, query groups of 4 to 65).
+// Whether it is expected to beat plan + sweep + merge.  It reads what requests share once per request (5 to 6 TB/s from
+// HBM, 8 and more where the L2s hold it), which the host cannot know; nor does it know whether the plan would serve other
+// layers of the step as well.  So it is taken where it wins (or loses next to nothing) whatever is shared and however often
+// the plan is used again.  Measured on 5000 matrix-core and 1600 vector-unit shapes (1 to 4096 requests, 16 to 65536 tokens,
+// query groups of 1 to 96, 0, 90 and 98 % shared), alone and against a reused plan.  On the matrix-core path:
+//  - up to 64 MB of KV histories.  Nothing shared: 8 requests of 1024 tokens 13.5 against 24.8 us.
+//  - up to 100 MB in few enough workgroups (6 to a compute unit; each has a few us of start-up): bf16 32/8/128, 32 requests of
+//    752 tokens, 19.0 against 35.2 and, of the reused plan, 24.5; 90 % shared 12.1 against 33.9 and 21.9.  In eight rounds of
+//    workgroups, 256 requests of 80 tokens, 31.7 against 37.8 and 26.2.
+//  - tables of one or two tiles up to 128 MB: 2000 requests of one block 61 against 103 us (above it, a reused plan wins by a tenth).
+//  - few query heads (the sweep's strength is many), one round of workgroups of up to 1 MB each (1.33 at head_dim 256), or two of
+//    256 KB: bf16 32/8/128, 32 requests of 1520 tokens 36.1 against 52.1 and 40.9, 90 % shared 19.2 against 39.7 and 27.3.
+//    Longer histories lose to a reused plan: 8/2/64, 128 requests of 4112 tokens, 90 % shared, 28.1 against 38.6 and 22.2.
+// The vector-unit sweep costs 26 to 120 us to start with, and from some hundred thousand (query row, token) pairs on time in
+// proportion to them; the plan-free kernel loses to it only with one or two query heads per KV head on histories that are
+// shared and long (float32 4/4/32, 35 requests of 23472 tokens, 98 % shared: 181 against 99 us).
 static bool direct_pays(const fea_attn_params* p, int64_t B, int64_t stride, int variant) {
     const bool f32 = p->dtype == FEA_DTYPE_F32;
-    const int64_t row_tiles = (p->num_q_heads / p->num_kv_heads + 15) / 16;
+    const double group = (double)(p->num_q_heads / p->num_kv_heads), groups = (double)direct_groups(p, B), cus = cu_count();
     const double tokens = (double)stride * kBlock, dd = p->head_dim / 64.0;
-    const double bytes = (double)B * tokens * p->num_kv_heads * p->head_dim * (f32 ? 8.0 : 4.0) * (double)row_tiles;
-    if (variant == 1) return bytes <= 64e6;
+    const double per_group = tokens * p->head_dim * (f32 ? 8.0 : 4.0), bytes = groups * per_group;   // K and V read by a workgroup, by all
+    if (variant == 1) {
+        if (bytes <= 64e6 || (bytes <= 100e6 && groups <= 6 * cus) || (bytes <= 128e6 && direct_tiles(p, stride) <= 2)) return true;
+        return group <= 4 && ((groups <= cus && per_group <= (p->head_dim == 256 ? 1.33e6 : 1 << 20)) || (groups <= 2 * cus && per_group <= 1 << 18));
+    }
     const int64_t pieces = direct_pieces(p, B, stride);
-    const double serial_us = 2.7 * (double)((direct_rounds(p, stride) + pieces - 1) / pieces);   // one workgroup's tiles, a round after the other
-    const double direct_us = 7.0 + (pieces > 1 ? 4.0 : 0.0) + std::max(serial_us, bytes / 5.0e6);
-    const double G = (double)(p->num_q_heads / p->num_kv_heads);   // (the vector sweep passes over its tokens once per 4 or 16 stacked rows)
-    const double base = B < 4 ? 20.0 + 1.5 * G : std::min(30.0 + 4.0 * G, 120.0);
-    const double planned_us = (B < 16 ? base : std::max(94.0, base)) * (p->head_dim >= 128 ? 1.4 : 1.0) +
+    const double serial_us = 2.0 * (double)((direct_rounds(p, stride) + pieces - 1) / pieces);   // one workgroup's tiles, a round after the other
+    const double direct_us = 7.0 + (pieces > 1 ? 4.0 : 0.0) + std::max(serial_us, bytes / 8.0e6);
+    const double base = B < 4 ? 20.0 + 1.5 * group : std::min(30.0 + 4.0 * group, 120.0);
+    const double planned_us = (B < 16 ? base : std::max(94.0, base)) * (p->head_dim >= 128 ? 1.4 : 1.0) +   // (it passes over its tokens once per 4 or 16 stacked rows)
                               (f32 ? 0.027e-3 : 0.0175e-3) * std::pow(dd, 1.6) * (double)(B * p->num_q_heads) * tokens;
     return 1.1 * direct_us < planned_us;
 }

@@ -844,36 +844,50 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
     // to the segment's end.  (The units before the first tile may be all a share has left: that makes no piece.  A
     // share holds more than those, so its first units always make one.)
     auto for_pieces = [&](int units, int& k, int& rem, auto&& f) {
-        int u = 0;
-        while (u < units) {
-            int take;
-            bool starts = false;
-            if (fixed_tiles > 0) {
-                take = min(units - u, fixed_tiles);
-            } else {
-                take = min(units - u, q - rem);
-                starts = rem == 0;
-            }
-            const int jb = max(u - per_seg, 0), je = u + take - per_seg;
-            if (je > jb) f(jb, je, starts, k);
-            u += take;
-            if (fixed_tiles == 0) {
-                rem += take;
-                if (rem == q) { rem = 0; ++k; }
-            }
+        if (units == 0) return;
+        const int tiles = units - per_seg;
+        if (fixed_tiles > 0) {
+            for (int j = 0; j < tiles; j += fixed_tiles) f(j, min(tiles, j + fixed_tiles), false, k);
+            return;
         }
+        int room = q - rem - per_seg;
+        bool starts = rem == 0;
+        if (room == 0) { room = q; starts = true; ++k; }
+        for (int j = 0;;) {
+            const int take = min(tiles - j, room);
+            f(j, j + take, starts, k);
+            j += take;
+            room -= take;
+            if (j >= tiles) break;
+            room = q;
+            starts = true;
+            ++k;
+        }
+        rem = q - room;
+        if (rem == q) { rem = 0; ++k; }
     };
     const WideDiv by_q(max(q, 1));
     const int k_start = by_q.div(tbase), rem_start = tbase - k_start * q;
 
-    // ---- item counts of the thread's segments, scanned in stream order
+    // ---- item counts of the thread's segments, scanned in stream order.  The pieces are not walked for that (a batch of few
+    // long histories has hundreds to a segment, one thread's): a segment has a piece for the share it starts in - unless its
+    // charge is all that is left there - and one for every share it reaches into.
     int li = 0;
     {
-        int k = k_start, rem = rem_start;
+        const WideDiv by_fixed(max(fixed_tiles, 1));
+        int rem = rem_start;
         for (int e = e0, seen = -1, t = 0; e < e1; ++e) {
             const int i = by_hkv.div(e);
             if (i != seen) { seen = i; t = priv_units(i); }
-            for_pieces(t, k, rem, [&](int, int, bool, int) { ++li; });
+            if (t == 0) continue;
+            if (fixed_tiles > 0) {
+                li += by_fixed.div(t + fixed_tiles - 1);
+            } else {
+                const int end = rem + t, last = by_q.div(end - 1);      // (end < 2^31: a share's units and a segment's)
+                li += last + (q - rem > per_seg ? 1 : 0);
+                rem = end - last * q;
+                if (rem == q) rem = 0;
+            }
         }
     }
     int priv_items;

@@ -633,7 +633,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
     auto viable = [&](int i) { return s_lead[i] == i && u.c.cnt[i] >= 2 && u.c.run[i] >= a.tune.min_run; };
 
     // ---- member-list offsets (exclusive scan over leaders) and the list of groups; and, for the cost model below, the
-    // private stream: request i owns Hkv * priv_units(i) consecutive units, KV head by KV head.  Its segments (request,
+    // private stream: request i owns Hkv * priv_units(i) consecutive units (its tiles and its charge), KV head by KV head.  Its segments (request,
     // KV head) are the entries the threads share out, so that a batch of few requests still spreads over many lanes.
     auto run_of = [&](int i) {   // shared columns of request i (0 if ungrouped)
         if (i >= nG) return 0;
@@ -645,19 +645,16 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
     // (query rows, the first tile's way through the pipeline, the partial rows).  Measured, per segment more in a share:
     // 1.2 us at head_dim 64 and 128, 2.4 at 256, where a tile takes 0.9, 1.5 to 1.9 and 1.65.  Shares cut by tiles alone
     // ended that much apart (22 to 32 us in a batch of head_dim 64, 22 to 27 since), and the batch ends with the last.
-    // Whole calls, 0, 1 and 2 tiles charged: head_dim 64 56.8, 54.6 and 57.8 us; 256 56.5, 52.5 and 51.9; four layers
-    // under a refreshed plan 149.8, 135.9 and 134.9, under a new one 176, 168 and 173; 256 requests in 8 groups 174, 170
-    // and 173.
-    const int per_seg = a.variant == 1 && a.split_user == 0 ? kSegmentTiles : 0;
-    auto priv_units = [&](int i) {
-        const int t = ((((len_of(i) + kBlock - 1) / kBlock) - run_of(i)) + 1) >> 1;
-        return t > 0 ? t + per_seg : 0;
-    };
+    // One tile charged against none, attention under a reused plan, mean over 1500 shapes: head_dim 64 0.95 of the time
+    // where something is shared and 0.99 where nothing is, 256 0.93 and 0.99, 128 0.98 and 0.99.  Not charged at head_dim 128
+    // where the requests share runs and have less than a tile of their own for every wave: the shares of the runs, which
+    // teams sweep, come out longer for the sake of private ones that hardly count (up to 1.24 times the time, in the mean the same).
+    auto priv_tiles = [&](int i) { return ((((len_of(i) + kBlock - 1) / kBlock) - run_of(i)) + 1) >> 1; };
     const int NE = B * Hkv;
     const int per = (NE + kPlanThreads - 1) / kPlanThreads;
     const int e0 = tid * per, e1 = min(NE, e0 + per);
     const FastDiv by_hkv(Hkv);
-    int T_pr, tbase, segs_pr;    // units of the private stream, those before the thread's first segment, segments that have any
+    int T_pr, tbase, segs_pr, per_seg;    // units of the private stream, those before the thread's first segment, segments that have any, a segment's charge
     {
         const int per_lead = (nG + kPlanThreads - 1) / kPlanThreads;   // 0, 1 or 2
         const int i0 = tid * per_lead, i1 = min(nG, i0 + per_lead);
@@ -666,7 +663,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
             if (viable(i)) local += u.c.cnt[i];
         for (int e = e0, seen = -1, t = 0; e < e1; ++e) {     // (neighbouring segments mostly are one request's)
             const int i = by_hkv.div(e);
-            if (i != seen) { seen = i; t = priv_units(i); }
+            if (i != seen) { seen = i; t = priv_tiles(i); }
             lt += t;
             ls += t > 0 ? 1 : 0;
         }
@@ -674,15 +671,21 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
         if (lane == 63) { s_sums[1][wave] = tiles_in_wave; s_sums[3][wave] = segs_in_wave; }
         int total;
         int base = block_scan_excl(local, s_sums[0], total);
+        int sbase = segs_in_wave - ls;
         tbase = tiles_in_wave - lt;
         T_pr = segs_pr = 0;
 #pragma unroll
         for (int w = 0; w < kPlanThreads / 64; ++w) {
-            const int part = s_sums[1][w];
+            const int part = s_sums[1][w], part_s = s_sums[3][w];
             tbase += w < wave ? part : 0;
+            sbase += w < wave ? part_s : 0;
             T_pr += part;
-            segs_pr += s_sums[3][w];
+            segs_pr += part_s;
         }
+        const bool few_own = teams && total > 0 && T_pr < a.tune.n_waves;
+        per_seg = a.variant == 1 && a.split_user == 0 && !few_own ? kSegmentTiles : 0;
+        tbase += per_seg * sbase;
+        T_pr += per_seg * segs_pr;
         for (int i = i0; i < i1; ++i)
             if (viable(i)) {
                 u.c.moff[i] = base;
@@ -838,6 +841,11 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
     }
     __syncthreads();
     const int fixed_tiles = s_plan[0], q = s_plan[1], n_sh = s_plan[2], rows_sh = s_plan[3];
+
+    auto priv_units = [&](int i) {
+        const int t = priv_tiles(i);
+        return t > 0 ? t + per_seg : 0;
+    };
 
     // Cutting one segment of `units` into pieces, walking along the stream: `rem` units of share `k` are used up
     // at the segment's start.  Calls f(jb, je, starts_share, k) for every piece of tiles, in order, and moves (k, rem)

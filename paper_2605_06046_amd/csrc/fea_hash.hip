@@ -37,10 +37,11 @@ struct HashArgs {
     int64_t n_tokens, n_hashes;
 };
 
-// Lane c of (lo, hi) = x; x and c are wave-uniform.  (Sources in scalar registers, written by the scalar unit: the hardware
-// orders those before the vector unit's read.)
+// Lane c of (lo, hi) = x; x and c are wave-uniform.  Whichever unit wrote their registers: the scalar unit reads c (the lane
+// must be in M0, two scalar sources are one too many), which the hardware orders, and a value the vector unit has just
+// written wants two wait states before another vector instruction reads it, which the write of M0 and the s_nop are.
 __device__ __forceinline__ void put_lane(int& lo, int& hi, unsigned long long x, int c) {
-    asm("s_mov_b32 m0, %4\n\tv_writelane_b32 %0, %2, m0\n\tv_writelane_b32 %1, %3, m0"   // (a second scalar source must be M0)
+    asm("s_mov_b32 m0, %4\n\ts_nop 0\n\tv_writelane_b32 %0, %2, m0\n\tv_writelane_b32 %1, %3, m0"
         : "+v"(lo), "+v"(hi) : "s"((uint32_t)x), "s"((uint32_t)(x >> 32)), "s"(c) : "m0");
 }
 

@@ -360,7 +360,8 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
     // column group) pairs are spread flat over the threads, six at a time so that
     // their loads are in flight together; a mismatch lowers the follower's run with
     // an LDS atomic.  Columns below from(i) are known to agree and are not read, and columns past the
-    // longest history are not looked at (a table is often as wide as the longest history that is allowed).
+    // longest history are not looked at (a table is often as wide as the longest history that is allowed) - but
+    // where run_kernel has found the runs, the search for nested ones goes over the table's width.
     int columns = a.stride;
     if (!a.pre) {
         int longest = 0;
@@ -646,9 +647,13 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
     // 1.2 us at head_dim 64 and 128, 2.4 at 256, where a tile takes 0.9, 1.5 to 1.9 and 1.65.  Shares cut by tiles alone
     // ended that much apart (22 to 32 us in a batch of head_dim 64, 22 to 27 since), and the batch ends with the last.
     // One tile charged against none, attention under a reused plan, mean over 1500 shapes: head_dim 64 0.95 of the time
-    // where something is shared and 0.99 where nothing is, 256 0.93 and 0.99, 128 0.98 and 0.99.  Not charged at head_dim 128
-    // where the requests share runs and have less than a tile of their own for every wave: the shares of the runs, which
-    // teams sweep, come out longer for the sake of private ones that hardly count (up to 1.24 times the time, in the mean the same).
+    // where something is shared and 0.99 where nothing is, 256 0.93 and 0.99, 128 0.98 and 0.99.  Not charged
+    //  - at head_dim 128 where the requests share runs and have less than a tile of their own for every wave: the shares of the
+    //    runs, which teams sweep, come out longer for the sake of private ones that hardly count (up to 1.24 times the time, in
+    //    the mean the same);
+    //  - where nothing is shared and every wave has 24 tiles or more: memory binds such a stream whatever the shares (0.995 in
+    //    the mean), and even ones do better (sweep of 64 requests of 4224 to 5120 tokens, 32/8/128, 236 against 231 us; 512 of
+    //    512 to 4096, 64/8/128, 897 against 890; with 4 to 8 tiles to a wave the charge takes 0.98 of the time).
     auto priv_tiles = [&](int i) { return ((((len_of(i) + kBlock - 1) / kBlock) - run_of(i)) + 1) >> 1; };
     const int NE = B * Hkv;
     const int per = (NE + kPlanThreads - 1) / kPlanThreads;
@@ -682,8 +687,8 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
             T_pr += part;
             segs_pr += part_s;
         }
-        const bool few_own = teams && total > 0 && T_pr < a.tune.n_waves;
-        per_seg = a.variant == 1 && a.split_user == 0 && !few_own ? kSegmentTiles : 0;
+        const bool few_own = teams && total > 0 && T_pr < a.tune.n_waves, long_own = total == 0 && T_pr / 24 >= a.tune.n_waves;
+        per_seg = a.variant == 1 && a.split_user == 0 && !few_own && !long_own ? kSegmentTiles : 0;
         tbase += per_seg * sbase;
         T_pr += per_seg * segs_pr;
         for (int i = i0; i < i1; ++i)

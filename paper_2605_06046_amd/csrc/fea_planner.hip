@@ -761,7 +761,8 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
             q = max(1, idiv(T_pr + n_pr - 1, n_pr));
             return idiv(T_pr + q - 1, q);
         };
-        int Q = (int)min(1ll << 25, max(16ll, ddiv(U + n_act - 1, n_act)));   // the even split
+        int Q = U + n_act <= INT_MAX ? idiv((int)U + n_act - 1, n_act) : (int)min(1ll << 25, ddiv(U + n_act - 1, n_act));   // the even split
+        Q = min(1 << 25, max(16, Q));
         int q = 1, n_sh = 0;
         bool searched = false;
         if (fixed_tiles == 0 && n_groups > 0 && n_groups <= 32) {
@@ -887,16 +888,16 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
     // charge is all that is left there - and one for every share it reaches into.
     int li = 0;
     {
-        const WideDiv by_fixed(max(fixed_tiles, 1));
+        const float rcp_q = __builtin_amdgcn_rcpf((float)q);
         int rem = rem_start;
         for (int e = e0, seen = -1, t = 0; e < e1; ++e) {
             const int i = by_hkv.div(e);
             if (i != seen) { seen = i; t = priv_units(i); }
             if (t == 0) continue;
             if (fixed_tiles > 0) {
-                li += by_fixed.div(t + fixed_tiles - 1);
+                li += idiv(t + fixed_tiles - 1, fixed_tiles);
             } else {
-                const int end = rem + t, last = by_q.div(end - 1);      // (end < 2^31: a share's units and a segment's)
+                const int end = rem + t, last = near_div(end - 1, q, rcp_q);   // (end < 2^31: a share's units and a segment's; at most as many shares as waves)
                 li += last + (q - rem > per_seg ? 1 : 0);
                 rem = end - last * q;
                 if (rem == q) rem = 0;

@@ -97,8 +97,8 @@ static int64_t direct_pieces(const fea_attn_params* p, int64_t B, int64_t stride
     return rounds - (rounds + n - 1) / n >= 3 ? n : 1;
 }
 
-// Whether it is expected to beat plan + sweep + merge.  It reads what requests share once per request (5 to 6 TB/s from
-// HBM, 8 and more where the L2s hold it), which the host cannot know; nor does it know whether the plan would serve other
+// Whether it is expected to beat plan + sweep + merge.  It reads what requests share once per request (5.0 to 5.9 TB/s
+// from HBM, 8 and more where the L2s hold it), which the host cannot know; nor does it know whether the plan would serve other
 // layers of the step as well.  So it is taken where it wins (or loses next to nothing) whatever is shared and however often
 // the plan is used again.  Measured on 5000 matrix-core and 1600 vector-unit shapes (1 to 4096 requests, 16 to 65536 tokens,
 // query groups of 1 to 96, 0, 90 and 98 % shared), alone and against a reused plan.  On the matrix-core path:

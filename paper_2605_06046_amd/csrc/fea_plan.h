@@ -24,7 +24,7 @@ enum Hdr {
     H_QUEUE = 1,       // zero but while plain_split runs: its workgroups that have read the header
     H_GROUPS = 2,      // prefix groups found
     H_GROUPED = 3,     // requests that belong to a group
-    H_SPLIT = 4,       // KV blocks per wave (balanced mode) or per item (fixed split)
+    H_SPLIT = 4,       // KV blocks per wave, what its segments are charged included (balanced mode), or per item (fixed split)
     H_ROWS = 5,        // partial rows in use
     H_SHARED_BLOCKS = 6,
     H_VARIANT = 7,     // 0 generic, 1 MFMA, 2 no plan (fea_direct.hip)

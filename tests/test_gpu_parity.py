@@ -744,7 +744,7 @@ def test_random_shapes_against_the_oracle(seed):
     print(seed, dtype, d, G * Hkv, Hkv, groups, info, assert_close(out, oracle_for(wl, bt, lens), dtype, what=f"random shape {seed}"))
 
 
-# ---- batches small enough for one launch (no plan, no partial results) ----
+# ---- batches small enough to need no plan (one launch, or two where histories are cut into pieces) ----
 
 def test_c1_takes_one_launch_by_default():
     wl = W.generate(W.CONFIGS["c1"])

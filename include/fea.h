@@ -248,6 +248,8 @@ int32_t fea_validate_block_tables(const int32_t* block_tables, int32_t table_str
  * against its whole KV history (Section 2.1; the full-cache sweep per decode
  * step of Section 1).  seq_lens[i] counts the tokens attended to; the current
  * token's K/V must already be in the cache.  seq_lens[i] == 0 gives a zero row.
+ * A score of -inf has weight 0 next to any finite one; where a history holds nothing
+ * else the row is NaN.
  *
  * Layouts (all contiguous):
  *   q, out        [B, num_q_heads, head_dim]

@@ -51,8 +51,8 @@ struct __attribute__((packed, aligned(4))) Tok4 { uint32_t t[4]; };
 // Bound: the chain, two mixing steps per chunk one after the other.  One wave runs it in scalar registers (a 64-bit
 // product is six scalar instructions of one issue slot each; on the vector unit its multiplications take four slots
 // each): a wave's worth of leaves is handed over lane by lane, the hashes are collected lane by lane and stored
-// together.  64 requests of 4224 to 5120 tokens: 48.1 us with the chain in vector registers and through LDS, 33.4 now
-// (84 ns a chunk; launch, tokens and leaves are the other 6 us).
+// together.  64 requests of 4224 to 5120 tokens: 48.1 us with the chain in vector registers and through LDS, 34.0 now
+// (87 ns a chunk; launch, tokens and leaves are the other 6 us).
 constexpr int kHashThreads = 512;
 __global__ __launch_bounds__(kHashThreads) void chunk_hash_kernel(HashArgs a) {
     __shared__ unsigned long long s_leaf[kLeafTile];

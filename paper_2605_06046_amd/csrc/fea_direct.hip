@@ -18,12 +18,13 @@
 // left over, rounded: 2^-17 of the weight is lost), the denominator as unrounded float32.  Against weights in
 // float32, over 56 shapes of 33 to 2000 tokens: the same error against float64 to within 2e-6 of it.
 //
-// Bound: latency (the chain length, table row and q -> K -> V -> fold over the waves) for short histories, 7 to 8 us
-// in all; then memory, at 5.0 to 5.9 TB/s where the chip is full (8 and more where what requests share sits in L2); with float32 and few workgroups the matrix cores'
-// float32 rate (a block of 16 tokens is 64 instructions of 32 cycles at head_dim 128, whatever part of the 16 query
-// rows is real).  Measured against the vector-unit kernel it replaces: float32 8/2/64, 4 requests of 320 tokens
-// 11.6 -> 9.1 us a call; float32 32/8/128, 16 requests of 1152 to 2048 tokens 78.7 -> 35.0; against plan, sweep
-// and merge: bf16 28/4/128, 8 requests of 90 to 700 tokens 23.6 -> 9.1.
+// Bound: latency (the chain length, table row and q -> K -> V -> fold over the waves) for short histories, 6 to 8 us
+// in all; then memory, at 5.0 to 5.9 TB/s where the chip is full (8 and more where what requests share sits in L2; a compute
+// unit fetches 53 GB/s at most); with float32, more than four query heads and few workgroups the matrix cores' float32 rate (a
+// block of 16 tokens is 64 instructions of 32 cycles at head_dim 128, whatever part of the 16 query rows is real).  Measured
+// against the vector-unit kernel it replaces: float32 8/2/64, 4 requests of 320 tokens 11.6 -> 9.1 us a call; float32
+// 32/8/128, 16 requests of 1152 to 2048 tokens 78.7 -> 34.6; against plan, sweep and merge: bf16 28/4/128, 8 requests of 90
+// to 700 tokens 23.6 -> 9.1.
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 
@@ -47,20 +48,49 @@ __device__ __forceinline__ uint32_t bf16_rne(float v) {
     return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
 }
 
-// 16 bytes of a cache row hold EPC elements; a lane's registers of one tile, and the two products.
-template <typename T, int D> struct Tile;
+// Sums, maxima and exchanges across the halves and the rows of 16 lanes of a wave, without a detour through LDS.
+struct Pair { float a, b; };
+__device__ __forceinline__ Pair swap32(float x, float y) {   // the upper half of x against the lower half of y
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return {__uint_as_float(r[0]), __uint_as_float(r[1])};
+}
+__device__ __forceinline__ Pair swap16(float x, float y) {   // the odd rows of x against the even rows of y
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return {__uint_as_float(r[0]), __uint_as_float(r[1])};
+}
+template <int CTRL> __device__ __forceinline__ float lanes_moved(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float max_over_kg(float x) {
+    const Pair p = swap32(x, x);
+    x = fmaxf(p.a, p.b);
+    const Pair q = swap16(x, x);
+    return fmaxf(q.a, q.b);
+}
+__device__ __forceinline__ float sum_over_kg(float x) {
+    const Pair p = swap32(x, x);
+    x = p.a + p.b;
+    const Pair q = swap16(x, x);
+    return q.a + q.b;
+}
 
-template <int D> struct Tile<float, D> {
+// A lane's registers of one tile, and the two products, for row tiles of R query heads.  A lane works out the weights of
+// PN tokens for one head.
+template <typename T, int D, int R> struct Tile;
+
+template <int D> struct Tile<float, D, 16> {
     static constexpr int TB = D >= 128 ? 1 : 2;            // blocks per tile
+    static constexpr int PN = 4 * TB;
     static constexpr int KC = D / 16;                      // chunks of a K row per lane
     static constexpr int VH = D >= 64 ? D / 64 : 1;        // chunks of a V row per lane
     static constexpr int NI = 4 * VH;                      // output products (head_dim 32: half of their rows count)
     static constexpr int ES = 4;
     f32x4 k[TB][KC], v[TB][4][VH], q[KC];
 
-    __device__ __forceinline__ void load_q(const char* row, int kg, bool live) {
+    __device__ __forceinline__ void load_q(const char* rows, int nh, int n, int kg) {
+        const char* row = rows + min(n, nh - 1) * (D * ES);
 #pragma unroll
-        for (int j = 0; j < KC; ++j) q[j] = live ? *reinterpret_cast<const f32x4*>(row + (4 * j + kg) * 16) : f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < KC; ++j) q[j] = n < nh ? *reinterpret_cast<const f32x4*>(row + (4 * j + kg) * 16) : f32x4{0.f, 0.f, 0.f, 0.f};
     }
     __device__ __forceinline__ void load_k(int b, const char* blk, int n, int kg) {
 #pragma unroll
@@ -73,11 +103,18 @@ template <int D> struct Tile<float, D> {
             for (int h = 0; h < VH; ++h)
                 v[b][r][h] = *reinterpret_cast<const f32x4*>(blk + (uint32_t)((4 * kg + r) * (D * 4) + (D >= 64 ? n : n & 7) * 16 + h * 256));
     }
-    __device__ __forceinline__ void zero_v(int b, int r) {
+    __device__ __forceinline__ void mask(float (&p)[PN], int rest, int, int kg) {
 #pragma unroll
-        for (int h = 0; h < VH; ++h) v[b][r][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int b = 0; b < TB; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (16 * b + 4 * kg + r >= rest) {
+                    p[4 * b + r] = -INFINITY;
+#pragma unroll
+                    for (int h = 0; h < VH; ++h) v[b][r][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+                }
     }
-    __device__ __forceinline__ void scores(f32x4 (&s)[TB]) {
+    __device__ __forceinline__ void scores(float (&p)[PN]) {
         // Partial sums of 8 products, added up in pairs: a single chain over the head dims would be one rounding after
         // another, which doubles the error of the scores.
         constexpr int GC = KC < 4 ? KC : 4, Y = D == 256 ? 1 : GC / 2;    // chunks taken together, partial sums over them (head_dim 256: 16 products each, 8 spill registers)
@@ -99,10 +136,11 @@ template <int D> struct Tile<float, D> {
                     for (int e = 0; e < 4; ++e) c[0][e] += c[1][e];
                 }
                 const f32x4 part = (c[0][0] + c[0][1]) + (c[0][2] + c[0][3]);
-                s[b] = j0 == 0 ? part : s[b] + part;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) p[4 * b + r] = j0 == 0 ? part[r] : p[4 * b + r] + part[r];
             }
     }
-    __device__ __forceinline__ void accumulate(const float (&p)[TB * 4], f32x4 (&o)[NI]) {
+    __device__ __forceinline__ void accumulate(const float (&p)[PN], f32x4 (&o)[NI], int) {
         // The sums over a block start at zero and are added to the running ones: a short chain of products, and a chain
         // of one addition per block (the error grows with the length of a chain).
 #pragma unroll
@@ -119,8 +157,18 @@ template <int D> struct Tile<float, D> {
                 for (int e = 0; e < 4; ++e) o[4 * h + e] += c[e];
             }
     }
+    static __device__ __forceinline__ int head(int n) { return n; }
+    static __device__ __forceinline__ bool one_of_row(int, int kg) { return kg == 0; }   // (of the lanes that hold a row's sums)
+    static __device__ __forceinline__ float row_max(float x) { return max_over_kg(x); }
+    static __device__ __forceinline__ float row_sum(float x) { return sum_over_kg(x); }
+    static __device__ __forceinline__ void rescale(f32x4 (&o)[NI], float al) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) o[i] *= al;
+    }
     // product i = 4 h + e, output row m = 4 kg + r: dim 64 h + 4 m + e
-    __device__ __forceinline__ static void to_lds(float* row, const f32x4 (&o)[NI], int kg) {
+    template <int PAD> static __device__ __forceinline__ void to_lds(float (*rows)[PAD], const f32x4 (&o)[NI], int nh, int n, int kg) {
+        if (n >= nh) return;
+        float* row = rows[n];
 #pragma unroll
         for (int h = 0; h < VH; ++h)
 #pragma unroll
@@ -130,17 +178,18 @@ template <int D> struct Tile<float, D> {
     }
 };
 
-template <int D> struct Tile<bf16_t, D> {
-    static constexpr int TB = 2;
+template <int D> struct Tile<bf16_t, D, 16> {
+    static constexpr int TB = 2, PN = 8;
     static constexpr int KC = D / 32;
     static constexpr int VH = D == 256 ? 2 : 1;
     static constexpr int NI = D / 16;
     static constexpr int ES = 2;
     u32x4 k[TB][KC], v[TB][4][VH], q[KC];
 
-    __device__ __forceinline__ void load_q(const char* row, int kg, bool live) {
+    __device__ __forceinline__ void load_q(const char* rows, int nh, int n, int kg) {
+        const char* row = rows + min(n, nh - 1) * (D * ES);
 #pragma unroll
-        for (int j = 0; j < KC; ++j) q[j] = live ? ld16(row + (4 * j + kg) * 16) : u32x4{0u, 0u, 0u, 0u};
+        for (int j = 0; j < KC; ++j) q[j] = n < nh ? ld16(row + (4 * j + kg) * 16) : u32x4{0u, 0u, 0u, 0u};
     }
     __device__ __forceinline__ void load_k(int b, const char* blk, int n, int kg) {
 #pragma unroll
@@ -152,11 +201,19 @@ template <int D> struct Tile<bf16_t, D> {
 #pragma unroll
             for (int h = 0; h < VH; ++h) v[b][r][h] = ld16(blk + (uint32_t)((4 * kg + r) * (D * 2) + (D >= 128 ? n : n & 7) * 16 + h * 256));
     }
-    __device__ __forceinline__ void zero_v(int b, int r) {
+    __device__ __forceinline__ void mask(float (&p)[PN], int rest, int, int kg) {
 #pragma unroll
-        for (int h = 0; h < VH; ++h) v[b][r][h] = u32x4{0u, 0u, 0u, 0u};
+        for (int b = 0; b < TB; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (16 * b + 4 * kg + r >= rest) {
+                    p[4 * b + r] = -INFINITY;
+#pragma unroll
+                    for (int h = 0; h < VH; ++h) v[b][r][h] = u32x4{0u, 0u, 0u, 0u};
+                }
     }
-    __device__ __forceinline__ void scores(f32x4 (&s)[TB]) {
+    __device__ __forceinline__ void scores(float (&p)[PN]) {
+        f32x4 s[TB];
 #pragma unroll
         for (int b = 0; b < TB; ++b) s[b] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -164,8 +221,12 @@ template <int D> struct Tile<bf16_t, D> {
 #pragma unroll
             for (int b = 0; b < TB; ++b)
                 s[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, k[b][j]), __builtin_bit_cast(bf16x8, q[j]), s[b], 0, 0, 0);
+#pragma unroll
+        for (int b = 0; b < TB; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) p[4 * b + r] = s[b][r];
     }
-    __device__ __forceinline__ void accumulate(const float (&p)[TB * 4], f32x4 (&o)[NI], int n) {
+    __device__ __forceinline__ void accumulate(const float (&p)[PN], f32x4 (&o)[NI], int n) {
         bf16x8 hi, lo;
 #pragma unroll
         for (int x = 0; x < 8; ++x) {
@@ -199,8 +260,18 @@ template <int D> struct Tile<bf16_t, D> {
             o[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, lo, o[i], 0, 0, 0);
         }
     }
+    static __device__ __forceinline__ int head(int n) { return n; }
+    static __device__ __forceinline__ bool one_of_row(int, int kg) { return kg == 0; }
+    static __device__ __forceinline__ float row_max(float x) { return max_over_kg(x); }
+    static __device__ __forceinline__ float row_sum(float x) { return sum_over_kg(x); }
+    static __device__ __forceinline__ void rescale(f32x4 (&o)[NI], float al) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) o[i] *= al;
+    }
     // product i, output row m = 4 kg + r: dim 128 (i / 8) + 8 m + i % 8; head_dim 64: 8 m + i, or 8 (m - 8) + 4 + i
-    __device__ __forceinline__ static void to_lds(float* row, const f32x4 (&o)[NI], int kg) {
+    template <int PAD> static __device__ __forceinline__ void to_lds(float (*rows)[PAD], const f32x4 (&o)[NI], int nh, int n, int kg) {
+        if (n >= nh) return;
+        float* row = rows[n];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int m = 4 * kg + r;
@@ -218,6 +289,138 @@ template <int D> struct Tile<bf16_t, D> {
     }
 };
 
+// float32, query groups of up to four heads: products of 4x4, sixteen of them to an instruction of 8 cycles.  A 16x16 product
+// of four real rows does four times the work, and its 32 cycles bound the batches that L2 serves.  Measured against it, over
+// 180 shapes: 0.86 of the time in the mean (0.63 to 1.03); 32/8/128, 16 requests of 1152 to 2048 tokens 34.6 -> 31.1 us,
+// 32/8/32, 200 requests of 1600 tokens, 90 % shared, 94 -> 57.  Not with two such sets for five to eight heads: 1.06 of the
+// time (0.87 to 1.34: twice the registers for q, and short histories wait for its loads).
+//     S = K Q^T      product (tq, kg) = lane / 4: token rows 4 tq .. 4 tq + 3 of a block (lane n = 4 tq + row), chunks 4 j + kg;
+//                    its four sums over kg are exchanged so that lane (n, kg) ends with token 4 tq + kg and head n % 4
+//     O += P V       one token's weights are one product's A operand, handed to all products whose lanes hold that token's V
+//                    row: a load of 16 bytes a lane covers 64 / LR rows, and instruction x takes, for each of them, the weights
+//                    of the x-th of the products in their lanes (the row's token follows from that: token_of).
+template <int CB, int X> __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, CB, X, 0);
+}
+template <int D> struct Tile<float, D, 4> {
+    static constexpr int TB = D >= 128 ? 1 : 2, PN = TB;   // blocks per tile; a lane has one token of each
+    static constexpr int KC = D / 16, NI = 4, ES = 4;
+    static constexpr int LR = D / 4;                       // lanes that a V row takes
+    static constexpr int NX = LR / 4;                      // loads of V per block, products per V row
+    static constexpr int CB = NX == 2 ? 1 : NX == 4 ? 2 : NX == 8 ? 3 : 4;
+    f32x4 k[TB][KC], v[TB][NX], q[KC];
+
+    static __device__ __forceinline__ int token_of(int x, int n, int kg) {   // of the V row that this lane holds of load x
+        const int from = (n + 16 * kg) / LR * NX + x;      // the product whose weights it meets
+        return 4 * (from & 3) + (from >> 2);
+    }
+    __device__ __forceinline__ void load_q(const char* rows, int nh, int n, int kg) {
+        const char* row = rows + min(head(n), nh - 1) * (D * ES);
+#pragma unroll
+        for (int j = 0; j < KC; ++j) q[j] = head(n) < nh ? *reinterpret_cast<const f32x4*>(row + (4 * j + kg) * 16) : f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    __device__ __forceinline__ void load_k(int b, const char* blk, int n, int kg) {
+#pragma unroll
+        for (int j = 0; j < KC; ++j) k[b][j] = *reinterpret_cast<const f32x4*>(blk + (uint32_t)(n * (D * 4) + kg * 16 + j * 64));
+    }
+    __device__ __forceinline__ void load_v(int b, const char* blk, int n, int kg) {
+#pragma unroll
+        for (int x = 0; x < NX; ++x)
+            v[b][x] = *reinterpret_cast<const f32x4*>(blk + (uint32_t)(token_of(x, n, kg) * (D * 4) + (n + 16 * kg) % LR * 16));
+    }
+    __device__ __forceinline__ void mask(float (&p)[PN], int rest, int n, int kg) {
+#pragma unroll
+        for (int b = 0; b < TB; ++b) {
+            if (16 * b + (n & ~3) + kg >= rest) p[b] = -INFINITY;
+#pragma unroll
+            for (int x = 0; x < NX; ++x)
+                if (16 * b + token_of(x, n, kg) >= rest) v[b][x] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+    __device__ __forceinline__ void scores(float (&p)[PN]) {
+        constexpr int GC = KC < 8 ? KC : 8;                // products in one chain
+#pragma unroll
+        for (int b = 0; b < TB; ++b) {
+            f32x4 s;
+#pragma unroll
+            for (int j0 = 0; j0 < KC; j0 += GC) {
+                f32x4 c[4];
+#pragma unroll
+                for (int j = j0; j < j0 + GC; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) c[e] = mfma4<0, 0>(k[b][j][e], q[j][e], j == j0 ? f32x4{0.f, 0.f, 0.f, 0.f} : c[e]);
+                const f32x4 part = (c[0] + c[1]) + (c[2] + c[3]);
+                s = j0 == 0 ? part : s + part;
+            }
+            const Pair even = swap32(s[0], s[2]), odd = swap32(s[1], s[3]);   // lower half: tokens 0 and 1, upper: 2 and 3
+            const Pair all = swap16(even.a + even.b, odd.a + odd.b);
+            p[b] = all.a + all.b;
+        }
+    }
+    template <int X> __device__ __forceinline__ void take(int b, float w, f32x4 (&c)[4]) {
+        if constexpr (X < NX) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) c[e] = mfma4<CB, X>(w, v[b][X][e], X == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : c[e]);
+            take<X + 1>(b, w, c);
+        }
+    }
+    __device__ __forceinline__ void accumulate(const float (&p)[PN], f32x4 (&o)[NI], int) {
+        // (chains as short as above: a block's sums start at zero)
+#pragma unroll
+        for (int b = 0; b < TB; ++b) {
+            f32x4 c[4];
+            take<0>(b, p[b], c);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] += c[e];
+        }
+    }
+    static __device__ __forceinline__ int head(int n) { return n & 3; }
+    static __device__ __forceinline__ bool one_of_row(int n, int kg) { return n < 4 && kg == 0; }
+    static __device__ __forceinline__ float row_max(float x) {
+        x = fmaxf(x, lanes_moved<0x124>(x));               // rotated by 4 and by 8 within 16 lanes
+        x = fmaxf(x, lanes_moved<0x128>(x));
+        return max_over_kg(x);
+    }
+    static __device__ __forceinline__ float row_sum(float x) {
+        x += lanes_moved<0x124>(x);
+        x += lanes_moved<0x128>(x);
+        return sum_over_kg(x);
+    }
+    static __device__ __forceinline__ void rescale(f32x4 (&o)[NI], float al) {
+        const f32x4 f = {lanes_moved<0x00>(al), lanes_moved<0x55>(al), lanes_moved<0xAA>(al), lanes_moved<0xFF>(al)};   // of heads 0..3
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] *= f;
+    }
+    // o[e][r]: head r, dim 4 (lane % LR) + e; the 64 / LR groups of lanes hold sums over tokens of their own
+    template <int PAD> static __device__ __forceinline__ void to_lds(float (*rows)[PAD], const f32x4 (&o)[NI], int, int n, int kg) {
+        const int at = 4 * ((n + 16 * kg) % LR);
+        if constexpr (LR == 64) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) *reinterpret_cast<f32x4*>(&rows[r][at]) = f32x4{o[0][r], o[1][r], o[2][r], o[3][r]};
+        } else {
+            f32x4 x, y;                                    // lower half: heads 0 and 1, upper: 2 and 3
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const Pair a = swap32(o[e][0], o[e][2]), b = swap32(o[e][1], o[e][3]);
+                x[e] = a.a + a.b;
+                y[e] = b.a + b.b;
+            }
+            if constexpr (LR == 32) {
+                *reinterpret_cast<f32x4*>(&rows[kg & 2][at]) = x;
+                *reinterpret_cast<f32x4*>(&rows[(kg & 2) + 1][at]) = y;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {              // row kg of lanes: head kg
+                    const Pair a = swap16(x[e], y[e]);
+                    x[e] = a.a + a.b;
+                    if constexpr (LR == 8) x[e] += lanes_moved<0x128>(x[e]);
+                }
+                if (LR == 16 || n < 8) *reinterpret_cast<f32x4*>(&rows[kg][at]) = x;
+            }
+        }
+    }
+};
+
 // Waves of a workgroup: eight, two to a SIMD (a lane holds a whole tile: up to 256 registers); at head_dim 256 four.  Two
 // where the table has no more than two tiles: the others would only hold registers, of which a workgroup of eight takes
 // all that a compute unit has (bf16 32/8/128, 2000 requests of one block 185 -> 61 us; float32 64/1/64, 250 of one block
@@ -227,14 +430,14 @@ template <int D> constexpr int direct_waves() { return D == 256 ? 4 : 8; }
 // (the rounding of score - reference grows with its size, so the largest weights want theirs near zero).
 template <typename T> constexpr float direct_slack() { return sizeof(T) == 4 ? 0.f : 24.f; }
 
-template <typename T, int D, int W>
+template <typename T, int D, int R, int W>
 __global__ __launch_bounds__(64 * W) void decode_direct_kernel(SweepArgs a, int row_tiles, int pieces) {
-    using TileT = Tile<T, D>;
-    constexpr int TB = TileT::TB, NI = TileT::NI, ES = TileT::ES;
+    using TileT = Tile<T, D, R>;
+    constexpr int TB = TileT::TB, NI = TileT::NI, ES = TileT::ES, PN = TileT::PN;
     constexpr int BLK = kBlock * D * ES;           // bytes of one (block, KV head)
     constexpr int PAD = D + 4;                     // floats between the rows of the fold buffer (16 rows written side by side)
-    __shared__ __attribute__((aligned(16))) float s_acc[W][16][PAD];
-    __shared__ float2 s_ml[W][16];
+    __shared__ __attribute__((aligned(16))) float s_acc[W][R][PAD];
+    __shared__ float2 s_ml[W][R];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 15, kg = lane >> 4;
@@ -256,14 +459,14 @@ __global__ __launch_bounds__(64 * W) void decode_direct_kernel(SweepArgs a, int 
     const int raw_len = a.seq_lens[i];
     int ids = a.stride > 0 ? ids_from(first) : 0;
     TileT tile;
-    tile.load_q(static_cast<const char*>(a.q) + ((size_t)i * a.Hq + g * a.G + 16 * rt + min(n, nh - 1)) * (D * ES), kg, n < nh);
+    tile.load_q(static_cast<const char*>(a.q) + ((size_t)i * a.Hq + g * a.G + 16 * rt) * (D * ES), nh, n, kg);
     const int L = __builtin_amdgcn_readfirstlane(min(max(raw_len, 0), a.stride * kBlock));
     const int nb = (L + kBlock - 1) / kBlock, ntiles = (nb + TB - 1) / TB;
 
     f32x4 o[NI];
 #pragma unroll
     for (int j = 0; j < NI; ++j) o[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float m = kLowest, l = 0.f;                    // of head n: reference exponent (alike in its four lanes), this lane's part of the denominator
+    float m = kLowest, l = 0.f;                    // of the lane's head: reference exponent (alike in all its lanes), this lane's part of the denominator
     const char* kb[TB];
     const char* vb[TB];
     auto locate = [&](int t, int at) {             // the blocks of tile t, whose ids sit in lanes TB at + b
@@ -284,8 +487,8 @@ __global__ __launch_bounds__(64 * W) void decode_direct_kernel(SweepArgs a, int 
         for (int b = 0; b < TB; ++b) tile.load_v(b, vb[b], n, kg);
         int at = 0;
         for (int t = first; t < ntiles; t += step) {
-            f32x4 s[TB];
-            tile.scores(s);
+            float p[PN];
+            tile.scores(p);
             const bool more = t + step < ntiles;
             if (more) {                            // K of the next tile while this one's weights and second product are worked out
                 if (++at == 64 / TB) { ids = ids_from(t + step); at = 0; }
@@ -293,55 +496,37 @@ __global__ __launch_bounds__(64 * W) void decode_direct_kernel(SweepArgs a, int 
 #pragma unroll
                 for (int b = 0; b < TB; ++b) tile.load_k(b, kb[b], n, kg);
             }
-            float p[TB * 4];
-            const int pos = t * (TB * kBlock);
-            const bool ragged = pos + TB * kBlock > L;
-#pragma unroll
-            for (int b = 0; b < TB; ++b)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) p[4 * b + r] = s[b][r];
-            if (ragged) {                          // tokens past the end: weight 0, and whatever their V rows hold is left out
-#pragma unroll
-                for (int b = 0; b < TB; ++b)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        if (pos + 16 * b + 4 * kg + r >= L) { p[4 * b + r] = -INFINITY; tile.zero_v(b, r); }
-            }
+            const int rest = L - t * (TB * kBlock);
+            // tokens past the end: weight 0, and whatever their V rows hold is left out
+            if (rest < TB * kBlock) tile.mask(p, rest, n, kg);
             float mx = p[0];
 #pragma unroll
-            for (int y = 1; y < TB * 4; ++y) mx = fmaxf(mx, p[y]);
+            for (int y = 1; y < PN; ++y) mx = fmaxf(mx, p[y]);
             mx *= a.scale_log2;
             // (bfloat16: raised to the row maximum only when a score outgrows it by 2^24, which the float32 sums absorb
             // without loss; the first score above -inf always does)
             if (__any(mx > m + direct_slack<T>())) {
-                mx = fmaxf(mx, __shfl_xor(mx, 16));
-                mx = fmaxf(mx, __shfl_xor(mx, 32));
-                const float mn = fmaxf(m, mx);
+                const float mn = fmaxf(m, TileT::row_max(mx));
                 const float al = exp2_fast(m - mn);   // (0 where the reference was the lowest number)
                 l *= al;
-#pragma unroll
-                for (int j = 0; j < NI; ++j) o[j] *= al;
+                TileT::rescale(o, al);
                 m = mn;
             }
 #pragma unroll
-            for (int y = 0; y < TB * 4; ++y) {
+            for (int y = 0; y < PN; ++y) {
                 p[y] = exp2_fast(fmaf(p[y], a.scale_log2, -m));
                 l += p[y];
             }
-            if constexpr (ES == 4) tile.accumulate(p, o);
-            else tile.accumulate(p, o, n);
+            tile.accumulate(p, o, n);
             if (more) {
 #pragma unroll
                 for (int b = 0; b < TB; ++b) tile.load_v(b, vb[b], n, kg);
             }
         }
     }
-    l += __shfl_xor(l, 16);
-    l += __shfl_xor(l, 32);
-    if (n < nh) {
-        TileT::to_lds(&s_acc[wave][n][0], o, kg);
-        if (kg == 0) s_ml[wave][n] = make_float2(m, l);
-    }
+    TileT::template to_lds<PAD>(s_acc[wave], o, nh, n, kg);
+    l = TileT::row_sum(l);
+    if (TileT::one_of_row(n, kg)) s_ml[wave][TileT::head(n)] = make_float2(m, l);
     __syncthreads();
 
     // fold the waves (fixed order) at the common reference exponent
@@ -394,18 +579,26 @@ __global__ __launch_bounds__(64 * W) void decode_direct_kernel(SweepArgs a, int 
         reinterpret_cast<int*>(a.ws)[tid] = tid == H_VARIANT ? 2 : tid == H_WAVES ? (int)gridDim.x * W : 0;
 }
 
-template <typename T, int D, int W>
+template <typename T, int D, int R, int W>
 void launch_waves(const SweepArgs& a, int pieces, const Launch& L) {
     const int row_tiles = (a.G + 15) / 16;
-    hipExtLaunchKernelGGL((decode_direct_kernel<T, D, W>), dim3((unsigned)(a.B * a.Hkv * row_tiles * pieces)), dim3(64 * W), 0,
+    hipExtLaunchKernelGGL((decode_direct_kernel<T, D, R, W>), dim3((unsigned)(a.B * a.Hkv * row_tiles * pieces)), dim3(64 * W), 0,
                           static_cast<hipStream_t>(L.stream), static_cast<hipEvent_t>(L.ev_start), static_cast<hipEvent_t>(L.ev_stop), 0,
                           a, row_tiles, pieces);
 }
 
+template <typename T, int D, int R>
+void launch_rows(const SweepArgs& a, int pieces, const Launch& L) {
+    if (a.stride <= 2 * Tile<T, D, R>::TB) launch_waves<T, D, R, 2>(a, pieces, L);
+    else launch_waves<T, D, R, direct_waves<D>()>(a, pieces, L);
+}
+
 template <typename T, int D>
 void launch(const SweepArgs& a, int pieces, const Launch& L) {
-    if (a.stride <= 2 * Tile<T, D>::TB) launch_waves<T, D, 2>(a, pieces, L);
-    else launch_waves<T, D, direct_waves<D>()>(a, pieces, L);
+    if constexpr (sizeof(T) == 4) {
+        if (a.G <= 4) return launch_rows<T, D, 4>(a, pieces, L);
+    }
+    launch_rows<T, D, 16>(a, pieces, L);
 }
 
 }  // namespace

@@ -37,22 +37,52 @@ struct HashArgs {
     int64_t n_tokens, n_hashes;
 };
 
-// Lane c of (lo, hi) = x; x and c are wave-uniform.  Whichever unit wrote their registers: the scalar unit reads c (the lane
-// must be in M0, two scalar sources are one too many), which the hardware orders, and a value the vector unit has just
-// written wants two wait states before another vector instruction reads it, which the write of M0 and the s_nop are.
-__device__ __forceinline__ void put_lane(int& lo, int& hi, unsigned long long x, int c) {
-    asm("s_mov_b32 m0, %4\n\ts_nop 0\n\tv_writelane_b32 %0, %2, m0\n\tv_writelane_b32 %1, %3, m0"
-        : "+v"(lo), "+v"(hi) : "s"((uint32_t)x), "s"((uint32_t)(x >> 32)), "s"(c) : "m0");
+// h + gamma, wave-uniform, and lane C of (lo, hi) = h.  Whichever unit wrote h: the scalar unit's reads of it are ordered by
+// the hardware, and a value the vector unit has just written wants two wait states before another vector instruction reads
+// it, which the two scalar additions are.
+template <int C> __device__ __forceinline__ unsigned long long put_lane(int& lo, int& hi, unsigned long long h, unsigned long long gamma) {
+    uint32_t nl, nh;
+    asm("s_add_u32 %0, %4, %6\n\ts_addc_u32 %1, %5, %7\n\tv_writelane_b32 %2, %4, %8\n\tv_writelane_b32 %3, %5, %8"
+        : "=&s"(nl), "=&s"(nh), "+v"(lo), "+v"(hi)
+        : "s"((uint32_t)h), "s"((uint32_t)(h >> 32)), "s"((uint32_t)gamma), "s"((uint32_t)(gamma >> 32)), "n"(C) : "scc");
+    return (unsigned long long)nl | ((unsigned long long)nh << 32);
+}
+
+// The multipliers of a mixing step and the chain's increment, kept in scalar registers: as literals they would make two
+// words of an instruction, and one wave alone waits for what it fetches.
+struct MixConsts { unsigned long long m1, m2, gamma; };
+__device__ __forceinline__ unsigned long long low64(unsigned long long x, unsigned long long m) {
+    const uint32_t xl = (uint32_t)x, xh = (uint32_t)(x >> 32), ml = (uint32_t)m, mh = (uint32_t)(m >> 32);
+    const uint32_t hi = __umulhi(xl, ml) + xl * mh + xh * ml;
+    return (unsigned long long)(xl * ml) | ((unsigned long long)hi << 32);
+}
+__device__ __forceinline__ unsigned long long mixs(unsigned long long x, const MixConsts& k) {
+    x = low64(x ^ (x >> 30), k.m1);
+    x = low64(x ^ (x >> 27), k.m2);
+    return x ^ (x >> 31);
+}
+
+// Chunks 0 .. 15 of a batch: leaves and hashes in lanes 0 .. 15; hg: the last hash + gamma.
+constexpr int kBatch = 16;
+template <int C, bool SHORT> __device__ __forceinline__ void chain(unsigned long long& hg, const MixConsts& k, int left, int leaf_lo, int leaf_hi, int& out_lo, int& out_hi) {
+    if constexpr (C < kBatch) {
+        if (SHORT && C >= left) return;
+        const unsigned long long x = (unsigned long long)(uint32_t)__builtin_amdgcn_readlane(leaf_lo, C) |
+                                     ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane(leaf_hi, C) << 32);
+        hg = put_lane<C>(out_lo, out_hi, mixs(mixs(hg, k) ^ x, k), k.gamma);
+        chain<C + 1, SHORT>(hg, k, left, leaf_lo, leaf_hi, out_lo, out_hi);
+    }
 }
 
 // Four neighbouring tokens, loadable from any 4-byte boundary.
 struct __attribute__((packed, aligned(4))) Tok4 { uint32_t t[4]; };
 
-// Bound: the chain, two mixing steps per chunk one after the other.  One wave runs it in scalar registers (a 64-bit
-// product is six scalar instructions of one issue slot each; on the vector unit its multiplications take four slots
-// each): a wave's worth of leaves is handed over lane by lane, the hashes are collected lane by lane and stored
-// together.  64 requests of 4224 to 5120 tokens: 48.1 us with the chain in vector registers and through LDS, 34.0 now
-// (87 ns a chunk; launch, tokens and leaves are the other 6 us).
+// Bound: the chain, two mixing steps per chunk one after the other, 43 instructions of one wave at 4.1 cycles each (a wave
+// issues one every four).  It runs in scalar registers (a 64-bit product is six scalar instructions of one issue slot each;
+// on the vector unit its multiplications take four slots each); leaves are handed over and hashes collected in batches of 16
+// lanes, whose numbers are then part of the instructions, and the constants sit in registers.  64 requests of 4224 to 5120
+// tokens: 48.1 us with the chain in vector registers and through LDS, 34.0 with lanes numbered at run time and literals (87 ns a
+// chunk), 30.8 now (74; launch, tokens and leaves are the other 7 us).
 constexpr int kHashThreads = 512;
 __global__ __launch_bounds__(kHashThreads) void chunk_hash_kernel(HashArgs a) {
     __shared__ unsigned long long s_leaf[kLeafTile];
@@ -63,7 +93,7 @@ __global__ __launch_bounds__(kHashThreads) void chunk_hash_kernel(HashArgs a) {
     const int64_t h0 = a.hash_offsets[i];
     if (h0 < 0 || h0 + C > a.n_hashes) return;
     const int32_t* tok = a.tokens + t0;
-    unsigned long long h = kH0D;                                  // carried by the first wave across tiles
+    unsigned long long hg = kH0D + kGammaD;                       // carried by the first wave across tiles
     for (int64_t base = 0; base < C; base += kLeafTile) {
         const int n = __builtin_amdgcn_readfirstlane((int)(C - base < kLeafTile ? C - base : kLeafTile));
         for (int c = tid; c < n; c += kHashThreads) {             // parallel phase: independent leaves
@@ -83,26 +113,20 @@ __global__ __launch_bounds__(kHashThreads) void chunk_hash_kernel(HashArgs a) {
         }
         __syncthreads();
         if (wave == 0) {                                          // sequential phase: the chain
-            h = (unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)h) |
-                ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(h >> 32)) << 32);
-            for (int c0 = 0; c0 < n; c0 += 64) {
-                const unsigned long long leaf = c0 + tid < n ? s_leaf[c0 + tid] : 0ull;
+            hg = (unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)hg) |
+                 ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(hg >> 32)) << 32);
+            MixConsts k = {0xBF58476D1CE4E5B9ull, 0x94D049BB133111EBull, kGammaD};
+            asm("" : "+s"(k.m1), "+s"(k.m2), "+s"(k.gamma));
+            const int at = tid & (kBatch - 1);
+            unsigned long long leaf = s_leaf[at];                 // (past the end: anything, which nothing is made of)
+            for (int c0 = 0; c0 < n; c0 += kBatch) {
                 const int leaf_lo = (int)(uint32_t)leaf, leaf_hi = (int)(uint32_t)(leaf >> 32);
+                leaf = s_leaf[min(c0 + kBatch, kLeafTile - kBatch) + at];
                 int out_lo = 0, out_hi = 0;
-                const int m = n - c0 < 64 ? n - c0 : 64;
-                auto link = [&](int c) {
-                    const unsigned long long x = (unsigned long long)(uint32_t)__builtin_amdgcn_readlane(leaf_lo, c) |
-                                                 ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane(leaf_hi, c) << 32);
-                    h = mixd(mixd(h + kGammaD) ^ x);
-                    put_lane(out_lo, out_hi, h, c);
-                };
-                if (m == 64) {
-#pragma unroll 8
-                    for (int c = 0; c < 64; ++c) link(c);
-                } else {
-                    for (int c = 0; c < m; ++c) link(c);
-                }
-                if (tid < m) a.hashes[h0 + base + c0 + tid] = (unsigned long long)(uint32_t)out_lo | ((unsigned long long)(uint32_t)out_hi << 32);
+                if (n - c0 >= kBatch) chain<0, false>(hg, k, kBatch, leaf_lo, leaf_hi, out_lo, out_hi);
+                else chain<0, true>(hg, k, n - c0, leaf_lo, leaf_hi, out_lo, out_hi);
+                if (tid < kBatch && c0 + tid < n)
+                    a.hashes[h0 + base + c0 + tid] = (unsigned long long)(uint32_t)out_lo | ((unsigned long long)(uint32_t)out_hi << 32);
             }
         }
         __syncthreads();

@@ -237,7 +237,24 @@ def fea_decode_workspace_bytes(params: AttnParams, B: int, table_stride: int) ->
 
 
 def _dev_ptr(t):
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+def _stream_handle(torch, stream):
+    """The HIP stream of a torch.cuda.Stream; None: the current one, without building a Stream object for it (2 to 3 us,
+    a third of what a call of one launch costs the host)."""
+    return stream.cuda_stream if stream is not None else torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+
+
+def _check_gpu_tensors(torch, names, tensors, block_tables, seq_lens) -> None:
+    for k, t in enumerate(tensors):
+        if not (t.is_cuda and t.is_contiguous()):
+            raise ValueError(f"{names[k]} must be a contiguous GPU tensor")
+    if block_tables.dtype != torch.int32 or seq_lens.dtype != torch.int32:
+        raise ValueError("block_tables and seq_lens must be int32")
+
+
+_ATTENTION_TENSORS = ("q", "k_cache", "v_cache", "block_tables", "seq_lens", "out", "workspace")
 
 
 def fea_decode_attention(params: AttnParams, q, k_cache, v_cache, block_tables, seq_lens, out, workspace,
@@ -245,32 +262,21 @@ def fea_decode_attention(params: AttnParams, q, k_cache, v_cache, block_tables, 
     """All tensor arguments are contiguous torch tensors on the GPU; `stream` is a
     torch.cuda.Stream (default: the current one).  Asynchronous."""
     import torch
-    for name, t in (("q", q), ("k_cache", k_cache), ("v_cache", v_cache), ("block_tables", block_tables),
-                    ("seq_lens", seq_lens), ("out", out), ("workspace", workspace)):
-        if not t.is_cuda or not t.is_contiguous():
-            raise ValueError(f"{name} must be a contiguous GPU tensor")
-    if block_tables.dtype != torch.int32 or seq_lens.dtype != torch.int32:
-        raise ValueError("block_tables and seq_lens must be int32")
-    st = stream if stream is not None else torch.cuda.current_stream()
+    _check_gpu_tensors(torch, _ATTENTION_TENSORS, (q, k_cache, v_cache, block_tables, seq_lens, out, workspace),
+                       block_tables, seq_lens)
     _check(load_library().fea_decode_attention(
-        C.byref(params), _dev_ptr(q), _dev_ptr(k_cache), _dev_ptr(v_cache), _dev_ptr(block_tables),
-        block_tables.shape[1], _dev_ptr(seq_lens), q.shape[0], _dev_ptr(out), _dev_ptr(workspace),
-        workspace.numel() * workspace.element_size(), C.c_void_p(st.cuda_stream)))
+        C.byref(params), q.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(), block_tables.data_ptr(),
+        block_tables.size(1), seq_lens.data_ptr(), q.size(0), out.data_ptr(), workspace.data_ptr(),
+        workspace.nbytes, _stream_handle(torch, stream)))
 
 
 def fea_decode_attention_static(params: AttnParams, q, k_cache, v_cache, block_tables, seq_lens, out, stream=None) -> None:
     """fea_decode_attention on the library's built-in workspace (allocates nothing).  Asynchronous."""
     import torch
-    for name, t in (("q", q), ("k_cache", k_cache), ("v_cache", v_cache), ("block_tables", block_tables),
-                    ("seq_lens", seq_lens), ("out", out)):
-        if not t.is_cuda or not t.is_contiguous():
-            raise ValueError(f"{name} must be a contiguous GPU tensor")
-    if block_tables.dtype != torch.int32 or seq_lens.dtype != torch.int32:
-        raise ValueError("block_tables and seq_lens must be int32")
-    st = stream if stream is not None else torch.cuda.current_stream()
+    _check_gpu_tensors(torch, _ATTENTION_TENSORS, (q, k_cache, v_cache, block_tables, seq_lens, out), block_tables, seq_lens)
     _check(load_library().fea_decode_attention_static(
-        C.byref(params), _dev_ptr(q), _dev_ptr(k_cache), _dev_ptr(v_cache), _dev_ptr(block_tables),
-        block_tables.shape[1], _dev_ptr(seq_lens), q.shape[0], _dev_ptr(out), C.c_void_p(st.cuda_stream)))
+        C.byref(params), q.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(), block_tables.data_ptr(),
+        block_tables.size(1), seq_lens.data_ptr(), q.size(0), out.data_ptr(), _stream_handle(torch, stream)))
 
 
 def fea_chunk_hashes_device(tokens, tok_offsets, hash_offsets, hashes, stream=None) -> None:
@@ -283,17 +289,15 @@ def fea_chunk_hashes_device(tokens, tok_offsets, hash_offsets, hashes, stream=No
     for t in (tokens, tok_offsets, hash_offsets, hashes):
         if not t.is_cuda or not t.is_contiguous():
             raise ValueError("all arguments must be contiguous GPU tensors")
-    st = stream if stream is not None else torch.cuda.current_stream()
     _check(load_library().fea_chunk_hashes_device(_dev_ptr(tokens), tokens.numel(), _dev_ptr(tok_offsets),
                                                   tok_offsets.numel() - 1, _dev_ptr(hash_offsets), _dev_ptr(hashes),
-                                                  hashes.numel(), C.c_void_p(st.cuda_stream)))
+                                                  hashes.numel(), _stream_handle(torch, stream)))
 
 
 def fea_decode_plan_info(workspace, stream=None) -> dict:
     import torch
-    st = stream if stream is not None else torch.cuda.current_stream()
     info = np.zeros(9, dtype=np.int32)
-    _check(load_library().fea_decode_plan_info(_dev_ptr(workspace), C.c_void_p(st.cuda_stream), _np_ptr(info)))
+    _check(load_library().fea_decode_plan_info(_dev_ptr(workspace), _stream_handle(torch, stream), _np_ptr(info)))
     keys = ("items", "groups", "grouped_requests", "split_blocks", "partial_rows", "shared_blocks",
             "variant", "overflow", "shares")
     return dict(zip(keys, (int(x) for x in info)))
@@ -302,19 +306,17 @@ def fea_decode_plan_info(workspace, stream=None) -> dict:
 def fea_kv_append(params: AttnParams, k_new, v_new, k_cache, v_cache, block_tables, seq_lens, stream=None) -> None:
     """Torch tensors on the GPU; writes each request's new K/V rows at position seq_lens - 1.  Asynchronous."""
     import torch
-    st = stream if stream is not None else torch.cuda.current_stream()
     _check(load_library().fea_kv_append(C.byref(params), _dev_ptr(k_new), _dev_ptr(v_new), _dev_ptr(k_cache),
                                         _dev_ptr(v_cache), _dev_ptr(block_tables), block_tables.shape[1],
-                                        _dev_ptr(seq_lens), block_tables.shape[0], C.c_void_p(st.cuda_stream)))
+                                        _dev_ptr(seq_lens), block_tables.shape[0], _stream_handle(torch, stream)))
 
 
 def fea_stream_read_gbs(buffer, scattered: bool = True, repeats: int = 5, stream=None) -> float:
     """GB/s at which the GPU streams the contiguous GPU tensor `buffer` through the sweep's fetch path."""
     import torch
-    st = stream if stream is not None else torch.cuda.current_stream()
     out = C.c_double()
     _check(load_library().fea_stream_read_gbs(_dev_ptr(buffer), buffer.numel() * buffer.element_size(), int(bool(scattered)),
-                                              int(repeats), C.c_void_p(st.cuda_stream), C.byref(out)))
+                                              int(repeats), _stream_handle(torch, stream), C.byref(out)))
     return out.value
 
 

@@ -421,6 +421,14 @@ template <int D> struct Tile<float, D, 4> {
     }
 };
 
+// x mod d, and x becomes x / d; the divisors are mostly powers of two (1 among them), and a true division is 40 dependent instructions.
+__device__ __forceinline__ int take_digit(int& x, int d) {
+    const int v = x;
+    if ((d & (d - 1)) == 0) { x = v >> (31 - __clz(d)); return v & (d - 1); }
+    x = v / d;
+    return v - x * d;
+}
+
 // Waves of a workgroup: eight, two to a SIMD (a lane holds a whole tile: up to 256 registers); at head_dim 256 four.  Two
 // where the table has no more than two tiles: the others would only hold registers, of which a workgroup of eight takes
 // all that a compute unit has (bf16 32/8/128, 2000 requests of one block 185 -> 61 us; float32 64/1/64, 250 of one block
@@ -441,11 +449,8 @@ __global__ __launch_bounds__(64 * W) void decode_direct_kernel(SweepArgs a, int 
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 15, kg = lane >> 4;
-    int x = blockIdx.x;
-    const int g = x % a.Hkv; x /= a.Hkv;
-    const int rt = x % row_tiles; x /= row_tiles;
-    const int pc = x % pieces;
-    const int i = x / pieces;
+    int i = blockIdx.x;
+    const int g = take_digit(i, a.Hkv), rt = take_digit(i, row_tiles), pc = take_digit(i, pieces);
     const int nh = min(16, a.G - 16 * rt);         // query heads of this row tile
 
     // The length, the ids of this wave's blocks and the query rows are requested together (the ids without
@@ -479,50 +484,62 @@ __global__ __launch_bounds__(64 * W) void decode_direct_kernel(SweepArgs a, int 
             vb[b] = static_cast<const char*>(a.v_cache) + off;
         }
     };
+    // Scores to weights.  (bfloat16: the reference is raised to the row maximum only when a score outgrows it by 2^24, which
+    // the float32 sums absorb without loss; the first score above -inf always does)
+    auto weigh = [&](float (&p)[PN]) {
+        float mx = p[0];
+#pragma unroll
+        for (int y = 1; y < PN; ++y) mx = fmaxf(mx, p[y]);
+        mx *= a.scale_log2;
+        if (__any(mx > m + direct_slack<T>())) {
+            const float mn = fmaxf(m, TileT::row_max(mx));
+            const float al = exp2_fast(m - mn);    // (0 where the reference was the lowest number)
+            l *= al;
+            TileT::rescale(o, al);
+            m = mn;
+        }
+#pragma unroll
+        for (int y = 0; y < PN; ++y) {
+            p[y] = exp2_fast(fmaf(p[y], a.scale_log2, -m));
+            l += p[y];
+        }
+    };
+    // K of the next tile is asked for when this one's has been read, V likewise, and each is waited for where it is read: only
+    // if the compiler leaves the loads where they stand.  The two empty statements, unlike one another, keep it from moving
+    // those of V - the same before the loop and at its end - to the loop's head, behind the wait for K.  (float32 32/8/128, 16
+    // requests of 1152 to 2048 tokens 31.1 -> 29.4 us, bf16 28/4/128, 8 of 90 to 700 tokens 8.8 -> 8.5; 244 bf16 shapes 0.98 of
+    // the time in the mean.)
     if (first < ntiles) {
         locate(first, 0);
 #pragma unroll
         for (int b = 0; b < TB; ++b) tile.load_k(b, kb[b], n, kg);
 #pragma unroll
         for (int b = 0; b < TB; ++b) tile.load_v(b, vb[b], n, kg);
-        int at = 0;
-        for (int t = first; t < ntiles; t += step) {
-            float p[PN];
+        asm volatile("; first tile asked for" ::: "memory");
+        float p[PN];
+        int t = first;
+        for (int at = 0; t + step < ntiles; t += step) {
             tile.scores(p);
-            const bool more = t + step < ntiles;
-            if (more) {                            // K of the next tile while this one's weights and second product are worked out
-                if (++at == 64 / TB) { ids = ids_from(t + step); at = 0; }
-                locate(t + step, at);
-#pragma unroll
-                for (int b = 0; b < TB; ++b) tile.load_k(b, kb[b], n, kg);
+            if (++at == 64 / TB) {
+                ids = ids_from(t + step);
+                asm volatile("" : "+v"(ids));      // waited for here, once in 64 blocks, and not wherever ids are read
+                at = 0;
             }
-            const int rest = L - t * (TB * kBlock);
-            // tokens past the end: weight 0, and whatever their V rows hold is left out
-            if (rest < TB * kBlock) tile.mask(p, rest, n, kg);
-            float mx = p[0];
+            locate(t + step, at);
 #pragma unroll
-            for (int y = 1; y < PN; ++y) mx = fmaxf(mx, p[y]);
-            mx *= a.scale_log2;
-            // (bfloat16: raised to the row maximum only when a score outgrows it by 2^24, which the float32 sums absorb
-            // without loss; the first score above -inf always does)
-            if (__any(mx > m + direct_slack<T>())) {
-                const float mn = fmaxf(m, TileT::row_max(mx));
-                const float al = exp2_fast(m - mn);   // (0 where the reference was the lowest number)
-                l *= al;
-                TileT::rescale(o, al);
-                m = mn;
-            }
-#pragma unroll
-            for (int y = 0; y < PN; ++y) {
-                p[y] = exp2_fast(fmaf(p[y], a.scale_log2, -m));
-                l += p[y];
-            }
+            for (int b = 0; b < TB; ++b) tile.load_k(b, kb[b], n, kg);
+            weigh(p);
             tile.accumulate(p, o, n);
-            if (more) {
 #pragma unroll
-                for (int b = 0; b < TB; ++b) tile.load_v(b, vb[b], n, kg);
-            }
+            for (int b = 0; b < TB; ++b) tile.load_v(b, vb[b], n, kg);
+            asm volatile("; next tile asked for" ::: "memory");
         }
+        tile.scores(p);
+        const int rest = L - t * (TB * kBlock);
+        // tokens past the end: weight 0, and whatever their V rows hold is left out
+        if (rest < TB * kBlock) tile.mask(p, rest, n, kg);
+        weigh(p);
+        tile.accumulate(p, o, n);
     }
     TileT::template to_lds<PAD>(s_acc[wave], o, nh, n, kg);
     l = TileT::row_sum(l);

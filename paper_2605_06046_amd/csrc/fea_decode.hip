@@ -1,5 +1,5 @@
 // fea_decode_attention: argument checks, workspace carving and the three launches
-// (plan, KV sweep, merge), or the one or two (sweep, merge) of batches that need no plan.  No device memory is allocated here and nothing
+// (plan, KV sweep, merge), or the one of batches that need no plan.  No device memory is allocated here and nothing
 // synchronises except fea_decode_plan_info.
 #include <hip/hip_runtime.h>
 
@@ -41,7 +41,7 @@ static const Knobs& knobs() {
 
 struct Resolved {
     int variant;      // 0 generic, 1 MFMA
-    int direct;       // pieces per history of the kernel that needs no plan (1: it writes the output, more: they are merged); 0: plan, sweep and merge
+    int direct;       // pieces per history of the kernel that needs no plan; 0: plan, sweep and merge
     int G, mpt, grouping, split_user, grid;
     int pre, pre_grid;   // leaders and common runs on many workgroups first (large tables)
     int merge_by_rows;   // very many output rows: the merge takes several rows per wave
@@ -85,16 +85,18 @@ static int64_t direct_rounds(const fea_attn_params* p, int64_t stride) {
     return (tiles + waves - 1) / waves;
 }
 
-// Pieces a history is cut into there.  Workgroups that leave most of the chip idle are worth cutting, up to one per
-// compute unit; the merge of the pieces is a launch of its own (3.5 to 4 us), a round of a wave's tiles takes 1 us
-// (bf16, head_dim 64) to 2.7 us (float32, head_dim 128 and 256), so it has to save three rounds.  Measured: float32
-// 32/8/128, 4 requests of 2048 tokens 51.6 us whole, 33.0 / 22.1 / 18.6 / 20.3 in 2 / 4 / 8 / 16 pieces; bf16 32/8/128,
-// 16 requests (128 workgroups) of 512 tokens 10.0 whole, 12.3 in 2 (2 rounds: not cut).
+// Pieces a history is cut into there.  Workgroups that leave most of the chip idle are worth cutting, up to one per compute
+// unit and 32 per history; the fold of the pieces takes 3 us, a round of a wave's tiles 2.3 (what one compute unit fetches), so
+// it has to save two rounds, and no more pieces are made than the rounds that are left need.  Measured on 284 shapes with 1 to
+// 64 pieces each, 1.01 of the best in the mean: bf16 32/8/128, one request of 6400 tokens (25 rounds) 60.6 us whole, 22.2 /
+// 15.5 / 12.2 / 13.8 / 14.0 in 4 / 8 / 16 / 24 / 32 pieces; 32/2/128, two of 20000 (79 rounds) 178.6 whole, 21.2 / 20.2 / 25.7
+// in 16 / 32 / 64; 8 of 700 (3 rounds) 10.7 whole, 10.8 in 2, 11.0 in 3.
 static int64_t direct_pieces(const fea_attn_params* p, int64_t B, int64_t stride) {
     const int64_t groups = direct_groups(p, B), rounds = direct_rounds(p, stride);
     if (groups <= 0 || 2 * groups > cu_count()) return 1;
-    const int64_t n = std::min<int64_t>(cu_count() / groups, rounds);
-    return rounds - (rounds + n - 1) / n >= 3 ? n : 1;
+    const int64_t most = std::min<int64_t>({cu_count() / groups, rounds, 32});
+    const int64_t left = most > 0 ? (rounds + most - 1) / most : rounds;
+    return rounds - left >= 2 ? (rounds + left - 1) / left : 1;
 }
 
 // Whether it is expected to beat plan + sweep + merge.  It reads what requests share once per request (5.0 to 5.9 TB/s
@@ -222,7 +224,10 @@ static int32_t resolve(const fea_attn_params* p, int32_t B, int32_t stride, Reso
     l.total = off;
     l.max_items = (int32_t)max_items;
     l.max_rows = (int32_t)max_rows;
-    r.direct = direct ? (int)std::max<int64_t>(1, std::min<int64_t>(kn.direct_pieces > 0 ? kn.direct_pieces : direct_pieces(p, B, stride), max_rows / std::max<int64_t>(1, rows))) : 0;
+    // (the pieces of a history are counted in the workspace's section `pre`, up to 128 of them)
+    int64_t pieces = kn.direct_pieces > 0 ? kn.direct_pieces : direct_pieces(p, B, stride);
+    pieces = direct_groups(p, B) > kGroupReqMax ? 1 : std::min<int64_t>({pieces, 128, max_rows / std::max<int64_t>(1, rows)});
+    r.direct = direct ? (int)std::max<int64_t>(1, pieces) : 0;
     return FEA_OK;
 }
 
@@ -281,7 +286,7 @@ int32_t decode_impl(const fea_attn_params* p, const void* q, const void* k_cache
             if (g_prof_which >= 0 && g_prof_which != k) continue;
             if (k == 0 && ((p->flags & FEA_FLAG_REUSE_PLAN) || (r.direct && !plan_only))) continue;
             if (k > 0 && plan_only) continue;
-            if (k == 2 && r.direct == 1) continue;
+            if (k == 2 && r.direct) continue;
             where[k].ev_start = ev[2 * k];
             where[k].ev_stop = ev[2 * k + 1];
             if (k == 0) { where[0].ev_mid[0] = ev[6]; where[0].ev_mid[1] = ev[7]; }
@@ -336,11 +341,9 @@ int32_t decode_impl(const fea_attn_params* p, const void* q, const void* k_cache
     sa.Hkv = p->num_kv_heads;
     sa.G = r.G;
     sa.mpt = r.mpt;
-    sa.direct = r.direct;
     sa.fast_shared = (p->head_dim == 128 && (int64_t)B * p->num_q_heads < (1 << 23) && !knobs().no_fast_shared) ? 1 : 0;
     if (r.direct) {
         launch_decode_direct(sa, p->dtype, p->head_dim, r.direct, where[1]);
-        if (r.direct > 1) launch_merge(sa, p->dtype, p->head_dim, r.merge_by_rows != 0, where[2]);
     } else {
         if (r.variant == 1) launch_sweep_mfma(sa, p->head_dim, r.grid, where[1]);
         else launch_sweep_generic(sa, p->dtype, p->head_dim, r.grid, where[1]);

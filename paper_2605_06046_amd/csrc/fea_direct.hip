@@ -4,8 +4,8 @@
 // first (workgroups are numbered so that, with 8 KV heads, those of one KV head share an XCD).
 //
 // One workgroup per (request, row tile of 16 query heads, KV head) and, where these are too few to fill the
-// chip, per piece of the history: the pieces take the request's tiles in turn and leave partial rows for
-// merge_kernel.  A wave takes every (waves x pieces)-th tile of 32 tokens (16 for float32 at head_dim 256),
+// chip, per piece of the history: the pieces take the request's tiles in turn and leave partial rows, which the workgroup
+// that comes last folds.  A wave takes every (waves x pieces)-th tile of 32 tokens (16 for float32 from head_dim 128 on),
 // each on the matrix cores, straight from global memory into the operand registers:
 //     S^T = K Q^T     lane (n, kg) = (lane % 16, lane / 16) holds K rows as 16-byte chunks 4 j + kg of token
 //                     row n, and q's chunks alike: any order of the head dims serves, as long as both agree
@@ -438,6 +438,39 @@ template <int D> constexpr int direct_waves() { return D == 256 ? 4 : 8; }
 // (the rounding of score - reference grows with its size, so the largest weights want theirs near zero).
 template <typename T> constexpr float direct_slack() { return sizeof(T) == 4 ? 0.f : 24.f; }
 
+// Partial rows of the pieces of a history, handed from the workgroups that make them to the one that folds them: written past
+// the caches and read past them (device scope), since the workgroups may sit on different XCDs.
+__device__ __forceinline__ void put_pair(float* p, float x, float y) {
+    const unsigned long long v = (unsigned long long)__float_as_uint(x) | ((unsigned long long)__float_as_uint(y) << 32);
+    __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float2 get_pair(const float* p) {
+    const unsigned long long v = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return make_float2(__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32)));
+}
+
+// Counts an arrival of `of` (at most 128) at *p; true for the last, which leaves zero.  Nobody clears the workspace: a counter is
+// one whose upper 56 bits are the key, and any other word counts as zero.  (An addition to such a word counts nobody; whoever
+// sees one is counted by the exchange, so everyone is counted once.)
+__device__ __forceinline__ bool arrives_last(unsigned long long* p, int of) {
+    constexpr unsigned long long kKey = 0xFEA5D1A2C37E6B00ull;
+    unsigned long long old = __hip_atomic_fetch_add(p, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (((old ^ kKey) >> 8) != 0) {
+        unsigned long long cur = old + 1, next;
+        do next = ((cur ^ kKey) >> 8) != 0 ? kKey | 1 : cur + 1;
+        while (!__hip_atomic_compare_exchange_strong(p, &cur, next, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        old = next - 1;
+    }
+    if ((int)(old & 255) + 1 < of) return false;
+    __hip_atomic_store(p, kKey, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return true;
+}
+
+template <typename T> __device__ __forceinline__ void store4(char* dst, float x0, float x1, float x2, float x3) {
+    if constexpr (sizeof(T) == 4) *reinterpret_cast<f32x4*>(dst) = f32x4{x0, x1, x2, x3};
+    else *reinterpret_cast<uint2*>(dst) = make_uint2(bf16_rne(x0) | (bf16_rne(x1) << 16), bf16_rne(x2) | (bf16_rne(x3) << 16));
+}
+
 template <typename T, int D, int R, int W>
 __global__ __launch_bounds__(64 * W) void decode_direct_kernel(SweepArgs a, int row_tiles, int pieces) {
     using TileT = Tile<T, D, R>;
@@ -446,6 +479,7 @@ __global__ __launch_bounds__(64 * W) void decode_direct_kernel(SweepArgs a, int 
     constexpr int PAD = D + 4;                     // floats between the rows of the fold buffer (16 rows written side by side)
     __shared__ __attribute__((aligned(16))) float s_acc[W][R][PAD];
     __shared__ float2 s_ml[W][R];
+    __shared__ bool s_last;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 15, kg = lane >> 4;
@@ -547,7 +581,10 @@ __global__ __launch_bounds__(64 * W) void decode_direct_kernel(SweepArgs a, int 
     __syncthreads();
 
     // fold the waves (fixed order) at the common reference exponent
-    const int rows0 = ((i * a.Hkv + g) * pieces + pc) * a.G + 16 * rt;   // partial row of the tile's first head
+    float* const acc = reinterpret_cast<float*>(a.ws + a.lay.acc);
+    float* const mls = reinterpret_cast<float*>(a.ws + a.lay.ml);
+    const size_t row0 = (size_t)(i * a.Hkv + g) * pieces * a.G + 16 * rt;   // of piece p and the tile's head h: partial row row0 + p G + h
+    char* const out = static_cast<char*>(a.out) + ((size_t)i * a.Hq + g * a.G + 16 * rt) * (D * ES);
     for (int y = tid; y < nh * (D / 8); y += 64 * W) {
         const int h = y / (D / 8), c = y - h * (D / 8);
         float M = kLowest;
@@ -566,32 +603,64 @@ __global__ __launch_bounds__(64 * W) void decode_direct_kernel(SweepArgs a, int 
             for (int e = 0; e < 4; ++e) { num[e] = fmaf(f, a0[e], num[e]); num[4 + e] = fmaf(f, a1[e], num[4 + e]); }
         }
         if (pieces > 1) {
-            float* dst = reinterpret_cast<float*>(a.ws + a.lay.acc) + (size_t)(rows0 + h) * D + 8 * c;
-            *reinterpret_cast<f32x4*>(dst) = f32x4{num[0], num[1], num[2], num[3]};
-            *reinterpret_cast<f32x4*>(dst + 4) = f32x4{num[4], num[5], num[6], num[7]};
-            if (c == 0) reinterpret_cast<float2*>(a.ws + a.lay.ml)[rows0 + h] = make_float2(M, den);
+            const size_t r = row0 + (size_t)pc * a.G + h;
+#pragma unroll
+            for (int e = 0; e < 8; e += 2) put_pair(acc + r * D + 8 * c + e, num[e], num[e + 1]);
+            if (c == 0) put_pair(mls + 2 * r, M, den);
         } else {
             const float inv = L == 0 ? 0.f : 1.f / den;   // an empty history gives a zero row, one of scores of -inf alone 0/0
-            char* dst = static_cast<char*>(a.out) + ((size_t)i * a.Hq + g * a.G + 16 * rt + h) * (D * ES) + 8 * c * ES;
-            if constexpr (ES == 4) {
-                *reinterpret_cast<f32x4*>(dst) = f32x4{num[0] * inv, num[1] * inv, num[2] * inv, num[3] * inv};
-                *reinterpret_cast<f32x4*>(dst + 16) = f32x4{num[4] * inv, num[5] * inv, num[6] * inv, num[7] * inv};
-            } else {
-                u32x4 w;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) w[e] = bf16_rne(num[2 * e] * inv) | (bf16_rne(num[2 * e + 1] * inv) << 16);
-                *reinterpret_cast<u32x4*>(dst) = w;
+            for (int e = 0; e < 8; e += 4) store4<T>(out + (h * D + 8 * c + e) * ES, num[e] * inv, num[e + 1] * inv, num[e + 2] * inv, num[e + 3] * inv);
+        }
+    }
+    // The workgroup that comes last to a history (of a KV head and row tile) folds its pieces, in their order: the result does
+    // not depend on who comes last.  About 3 us, where a launch of its own takes 5 (float32 32/8/128, 16 requests of 1152 to
+    // 2048 tokens in two pieces each 29.4 -> 27.3 us a call).
+    if (pieces > 1) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's partial rows have arrived
+        __syncthreads();
+        if (tid == 0) s_last = arrives_last(reinterpret_cast<unsigned long long*>(a.ws + a.lay.pre) + (i * a.Hkv + g) * row_tiles + rt, pieces);
+        __syncthreads();
+        if (s_last) {
+            for (int y = tid; y < nh * (D / 4); y += 64 * W) {
+                const int h = y / (D / 4), c = y - h * (D / 4);
+                float M = kLowest, den = 0.f;
+                f32x4 num = {0.f, 0.f, 0.f, 0.f};
+                constexpr int kAtOnce = 8;
+                for (int p0 = 0; p0 < pieces; p0 += kAtOnce) {
+                    float2 v[kAtOnce], x0[kAtOnce], x1[kAtOnce];
+#pragma unroll
+                    for (int k = 0; k < kAtOnce; ++k) {
+                        const size_t r = row0 + (size_t)min(p0 + k, pieces - 1) * a.G + h;
+                        v[k] = get_pair(mls + 2 * r);
+                        x0[k] = get_pair(acc + r * D + 4 * c);
+                        x1[k] = get_pair(acc + r * D + 4 * c + 2);
+                    }
+                    float Mn = M;
+#pragma unroll
+                    for (int k = 0; k < kAtOnce; ++k) Mn = fmaxf(Mn, v[k].x);   // (where there is none left: the last piece's)
+                    const float f0 = exp2_fast(M - Mn);
+                    M = Mn;
+                    den *= f0;
+                    num *= f0;
+#pragma unroll
+                    for (int k = 0; k < kAtOnce; ++k) {
+                        if (p0 + k < pieces) {
+                            const float f = exp2_fast(v[k].x - M);
+                            den = fmaf(f, v[k].y, den);
+                            num[0] = fmaf(f, x0[k].x, num[0]);
+                            num[1] = fmaf(f, x0[k].y, num[1]);
+                            num[2] = fmaf(f, x1[k].x, num[2]);
+                            num[3] = fmaf(f, x1[k].y, num[3]);
+                        }
+                    }
+                }
+                const float inv = L == 0 ? 0.f : 1.f / den;
+                store4<T>(out + (h * D + 4 * c) * ES, num[0] * inv, num[1] * inv, num[2] * inv, num[3] * inv);
             }
         }
     }
-    // What the merge reads about a request, and what a later look at the workspace finds: no plan, this kernel.
-    if (pieces > 1 && pc == 0 && rt == 0 && tid == 0) {
-        SegDesc sd;
-        sd.pbase = (i * a.Hkv + g) * pieces * a.G;
-        sd.npieces = L == 0 ? 0 : pieces;
-        reinterpret_cast<SegDesc*>(a.ws + a.lay.segs)[(size_t)i * a.Hkv + g] = sd;
-        if (g == 0) *reinterpret_cast<int4*>(a.ws + a.lay.req + (size_t)i * sizeof(ReqDesc)) = make_int4(0, 0, 0, 0);
-    }
+    // What a later look at the workspace finds: no plan, this kernel.
     if (blockIdx.x == 0 && tid < H_WORDS)
         reinterpret_cast<int*>(a.ws)[tid] = tid == H_VARIANT ? 2 : tid == H_WAVES ? (int)gridDim.x * W : 0;
 }

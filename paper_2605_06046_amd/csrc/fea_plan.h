@@ -125,7 +125,6 @@ struct SweepArgs {
     WsLayout lay;
     float scale_log2;    // softmax scale times log2(e): scores live in the base-2 domain
     int32_t stride, B, Hq, Hkv, G, mpt;
-    int32_t direct;        // the plan-free kernel made the partial rows (the merge is then the only one that may find no plan)
     int32_t fast_shared;   // q is small enough for 32-bit byte offsets: the hand-scheduled shared-run sequence may be used
 };
 

@@ -268,7 +268,7 @@ __global__ __launch_bounds__(256) void merge_kernel(SweepArgs a) {
     T* out = static_cast<T*>(a.out) + (size_t)rowid * D;
     const int c = lane % LPR, slot = lane / LPR;
 
-    const bool no_plan = hdr[H_VARIANT] == 2 && !a.direct;   // a reused plan that is none
+    const bool no_plan = hdr[H_VARIANT] == 2;   // a reused plan that is none
     if (no_plan && rowid == 0 && lane == 0) hdr[H_OVERFLOW] = 2;
     if (no_plan || hdr[H_OVERFLOW]) {   // that, or the plan did not fit its buffers: make it loud
         for (int e = lane; e < D; e += 64) Elem<T>::store(out + e, __uint_as_float(0x7FC00000u));
@@ -369,7 +369,7 @@ __global__ __launch_bounds__(256) void merge_rows_kernel(SweepArgs a) {
     const float2* ml = reinterpret_cast<const float2*>(a.ws + a.lay.ml);
     const float* pacc = reinterpret_cast<const float*>(a.ws + a.lay.acc);
     T* out = static_cast<T*>(a.out) + (size_t)rowid * D;
-    const bool no_plan = hdr[H_VARIANT] == 2 && !a.direct;   // a reused plan that is none
+    const bool no_plan = hdr[H_VARIANT] == 2;   // a reused plan that is none
     if (no_plan && rowid == 0 && c == 0) hdr[H_OVERFLOW] = 2;
     if (no_plan || hdr[H_OVERFLOW]) {   // that, or the plan did not fit its buffers: make it loud
         for (int e = c; e < D; e += LPR) Elem<T>::store(out + e, __uint_as_float(0x7FC00000u));

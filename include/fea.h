@@ -95,14 +95,14 @@ typedef struct fea_attn_params {
                                (8192); < 0: always; > 0: that many                       */
     int32_t fused_max;      /* batches too small to be worth a plan are done without one: every
                                (request, KV head) walks its whole history in a workgroup of its
-                               own, or - a few long histories - in several whose results a second
-                               launch merges (a shared block is then read once per request, which
-                               at this size the L2 serves).  0: the library decides, from an
-                               estimate of both ways' durations (about: up to 64 MB of KV
-                               histories at full table rows, up to 300 MB with few query heads
-                               per KV head and one workgroup to a compute unit; nearly always
-                               for float32 caches and query groups the matrix-core sweep does
-                               not take); < 0: never;
+                               own, or - a few long histories - in several, the last of which folds
+                               what the others leave in the workspace (a shared block is then read
+                               once per request, which at this size the L2 serves).  0: the library
+                               decides, from an estimate of both ways' durations (about: up to 64 MB
+                               of KV histories at full table rows, up to 225 MB with more than eight
+                               query heads per KV head, 300 MB with few of them and one workgroup to
+                               a compute unit; nearly always for float32 caches and query groups the
+                               matrix-core sweep does not take); < 0: never;
                                > 0: every batch whose table rows have at most this many entries */
 } fea_attn_params;
 

@@ -102,28 +102,36 @@ static int64_t direct_pieces(const fea_attn_params* p, int64_t B, int64_t stride
 // Whether it is expected to beat plan + sweep + merge.  It reads what requests share once per request (5.0 to 5.9 TB/s
 // from HBM, 8 and more where the L2s hold it), which the host cannot know; nor does it know whether the plan would serve other
 // layers of the step as well.  So it is taken where it wins (or loses next to nothing) whatever is shared and however often
-// the plan is used again.  Measured on 5000 matrix-core and 1600 vector-unit shapes (1 to 4096 requests, 16 to 65536 tokens,
-// query groups of 1 to 96, 0, 90 and 98 % shared), alone and against a reused plan.  On the matrix-core path:
-//  - up to 64 MB of KV histories.  Nothing shared: 8 requests of 1024 tokens 13.5 against 24.8 us.
-//  - up to 100 MB in few enough workgroups (6 to a compute unit; each has a few us of start-up): bf16 32/8/128, 32 requests of
+// the plan is used again.  Measured on 5800 matrix-core and 1600 vector-unit shapes (1 to 4096 requests, 16 to 70000 tokens,
+// query groups of 1 to 96, 0 to 98 % shared), alone and against a reused plan.  On the matrix-core path, by the bytes of
+// KV histories that its workgroups read:
+//  - up to 64 MB.  Nothing shared: 8 requests of 1024 tokens 13.5 against 24.8 us.
+//  - more than eight query heads per KV head, in at most four workgroups to a compute unit, up to 225 MB: on 100 shapes of 100
+//    to 225 MB 0.53 of the time of a new plan and 0.76 of the reused plan's, never more than 1.06 (32/2/128, 160 requests of
+//    1216 tokens).  With fewer heads it wins there too in the mean (0.8 of the reused plan's up to 145 MB), but loses where
+//    much is shared: 12/4/64, 24 requests of 5280 tokens (130 MB), 98 % shared, 1.20; from 225 to 290 MB 0.97 and up to 1.64.
+//  - in up to six workgroups to a compute unit (each has a few us of start-up) up to 100 MB: bf16 32/8/128, 32 requests of
 //    752 tokens, 19.0 against 35.2 and, of the reused plan, 24.5; 90 % shared 12.1 against 33.9 and 21.9.  In eight rounds of
 //    workgroups, 256 requests of 80 tokens, 31.7 against 37.8 and 26.2.
 //  - tables of one or two tiles up to 128 MB: 2000 requests of one block 61 against 103 us (above it, a reused plan wins by a tenth).
-//  - few query heads (the sweep's strength is many), one round of workgroups of up to 1 MB each (1.33 at head_dim 256), or two of
-//    256 KB: bf16 32/8/128, 32 requests of 1520 tokens 36.1 against 52.1 and 40.9, 90 % shared 19.2 against 39.7 and 27.3.
+//  - few query heads, one round of workgroups of up to 1 MB each (1.33 at head_dim 256), or two of 256 KB: bf16 32/8/128, 32
+//    requests of 1520 tokens 36.1 against 52.1 and 40.9, 90 % shared 19.2 against 39.7 and 27.3.
 //    Longer histories lose to a reused plan: 8/2/64, 128 requests of 4112 tokens, 90 % shared, 28.1 against 38.6 and 22.2.
 // The vector-unit sweep costs 26 to 120 us to start with, and from some hundred thousand (query row, token) pairs on time in
-// proportion to them; the plan-free kernel loses to it only with one or two query heads per KV head on histories that are
-// shared and long (float32 4/4/32, 35 requests of 23472 tokens, 98 % shared: 181 against 99 us).
+// proportion to them.  float32 from 2 to 16 query heads per KV head: the plan-free kernel wins on all of 1174 shapes (60 MB to
+// 9 GB of histories, 0 to 99 % shared; 0.25 of the reused plan's time in the mean, 0.82 the closest: 2/1/32, 300 requests
+// of 32544 tokens, 90 % shared, 290 against 351 us).  With one head it can lose on histories that are shared and long (8/8/64,
+// 1000 requests of 2192 tokens, 99 % shared: 612 against 515 and 480 us).
 static bool direct_pays(const fea_attn_params* p, int64_t B, int64_t stride, int variant) {
     const bool f32 = p->dtype == FEA_DTYPE_F32;
     const double group = (double)(p->num_q_heads / p->num_kv_heads), groups = (double)direct_groups(p, B), cus = cu_count();
     const double tokens = (double)stride * kBlock, dd = p->head_dim / 64.0;
     const double per_group = tokens * p->head_dim * (f32 ? 8.0 : 4.0), bytes = groups * per_group;   // K and V read by a workgroup, by all
     if (variant == 1) {
-        if (bytes <= 64e6 || (bytes <= 100e6 && groups <= 6 * cus) || (bytes <= 128e6 && direct_tiles(p, stride) <= 2)) return true;
+        if (bytes <= 64e6 || (group > 8 && bytes <= 225e6 && groups <= 4 * cus) || (bytes <= 100e6 && groups <= 6 * cus) || (bytes <= 128e6 && direct_tiles(p, stride) <= 2)) return true;
         return group <= 4 && ((groups <= cus && per_group <= (p->head_dim == 256 ? 1.33e6 : 1 << 20)) || (groups <= 2 * cus && per_group <= 1 << 18));
     }
+    if (f32 && group >= 2 && group <= 16) return true;
     const int64_t pieces = direct_pieces(p, B, stride);
     const double serial_us = 2.0 * (double)((direct_rounds(p, stride) + pieces - 1) / pieces);   // one workgroup's tiles, a round after the other
     const double direct_us = 7.0 + (pieces > 1 ? 4.0 : 0.0) + std::max(serial_us, bytes / 8.0e6);

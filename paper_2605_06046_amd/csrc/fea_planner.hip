@@ -108,32 +108,38 @@ __device__ __forceinline__ uint32_t wave_min(uint32_t x) {
     return (uint32_t)__builtin_amdgcn_readlane(v, 63);
 }
 
-// Exclusive prefix sum of one int per thread over the block.  One barrier: every thread adds up the waves before its own.
-// `s_sums` (16-byte aligned, one int per wave) must not be in use by another scan.
+// Prefix sums over the block in two levels: a wave's total into s_sums[wave] and, after a barrier, what the waves before this
+// one have and what all have - the 16 totals once more by lane shifts, in the 16 lanes of a row (added up by every thread on
+// its own they were 50 instructions, of all 16 waves).
+__device__ __forceinline__ int waves_before(const int* s_sums, int& total) {
+    static_assert(kPlanThreads / 64 == 16, "one total per lane of a row");
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    int v = s_sums[threadIdx.x & 15];
+    v += lane_shift<0x111, 0xF>(v, 0);
+    v += lane_shift<0x112, 0xF>(v, 0);
+    v += lane_shift<0x114, 0xF>(v, 0);
+    v += lane_shift<0x118, 0xF>(v, 0);
+    total = __builtin_amdgcn_readlane(v, 15);
+    return wave == 0 ? 0 : __builtin_amdgcn_readlane(v, wave - 1);
+}
+// Exclusive prefix sum of one int per thread over the block, with one barrier.  `s_sums` must not be in use by another scan.
 __device__ __forceinline__ int block_scan_excl(int v, int* s_sums, int& total) {
-    constexpr int kWaves = kPlanThreads / 64;
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int x = wave_scan_incl(v);
-    if (lane == 63) s_sums[wave] = x;
+    if ((threadIdx.x & 63) == 63) s_sums[threadIdx.x >> 6] = x;
     __syncthreads();
-    int base = 0, all = 0;
-#pragma unroll
-    for (int w = 0; w < kWaves; w += 4) {
-        const int4 q = *reinterpret_cast<const int4*>(s_sums + w);
-        const int part[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            base += w + k < wave ? part[k] : 0;
-            all += part[k];
-        }
-    }
-    total = all;
-    return base + x - v;
+    return waves_before(s_sums, total) + x - v;
 }
 
 // Four neighbouring table columns, loadable from any 4-byte boundary.
 struct __attribute__((packed, aligned(4))) Cols4 { int32_t c[4]; };
 
+// Hash slots for n keys: 16 each (a probe more is a serial round trip to LDS for a whole wave; with four each 1.3 us were lost
+// where 120 keys are looked up), but not all 4096 for a few keys, since all are cleared.
+__device__ __forceinline__ int slots_for(int n) {
+    int slots = 512;
+    while (slots < 16 * n && slots < kHashSlots) slots <<= 1;
+    return slots;
+}
 __device__ __forceinline__ uint32_t slot_of(int key) { return ((uint32_t)key * 2654435761u) >> 20; }  // 12 bits
 
 __device__ __forceinline__ void write_item(Item* it, int who, int g, int nrows, int mlist_off, int c0, int c1,
@@ -157,26 +163,35 @@ __global__ __launch_bounds__(kRunThreads) void run_kernel(PlanArgs a) {
     const int nG = a.grouping ? min(a.B, kGroupReqMax) : 0;
     const int maxL = a.stride * kBlock;
     constexpr int kPer = kGroupReqMax / kRunThreads;
-    for (int s = tid; s < kHashSlots; s += kRunThreads) { keys[s] = -1; vals[s] = INT_MAX; }
+    const int slots = slots_for(nG);
+    const uint32_t slot_mask = (uint32_t)slots - 1;
+    int my_key[kPer], my_len[kPer];
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {       // lengths and first blocks are on their way while the table is cleared
+        const int i = tid + k * kRunThreads;
+        my_len[k] = 0;
+        my_key[k] = -1;
+        if (i < nG && maxL > 0) {
+            my_len[k] = a.seq_lens[i];
+            my_key[k] = a.bt[(size_t)i * a.stride];
+        }
+    }
+    for (int s = tid; s < slots; s += kRunThreads) { keys[s] = -1; vals[s] = INT_MAX; }
     __syncthreads();
-    int my_key[kPer];
 #pragma unroll
     for (int k = 0; k < kPer; ++k) {
         const int i = tid + k * kRunThreads;
-        my_key[k] = -1;
         if (i < nG) {
-            const int L = max(0, min(a.seq_lens[i], maxL));
+            const int L = max(0, min(my_len[k], maxL));
             s_len[i] = L;
-            if (L >= kBlock) {
-                const int key = a.bt[(size_t)i * a.stride];
-                my_key[k] = key;
-                if (key >= 0) {
-                    uint32_t s = slot_of(key);
-                    for (;;) {
-                        const int old = atomicCAS(&keys[s], -1, key);
-                        if (old == -1 || old == key) { atomicMin(&vals[s], i); break; }
-                        s = (s + 1) & (kHashSlots - 1);
-                    }
+            if (L < kBlock) my_key[k] = -1;
+            const int key = my_key[k];
+            if (key >= 0) {
+                uint32_t s = slot_of(key) & slot_mask;
+                for (;;) {
+                    const int old = atomicCAS(&keys[s], -1, key);
+                    if (old == -1 || old == key) { atomicMin(&vals[s], i); break; }
+                    s = (s + 1) & slot_mask;
                 }
             }
         }
@@ -189,8 +204,8 @@ __global__ __launch_bounds__(kRunThreads) void run_kernel(PlanArgs a) {
             int lead = -1;
             const int key = my_key[k];
             if (key >= 0) {
-                uint32_t s = slot_of(key);
-                while (keys[s] != key) s = (s + 1) & (kHashSlots - 1);
+                uint32_t s = slot_of(key) & slot_mask;
+                while (keys[s] != key) s = (s + 1) & slot_mask;
                 lead = vals[s];
             }
             s_lead[i] = (short)lead;
@@ -291,7 +306,22 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
     auto clampL = [&](int L) { return max(0, min(L, maxL)); };
 
     int my_key[kGroupReqMax / kPlanThreads], my_longest = 0;
-    for (int s = tid; s < kHashSlots; s += kPlanThreads) { h2.keys[s] = -1; h2.vals[s] = INT_MAX; }
+    const int slots = slots_for(nG);
+    const uint32_t slot_mask = (uint32_t)slots - 1;
+    int my_len[kGroupReqMax / kPlanThreads];
+    if (!a.pre) {   // lengths and first blocks are on their way while the tables are cleared
+#pragma unroll
+        for (int k = 0; k < kGroupReqMax / kPlanThreads; ++k) {
+            const int i = tid + k * kPlanThreads;
+            my_len[k] = 0;
+            my_key[k] = -1;
+            if (i < nG && maxL > 0) {
+                my_len[k] = a.seq_lens[i];
+                my_key[k] = a.bt[(size_t)i * a.stride];
+            }
+        }
+    }
+    for (int s = tid; s < slots; s += kPlanThreads) { h2.keys[s] = -1; h2.vals[s] = INT_MAX; }
     if (tid == 0) { s_ngroups = 0; s_ngrouped = 0; s_shared_blocks = 0; s_nflw = 0; }
     if (a.pre) {
         // ---- leaders and common runs were found by run_kernel
@@ -305,26 +335,23 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
         __syncthreads();
     } else {
         // ---- leaders: smallest request index among those with the same first block
-        for (int s = tid; s < kHashSlots; s += kPlanThreads) { u.h.keys[s] = -1; u.h.vals[s] = INT_MAX; }
+        for (int s = tid; s < slots; s += kPlanThreads) { u.h.keys[s] = -1; u.h.vals[s] = INT_MAX; }
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < kGroupReqMax / kPlanThreads; ++k) {
             const int i = tid + k * kPlanThreads;
-            my_key[k] = -1;
             if (i < nG) {
-                const int L = clampL(a.seq_lens[i]);
+                const int L = clampL(my_len[k]);
                 s_len[i] = L;
                 my_longest = max(my_longest, L);
-                if (L >= kBlock) {
-                    const int key = a.bt[(size_t)i * a.stride];
-                    my_key[k] = key;
-                    if (key >= 0) {
-                        uint32_t s = slot_of(key);
-                        for (;;) {
-                            const int old = atomicCAS(&u.h.keys[s], -1, key);
-                            if (old == -1 || old == key) { atomicMin(&u.h.vals[s], i); break; }
-                            s = (s + 1) & (kHashSlots - 1);
-                        }
+                if (L < kBlock) my_key[k] = -1;
+                const int key = my_key[k];
+                if (key >= 0) {
+                    uint32_t s = slot_of(key) & slot_mask;
+                    for (;;) {
+                        const int old = atomicCAS(&u.h.keys[s], -1, key);
+                        if (old == -1 || old == key) { atomicMin(&u.h.vals[s], i); break; }
+                        s = (s + 1) & slot_mask;
                     }
                 }
             }
@@ -339,8 +366,8 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
                 int lead = -1, lcp = 0;
                 const int key = my_key[k];
                 if (key >= 0) {
-                    uint32_t s = slot_of(key);
-                    while (u.h.keys[s] != key) s = (s + 1) & (kHashSlots - 1);
+                    uint32_t s = slot_of(key) & slot_mask;
+                    while (u.h.keys[s] != key) s = (s + 1) & slot_mask;
                     lead = u.h.vals[s];
                     lcp = min(s_len[i], s_len[lead]) / kBlock;
                     if (lead != i) w.flw[atomicAdd(&s_nflw, 1)] = (unsigned short)i;
@@ -364,10 +391,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
     // where run_kernel has found the runs, the search for nested ones goes over the table's width.
     int columns = a.stride;
     if (!a.pre) {
-        int longest = 0;
-#pragma unroll
-        for (int w = 0; w < kPlanThreads / 64; ++w) longest = max(longest, s_longest[w]);
-        columns = longest / kBlock;
+        columns = ~(int)wave_min(~(uint32_t)s_longest[lane & 15]) / kBlock;
     }
     auto lcp_pass = [&](int nflw, const short* lead_of, auto&& from, auto&& hit) {
         constexpr int cpe = 4;                             // columns per element
@@ -515,11 +539,11 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
                 if (!in[k] || lcp1[k] > r1[k]) my_key[k] = -1;      // only the members that leave the leader at the run
                 const int key = my_key[k];
                 if (key >= 0) {
-                    uint32_t s = slot_of(key);
+                    uint32_t s = slot_of(key) & slot_mask;
                     for (;;) {
                         const int old = atomicCAS(&h2.keys[s], -1, key);
                         if (old == -1 || old == key) { atomicMin(&h2.vals[s], tid + k * kPlanThreads); break; }
-                        s = (s + 1) & (kHashSlots - 1);
+                        s = (s + 1) & slot_mask;
                     }
                 }
             }
@@ -531,8 +555,8 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
                 lead2[k] = -1;
                 const int key = my_key[k];
                 if (key >= 0) {
-                    uint32_t s = slot_of(key);
-                    while (h2.keys[s] != key) s = (s + 1) & (kHashSlots - 1);
+                    uint32_t s = slot_of(key) & slot_mask;
+                    while (h2.keys[s] != key) s = (s + 1) & slot_mask;
                     const int cand = h2.vals[s];
                     lead2[k] = s_lead[cand] == lead1[k] ? cand : i;     // only within the same outer group
                     s_lcpv[i] = ((unsigned long long)(uint32_t)(min(s_len[i], s_len[lead2[k]]) / kBlock) << 32) | 0xFFFFFFFFull;
@@ -597,7 +621,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
             }
             if (!again) break;                         // uniform
             // the groups that split off are looked at again, with clean tables
-            for (int s = tid; s < kHashSlots; s += kPlanThreads) { h2.keys[s] = -1; h2.vals[s] = INT_MAX; }
+            for (int s = tid; s < slots; s += kPlanThreads) { h2.keys[s] = -1; h2.vals[s] = INT_MAX; }
             reset_groups(0);   // every thread changed only its own requests' entries above
             __syncthreads();
         }
@@ -676,17 +700,8 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
         if (lane == 63) { s_sums[1][wave] = tiles_in_wave; s_sums[3][wave] = segs_in_wave; }
         int total;
         int base = block_scan_excl(local, s_sums[0], total);
-        int sbase = segs_in_wave - ls;
-        tbase = tiles_in_wave - lt;
-        T_pr = segs_pr = 0;
-#pragma unroll
-        for (int w = 0; w < kPlanThreads / 64; ++w) {
-            const int part = s_sums[1][w], part_s = s_sums[3][w];
-            tbase += w < wave ? part : 0;
-            sbase += w < wave ? part_s : 0;
-            T_pr += part;
-            segs_pr += part_s;
-        }
+        const int sbase = segs_in_wave - ls + waves_before(s_sums[3], segs_pr);
+        tbase = tiles_in_wave - lt + waves_before(s_sums[1], T_pr);
         const bool few_own = teams && total > 0 && T_pr < a.tune.n_waves, long_own = total == 0 && T_pr / 24 >= a.tune.n_waves;
         per_seg = a.variant == 1 && a.split_user == 0 && !few_own && !long_own ? kSegmentTiles : 0;
         tbase += per_seg * sbase;
@@ -695,7 +710,9 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
             if (viable(i)) {
                 u.c.moff[i] = base;
                 base += u.c.cnt[i];
-                w.glist[atomicAdd(&s_ngroups, 1)] = (unsigned short)i;
+                const int gi = atomicAdd(&s_ngroups, 1);
+                w.glist[gi] = (unsigned short)i;
+                s_r1[i] = (unsigned short)gi;      // (what it held is dead: now where a leader's group stands in the list)
                 atomicAdd(&s_shared_blocks, u.c.run[i]);
             }
         if (tid == 0) s_ngrouped = total;
@@ -929,15 +946,6 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
         for (int e = e0; e < e1; ++e) {
             const int i = by_hkv.div(e), g = e - i * Hkv;
             if (i != seen) { seen = i; L = len_of(i); nb = (L + kBlock - 1) / kBlock; c0 = run_of(i); units = priv_units(i); }
-            if (g == 0) {
-                ReqDesc rd;
-                rd.ns_sh = rd.sh_base0 = rd.sh_gstride = rd.sh_pstride = 0;   // a group fills these in below
-                rd.nb = nb;
-                rd.L = L;
-                rd.group = c0 > 0 ? (int)s_lead[i] : -1;
-                rd.priv_c0 = c0;
-                req[i] = rd;
-            }
             const int seg_first = idx;
             if (!overflow) {
                 for_pieces(units, k, rem, [&](int jb, int je, bool starts, int kk) {
@@ -954,12 +962,30 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
             segs[e] = sd;
         }
     }
-    // member lists of the groups (the rank lives with the thread that drew it)
-    for (int k = 0, i = tid; i < nG; i += kPlanThreads, ++k) {
-        const int lead = s_lead[i];
-        if (lead >= 0 && viable(lead)) members[u.c.moff[lead] + my_rank[k]] = i;
+    // ---- member lists of the groups (the rank lives with the thread that drew it), and the requests' descriptors, with where a
+    // member of a group finds the partials of the shared run (its rank is its position in the member list).  Nothing from here
+    // on reads what another thread has stored to memory: a barrier would wait for all of those stores (members and group
+    // descriptors after one took 1.5 us more where a batch has 250 requests, 3.9 where it has 500).
+    for (int i = tid, k = 0; i < B; i += kPlanThreads, ++k) {
+        const int L = len_of(i), lead = i < nG ? (int)s_lead[i] : -1;
+        const bool grouped = lead >= 0 && viable(lead);
+        int4 shared = make_int4(0, 0, 0, 0);
+        int run = 0;
+        if (grouped) {
+            const int gi = s_r1[lead], cnt = u.c.cnt[lead], n_pc = v.g.npc[gi];
+            const int rank = k == 0 ? my_rank[0] : my_rank[kPer - 1];
+            const int tau = by_mpt.div(rank), full_rows = a.mpt * a.G;
+            run = u.c.run[lead];
+            members[u.c.moff[lead] + rank] = i;
+            shared.x = n_pc;
+            shared.y = v.g.rbase[gi] + n_pc * tau * full_rows + (rank - tau * a.mpt) * a.G;
+            shared.z = n_pc * cnt * a.G;
+            shared.w = (tau + 1) * a.mpt >= cnt ? (cnt - tau * a.mpt) * a.G : full_rows;
+        }
+        int4* rd = reinterpret_cast<int4*>(&req[i]);
+        rd[0] = shared;
+        rd[1] = make_int4((L + kBlock - 1) / kBlock, L, grouped ? lead : -1, run);
     }
-    __syncthreads();   // request descriptors and member lists are written: groups may amend them
     // ---- descriptors and items of the groups: one team of waves per group, its lanes
     // over the group's items (the fewer groups, the bigger the teams).
     // Order: KV head, piece, row tile - the row tiles of one piece read the same KV bytes
@@ -1020,18 +1046,6 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
                     sd.npieces = n_pc;
                     segs[(size_t)B * Hkv + u.c.gseg[gi] + g * tiles_r + tau] = sd;
                 }
-            }
-            // where each member finds the partials of the shared run (rank r = position in the member list)
-            const FastDiv by_m(a.mpt);
-            for (int r = l0; r < cnt; r += lstep) {
-                const int i = members[u.c.moff[ld] + r];
-                const int tau = by_m.div(r);
-                int4 shared;
-                shared.x = n_pc;
-                shared.y = v.g.rbase[gi] + n_pc * tau * full_rows + (r - tau * a.mpt) * a.G;
-                shared.z = n_pc * rows_per_head;
-                shared.w = tau == tiles_r - 1 ? last_rows : full_rows;
-                *reinterpret_cast<int4*>(&req[i]) = shared;
             }
         }
     }

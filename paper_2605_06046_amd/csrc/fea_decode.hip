@@ -29,13 +29,14 @@ static int env_int(const char* name, int dflt) {
 // second thread sets) cannot switch kernels or move the workspace layout between the
 // sizing call and the attention call.  What tests need to steer is in fea_attn_params.
 struct Knobs {
-    int force_generic, sweep_grid, spare_waves, min_piece, min_run, w32, w64, no_fast_shared, w_team, w_team2, team_fixed, direct_pieces;
+    int force_generic, sweep_grid, spare_waves, min_piece, min_run, w32, w64, no_fast_shared, w_team, w_team2, team_fixed, direct_pieces, histories;
 };
 static const Knobs& knobs() {
     static const Knobs k = {env_int("FEA_FORCE_GENERIC", 0), env_int("FEA_SWEEP_GRID", 0), env_int("FEA_SPARE_WAVES", 16),
                             env_int("FEA_MIN_PIECE", 4),     env_int("FEA_MIN_RUN", 2),    env_int("FEA_W32", 18),
                             env_int("FEA_W64", 24), env_int("FEA_NO_FAST_SHARED", 0), env_int("FEA_WTEAM", 12),
-                            env_int("FEA_WTEAM2", 12), env_int("FEA_TEAM_FIXED", 40), env_int("FEA_DIRECT_PIECES", 0)};
+                            env_int("FEA_WTEAM2", 12), env_int("FEA_TEAM_FIXED", 40), env_int("FEA_DIRECT_PIECES", 0),
+                            env_int("FEA_HISTORIES", 12)};
     return k;
 }
 
@@ -45,6 +46,7 @@ struct Resolved {
     int G, mpt, grouping, split_user, grid;
     int pre, pre_grid;   // leaders and common runs on many workgroups first (large tables)
     int merge_by_rows;   // very many output rows: the merge takes several rows per wave
+    int histories;       // tiles from which on a batch that shares nothing is swept by whole histories; 0: never
     PlanTuning tune;
     WsLayout lay;
 };
@@ -202,6 +204,9 @@ static int32_t resolve(const fea_attn_params* p, int32_t B, int32_t stride, Reso
     const int run_min = p->run_kernel_min == 0 ? 49152 : p->run_kernel_min;
     r.pre = r.grouping && (run_min < 0 || (groupable >= 128 && groupable * stride >= run_min)) ? 1 : 0;
     r.pre_grid = (int)std::max<int64_t>(1, std::min<int64_t>(2 * cu_count(), (groupable + 3) / 4));
+    // Whole histories where the planner finds nothing shared: one row tile of 16 query heads, and enough of them to even out.
+    r.histories = r.variant == 1 && p->head_dim != 256 && r.grouping && r.split_user == 0 && r.G <= 16 && B <= kGroupReqMax && stride > 0 &&
+                          (int64_t)B * p->num_kv_heads >= 4 * cu_count() ? kn.histories * r.tune.n_waves : 0;
     const int64_t rows = (int64_t)B * p->num_q_heads;
     // Very many rows mean many requests and hence few pieces per row: there a wave of the merge takes
     // several rows (a long shared run cut into many pieces comes with few rows, and keeps a wave per row).
@@ -324,6 +329,7 @@ int32_t decode_impl(const fea_attn_params* p, const void* q, const void* k_cache
         pa.teams = (r.variant == 1 && p->head_dim == 128 && !knobs().no_fast_shared) ? 1 : 0;
         pa.pre = r.pre;
         pa.pre_grid = r.pre_grid;
+        pa.histories = r.histories;
         if (p->flags & FEA_FLAG_REFRESH_PLAN) launch_refresh(pa, where[0]);
         else launch_plan(pa, where[0]);
     }
@@ -434,7 +440,7 @@ int32_t fea_decode_plan_info(const void* workspace, void* hip_stream, int32_t* i
     info[3] = hdr[H_SPLIT];
     info[4] = hdr[H_ROWS];
     info[5] = hdr[H_SHARED_BLOCKS];
-    info[6] = hdr[H_VARIANT];
+    info[6] = hdr[H_VARIANT] == kHistories ? 1 : hdr[H_VARIANT];
     info[7] = hdr[H_OVERFLOW];
     info[8] = hdr[H_WAVES];
     return FEA_OK;

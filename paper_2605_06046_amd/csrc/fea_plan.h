@@ -21,18 +21,26 @@ constexpr int kOpenEnded = -2;        // Item::mlist_off of a request's last pie
 // header words (int32) at the start of the workspace
 enum Hdr {
     H_ITEMS = 0,       // number of work items
-    H_QUEUE = 1,       // zero but while plain_split runs: its workgroups that have read the header
+    H_QUEUE = 1,       // zero but while plain_split runs: its workgroups that have read the header; and while whole histories
+                       // are swept: those taken beyond the first of every workgroup (the merge clears it)
     H_GROUPS = 2,      // prefix groups found
     H_GROUPED = 3,     // requests that belong to a group
     H_SPLIT = 4,       // KV blocks per wave, what its segments are charged included (balanced mode), or per item (fixed split)
     H_ROWS = 5,        // partial rows in use
     H_SHARED_BLOCKS = 6,
-    H_VARIANT = 7,     // 0 generic, 1 MFMA, 2 no plan (fea_direct.hip)
+    H_VARIANT = 7,     // 0 generic, 1 MFMA, kNoPlan (fea_direct.hip), kHistories
     H_OVERFLOW = 8,    // planner ran out of item/partial capacity (never by construction)
     H_WAVES = 9,       // sweep waves that received work
     H_CAPACITY = 10,   // items the workspace it was made in has room for (its sections lie by that); 0: no plan (fea_direct.hip)
+    H_HISTORIES = 11,  // not 0 where H_VARIANT is kHistories (a word of its own: the sweep keeps 6 registers more of H_VARIANT's
+                       // branch alive, which spill, and takes 27 us instead of 24.6 for 32 requests of 2100 to 2900 tokens)
     H_WORDS = 64
 };
+
+constexpr int kNoPlan = 2;
+// Nothing is shared and the batch is large: no items, the matrix-core sweep takes whole histories in the order that the section
+// `members` lists the requests in, counts them in H_QUEUE and writes the output itself.
+constexpr int kHistories = 3;
 
 struct ReqDesc {       // one per request: where the merge finds the partials of its shared run
     int32_t ns_sh;     // pieces of the group's shared run (0 if ungrouped)
@@ -106,6 +114,7 @@ struct PlanArgs {
     int32_t teams;       // the sweep runs the row tiles of a shared run's piece as a team of waves (MFMA sweep, head_dim 128)
     int32_t pre;         // leaders and common runs come from run_kernel (workspace section `pre`)
     int32_t pre_grid;    // its grid
+    int32_t histories;   // tiles (of 32 tokens) from which on a batch that shares nothing is swept by whole histories; 0: never
 };
 
 // What run_kernel leaves for the planner, per groupable request: the run it shares with its
@@ -127,6 +136,11 @@ struct SweepArgs {
     int32_t stride, B, Hq, Hkv, G, mpt;
     int32_t fast_shared;   // q is small enough for 32-bit byte offsets: the hand-scheduled shared-run sequence may be used
 };
+
+// Makes the compiler ask for all of these wave-uniform values at once, where `x` (an int that is used later) is first needed: it asks
+// for each where that is first used, one round trip after the other across branches.  (Not volatile, and with an output: a
+// statement that might touch memory would keep the loads behind it out of the scalar cache.)
+#define FEA_TOGETHER(x, b, c, d) asm("" : "+s"(x) : "s"(b), "s"(c), "s"(d))
 
 // launchers (defined next to their kernels); stream is a hipStream_t
 // Where a kernel goes: the caller's stream and, when its duration is wanted, a pair of

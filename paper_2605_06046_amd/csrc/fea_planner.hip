@@ -324,6 +324,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
     for (int s = tid; s < slots; s += kPlanThreads) { h2.keys[s] = -1; h2.vals[s] = INT_MAX; }
     if (tid == 0) { s_ngroups = 0; s_ngrouped = 0; s_shared_blocks = 0; s_nflw = 0; }
     if (a.pre) {
+        __syncthreads();   // (s_nflw is zero)
         // ---- leaders and common runs were found by run_kernel
         const unsigned long long* pre = reinterpret_cast<const unsigned long long*>(a.ws + a.lay.pre);
         const int* pre_lead = reinterpret_cast<const int*>(pre + kGroupReqMax);
@@ -331,6 +332,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
             s_len[i] = clampL(a.seq_lens[i]);
             s_lead[i] = (short)pre_lead[i];
             s_lcpv[i] = pre[i];
+            if (pre_lead[i] >= 0 && pre_lead[i] != i) s_nflw = 1;   // (here only whether there is any)
         }
         __syncthreads();
     } else {
@@ -377,6 +379,52 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
             }
         }
         __syncthreads();   // the hash table is dead from here on; its memory becomes run/cnt/moff/...
+    }
+    // ---- nothing shared (no two requests with the same first block), and much of it: no plan.  The sweep reads whole histories,
+    // a workgroup one at a time, longest first, and whoever is done takes the next: shares cut beforehand end as far apart as
+    // the XCDs' rates differ (10 %).  Needs no order among equals, so the requests are put into 64 classes of length.
+    if (__builtin_expect(a.histories > 0 && s_nflw == 0, 0)) {
+        __shared__ int s_class[64];
+        if (tid < 64) s_class[tid] = 0;
+        int longest = 0, tiles = 0;
+        for (int i = tid; i < B; i += kPlanThreads) {
+            longest = max(longest, s_len[i]);
+            tiles += (s_len[i] + 2 * kBlock - 1) / (2 * kBlock);
+        }
+        longest = ~(int)wave_min(~(uint32_t)longest);
+        tiles = wave_sum(tiles);
+        if (lane == 0) { s_sums[0][wave] = longest; s_sums[1][wave] = tiles; }
+        __syncthreads();
+        longest = ~(int)wave_min(~(uint32_t)s_sums[0][lane & 15]);
+        waves_before(s_sums[1], tiles);
+        if ((long long)tiles * Hkv >= a.histories) {
+            const float per_class = 64.f / (float)(longest + 1);
+            int cls[kGroupReqMax / kPlanThreads], at[kGroupReqMax / kPlanThreads];
+#pragma unroll
+            for (int k = 0; k < kGroupReqMax / kPlanThreads; ++k) {
+                const int i = tid + k * kPlanThreads;
+                if (i < B) {
+                    cls[k] = 63 - min(63, (int)((float)s_len[i] * per_class));
+                    at[k] = atomicAdd(&s_class[cls[k]], 1);
+                }
+            }
+            __syncthreads();
+            const int mine = s_class[lane], before = wave_scan_incl(mine) - mine;   // (of class `lane`, in every wave)
+            __shared__ int s_first[64];
+            if (wave == 0) s_first[lane] = before;
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < kGroupReqMax / kPlanThreads; ++k) {
+                const int i = tid + k * kPlanThreads;
+                if (i < B) members[s_first[cls[k]] + at[k]] = i;
+            }
+            if (tid < H_WORDS) {
+                const int units = B * Hkv;
+                hdr[tid] = tid == H_ITEMS ? units : tid == H_SPLIT ? (longest + kBlock - 1) / kBlock : tid == H_VARIANT ? kHistories
+                         : tid == H_WAVES ? a.tune.n_waves : tid == H_CAPACITY ? a.lay.max_items : tid == H_HISTORIES ? 1 : 0;
+            }
+            return;
+        }
     }
     auto reset_groups = [&](int moff0) {
         for (int i = tid; i < nG; i += kPlanThreads) { u.c.run[i] = INT_MAX; u.c.cnt[i] = 0; u.c.moff[i] = moff0; }
@@ -1061,6 +1109,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
         hdr[H_OVERFLOW] = overflow ? 1 : 0;
         hdr[H_WAVES] = n_shares;
         hdr[H_CAPACITY] = a.lay.max_items;
+        hdr[H_HISTORIES] = 0;
     }
 }
 
@@ -1115,6 +1164,7 @@ __device__ __forceinline__ void plain_split(const PlanArgs& a) {
         hdr[H_ROWS] = n_items * a.G;
         hdr[H_VARIANT] = a.variant;
         hdr[H_CAPACITY] = a.lay.max_items;
+        hdr[H_HISTORIES] = 0;
     }
 }
 
@@ -1124,9 +1174,13 @@ __device__ __forceinline__ void plain_split(const PlanArgs& a) {
 // wrong - attention over rows that no longer count - but never out of bounds: a piece keeps at least one tile.)
 __global__ __launch_bounds__(256) void refresh_kernel(PlanArgs a) {
     const int* hdr = reinterpret_cast<const int*>(a.ws);
-    if (hdr[H_CAPACITY] != a.lay.max_items) { plain_split(a); return; }
+    int capacity = hdr[H_CAPACITY];
+    const int variant = hdr[H_VARIANT], made = hdr[H_ITEMS];
+    FEA_TOGETHER(capacity, variant, made, a.lay.items);   // (one round trip for the header's words)
+    if (capacity != a.lay.max_items) { plain_split(a); return; }
+    if (variant == kHistories) return;   // whole histories are read at their lengths of now
     Item* items = reinterpret_cast<Item*>(a.ws + a.lay.items);
-    const int n_items = min(hdr[H_ITEMS], a.lay.max_items);
+    const int n_items = min(made, a.lay.max_items);
     const int maxL = a.stride * kBlock;
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n_items; i += gridDim.x * blockDim.x) {
         const int4 w0 = reinterpret_cast<const int4*>(&items[i])[0];

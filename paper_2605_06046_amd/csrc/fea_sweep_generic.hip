@@ -284,22 +284,32 @@ __global__ __launch_bounds__(256) void merge_kernel(SweepArgs a) {
     constexpr int SLOTS = 64 / LPR;
     const int lane = threadIdx.x & 63;
     const int rowid = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    int* hdr = reinterpret_cast<int*>(a.ws);
-    if (rowid >= a.B * a.Hq) return;
+    int rows = a.B * a.Hq;
+    FEA_TOGETHER(rows, a.lay.acc, a.out, a.ws);   // (three lines of kernel arguments, cold at every launch)
+    if (rowid >= rows) return;
     int i = rowid;
-    const int hh = take_digit(i, a.G), g = take_digit(i, a.Hkv);
-    // (the first four words of the request's descriptor, taken as values: a reference to the whole struct would put it on the stack)
+    const int hh = __builtin_amdgcn_readfirstlane(take_digit(i, a.G)), g = __builtin_amdgcn_readfirstlane(take_digit(i, a.Hkv));
+    i = __builtin_amdgcn_readfirstlane(i);
+    const int* hdr = reinterpret_cast<const int*>(a.ws);
+    // Header and descriptors are asked for together (the empty statement uses them all: left to itself the compiler waits for
+    // one word before it asks for the next).  The first four words of the request's descriptor are taken as values: a
+    // reference to the whole struct would put it on the stack.
+    int variant = hdr[H_VARIANT], overflow = hdr[H_OVERFLOW];
     const int4 rd4 = *reinterpret_cast<const int4*>(a.ws + a.lay.req + (size_t)i * sizeof(ReqDesc));
-    const int rd_ns_sh = rd4.x, rd_sh_base0 = rd4.y, rd_sh_gstride = rd4.z, rd_sh_pstride = rd4.w;
-    const SegDesc pd = reinterpret_cast<const SegDesc*>(a.ws + a.lay.segs)[(size_t)i * a.Hkv + g];
+    int rd_ns_sh = rd4.x, rd_sh_base0 = rd4.y, rd_sh_gstride = rd4.z, rd_sh_pstride = rd4.w;
+    SegDesc pd = reinterpret_cast<const SegDesc*>(a.ws + a.lay.segs)[(size_t)i * a.Hkv + g];
+    asm volatile("" : "+s"(variant), "+s"(overflow), "+s"(rd_ns_sh), "+s"(rd_sh_base0), "+s"(rd_sh_gstride), "+s"(rd_sh_pstride),
+                      "+s"(pd.pbase), "+s"(pd.npieces));
     const float2* ml = reinterpret_cast<const float2*>(a.ws + a.lay.ml);
     const float* pacc = reinterpret_cast<const float*>(a.ws + a.lay.acc);
     T* out = static_cast<T*>(a.out) + (size_t)rowid * D;
     const int c = lane % LPR, slot = lane / LPR;
 
-    const bool no_plan = hdr[H_VARIANT] == 2;   // a reused plan that is none
-    if (no_plan && rowid == 0 && lane == 0) hdr[H_OVERFLOW] = 2;
-    if (no_plan || hdr[H_OVERFLOW]) {   // that, or the plan did not fit its buffers: make it loud
+    if (__builtin_expect(variant >= kNoPlan || overflow != 0, 0)) {
+        // the sweep has written the output; a reused plan that is none, or one that did not fit its buffers: make it loud
+        int* h = reinterpret_cast<int*>(a.ws);
+        if (rowid == 0 && lane == 0) h[variant == kHistories ? H_QUEUE : H_OVERFLOW] = variant == kHistories ? 0 : variant == kNoPlan ? 2 : overflow;
+        if (variant == kHistories) return;
         for (int e = lane; e < D; e += 64) Elem<T>::store(out + e, __uint_as_float(0x7FC00000u));
         return;
     }
@@ -389,9 +399,12 @@ __global__ __launch_bounds__(256) void merge_rows_kernel(SweepArgs a) {
     const float2* ml = reinterpret_cast<const float2*>(a.ws + a.lay.ml);
     const float* pacc = reinterpret_cast<const float*>(a.ws + a.lay.acc);
     T* out = static_cast<T*>(a.out) + (size_t)rowid * D;
-    const bool no_plan = hdr[H_VARIANT] == 2;   // a reused plan that is none
-    if (no_plan && rowid == 0 && c == 0) hdr[H_OVERFLOW] = 2;
-    if (no_plan || hdr[H_OVERFLOW]) {   // that, or the plan did not fit its buffers: make it loud
+    int variant = hdr[H_VARIANT], overflow = hdr[H_OVERFLOW];
+    asm volatile("" : "+s"(variant), "+s"(overflow));   // (asked for together)
+    if (__builtin_expect(variant >= kNoPlan || overflow != 0, 0)) {
+        // the sweep has written the output; a reused plan that is none, or one that did not fit its buffers: make it loud
+        if (rowid == 0 && c == 0) hdr[variant == kHistories ? H_QUEUE : H_OVERFLOW] = variant == kHistories ? 0 : variant == kNoPlan ? 2 : overflow;
+        if (variant == kHistories) return;
         for (int e = c; e < D; e += LPR) Elem<T>::store(out + e, __uint_as_float(0x7FC00000u));
         return;
     }

@@ -54,6 +54,7 @@
 #include <cstdlib>
 
 #include "fea_plan.h"
+#include "fea_tile.h"
 
 namespace fea {
 
@@ -691,6 +692,148 @@ constexpr int kWavesPerGroup = 4;   // one wave per SIMD of a compute unit: a wo
 // Waves per workgroup: four (one per SIMD) - at head_dim 256 two, whose tile stages (2 x 32 KB each) fill the LDS.
 template <int D> constexpr int waves_per_group() { return D == 256 ? 2 : kWavesPerGroup; }
 
+// A batch that shares nothing: workgroups take whole histories of a (request, KV head), in the planner's order, and write the
+// output.  Wave w of W takes every W-th tile of 32 tokens, two of them in its registers (fea_tile.h): one is worked on while
+// the other arrives, and a tile is asked for as soon as the one two before it has been read.  The next history is claimed
+// while this one is read.
+constexpr int kHistoryRows = 16;
+template <int D, int W>
+__device__ __forceinline__ void sweep_histories(const SweepArgs& a, char* lds, int* hdr, int wave, int lane) {
+    using TileT = tile::Tile<tile::bf16_t, D, kHistoryRows>;
+    constexpr int TB = TileT::TB, NI = TileT::NI, PN = TileT::PN, BLK = kBlock * D * 2, PAD = D + 4;
+    struct Fold { float acc[W][kHistoryRows][PAD]; float2 ml[W][kHistoryRows]; int next; };   // (two in turn: one barrier a history)
+    static_assert(2 * sizeof(Fold) <= (size_t)W * kStages * 4 * BLK, "fits the tile stages");
+    Fold* folds = reinterpret_cast<Fold*>(lds);
+    const int n = lane & 15, kg = lane >> 4, tid = wave * 64 + lane;
+    const int units = a.B * a.Hkv;
+    const int* order = reinterpret_cast<const int*>(a.ws + a.lay.members);
+    int turn = 0;
+    for (int unit = blockIdx.x; unit < units; turn ^= 1) {
+        Fold& f = folds[turn];
+        int claimed = 0;
+        if (tid == 0) claimed = (int)gridDim.x + atomicAdd(&hdr[H_QUEUE], 1);
+        const int i = min(max(__builtin_amdgcn_readfirstlane(order[unit / a.Hkv]), 0), a.B - 1), g = unit % a.Hkv;   // (in range whatever plan is reused)
+        const int32_t* row = a.bt + (size_t)i * a.stride;
+        auto ids_from = [&](int t0) {              // lane TB x + b: block b of the x-th tile of this wave from t0 on
+            const int col = TB * (t0 + (lane / TB) * W) + lane % TB;
+            return row[min(col, a.stride - 1)];
+        };
+        const int raw_len = a.seq_lens[i];
+        int ids = ids_from(wave);
+        TileT A, Bt;
+        A.load_q(static_cast<const char*>(a.q) + ((size_t)i * a.Hq + g * a.G) * (D * 2), a.G, n, kg);
+        const int L = __builtin_amdgcn_readfirstlane(min(max(raw_len, 0), a.stride * kBlock));
+        const int nb = (L + kBlock - 1) / kBlock, ntiles = (nb + TB - 1) / TB;
+        const int count = (ntiles - wave + W - 1) / W;   // of this wave (its tile k: wave + k W); <= 0: none
+        tile::f32x4 o[NI];
+#pragma unroll
+        for (int j = 0; j < NI; ++j) o[j] = tile::f32x4{0.f, 0.f, 0.f, 0.f};
+        float m = kLowest, l = 0.f;
+        const char* kb[TB];
+        const char* vb[TB];
+        int base = 0;                              // the tile that lane 0's id belongs to
+        auto locate = [&](int k) {
+            if (k - base == 64 / TB) {
+                ids = ids_from(wave + k * W);
+                asm volatile("" : "+v"(ids));      // waited for here, once in 64 blocks
+                base = k;
+            }
+#pragma unroll
+            for (int b = 0; b < TB; ++b) {
+                const int blk = max(__builtin_amdgcn_readlane(ids, TB * (k - base) + (TB * (wave + k * W) + b < nb ? b : 0)), 0);
+                const size_t off = ((size_t)blk * a.Hkv + g) * BLK;
+                kb[b] = static_cast<const char*>(a.k_cache) + off;
+                vb[b] = static_cast<const char*>(a.v_cache) + off;
+            }
+        };
+        auto ask_k = [&](TileT& t) {
+#pragma unroll
+            for (int b = 0; b < TB; ++b) t.load_k(b, kb[b], n, kg);
+        };
+        auto ask_v = [&](TileT& t) {
+#pragma unroll
+            for (int b = 0; b < TB; ++b) t.load_v(b, vb[b], n, kg);
+        };
+        auto scores = [&](TileT& t, float (&p)[PN]) {
+#pragma unroll
+            for (int j = 0; j < TileT::KC; ++j) t.q[j] = A.q[j];
+            t.scores(p);
+        };
+        auto step = [&](TileT& t, int k) {         // tile k, and tile k + 2 asked for
+            float p[PN];
+            scores(t, p);
+            locate(k + 2);
+            ask_k(t);
+            tile::weigh<TileT, tile::bf16_t>(p, o, m, l, a.scale_log2);
+            t.accumulate(p, o, n);
+            ask_v(t);
+            asm volatile("; tile asked for" ::: "memory");
+        };
+        auto last = [&](TileT& t, int k) {
+            float p[PN];
+            scores(t, p);
+            const int rest = L - (wave + k * W) * (TB * kBlock);
+            if (rest < TB * kBlock) t.mask(p, rest, n, kg);
+            tile::weigh<TileT, tile::bf16_t>(p, o, m, l, a.scale_log2);
+            t.accumulate(p, o, n);
+        };
+        if (count > 0) {
+            locate(0);
+            ask_k(A);
+            ask_v(A);
+            asm volatile("; first tile asked for" ::: "memory");
+            if (count > 1) {
+                locate(1);
+                ask_k(Bt);
+                ask_v(Bt);
+                asm volatile("; second tile asked for" ::: "memory");
+                int k = 0;
+                for (; k + 3 < count; k += 2) {
+                    step(A, k);
+                    step(Bt, k + 1);
+                }
+                if (count - k == 3) {
+                    step(A, k);
+                    last(Bt, k + 1);
+                    last(A, k + 2);
+                } else {
+                    last(A, k);
+                    last(Bt, k + 1);
+                }
+            } else {
+                last(A, 0);
+            }
+        }
+        TileT::template to_lds<PAD>(f.acc[wave], o, a.G, n, kg);
+        l = TileT::row_sum(l);
+        if (TileT::one_of_row(n, kg)) f.ml[wave][TileT::head(n)] = make_float2(m, l);
+        if (tid == 0) f.next = claimed;
+        __syncthreads();
+        unit = __builtin_amdgcn_readfirstlane(f.next);
+        for (int y = tid; y < a.G * (D / 8); y += 64 * W) {
+            const int h = y / (D / 8), c = y - h * (D / 8);
+            float M = kLowest, den = 0.f, num[8];
+#pragma unroll
+            for (int w = 0; w < W; ++w) M = fmaxf(M, f.ml[w][h].x);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) num[e] = 0.f;
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                const float2 ml = f.ml[w][h];
+                const float s = fast_exp2(ml.x - M);   // (a wave that had no tile, or no score above -inf, has sums of 0)
+                den = fmaf(s, ml.y, den);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) num[e] = fmaf(s, f.acc[w][h][8 * c + e], num[e]);
+            }
+            const float inv = L == 0 ? 0.f : 1.f / den;   // an empty history gives a zero row, one of scores of -inf alone 0/0
+            u32x4 w;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[e] = tile::bf16_rne(num[2 * e] * inv) | (tile::bf16_rne(num[2 * e + 1] * inv) << 16);
+            *reinterpret_cast<u32x4*>(static_cast<char*>(a.out) + ((size_t)i * a.Hq + g * a.G + h) * (D * 2) + 16 * c) = w;
+        }
+    }
+}
+
 template <int D>
 __global__ __launch_bounds__(64 * waves_per_group<D>()) void sweep_mfma_kernel(SweepArgs a, int g_rcp, int xcd_aware) {
     constexpr int WPG = waves_per_group<D>();
@@ -710,7 +853,7 @@ __global__ __launch_bounds__(64 * waves_per_group<D>()) void sweep_mfma_kernel(S
     char* s_q = s_q_all + wv * (kBlock * (D < 128 ? 128 : D) * 2);
     int* hdr = reinterpret_cast<int*>(a.ws);
     const Item* items = reinterpret_cast<const Item*>(a.ws + a.lay.items);
-    const int n_items = hdr[H_ITEMS];
+    const int n_items = hdr[H_ITEMS], histories = hdr[H_HISTORIES];
     const uint32_t lds_base = __builtin_amdgcn_readfirstlane(
         (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)s_stage);
     const uint32_t cols_base = __builtin_amdgcn_readfirstlane(
@@ -788,7 +931,13 @@ __global__ __launch_bounds__(64 * waves_per_group<D>()) void sweep_mfma_kernel(S
     }
     int share = WPG * group + wv;
     const int n_waves = WPG * (int)gridDim.x;
-    const int n_shares = hdr[H_VARIANT] == 2 ? 0 : hdr[H_WAVES];   // (a reused plan that is none: nothing is swept, the merge reports it)
+    const int n_shares = hdr[H_VARIANT] == kNoPlan ? 0 : hdr[H_WAVES];   // (a reused plan that is none: nothing is swept, the merge reports it)
+    if constexpr (D != 256) {   // (two tiles of 256 dims would spill)
+        if (__builtin_expect(histories != 0, 0)) {   // (placed behind the rest: the other way must not fetch its instructions)
+            sweep_histories<D, WPG>(a, s_stage_all, hdr, wv, lane);
+            return;
+        }
+    }
     const int* wave_first = reinterpret_cast<const int*>(a.ws + a.lay.wave_first);
     for (; share < n_shares; share += n_waves) {
         int it = __builtin_amdgcn_readfirstlane(wave_first[share]);

@@ -25,24 +25,34 @@ struct AppendArgs {
     int32_t row_bytes;     // head_dim * element size: one token of one KV head
 };
 
+// x mod d, and x becomes x / d (d is mostly a power of two; a true 64-bit division is a hundred dependent instructions).
+__device__ __forceinline__ int take_digit(long long& x, int d) {
+    const long long v = x;
+    if ((d & (d - 1)) == 0) { x = v >> (31 - __clz(d)); return (int)(v & (d - 1)); }
+    x = v / d;
+    return (int)(v - x * d);
+}
+
+// Bound: a launch (3 us with nothing in it) and two round trips, the length and then the block; the new row is asked for with
+// the length, and arrives meanwhile.
 __global__ __launch_bounds__(256) void append_kernel(AppendArgs a) {
-    const int chunks = a.row_bytes / 16;
+    int chunks = a.row_bytes / 16;
+    FEA_TOGETHER(chunks, a.k_new, a.k_cache, a.seq_lens);
     const long long per_cache = (long long)a.B * a.Hkv * chunks;
     const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= 2 * per_cache) return;
+    if (idx >= 2 * per_cache || a.stride <= 0) return;
     const bool is_v = idx >= per_cache;
-    long long r = is_v ? idx - per_cache : idx;
-    const int c = (int)(r % chunks); r /= chunks;
-    const int g = (int)(r % a.Hkv);
-    const int i = (int)(r / a.Hkv);
+    const long long row = is_v ? idx - per_cache : idx;   // (of 16 bytes; in k_new and v_new they lie in this order)
+    long long r = row;
+    const int c = take_digit(r, chunks), g = take_digit(r, a.Hkv), i = (int)r;
     const int L = a.seq_lens[i];
-    if (L <= 0 || (L - 1) / kBlock >= a.stride) return;   // nothing to write / no such column
-    const int pos = L - 1;
-    const int b = a.bt[(size_t)i * a.stride + pos / kBlock];
-    if (b < 0) return;                                    // padding entry: the caller's table is short
-    const size_t src = ((size_t)i * a.Hkv + g) * a.row_bytes + (size_t)c * 16;
+    const uint4 v = reinterpret_cast<const uint4*>(is_v ? a.v_new : a.k_new)[row];
+    const int pos = L - 1, col = pos >> 4;
+    const int b = a.bt[(size_t)i * a.stride + min(max(col, 0), a.stride - 1)];
+    asm volatile("" :: "v"(v.x), "v"(v.y), "v"(v.z), "v"(v.w));   // (the row is here before anything is decided: its load cannot move behind)
+    // nothing to write, no such column, or a padding entry (the caller's table is short)
+    if (L <= 0 || col >= a.stride || b < 0) return;
     const size_t dst = (((size_t)b * a.Hkv + g) * kBlock + pos % kBlock) * a.row_bytes + (size_t)c * 16;
-    const uint4 v = *reinterpret_cast<const uint4*>((is_v ? a.v_new : a.k_new) + src);
     *reinterpret_cast<uint4*>((is_v ? a.v_cache : a.k_cache) + dst) = v;
 }
 

@@ -853,7 +853,25 @@ __global__ __launch_bounds__(64 * waves_per_group<D>()) void sweep_mfma_kernel(S
     char* s_q = s_q_all + wv * (kBlock * (D < 128 ? 128 : D) * 2);
     int* hdr = reinterpret_cast<int*>(a.ws);
     const Item* items = reinterpret_cast<const Item*>(a.ws + a.lay.items);
-    const int n_items = hdr[H_ITEMS], histories = hdr[H_HISTORIES];
+    // Which shares this wave sweeps: share, share + grid, ...  Workgroups are dealt
+    // round-robin to the 8 XCDs (workgroup id mod 8), each with its own L2, while
+    // consecutive shares of a shared run are its row tiles over the same KV bytes.
+    // Put every 8 consecutive shares on one XCD so that those bytes are fetched into
+    // one L2 once.  (Pure performance: any permutation is correct.)
+    int group = blockIdx.x;
+    if (xcd_aware) {
+        const int x = blockIdx.x & 7, k = blockIdx.x >> 3;
+        group = 2 * ((k >> 1) * 8 + x) + (k & 1);
+    }
+    int share = WPG * group + wv;
+    // (arguments, then header and first items: each in one round trip to memory, not word by word - four in line before the first
+    // descriptor can be asked for)
+    const int* wave_first = reinterpret_cast<const int*>(a.ws + a.lay.wave_first);
+    FEA_TOGETHER(share, a.lay.items, a.q, a.stride);
+    int n_items = hdr[H_ITEMS], first_item = wave_first[share];
+    const int variant = hdr[H_VARIANT], made = hdr[H_WAVES], histories = hdr[H_HISTORIES], first_end = wave_first[share + 1];
+    asm("" : "+s"(n_items), "+s"(first_item) : "s"(variant), "s"(made), "s"(histories), "s"(first_end));
+    const int n_shares = variant == kNoPlan ? 0 : made;   // (a reused plan that is none: nothing is swept, the merge reports it)
     const uint32_t lds_base = __builtin_amdgcn_readfirstlane(
         (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)s_stage);
     const uint32_t cols_base = __builtin_amdgcn_readfirstlane(
@@ -919,29 +937,21 @@ __global__ __launch_bounds__(64 * waves_per_group<D>()) void sweep_mfma_kernel(S
         return x;
     };
 
-    // Which shares this wave sweeps: share, share + grid, ...  Workgroups are dealt
-    // round-robin to the 8 XCDs (workgroup id mod 8), each with its own L2, while
-    // consecutive shares of a shared run are its row tiles over the same KV bytes.
-    // Put every 8 consecutive shares on one XCD so that those bytes are fetched into
-    // one L2 once.  (Pure performance: any permutation is correct.)
-    int group = blockIdx.x;
-    if (xcd_aware && (gridDim.x & 15) == 0) {
-        const int x = blockIdx.x & 7, k = blockIdx.x >> 3;
-        group = 2 * ((k >> 1) * 8 + x) + (k & 1);
-    }
-    int share = WPG * group + wv;
     const int n_waves = WPG * (int)gridDim.x;
-    const int n_shares = hdr[H_VARIANT] == kNoPlan ? 0 : hdr[H_WAVES];   // (a reused plan that is none: nothing is swept, the merge reports it)
     if constexpr (D != 256) {   // (two tiles of 256 dims would spill)
         if (__builtin_expect(histories != 0, 0)) {   // (placed behind the rest: the other way must not fetch its instructions)
             sweep_histories<D, WPG>(a, s_stage_all, hdr, wv, lane);
             return;
         }
     }
-    const int* wave_first = reinterpret_cast<const int*>(a.ws + a.lay.wave_first);
-    for (; share < n_shares; share += n_waves) {
-        int it = __builtin_amdgcn_readfirstlane(wave_first[share]);
-        const int it_end = min(n_items, __builtin_amdgcn_readfirstlane(wave_first[share + 1]));
+    for (int it_of_share = first_item, end_of_share = first_end; share < n_shares;) {
+        int it = it_of_share;
+        const int it_end = min(n_items, end_of_share);
+        share += n_waves;
+        if (share < n_shares) {
+            it_of_share = __builtin_amdgcn_readfirstlane(wave_first[share]);
+            end_of_share = __builtin_amdgcn_readfirstlane(wave_first[share + 1]);
+        }
         if (it >= it_end) continue;
         wait_vmcnt<0>();   // nothing of an earlier share is still on its way into LDS
         wait_lgkmcnt0();
@@ -961,7 +971,7 @@ __global__ __launch_bounds__(64 * waves_per_group<D>()) void sweep_mfma_kernel(S
         // workgroup: the team sweeps it together if it qualifies (every member sees the same columns, so
         // they all decide alike).  Members without rows of their own only take part in that.
         if constexpr (D == 128) {   // (the team sequence is written for head_dim 128)
-            if (a.fast_shared && team >= 2 && it + 1 == it_end && share + n_waves >= n_shares &&
+            if (a.fast_shared && team >= 2 && it + 1 == it_end && share >= n_shares &&
                 ((item.c1 - item.c0) & 1) == 0 && item.c1 - item.c0 >= 8 && item.c1 - item.c0 <= kTeamCols &&
                 item.tok_end == item.c1 * kBlock && (wv & (team - 1)) == rank) {
                 wait_lgkmcnt0();
@@ -993,7 +1003,8 @@ __global__ __launch_bounds__(64 * waves_per_group<D>()) void sweep_mfma_kernel(S
 
 void launch_sweep_mfma(const SweepArgs& a, int head_dim, int grid, const Launch& L) {
     const int g_rcp = (65536 + a.G - 1) / a.G;   // (row * g_rcp) >> 16 == row / G for the 64 rows of an item
-    static const int xcd_aware = [] { const char* v = std::getenv("FEA_XCD_AWARE"); return v && *v ? std::atoi(v) : 1; }();
+    static const int by_xcd = [] { const char* v = std::getenv("FEA_XCD_AWARE"); return v && *v ? std::atoi(v) : 1; }();
+    const int xcd_aware = by_xcd && (grid / (head_dim == 256 ? 2 : 4)) % 16 == 0;   // (of whole sets of two workgroups for each XCD)
     hipStream_t st = static_cast<hipStream_t>(L.stream);
     hipEvent_t e0 = static_cast<hipEvent_t>(L.ev_start), e1 = static_cast<hipEvent_t>(L.ev_stop);
     if (head_dim == 64) hipExtLaunchKernelGGL(sweep_mfma_kernel<64>, dim3(grid / 4), dim3(256), 0, st, e0, e1, 0, a, g_rcp, xcd_aware);

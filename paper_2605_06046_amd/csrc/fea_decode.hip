@@ -36,7 +36,7 @@ static const Knobs& knobs() {
                             env_int("FEA_MIN_PIECE", 4),     env_int("FEA_MIN_RUN", 2),    env_int("FEA_W32", 18),
                             env_int("FEA_W64", 24), env_int("FEA_NO_FAST_SHARED", 0), env_int("FEA_WTEAM", 12),
                             env_int("FEA_WTEAM2", 12), env_int("FEA_TEAM_FIXED", 40), env_int("FEA_DIRECT_PIECES", 0),
-                            env_int("FEA_HISTORIES", 12)};
+                            env_int("FEA_HISTORIES", 6)};
     return k;
 }
 
@@ -204,9 +204,15 @@ static int32_t resolve(const fea_attn_params* p, int32_t B, int32_t stride, Reso
     const int run_min = p->run_kernel_min == 0 ? 49152 : p->run_kernel_min;
     r.pre = r.grouping && (run_min < 0 || (groupable >= 128 && groupable * stride >= run_min)) ? 1 : 0;
     r.pre_grid = (int)std::max<int64_t>(1, std::min<int64_t>(2 * cu_count(), (groupable + 3) / 4));
-    // Whole histories where the planner finds nothing shared: one row tile of 16 query heads, and enough of them to even out.
+    // Whole histories where the planner finds nothing shared: one row tile of 16 query heads, as many of them as even out over the
+    // compute units (four to a unit, or not much less than a whole number), six tiles to every wave, 192 KB to a history.  Measured
+    // on 144 shapes of 48 to 400 requests against shares cut beforehand: 0.89 of a call's time with a new plan, 0.95 with a
+    // reused one (worst 0.97 and 1.01); 32/8/128, 256 requests of 512 to 1024 tokens 176 -> 146 us, 64/8/128, 512 of 512 to
+    // 4096 924 -> 829.  With histories of 64 KB on average it would be 1.08 and 1.38 (a history's start counts), at 128 to 192 KB 0.95 and 1.08.
+    // Not at head_dim 256, where two tiles in a wave's registers spill.
+    const double per_cu = (double)B * p->num_kv_heads / cu_count();
     r.histories = r.variant == 1 && p->head_dim != 256 && r.grouping && r.split_user == 0 && r.G <= 16 && B <= kGroupReqMax && stride > 0 &&
-                          (int64_t)B * p->num_kv_heads >= 4 * cu_count() ? kn.histories * r.tune.n_waves : 0;
+                          (per_cu >= 4 || (per_cu > 1 && std::ceil(per_cu) <= 1.1 * per_cu)) ? kn.histories * r.tune.n_waves : 0;
     const int64_t rows = (int64_t)B * p->num_q_heads;
     // Very many rows mean many requests and hence few pieces per row: there a wave of the merge takes
     // several rows (a long shared run cut into many pieces comes with few rows, and keeps a wave per row).
@@ -330,6 +336,7 @@ int32_t decode_impl(const fea_attn_params* p, const void* q, const void* k_cache
         pa.pre = r.pre;
         pa.pre_grid = r.pre_grid;
         pa.histories = r.histories;
+        pa.histories_each = 1536 / p->head_dim;
         if (p->flags & FEA_FLAG_REFRESH_PLAN) launch_refresh(pa, where[0]);
         else launch_plan(pa, where[0]);
     }

@@ -115,6 +115,7 @@ struct PlanArgs {
     int32_t pre;         // leaders and common runs come from run_kernel (workspace section `pre`)
     int32_t pre_grid;    // its grid
     int32_t histories;   // tiles (of 32 tokens) from which on a batch that shares nothing is swept by whole histories; 0: never
+    int32_t histories_each;   // ... and how many of them a history has to have on average
 };
 
 // What run_kernel leaves for the planner, per groupable request: the run it shares with its

@@ -397,7 +397,10 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
         __syncthreads();
         longest = ~(int)wave_min(~(uint32_t)s_sums[0][lane & 15]);
         waves_before(s_sums[1], tiles);
-        if ((long long)tiles * Hkv >= a.histories) {
+        // (enough for every wave, no history that alone takes longer than everything does on average, and none so short that
+        // its start - 6 us until its first tile is there - counts)
+        if ((long long)tiles * Hkv >= max((long long)a.histories, (long long)((longest + 2 * kBlock - 1) / (2 * kBlock)) * (a.tune.n_waves / 4)) &&
+            tiles >= (long long)a.histories_each * B) {
             const float per_class = 64.f / (float)(longest + 1);
             int cls[kGroupReqMax / kPlanThreads], at[kGroupReqMax / kPlanThreads];
 #pragma unroll

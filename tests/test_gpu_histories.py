@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 EDGES = [0, 1, 15, 16, 17, 31, 32, 33, 127, 128, 129, 255, 256, 257, 4095, 4096, 4097, 4129]
 
 
-@pytest.mark.parametrize("Hq,Hkv,d,B,typical", [(8, 8, 64, 140, 900), (14, 2, 128, 600, 900), (16, 1, 64, 1030, 800), (40, 8, 128, 130, 800)])
+@pytest.mark.parametrize("Hq,Hkv,d,B,typical", [(8, 8, 64, 140, 900), (14, 2, 128, 600, 900), (16, 1, 64, 1030, 1000), (40, 8, 128, 130, 800)])
 def test_whole_histories(Hq, Hkv, d, B, typical):
     import torch
     from paper_2605_06046_amd import (AttnParams, FEA_DTYPE_BF16, FEA_FLAG_REFRESH_PLAN, FEA_FLAG_REUSE_PLAN, fea_decode_attention,
@@ -73,3 +73,29 @@ def test_whole_histories(Hq, Hkv, d, B, typical):
     assert info["groups"] == 1 and info["grouped_requests"] == 2 and info["partial_rows"] > 0
     want = decode_attention(values(q), values(k), values(v), shared, L, requests=[a, b, 0])
     assert_close(out.float().cpu().numpy().astype(np.float64), want, "bf16", rows=[a, b, 0], what="one shared run")
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,B,tokens,longest,whole", [
+    (8, 8, 64, 128, 768, 768, True), (8, 8, 64, 128, 736, 736, False),          # 24 tiles a history
+    (8, 8, 128, 128, 384, 384, True), (8, 8, 128, 128, 352, 352, False),        # 12 tiles
+    (8, 8, 64, 128, 768, 3136, True), (8, 8, 64, 128, 768, 3264, False),        # 98 and 102 tiles, 252 workgroups for 24 800
+    (16, 1, 128, 500, 1000, 1000, True), (16, 1, 128, 530, 1000, 1000, False),  # nearly two to a compute unit, and a few more
+    (17, 1, 128, 512, 1000, 1000, False), (4, 4, 256, 300, 1000, 1000, False),
+    (8, 8, 128, 2048, 400, 400, True), (8, 8, 128, 2049, 400, 400, False),
+])
+def test_which_batches_are_read_whole(Hq, Hkv, d, B, tokens, longest, whole):
+    """By the plan alone: no caches are read."""
+    import torch
+    from paper_2605_06046_amd import AttnParams, FEA_DTYPE_BF16, FEA_FLAG_PLAN_ONLY, fea_decode_attention, fea_decode_plan_info, fea_decode_workspace_bytes
+    lens = np.full(B, tokens, dtype=np.int32)
+    lens[B // 2] = longest
+    width = -(-longest // 16) + 1
+    bt = np.arange(B * width, dtype=np.int32).reshape(B, width)
+    p = AttnParams(Hq, Hkv, d, FEA_DTYPE_BF16, flags=FEA_FLAG_PLAN_ONLY)
+    ws = torch.empty(fea_decode_workspace_bytes(p, B, width), dtype=torch.uint8, device="cuda")
+    none = torch.empty(16, dtype=torch.bfloat16, device="cuda")
+    q = torch.empty(B, Hq, d, dtype=torch.bfloat16, device="cuda")
+    fea_decode_attention(p, q, none, none, torch.from_numpy(bt).cuda(), torch.from_numpy(lens).cuda(), q, ws)
+    info = fea_decode_plan_info(ws)
+    assert info["variant"] == 1 and info["groups"] == 0 and info["overflow"] == 0
+    assert (info["partial_rows"] == 0) == whole

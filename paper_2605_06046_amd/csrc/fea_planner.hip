@@ -433,6 +433,9 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
         for (int i = tid; i < nG; i += kPlanThreads) { u.c.run[i] = INT_MAX; u.c.cnt[i] = 0; u.c.moff[i] = moff0; }
     };
     reset_groups(0);
+    // (where the runs are already known no other barrier stands between what is read and written above - whether anything is
+    // shared, which thread 0 clears below, and the groups' words, which the first round below counts in - and there)
+    if (a.pre) __syncthreads();
 
     // ---- longest common run of block ids with the leader's row.  All (follower,
     // column group) pairs are spread flat over the threads, six at a time so that

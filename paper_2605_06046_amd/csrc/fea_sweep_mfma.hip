@@ -701,8 +701,9 @@ template <int D, int W>
 __device__ __forceinline__ void sweep_histories(const SweepArgs& a, char* lds, int* hdr, int wave, int lane) {
     using TileT = tile::Tile<tile::bf16_t, D, kHistoryRows>;
     constexpr int TB = TileT::TB, NI = TileT::NI, PN = TileT::PN, BLK = kBlock * D * 2, PAD = D + 4;
-    struct Fold { float acc[W][kHistoryRows][PAD]; float2 ml[W][kHistoryRows]; int next; };   // (two in turn: one barrier a history)
+    struct alignas(16) Fold { float acc[W][kHistoryRows][PAD]; float2 ml[W][kHistoryRows]; int next; };   // (two in turn: one barrier a history)
     static_assert(2 * sizeof(Fold) <= (size_t)W * kStages * 4 * BLK, "fits the tile stages");
+    static_assert(sizeof(Fold) % 16 == 0 && PAD % 4 == 0, "rows of the second one are written 16 bytes at a time as well");
     Fold* folds = reinterpret_cast<Fold*>(lds);
     const int n = lane & 15, kg = lane >> 4, tid = wave * 64 + lane;
     const int units = a.B * a.Hkv;

@@ -101,8 +101,9 @@ typedef struct fea_attn_params {
                                decides, from an estimate of both ways' durations (about: up to 64 MB
                                of KV histories at full table rows, up to 225 MB with more than eight
                                query heads per KV head, 300 MB with few of them and one workgroup to
-                               a compute unit; nearly always for float32 caches and query groups the
-                               matrix-core sweep does not take); < 0: never;
+                               a compute unit; for float32 caches and query groups the matrix-core
+                               sweep does not take mostly, unless one workgroup would read more than
+                               1.5 MB of a history alone); < 0: never;
                                > 0: every batch whose table rows have at most this many entries */
 } fea_attn_params;
 

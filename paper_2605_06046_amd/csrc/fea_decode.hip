@@ -108,10 +108,12 @@ static int64_t direct_pieces(const fea_attn_params* p, int64_t B, int64_t stride
 // query groups of 1 to 96, 0 to 98 % shared), alone and against a reused plan.  On the matrix-core path, by the bytes of
 // KV histories that its workgroups read:
 //  - up to 64 MB.  Nothing shared: 8 requests of 1024 tokens 13.5 against 24.8 us.
-//  - more than eight query heads per KV head, in at most four workgroups to a compute unit, up to 225 MB: on 100 shapes of 100
-//    to 225 MB 0.53 of the time of a new plan and 0.76 of the reused plan's, never more than 1.06 (32/2/128, 160 requests of
-//    1216 tokens).  With fewer heads it wins there too in the mean (0.8 of the reused plan's up to 145 MB), but loses where
-//    much is shared: 12/4/64, 24 requests of 5280 tokens (130 MB), 98 % shared, 1.20; from 225 to 290 MB 0.97 and up to 1.64.
+//  - more than eight query heads per KV head, in at most four workgroups to a compute unit, up to 225 MB, where a wave has twelve
+//    tiles at most: on 100 shapes of 100 to 225 MB 0.53 of the time of a new plan and 0.76 of the reused plan's, never more than
+//    1.06 (32/2/128, 160 requests of 1216 tokens).  With fewer heads it wins there too in the mean (0.8 of the reused plan's up to
+//    145 MB), but loses where much is shared: 12/4/64, 24 requests of 5280 tokens (130 MB), 98 % shared, 1.20; from 225 to 290 MB
+//    0.97 and up to 1.64.  Some long histories among short ones (41 shapes): never more than 0.97 of a new plan up to twelve tiles, at
+//    worst 1.57 of a reused one (49 requests, 4448 tokens and 194); with 15 and 19 tiles 0.91 and 1.27, and 1.88 and 2.49.
 //  - in up to six workgroups to a compute unit (each has a few us of start-up) up to 100 MB: bf16 32/8/128, 32 requests of
 //    752 tokens, 19.0 against 35.2 and, of the reused plan, 24.5; 90 % shared 12.1 against 33.9 and 21.9.  In eight rounds of
 //    workgroups, 256 requests of 80 tokens, 31.7 against 37.8 and 26.2.
@@ -120,22 +122,30 @@ static int64_t direct_pieces(const fea_attn_params* p, int64_t B, int64_t stride
 //    requests of 1520 tokens 36.1 against 52.1 and 40.9, 90 % shared 19.2 against 39.7 and 27.3.
 //    Longer histories lose to a reused plan: 8/2/64, 128 requests of 4112 tokens, 90 % shared, 28.1 against 38.6 and 22.2.
 // The vector-unit sweep costs 26 to 120 us to start with, and from some hundred thousand (query row, token) pairs on time in
-// proportion to them.  float32 from 2 to 16 query heads per KV head: the plan-free kernel wins on all of 1174 shapes (60 MB to
-// 9 GB of histories, 0 to 99 % shared; 0.25 of the reused plan's time in the mean, 0.82 the closest: 2/1/32, 300 requests
-// of 32544 tokens, 90 % shared, 290 against 351 us).  With one head it can lose on histories that are shared and long (8/8/64,
-// 1000 requests of 2192 tokens, 99 % shared: 612 against 515 and 480 us).
+// proportion to them.  float32 from 2 to 16 query heads per KV head: the plan-free kernel wins on all of 1174 shapes of even
+// lengths (60 MB to 9 GB of histories, 0 to 99 % shared; 0.25 of the reused plan's time in the mean, 0.82 the closest: 2/1/32,
+// 300 requests of 32544 tokens, 90 % shared, 290 against 351 us).  But the table's width does not tell how long the others are,
+// and one long history among short ones is read by its own workgroups alone, at 53 GB/s each, where a plan spreads it over the
+// chip: 2/1/64, 134 requests, one of 46207 tokens and the rest of 34, 394 against 58 and, of the reused plan, 24 us.  So up to
+// 1.5 MB of a history to a workgroup: on 107 shapes there (one or a twentieth of the requests long, or all alike) at most 0.76 of
+// a new plan's time and 1.51 of a reused one's (0.44 and 0.54 in the mean); beyond it up to 1.44 of a new plan's time at 2.3 MB
+// and 6.8 at 24.  And up to the 10 GB that were measured.  Past either line the estimate decides, and with one head: that can lose on histories
+// that are shared and long (8/8/64, 1000 requests of 2192 tokens, 99 % shared: 612 against 515 and 480 us).
+// The estimate's 2 us a round and 4 us for the fold of pieces say where that line was measured to lie, not what the two cost
+// today (2.3 and 3): with those, 82 of 200 shapes near the line would change sides, 76 of them to a plan, which takes 1.38 of
+// their time now where it is new and 0.74 where it is reused.
 static bool direct_pays(const fea_attn_params* p, int64_t B, int64_t stride, int variant) {
     const bool f32 = p->dtype == FEA_DTYPE_F32;
     const double group = (double)(p->num_q_heads / p->num_kv_heads), groups = (double)direct_groups(p, B), cus = cu_count();
     const double tokens = (double)stride * kBlock, dd = p->head_dim / 64.0;
     const double per_group = tokens * p->head_dim * (f32 ? 8.0 : 4.0), bytes = groups * per_group;   // K and V read by a workgroup, by all
+    const int64_t pieces = direct_pieces(p, B, stride), rounds = (direct_rounds(p, stride) + pieces - 1) / pieces;
     if (variant == 1) {
-        if (bytes <= 64e6 || (group > 8 && bytes <= 225e6 && groups <= 4 * cus) || (bytes <= 100e6 && groups <= 6 * cus) || (bytes <= 128e6 && direct_tiles(p, stride) <= 2)) return true;
+        if (bytes <= 64e6 || (group > 8 && bytes <= 225e6 && groups <= 4 * cus && rounds <= 12) || (bytes <= 100e6 && groups <= 6 * cus) || (bytes <= 128e6 && direct_tiles(p, stride) <= 2)) return true;
         return group <= 4 && ((groups <= cus && per_group <= (p->head_dim == 256 ? 1.33e6 : 1 << 20)) || (groups <= 2 * cus && per_group <= 1 << 18));
     }
-    if (f32 && group >= 2 && group <= 16) return true;
-    const int64_t pieces = direct_pieces(p, B, stride);
-    const double serial_us = 2.0 * (double)((direct_rounds(p, stride) + pieces - 1) / pieces);   // one workgroup's tiles, a round after the other
+    if (f32 && group >= 2 && group <= 16 && bytes <= 10e9 && per_group <= 1.5e6 * (double)pieces) return true;
+    const double serial_us = 2.0 * (double)rounds;   // one workgroup's tiles, a round after the other
     const double direct_us = 7.0 + (pieces > 1 ? 4.0 : 0.0) + std::max(serial_us, bytes / 8.0e6);
     const double base = B < 4 ? 20.0 + 1.5 * group : std::min(30.0 + 4.0 * group, 120.0);
     const double planned_us = (B < 16 ? base : std::max(94.0, base)) * (p->head_dim >= 128 ? 1.4 : 1.0) +   // (it passes over its tokens once per 4 or 16 stacked rows)

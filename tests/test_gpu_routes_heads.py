@@ -1,5 +1,5 @@
 """Lines of the default route that go by the query heads of a KV head: bfloat16 with more than eight up to 225 MB of histories,
-float32 with two to sixteen at any length; on either side the other way's result and the oracle's."""
+float32 with two to sixteen up to 1.5 MB of a history to a workgroup; on either side the other way's result and the oracle's."""
 import pytest
 
 from test_gpu_routes import _check

@@ -159,6 +159,9 @@ __global__ __launch_bounds__(64 * W) void decode_direct_kernel(SweepArgs a, int 
         if (rest < TB * kBlock) tile.mask(p, rest, n, kg);
         weigh_tile(p);
         tile.accumulate(p, o, n);
+        if constexpr (sizeof(T) == 2) {
+            if (__builtin_expect(any_nan<TileT>(o), 0)) sweep_apart<TileT, D>(tile, o, m, l, a, row, g, L, first, step, n, kg);
+        }
     }
     TileT::template to_lds<PAD>(s_acc[wave], o, nh, n, kg);
     l = TileT::row_sum(l);

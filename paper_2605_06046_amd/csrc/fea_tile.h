@@ -201,7 +201,9 @@ template <int D> struct Tile<bf16_t, D, 16> {
 #pragma unroll
             for (int r = 0; r < 4; ++r) p[4 * b + r] = s[b][r];
     }
-    __device__ __forceinline__ void accumulate(const float (&p)[PN], f32x4 (&o)[NI], int n) {
+    // (APART: what is left of a weight meets zeros where V is infinite or NaN: the rounded weight has made that product, and
+    // zero or a negative rest times infinity would make the sum NaN)
+    template <bool APART = false> __device__ __forceinline__ void accumulate(const float (&p)[PN], f32x4 (&o)[NI], int n) {
         bf16x8 hi, lo;
 #pragma unroll
         for (int x = 0; x < 8; ++x) {
@@ -232,7 +234,12 @@ template <int D> struct Tile<bf16_t, D, 16> {
             }
             const bf16x8 a = __builtin_bit_cast(bf16x8, t);
             o[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, hi, o[i], 0, 0, 0);
-            o[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, lo, o[i], 0, 0, 0);
+            if constexpr (APART) {
+#pragma unroll
+                for (int w = 0; w < 4; ++w)
+                    t[w] &= ((t[w] & 0x7F80u) == 0x7F80u ? 0u : 0xFFFFu) | ((t[w] & 0x7F800000u) == 0x7F800000u ? 0u : 0xFFFF0000u);
+            }
+            o[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, t), lo, o[i], 0, 0, 0);
         }
     }
     static __device__ __forceinline__ int head(int n) { return n; }
@@ -428,6 +435,48 @@ __device__ __forceinline__ void weigh(float (&p)[TileT::PN], f32x4 (&o)[TileT::N
     for (int y = 0; y < TileT::PN; ++y) {
         p[y] = exp2_fast(fmaf(p[y], scale_log2, -m));
         l += p[y];
+    }
+}
+
+// Whether any of a wave's sums is NaN.  (The maximum that hands NaN on takes two of them an instruction: 16 to 32, once a history.)
+template <class TileT> __device__ __forceinline__ bool any_nan(const f32x4 (&o)[TileT::NI]) {
+    f32x4 x = o[0];
+#pragma unroll
+    for (int i = 1; i + 1 < TileT::NI; i += 2)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x[r] = __builtin_elementwise_maximum(__builtin_elementwise_maximum(x[r], o[i][r]), o[i + 1][r]);
+    static_assert(TileT::NI % 2 == 0, "the last one is left over");
+#pragma unroll
+    for (int r = 0; r < 4; ++r) x[r] = __builtin_elementwise_maximum(x[r], o[TileT::NI - 1][r]);
+    const float y = __builtin_elementwise_maximum(__builtin_elementwise_maximum(x[0], x[1]), __builtin_elementwise_maximum(x[2], x[3]));
+    return __any(y != y);
+}
+// The tiles first, first + step, ... of a history once more where a sum is NaN (bfloat16): V holds infinities or NaN then, or the
+// scores do, and only the rounded part of a weight may meet an infinity of V.  One tile after the other: nothing waits for such a
+// row.  Every other sum comes out as it was.
+template <class TileT, int D> __device__ __forceinline__ void sweep_apart(TileT& tile, f32x4 (&o)[TileT::NI], float& m, float& l, const SweepArgs& a,
+                                                                          const int32_t* row, int g, int L, int first, int step, int n, int kg) {
+    constexpr int TB = TileT::TB, PN = TileT::PN, BLK = kBlock * D * TileT::ES;
+    const int nb = (L + kBlock - 1) / kBlock, ntiles = (nb + TB - 1) / TB;
+#pragma unroll
+    for (int j = 0; j < TileT::NI; ++j) o[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    m = kLowest;
+    l = 0.f;
+#pragma unroll 1
+    for (int t = first; t < ntiles; t += step) {
+#pragma unroll
+        for (int b = 0; b < TB; ++b) {
+            const int blk = max(__builtin_amdgcn_readfirstlane(row[TB * t + (TB * t + b < nb ? b : 0)]), 0);
+            const size_t off = ((size_t)blk * a.Hkv + g) * BLK;
+            tile.load_k(b, static_cast<const char*>(a.k_cache) + off, n, kg);
+            tile.load_v(b, static_cast<const char*>(a.v_cache) + off, n, kg);
+        }
+        float p[PN];
+        tile.scores(p);
+        const int rest = L - t * (TB * kBlock);
+        if (rest < TB * kBlock) tile.mask(p, rest, n, kg);
+        weigh<TileT, bf16_t>(p, o, m, l, a.scale_log2);
+        tile.template accumulate<true>(p, o, n);
     }
 }
 

@@ -227,14 +227,14 @@ __global__ __launch_bounds__(64 * W) void decode_direct_kernel(SweepArgs a, int 
                     float Mn = M;
 #pragma unroll
                     for (int k = 0; k < kAtOnce; ++k) Mn = fmaxf(Mn, v[k].x);   // (where there is none left: the last piece's)
-                    const float f0 = exp2_fast(M - Mn);
+                    const float f0 = exp2f(M - Mn);   // (exp2f: pieces whose weights lie below 2^-126 count, as in a merge)
                     M = Mn;
                     den *= f0;
                     num *= f0;
 #pragma unroll
                     for (int k = 0; k < kAtOnce; ++k) {
                         if (p0 + k < pieces) {
-                            const float f = exp2_fast(v[k].x - M);
+                            const float f = exp2f(v[k].x - M);
                             den = fmaf(f, v[k].y, den);
                             num[0] = fmaf(f, x0[k].x, num[0]);
                             num[1] = fmaf(f, x0[k].y, num[1]);

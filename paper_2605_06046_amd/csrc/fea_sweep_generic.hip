@@ -347,7 +347,7 @@ __global__ __launch_bounds__(256) void merge_kernel(SweepArgs a) {
         for (int q = 0; q < kInFlight; ++q) mb = fmaxf(mb, v[q].x);
         const float Mn = fmaxf(M, mb);
         if (Mn > M) {                                   // raise the group's reference (a no-op on empty sums)
-            const float f = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - Mn);
+            const float f = M == -INFINITY ? 0.f : exp2f(M - Mn);
             den *= f;
 #pragma unroll
             for (int k = 0; k < 8; ++k) num[k] *= f;
@@ -355,7 +355,7 @@ __global__ __launch_bounds__(256) void merge_kernel(SweepArgs a) {
         }
 #pragma unroll
         for (int q = 0; q < kInFlight; ++q) {
-            const float w = v[q].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(v[q].x - M);
+            const float w = v[q].x == -INFINITY ? 0.f : exp2f(v[q].x - M);
             den = fmaf(w, v[q].y, den);
             num[0] = fmaf(w, x[q][0].x, num[0]); num[1] = fmaf(w, x[q][0].y, num[1]);
             num[2] = fmaf(w, x[q][0].z, num[2]); num[3] = fmaf(w, x[q][0].w, num[3]);
@@ -365,7 +365,7 @@ __global__ __launch_bounds__(256) void merge_kernel(SweepArgs a) {
     }
     // fold the lane groups (fixed order: deterministic) at the common reference
     const float Mg = over_groups<LPR>(M, [](float x, float y) { return fmaxf(x, y); });
-    const float f = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - Mg);
+    const float f = M == -INFINITY ? 0.f : exp2f(M - Mg);
     auto add = [](float x, float y) { return x + y; };
     den = over_groups<LPR>(den * f, add);
 #pragma unroll

@@ -62,3 +62,20 @@ def test_whole_histories(Hq, Hkv, d, B):
         want = decode_attention(values(q), values(k), values(v), bt, L, requests=rows)
     _check(out, want, "bf16", rows, f"{Hq}/{Hkv}/{d} {B}")
     assert np.isfinite(np.delete(out, rows[1:], axis=0)).all()
+
+
+@pytest.mark.parametrize("dtype,Hq,Hkv,d,low", [("f32", 8, 2, 64, -752), ("bf16", 8, 2, 64, -752), ("bf16", 14, 2, 128, -1064), ("bf16", 4, 2, 256, -1504)])
+@pytest.mark.parametrize("how", [dict(fused_max=-1, split_blocks=2), dict(fused_max=-1, split_blocks=2, merge_rows_min=-1), dict(fused_max=1 << 20)])
+def test_a_piece_whose_weight_is_subnormal(dtype, Hq, Hkv, d, low, how):
+    """The first 256 tokens weigh e^-94 (2^-136) of the others: a piece of their own that holds an infinity still makes the output
+    infinite."""
+    q, k, v, bt, L = _batch(dtype, Hq, Hkv, d, [1601], 33)
+    bits = (lambda x: W.f32_to_bf16_bits(np.array([x], np.float32))[0]) if dtype == "bf16" else np.float32
+    q[0, :Hq // Hkv, 0] = bits(1)
+    for t in range(256):
+        k[bt[0, t // 16], 0, t % 16, 0] = bits(low)
+    v[bt[0, 0], 0, 3, 1] = bits(np.inf)
+    out, info = run_hip(q, k, v, bt, L, Hq, Hkv, d, dtype, **how)
+    want = decode_attention(values(q), values(k), values(v), bt, L)
+    assert np.isposinf(want[0, :Hq // Hkv, 1]).all() and np.array_equal(np.isposinf(out), np.isposinf(want))
+    assert_close(np.where(np.isinf(want), 0, out), np.where(np.isinf(want), 0, want), dtype, what=f"{dtype} {Hq}/{Hkv}/{d} {how}")

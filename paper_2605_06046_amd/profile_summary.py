@@ -33,18 +33,26 @@ import glob
 import hashlib
 import json
 import os
+import re
 import sys
 
 GIB_KIB = 1 << 20   # a 1 GiB copy moves this many KiB each way
 
 
 def kernel_rev(root: str) -> str:
-    """Identifies the sweep kernel's code: its source files.  The counters of a summary stay valid for
-    a build whose sweep source is the same and whose plan for the workload (stored next to them) is the
-    same, since the kernel then does the same loads and stores."""
+    """Identifies the sweep kernel's code: its source file and what that includes of the library's own.  The counters
+    of a summary stay valid for a build whose sweep source is the same and whose plan for the workload (stored next to
+    them) is the same, since the kernel then does the same loads and stores."""
+    csrc, todo, texts = os.path.join(root, "paper_2605_06046_amd", "csrc"), ["fea_sweep_mfma.hip"], {}
+    while todo:
+        name = todo.pop()
+        if name not in texts:
+            with open(os.path.join(csrc, name), "rb") as f:
+                texts[name] = f.read()
+            todo += [x.decode() for x in re.findall(rb'#include "(fea_[^"]+)"', texts[name])]
     h = hashlib.sha256()
-    for name in ("fea_sweep_mfma.hip", "fea_sweep_core.inc", "fea_plan.h"):
-        h.update(open(os.path.join(root, "paper_2605_06046_amd", "csrc", name), "rb").read())
+    for name in sorted(texts):
+        h.update(texts[name])
     return h.hexdigest()[:12]
 
 

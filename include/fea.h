@@ -328,7 +328,12 @@ int32_t fea_decode_attention_static(const fea_attn_params* p,
  * kernel variant (0 generic, 1 MFMA, 2 no plan needed, see fused_max), overflow flag (1: the plan did not fit
  * its buffers, 2: FEA_FLAG_REFRESH_PLAN met a request it cannot stretch, or
  * FEA_FLAG_REUSE_PLAN a workspace whose last call needed no plan), sweep waves that
- * were given a share }. */
+ * were given a share }.
+ * A large batch in which nothing is shared may be left whole: the sweep then reads one
+ * history of a (request, KV head) after the other, in the order of their lengths, and
+ * merges nothing.  Kernel variant 1 and partial rows 0 tell such a plan; its work items
+ * are the B * num_kv_heads histories, blocks per work item those of the longest one, and
+ * the waves those that pieces would have been cut for. */
 int32_t fea_decode_plan_info(const void* workspace /* DEVICE */, void* hip_stream,
                              int32_t* info /* HOST [9] */);
 

@@ -24,7 +24,7 @@ def run_hip(q, k_cache, v_cache, bt, lens, num_q_heads, num_kv_heads, head_dim, 
     """q/k/v: numpy (float32 or bf16 bits); bt/lens: numpy int32.  Returns (out float64, plan info).
 
     Unless the caller says otherwise (fused_max), the call goes through plan, sweep and merge also where the
-    library would by default do a small batch without a plan (one launch, or two where histories are cut): most
+    library would by default do a small batch without a plan (one launch, also where histories are cut): most
     cases here are small so that the oracle finishes, and it is the planned path they are written for.  The
     plan-free kernel has tests of its own."""
     import torch

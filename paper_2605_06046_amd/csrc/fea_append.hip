@@ -9,6 +9,7 @@
 #include <hip/hip_ext.h>
 
 #include "../../include/fea.h"
+#include "fea_device.h"
 #include "fea_internal.h"
 #include "fea_plan.h"
 
@@ -24,14 +25,6 @@ struct AppendArgs {
     int32_t stride, B, Hkv;
     int32_t row_bytes;     // head_dim * element size: one token of one KV head
 };
-
-// x mod d, and x becomes x / d (d is mostly a power of two; a true 64-bit division is a hundred dependent instructions).
-__device__ __forceinline__ int take_digit(long long& x, int d) {
-    const long long v = x;
-    if ((d & (d - 1)) == 0) { x = v >> (31 - __clz(d)); return (int)(v & (d - 1)); }
-    x = v / d;
-    return (int)(v - x * d);
-}
 
 // Bound: a launch (3 us with nothing in it) and two round trips, the length and then the block; the new row is asked for with
 // the length, and arrives meanwhile.

@@ -168,28 +168,15 @@ __global__ __launch_bounds__(64 * W) void decode_direct_kernel(SweepArgs a, int 
     if (TileT::one_of_row(n, kg)) s_ml[wave][TileT::head(n)] = make_float2(m, l);
     __syncthreads();
 
-    // fold the waves (fixed order) at the common reference exponent
+    // fold the waves
     float* const acc = reinterpret_cast<float*>(a.ws + a.lay.acc);
     float* const mls = reinterpret_cast<float*>(a.ws + a.lay.ml);
     const size_t row0 = (size_t)(i * a.Hkv + g) * pieces * a.G + 16 * rt;   // of piece p and the tile's head h: partial row row0 + p G + h
     char* const out = static_cast<char*>(a.out) + ((size_t)i * a.Hq + g * a.G + 16 * rt) * (D * ES);
     for (int y = tid; y < nh * (D / 8); y += 64 * W) {
         const int h = y / (D / 8), c = y - h * (D / 8);
-        float M = kLowest;
-#pragma unroll
-        for (int w = 0; w < W; ++w) M = fmaxf(M, s_ml[w][h].x);
-        float den = 0.f, num[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) num[e] = 0.f;
-#pragma unroll
-        for (int w = 0; w < W; ++w) {
-            const float2 ml = s_ml[w][h];
-            const float f = exp2_fast(ml.x - M);   // (a wave that had no tile, or no score above -inf, has sums of 0)
-            den = fmaf(f, ml.y, den);
-            const f32x4 a0 = *reinterpret_cast<const f32x4*>(&s_acc[w][h][8 * c]), a1 = *reinterpret_cast<const f32x4*>(&s_acc[w][h][8 * c + 4]);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) { num[e] = fmaf(f, a0[e], num[e]); num[4 + e] = fmaf(f, a1[e], num[4 + e]); }
-        }
+        float M, den, num[8];
+        fold_waves(s_acc, s_ml, h, c, M, den, num);
         if (pieces > 1) {
             const size_t r = row0 + (size_t)pc * a.G + h;
 #pragma unroll

@@ -17,6 +17,7 @@
 #include <type_traits>
 
 #include "../../include/fea.h"
+#include "fea_device.h"
 #include "fea_plan.h"
 
 namespace fea {
@@ -245,9 +246,6 @@ __global__ __launch_bounds__(kGenThreads) void sweep_generic_kernel(SweepArgs a)
 
 // x combined over the lane groups of GROUP lanes, lane by lane, without a detour through LDS (groups of the first lanes of a
 // wave get it; within a row of 16 lanes by rotations, across rows by exchanging halves).
-template <int CTRL> __device__ __forceinline__ float lanes_moved(float x) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, true));
-}
 template <int GROUP, class F> __device__ __forceinline__ float over_groups(float x, F&& f) {
     if constexpr (GROUP <= 4) x = f(x, lanes_moved<0x124>(x));
     if constexpr (GROUP <= 8) x = f(x, lanes_moved<0x128>(x));
@@ -257,14 +255,6 @@ template <int GROUP, class F> __device__ __forceinline__ float over_groups(float
     }
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return f(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-
-// x mod d, and x becomes x / d; a true division is 40 dependent instructions, and d is mostly a power of two.
-__device__ __forceinline__ int take_digit(int& x, int d) {
-    const int v = x;
-    if ((d & (d - 1)) == 0) { x = v >> (31 - __clz(d)); return v & (d - 1); }
-    x = v / d;
-    return v - x * d;
 }
 
 // out[i,h,:] = sum_s 2^(m_s - M) acc_s / sum_s 2^(m_s - M) l_s over the partials

@@ -58,10 +58,6 @@
 
 namespace fea {
 
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
-typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
 constexpr int kD = 128;                 // head dim of the team sequence (the sweep itself is instantiated per head dim)
 constexpr int kTileTok = 32;            // tokens per tile (two blocks)
 constexpr int kBlkBytes = kBlock * kD * 2;      // one (block, KV head) at that head dim: 4096 bytes
@@ -71,8 +67,6 @@ constexpr int kDescWindow = 8;           // item descriptors fetched into LDS at
 constexpr float kSlack = 24.f;           // log2 of the largest softmax weight tolerated before the reference is raised
 
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
-__device__ __forceinline__ u32x4 ld16(const void* p) { return *reinterpret_cast<const u32x4*>(p); }
-__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // Wave-uniform values that must sit in scalar registers (folded away by the compiler
 // where it already knows them to be uniform).
@@ -534,7 +528,7 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const Item& item,
                 float rmax = fmaxf(tmax[nt], __shfl_xor(tmax[nt], 16));
                 rmax = fmaxf(rmax, __shfl_xor(rmax, 32));
                 const float m_new = fmaxf(m_run[nt], rmax);
-                const float alpha = fast_exp2(m_run[nt] - m_new);
+                const float alpha = exp2_fast(m_run[nt] - m_new);
                 scale_acc(lacc[nt], alpha);
 #pragma unroll
                 for (int i = 0; i < NI; ++i) scale_acc(oacc[nt][i], alpha);
@@ -550,7 +544,7 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const Item& item,
             scores(nt, r);
             bf16x8 pB;
 #pragma unroll
-            for (int x = 0; x < 8; ++x) pB[x] = (__bf16)fast_exp2(fmaf(r[x], a.scale_log2, neg_m));
+            for (int x = 0; x < 8; ++x) pB[x] = (__bf16)exp2_fast(fmaf(r[x], a.scale_log2, neg_m));
             lacc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pB, lacc[nt], 0, 0, 0);
 #pragma unroll
             for (int i = 0; i < NI; ++i)
@@ -726,9 +720,9 @@ __device__ __forceinline__ void sweep_histories(const SweepArgs& a, char* lds, i
         const int L = __builtin_amdgcn_readfirstlane(min(max(raw_len, 0), a.stride * kBlock));
         const int nb = (L + kBlock - 1) / kBlock, ntiles = (nb + TB - 1) / TB;
         const int count = (ntiles - wave + W - 1) / W;   // of this wave (its tile k: wave + k W); <= 0: none
-        tile::f32x4 o[NI];
+        f32x4 o[NI];
 #pragma unroll
-        for (int j = 0; j < NI; ++j) o[j] = tile::f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < NI; ++j) o[j] = f32x4{0.f, 0.f, 0.f, 0.f};
         float m = kLowest, l = 0.f;
         const char* kb[TB];
         const char* vb[TB];
@@ -814,23 +808,12 @@ __device__ __forceinline__ void sweep_histories(const SweepArgs& a, char* lds, i
         unit = __builtin_amdgcn_readfirstlane(f.next);
         for (int y = tid; y < a.G * (D / 8); y += 64 * W) {
             const int h = y / (D / 8), c = y - h * (D / 8);
-            float M = kLowest, den = 0.f, num[8];
-#pragma unroll
-            for (int w = 0; w < W; ++w) M = fmaxf(M, f.ml[w][h].x);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) num[e] = 0.f;
-#pragma unroll
-            for (int w = 0; w < W; ++w) {
-                const float2 ml = f.ml[w][h];
-                const float s = fast_exp2(ml.x - M);   // (a wave that had no tile, or no score above -inf, has sums of 0)
-                den = fmaf(s, ml.y, den);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) num[e] = fmaf(s, f.acc[w][h][8 * c + e], num[e]);
-            }
+            float M, den, num[8];
+            tile::fold_waves(f.acc, f.ml, h, c, M, den, num);
             const float inv = L == 0 ? 0.f : 1.f / den;   // an empty history gives a zero row, one of scores of -inf alone 0/0
             u32x4 w;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) w[e] = tile::bf16_rne(num[2 * e] * inv) | (tile::bf16_rne(num[2 * e + 1] * inv) << 16);
+            for (int e = 0; e < 4; ++e) w[e] = bf16_rne(num[2 * e] * inv) | (bf16_rne(num[2 * e + 1] * inv) << 16);
             *reinterpret_cast<u32x4*>(static_cast<char*>(a.out) + ((size_t)i * a.Hq + g * a.G + h) * (D * 2) + 16 * c) = w;
         }
     }

@@ -4,24 +4,14 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include "fea_device.h"
 #include "fea_plan.h"
 
 namespace fea {
 namespace tile {
 
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 struct bf16_t { uint16_t bits; };
 
-__device__ __forceinline__ u32x4 ld16(const void* p) { return *reinterpret_cast<const u32x4*>(p); }
-__device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
-
-__device__ __forceinline__ uint32_t bf16_rne(float v) {
-    uint32_t u = __float_as_uint(v);
-    if ((u & 0x7FFFFFFFu) > 0x7F800000u) return 0x7FC0u;
-    return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
-}
 
 // Sums, maxima and exchanges across the halves and the rows of 16 lanes of a wave, without a detour through LDS.
 struct Pair { float a, b; };
@@ -32,9 +22,6 @@ __device__ __forceinline__ Pair swap32(float x, float y) {   // the upper half o
 __device__ __forceinline__ Pair swap16(float x, float y) {   // the odd rows of x against the even rows of y
     const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
     return {__uint_as_float(r[0]), __uint_as_float(r[1])};
-}
-template <int CTRL> __device__ __forceinline__ float lanes_moved(float x) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, true));
 }
 __device__ __forceinline__ float max_over_kg(float x) {
     const Pair p = swap32(x, x);
@@ -403,14 +390,6 @@ template <int D> struct Tile<float, D, 4> {
     }
 };
 
-// x mod d, and x becomes x / d; the divisors are mostly powers of two (1 among them), and a true division is 40 dependent instructions.
-__device__ __forceinline__ int take_digit(int& x, int d) {
-    const int v = x;
-    if ((d & (d - 1)) == 0) { x = v >> (31 - __clz(d)); return v & (d - 1); }
-    x = v / d;
-    return v - x * d;
-}
-
 // log2 of the largest softmax weight before a row's reference exponent is raised.  float32: any score above it raises it
 // (the rounding of score - reference grows with its size, so the largest weights want theirs near zero).
 template <typename T> constexpr float direct_slack() { return sizeof(T) == 4 ? 0.f : 24.f; }
@@ -477,6 +456,26 @@ template <class TileT, int D> __device__ __forceinline__ void sweep_apart(TileT&
         if (rest < TB * kBlock) tile.mask(p, rest, n, kg);
         weigh<TileT, bf16_t>(p, o, m, l, a.scale_log2);
         tile.template accumulate<true>(p, o, n);
+    }
+}
+
+// Elements 8 c .. 8 c + 7 of head h's row, folded over the waves of a workgroup (in fixed order) at their common reference
+// exponent M.  A wave that had no tile, or no score above -inf, has sums of 0.
+template <int W, int R, int PAD> __device__ __forceinline__ void fold_waves(const float (&acc)[W][R][PAD], const float2 (&ml)[W][R], int h, int c,
+                                                                            float& M, float& den, float (&num)[8]) {
+    M = kLowest;
+#pragma unroll
+    for (int w = 0; w < W; ++w) M = fmaxf(M, ml[w][h].x);
+    den = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) num[e] = 0.f;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        const float f = exp2_fast(ml[w][h].x - M);
+        den = fmaf(f, ml[w][h].y, den);
+        const f32x4 a0 = *reinterpret_cast<const f32x4*>(&acc[w][h][8 * c]), a1 = *reinterpret_cast<const f32x4*>(&acc[w][h][8 * c + 4]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { num[e] = fmaf(f, a0[e], num[e]); num[4 + e] = fmaf(f, a1[e], num[4 + e]); }
     }
 }
 

@@ -133,8 +133,9 @@ __device__ __forceinline__ int block_scan_excl(int v, int* s_sums, int& total) {
 // Four neighbouring table columns, loadable from any 4-byte boundary.
 struct __attribute__((packed, aligned(4))) Cols4 { int32_t c[4]; };
 
-// Hash slots for n keys: 16 each (a probe more is a serial round trip to LDS for a whole wave; with four each 1.3 us were lost
-// where 120 keys are looked up), but not all 4096 for a few keys, since all are cleared.
+// Hash slots for n keys: 16 each up to 256 keys (a probe more is a serial round trip to LDS for a whole wave; with four each
+// 1.3 us were lost where 120 keys are looked up; not all 4096 for a few keys, since all are cleared), then 4096 in all, which
+// come down to two each at the limit of 2048.
 __device__ __forceinline__ int slots_for(int n) {
     int slots = 512;
     while (slots < 16 * n && slots < kHashSlots) slots <<= 1;

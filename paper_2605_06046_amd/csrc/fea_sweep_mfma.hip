@@ -689,7 +689,8 @@ template <int D> constexpr int waves_per_group() { return D == 256 ? 2 : kWavesP
 // A batch that shares nothing: workgroups take whole histories of a (request, KV head), in the planner's order, and write the
 // output.  Wave w of W takes every W-th tile of 32 tokens, two of them in its registers (fea_tile.h): one is worked on while
 // the other arrives, and a tile is asked for as soon as the one two before it has been read.  The next history is claimed
-// while this one is read.
+// while this one is read.  (A weight enters the second product as two bfloat16 numbers here, the denominator unrounded: 0.7 of
+// the shares' error against float64, 0.00166 against 0.00233 for 512 requests of 512 to 4096 tokens, 64/8/128.)
 constexpr int kHistoryRows = 16;
 template <int D, int W>
 __device__ __forceinline__ void sweep_histories(const SweepArgs& a, char* lds, int* hdr, int wave, int lane) {

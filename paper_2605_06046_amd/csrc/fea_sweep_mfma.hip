@@ -799,7 +799,7 @@ __device__ __forceinline__ void sweep_histories(const SweepArgs& a, char* lds, i
             } else {
                 last(A, 0);
             }
-            if (__builtin_expect(tile::any_nan<TileT>(o), 0)) tile::sweep_apart<TileT, D>(A, o, m, l, a, row, g, L, wave, W, n, kg);
+            if (__builtin_expect(__any(tile::any_nan(o)), 0)) tile::sweep_apart<TileT, D>(A, o, m, l, a, row, g, L, wave, 1, W, n, kg);
         }
         TileT::template to_lds<PAD>(f.acc[wave], o, a.G, n, kg);
         l = TileT::row_sum(l);

@@ -237,7 +237,11 @@ template <int D> struct Tile<bf16_t, D, 16> {
 #pragma unroll
         for (int i = 0; i < NI; ++i) o[i] *= al;
     }
-    // product i, output row m = 4 kg + r: dim 128 (i / 8) + 8 m + i % 8; head_dim 64: 8 m + i, or 8 (m - 8) + 4 + i
+    // product i, output row m = 4 kg + r
+    static __device__ __forceinline__ int dim_of(int i, int m) {
+        if constexpr (D >= 128) return 128 * (i >> 3) + 8 * m + (i & 7);
+        else return m < 8 ? 8 * m + i : 8 * (m - 8) + 4 + i;
+    }
     template <int PAD> static __device__ __forceinline__ void to_lds(float (*rows)[PAD], const f32x4 (&o)[NI], int nh, int n, int kg) {
         if (n >= nh) return;
         float* row = rows[n];
@@ -417,48 +421,6 @@ __device__ __forceinline__ void weigh(float (&p)[TileT::PN], f32x4 (&o)[TileT::N
     }
 }
 
-// Whether any of a wave's sums is NaN.  (The maximum that hands NaN on takes two of them an instruction: 16 to 32, once a history.)
-template <class TileT> __device__ __forceinline__ bool any_nan(const f32x4 (&o)[TileT::NI]) {
-    f32x4 x = o[0];
-#pragma unroll
-    for (int i = 1; i + 1 < TileT::NI; i += 2)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) x[r] = __builtin_elementwise_maximum(__builtin_elementwise_maximum(x[r], o[i][r]), o[i + 1][r]);
-    static_assert(TileT::NI % 2 == 0, "the last one is left over");
-#pragma unroll
-    for (int r = 0; r < 4; ++r) x[r] = __builtin_elementwise_maximum(x[r], o[TileT::NI - 1][r]);
-    const float y = __builtin_elementwise_maximum(__builtin_elementwise_maximum(x[0], x[1]), __builtin_elementwise_maximum(x[2], x[3]));
-    return __any(y != y);
-}
-// The tiles first, first + step, ... of a history once more where a sum is NaN (bfloat16): V holds infinities or NaN then, or the
-// scores do, and only the rounded part of a weight may meet an infinity of V.  One tile after the other: nothing waits for such a
-// row.  Every other sum comes out as it was.
-template <class TileT, int D> __device__ __forceinline__ void sweep_apart(TileT& tile, f32x4 (&o)[TileT::NI], float& m, float& l, const SweepArgs& a,
-                                                                          const int32_t* row, int g, int L, int first, int step, int n, int kg) {
-    constexpr int TB = TileT::TB, PN = TileT::PN, BLK = kBlock * D * TileT::ES;
-    const int nb = (L + kBlock - 1) / kBlock, ntiles = (nb + TB - 1) / TB;
-#pragma unroll
-    for (int j = 0; j < TileT::NI; ++j) o[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    m = kLowest;
-    l = 0.f;
-#pragma unroll 1
-    for (int t = first; t < ntiles; t += step) {
-#pragma unroll
-        for (int b = 0; b < TB; ++b) {
-            const int blk = max(__builtin_amdgcn_readfirstlane(row[TB * t + (TB * t + b < nb ? b : 0)]), 0);
-            const size_t off = ((size_t)blk * a.Hkv + g) * BLK;
-            tile.load_k(b, static_cast<const char*>(a.k_cache) + off, n, kg);
-            tile.load_v(b, static_cast<const char*>(a.v_cache) + off, n, kg);
-        }
-        float p[PN];
-        tile.scores(p);
-        const int rest = L - t * (TB * kBlock);
-        if (rest < TB * kBlock) tile.mask(p, rest, n, kg);
-        weigh<TileT, bf16_t>(p, o, m, l, a.scale_log2);
-        tile.template accumulate<true>(p, o, n);
-    }
-}
-
 // Elements 8 c .. 8 c + 7 of head h's row, folded over the waves of a workgroup (in fixed order) at their common reference
 // exponent M.  A wave that had no tile, or no score above -inf, has sums of 0.
 template <int W, int R, int PAD> __device__ __forceinline__ void fold_waves(const float (&acc)[W][R][PAD], const float2 (&ml)[W][R], int h, int c,
@@ -477,6 +439,59 @@ template <int W, int R, int PAD> __device__ __forceinline__ void fold_waves(cons
 #pragma unroll
         for (int e = 0; e < 4; ++e) { num[e] = fmaf(f, a0[e], num[e]); num[4 + e] = fmaf(f, a1[e], num[4 + e]); }
     }
+}
+
+// Whether one of a lane's sums is NaN.  (The maximum that hands NaN on takes two of them an instruction.)
+__device__ __forceinline__ bool any_nan(const float (&x)[8]) {
+    float y = x[0];
+#pragma unroll
+    for (int e = 1; e < 7; e += 2) y = __builtin_elementwise_maximum(__builtin_elementwise_maximum(y, x[e]), x[e + 1]);
+    y = __builtin_elementwise_maximum(y, x[7]);
+    return y != y;
+}
+template <int NI> __device__ __forceinline__ bool any_nan(const f32x4 (&o)[NI]) {
+    static_assert(NI % 2 == 0, "two at a time, and the first and the last");
+    f32x4 x = o[0];
+#pragma unroll
+    for (int i = 1; i + 1 < NI; i += 2)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x[r] = __builtin_elementwise_maximum(__builtin_elementwise_maximum(x[r], o[i][r]), o[i + 1][r]);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) x[r] = __builtin_elementwise_maximum(x[r], o[NI - 1][r]);
+    const float y = __builtin_elementwise_maximum(__builtin_elementwise_maximum(x[0], x[1]), __builtin_elementwise_maximum(x[2], x[3]));
+    return y != y;
+}
+
+// bfloat16, where a sum is NaN: V holds infinities or NaN then, or the scores do, and of a weight only the rounded part may meet an
+// infinity of V.  The tiles are read once more, `group` of them from `first` on and so every `step`, one after the other: nothing
+// waits for such a row.  Sums over the tiles of before, in their order, that were not NaN come out as they were.
+template <class TileT, int D>
+__device__ __forceinline__ void sweep_apart(TileT& tile, f32x4 (&o)[TileT::NI], float& m, float& l, const SweepArgs& a, const int32_t* row, int g, int L,
+                                            int first, int group, int step, int n, int kg) {
+    constexpr int TB = TileT::TB, PN = TileT::PN, BLK = kBlock * D * TileT::ES;
+    const int nb = (L + kBlock - 1) / kBlock, ntiles = (nb + TB - 1) / TB;
+#pragma unroll
+    for (int j = 0; j < TileT::NI; ++j) o[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    m = kLowest;
+    l = 0.f;
+#pragma unroll 1
+    for (int t0 = first; t0 < ntiles; t0 += step)
+#pragma unroll 1
+        for (int t = t0; t < min(t0 + group, ntiles); ++t) {
+#pragma unroll
+            for (int b = 0; b < TB; ++b) {
+                const int blk = max(__builtin_amdgcn_readfirstlane(row[TB * t + (TB * t + b < nb ? b : 0)]), 0);
+                const size_t off = ((size_t)blk * a.Hkv + g) * BLK;
+                tile.load_k(b, static_cast<const char*>(a.k_cache) + off, n, kg);
+                tile.load_v(b, static_cast<const char*>(a.v_cache) + off, n, kg);
+            }
+            float p[PN];
+            tile.scores(p);
+            const int rest = L - t * (TB * kBlock);
+            if (rest < TB * kBlock) tile.mask(p, rest, n, kg);
+            weigh<TileT, bf16_t>(p, o, m, l, a.scale_log2);
+            tile.template accumulate<true>(p, o, n);
+        }
 }
 
 }  // namespace tile

@@ -26,3 +26,9 @@ def test_chunk_counts_around_the_batches(counts, last):
     for i, s in enumerate(seqs):
         assert got[hoff[i]:hoff[i + 1]].tolist() == chunk_hashes(s), counts[i]
     assert (got[hoff[-1]:] == sentinel).all()
+
+
+@pytest.mark.parametrize("last", [1, 16])
+def test_chunk_counts_around_the_slabs(last):
+    """Leaves are made 256 at a time, in two buffers in turn; the chain takes them eight at a time out of their lanes."""
+    test_chunk_counts_around_the_batches([247, 248, 249, 255, 256, 257, 263, 264, 265, 511, 512, 513, 768, 769, 1025], last)

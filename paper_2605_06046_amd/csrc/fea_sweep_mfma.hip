@@ -637,7 +637,8 @@ __device__ __forceinline__ void sweep_team_core(const SweepArgs& a, const Item& 
     asm volatile("" : "+v"(lane));
     const int n = lane & 15, kg = lane >> 4;
     const uint32_t k_off0 = (uint32_t)(n * 256 + ((kg ^ n) & 15) * 16);             // token row n, chunk kg (k-step 0)
-    const uint32_t v_off0 = (uint32_t)(4 * kg * 256 + ((n ^ (4 * kg)) & 15) * 16);  // token row 4 kg, chunk n
+    const int vrow = 4 * kg + (n >> 2);
+    const uint32_t v_off0 = (uint32_t)(vrow * 256 + ((((n & 3) >> 1) ^ vrow) & 15) * 16 + (n & 1) * 8);   // token row 4 kg + n / 4, its dims 4 (n % 4) .. (product 0)
     const uint32_t d_off0 = (uint32_t)(kg * 256 + ((n ^ kg) & 15) * 16);            // load 0 of a block: row kg
     const int ntiles = (item.c1 - item.c0) >> 1;
     const int* mlist = reinterpret_cast<const int*>(a.ws + a.lay.members) + item.mlist_off;
@@ -667,7 +668,7 @@ __device__ __forceinline__ void sweep_team_core(const SweepArgs& a, const Item& 
     const uint64_t accbase = reinterpret_cast<uint64_t>(sgpr(a.ws + a.lay.acc + (size_t)item.pbase * (kD * sizeof(float))));
     const uint64_t mlbase = reinterpret_cast<uint64_t>(sgpr(a.ws + a.lay.ml + (size_t)item.pbase * sizeof(float2)));
     const uint32_t own_lo = sgpr((uint32_t)own), own_hi = sgpr((uint32_t)(own >> 32));
-    const uint32_t lane4 = (uint32_t)lane * 4u, dst0 = (uint32_t)n * (kD * 4u) + (uint32_t)kg * 128u;
+    const uint32_t lane4 = (uint32_t)lane * 4u, dst0 = (uint32_t)n * (kD * 4u) + (uint32_t)kg * 16u;
 #define FEA_TEAM_CORE_OPERANDS                                                                                                  \
     : [koff0] "v"(k_off0), [voff0] "v"(v_off0), [doff0] "v"(d_off0), [q0] "v"(qoff[0]), [q1] "v"(qoff[1]), [q2] "v"(qoff[2]),   \
       [q3] "v"(qoff[3]), [lane4] "v"(lane4), [dst0] "v"(dst0), [nrow] "v"(n), [qbase] "s"(qbase), [accbase] "s"(accbase),       \

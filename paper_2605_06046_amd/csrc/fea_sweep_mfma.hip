@@ -52,6 +52,7 @@
 #include <hip/hip_ext.h>
 
 #include <cstdlib>
+#include <type_traits>
 
 #include "fea_plan.h"
 #include "fea_tile.h"
@@ -97,7 +98,7 @@ __device__ __forceinline__ void dma16x4(const char* base, uint32_t off0, uint32_
         :: "v"(off0), "v"(off1), "v"(off2), "v"(off3), "s"(base), "s"(lds0), "s"(lds1), "s"(lds2), "s"(lds3)
         : "memory", "m0");
 }
-// Two such loads (a 2 KB block of head_dim 64).
+// Two such loads (query rows of head_dim 64).
 __device__ __forceinline__ void dma16x2(const char* base, uint32_t off0, uint32_t off1, uint32_t lds0, uint32_t lds1) {
     asm volatile(
         "s_nop 4\n\t"
@@ -105,6 +106,39 @@ __device__ __forceinline__ void dma16x2(const char* base, uint32_t off0, uint32_
         "s_mov_b32 m0, %4\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
         :: "v"(off0), "v"(off1), "s"(base), "s"(lds0), "s"(lds1)
         : "memory", "m0");
+}
+// A tile: the loads of its four blocks, into LDS one behind the other from lds on.  The immediate offset of such a load moves
+// both its addresses, so M0 is set once for 4 KB (head_dim 64: 2 KB) instead of for every load.
+template <int D>
+__device__ __forceinline__ void dma_tile(const char* k0, const char* k1, const char* v0, const char* v1, const uint32_t (&off)[8], uint32_t lds) {
+    if constexpr (D == 64) {
+        asm volatile(
+            "s_nop 4\n\ts_mov_b32 m0, %5\n\ts_nop 0\n\t"
+            "global_load_lds_dwordx4 %0, %1\n\tglobal_load_lds_dwordx4 %0, %1 offset:1024\n\ts_addk_i32 m0, 0x800\n\ts_nop 0\n\t"
+            "global_load_lds_dwordx4 %0, %2\n\tglobal_load_lds_dwordx4 %0, %2 offset:1024\n\ts_addk_i32 m0, 0x800\n\ts_nop 0\n\t"
+            "global_load_lds_dwordx4 %0, %3\n\tglobal_load_lds_dwordx4 %0, %3 offset:1024\n\ts_addk_i32 m0, 0x800\n\ts_nop 0\n\t"
+            "global_load_lds_dwordx4 %0, %4\n\tglobal_load_lds_dwordx4 %0, %4 offset:1024"
+            :: "v"(off[0]), "s"(k0), "s"(k1), "s"(v0), "s"(v1), "s"(lds) : "memory", "m0", "scc");
+    } else {
+#define FEA_DMA4(A, B, C, E, BASE) "global_load_lds_dwordx4 " A ", " BASE "\n\tglobal_load_lds_dwordx4 " B ", " BASE " offset:1024\n\t" \
+        "global_load_lds_dwordx4 " C ", " BASE " offset:2048\n\tglobal_load_lds_dwordx4 " E ", " BASE " offset:3072\n\t"
+#define FEA_M0_ON "s_addk_i32 m0, 0x1000\n\ts_nop 0\n\t"
+        if constexpr (D == 128) {
+            asm volatile("s_nop 4\n\ts_mov_b32 m0, %8\n\ts_nop 0\n\t"
+                         FEA_DMA4("%0", "%1", "%2", "%3", "%4") FEA_M0_ON FEA_DMA4("%0", "%1", "%2", "%3", "%5") FEA_M0_ON
+                         FEA_DMA4("%0", "%1", "%2", "%3", "%6") FEA_M0_ON FEA_DMA4("%0", "%1", "%2", "%3", "%7")
+                         :: "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(k0), "s"(k1), "s"(v0), "s"(v1), "s"(lds) : "memory", "m0", "scc");
+        } else {
+#define FEA_DMA8(BASE) FEA_DMA4("%0", "%1", "%2", "%3", BASE) FEA_M0_ON FEA_DMA4("%4", "%5", "%6", "%7", BASE)
+            asm volatile("s_nop 4\n\ts_mov_b32 m0, %12\n\ts_nop 0\n\t"
+                         FEA_DMA8("%8") FEA_M0_ON FEA_DMA8("%9") FEA_M0_ON FEA_DMA8("%10") FEA_M0_ON FEA_DMA8("%11")
+                         :: "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "v"(off[4]), "v"(off[5]), "v"(off[6]), "v"(off[7]),
+                            "s"(k0), "s"(k1), "s"(v0), "s"(v1), "s"(lds) : "memory", "m0", "scc");
+#undef FEA_DMA8
+        }
+#undef FEA_DMA4
+#undef FEA_M0_ON
+    }
 }
 // One load of 4 bytes per lane (block ids of 64 table columns), same conventions.
 __device__ __forceinline__ void dma4(const void* base, uint32_t lane_off, uint32_t lds_addr) {
@@ -137,8 +171,15 @@ __device__ __forceinline__ void scale_acc(f32x4& acc, float f) {
 // the data registers of a wide store a little after issue and does not interlock
 // against a vector instruction overwriting them meanwhile; the compiler pads its own
 // stores for that but cannot see these, hence the trailing s_nop.
-__device__ __forceinline__ void store_f32x4(const char* base, uint32_t off, f32x4 v) {
-    asm volatile("s_nop 4\n\tglobal_store_dwordx4 %0, %1, %2\n\ts_nop 1" :: "v"(off), "v"(v), "s"(base) : "memory");
+template <int AT> __device__ __forceinline__ void store_f32x4(const char* base, uint32_t off, f32x4 v) {
+    asm volatile("s_nop 4\n\tglobal_store_dwordx4 %0, %1, %2 offset:%3\n\ts_nop 1" :: "v"(off), "v"(v), "s"(base), "n"(AT) : "memory");
+}
+// ... and the 16-byte pieces of one row, 64 bytes apart.
+template <int I = 0, int N> __device__ __forceinline__ void store_row(const char* base, uint32_t off, const f32x4 (&v)[N]) {
+    if constexpr (I < N) {
+        store_f32x4<64 * I>(base, off, v[I]);
+        store_row<I + 1>(base, off, v);
+    }
 }
 __device__ __forceinline__ void store_f32x2(const char* base, uint32_t off, float x, float y) {
     typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -151,30 +192,22 @@ __device__ __forceinline__ void wait_lgkmcnt0() { asm volatile("s_waitcnt lgkmcn
 struct Lanes {
     int n;                 // lane % 16: query row of a 16-row tile / token of a block / 16-byte chunk
     int kg;                // lane / 16: k-slot group of the MFMA operands
-    uint32_t dma_off[8];   // global byte offset inside a block for load i (rows 4i + kg, swizzled chunk)
+    uint32_t dma_off[8];   // global byte offset of load i (rows 4i + kg of a block, swizzled chunk), without the load's immediate one
     uint32_t k_off[8];     // LDS byte offset inside a K block of the A operand for k-step ks
-    uint32_t v_off[4];     // LDS byte offset inside a V block of token row 4 kg + j
+    uint32_t v_off;        // LDS byte offset inside a V block of token row 4 kg + n / 4, its dims 4 (n % 4) ..; dims 16 i on: with 32 i exclusive-or'ed in
 };
 
 // Fetch blocks b0, b1 of KV head g into the stage at LDS address `stage` (16 loads).
 template <int D>
 __device__ __forceinline__ void fetch_tile(const SweepArgs& a, int g, int b0, int b1, uint32_t stage, const Lanes& L) {
     constexpr int BLK = kBlock * D * 2;
-    const size_t o0 = ((size_t)b0 * a.Hkv + g) * BLK;
-    const size_t o1 = ((size_t)b1 * a.Hkv + g) * BLK;
+    const size_t o0 = (size_t)((uint32_t)b0 * (uint32_t)a.Hkv + (uint32_t)g) * BLK;   // (blocks times KV heads: below 2^32, a block has 2 KB or more)
+    const size_t o1 = (size_t)((uint32_t)b1 * (uint32_t)a.Hkv + (uint32_t)g) * BLK;
     const char* k0 = sgpr(static_cast<const char*>(a.k_cache) + o0);
     const char* k1 = sgpr(static_cast<const char*>(a.k_cache) + o1);
     const char* v0 = sgpr(static_cast<const char*>(a.v_cache) + o0);
     const char* v1 = sgpr(static_cast<const char*>(a.v_cache) + o1);
-    stage = sgpr(stage);
-    const char* bases[4] = {k0, k1, v0, v1};
-#pragma unroll
-    for (int x = 0; x < 4; ++x) {
-        const uint32_t l = stage + x * BLK;
-        if constexpr (D == 64) dma16x2(bases[x], L.dma_off[0], L.dma_off[1], l, l + 1024);
-        else dma16x4(bases[x], L.dma_off[0], L.dma_off[1], L.dma_off[2], L.dma_off[3], l, l + 1024, l + 2048, l + 3072);
-        if constexpr (D == 256) dma16x4(bases[x], L.dma_off[4], L.dma_off[5], L.dma_off[6], L.dma_off[7], l + 4096, l + 5120, l + 6144, l + 7168);
-    }
+    dma_tile<D>(k0, k1, v0, v1, L.dma_off, sgpr(stage));
 }
 
 // Tile stream of one wave.  `phase` is the stage the current item's tile 0 uses,
@@ -207,21 +240,23 @@ struct Stream {
 
 __device__ __forceinline__ uint32_t pick3(int i, uint32_t a, uint32_t b, uint32_t c) { return i == 0 ? a : (i == 1 ? b : c); }
 
-// Wait until the load with this mark (and with it every older one) has landed.
-__device__ __forceinline__ void wait_for(Stream& sm, uint32_t mark) {
+// Wait until the load with this mark (and with it every older one) has landed.  The wait takes its count as an immediate: the
+// one that a tile mostly needs (a tile's T loads are younger) comes first, then a few, rounded down.  (All 50 as a switch were
+// a tree of 250 instructions wherever it stood, and a dozen jumps each time.)
+template <int T> __device__ __forceinline__ void wait_for(Stream& sm, uint32_t mark) {
     if ((int32_t)(mark - sm.done) <= 0) return;
     uint32_t n = sm.seq - mark;   // younger loads: they may stay in flight
-    if (n > 50) n = 50;
-    switch (n) {                  // the wait takes its count as an immediate
-#define FEA_W(N) case N: wait_vmcnt<N>(); break;
-        FEA_W(0) FEA_W(1) FEA_W(2) FEA_W(3) FEA_W(4) FEA_W(5) FEA_W(6) FEA_W(7) FEA_W(8) FEA_W(9)
-        FEA_W(10) FEA_W(11) FEA_W(12) FEA_W(13) FEA_W(14) FEA_W(15) FEA_W(16) FEA_W(17) FEA_W(18) FEA_W(19)
-        FEA_W(20) FEA_W(21) FEA_W(22) FEA_W(23) FEA_W(24) FEA_W(25) FEA_W(26) FEA_W(27) FEA_W(28) FEA_W(29)
-        FEA_W(30) FEA_W(31) FEA_W(32) FEA_W(33) FEA_W(34) FEA_W(35) FEA_W(36) FEA_W(37) FEA_W(38) FEA_W(39)
-        FEA_W(40) FEA_W(41) FEA_W(42) FEA_W(43) FEA_W(44) FEA_W(45) FEA_W(46) FEA_W(47) FEA_W(48) FEA_W(49)
-        default: wait_vmcnt<50>(); break;
-#undef FEA_W
-    }
+    auto leave = [&](auto count) { wait_vmcnt<decltype(count)::value>(); n = decltype(count)::value; };
+    using std::integral_constant;
+    constexpr int kMost = 2 * T + 4 < 50 ? 2 * T + 4 : 50;
+    if (__builtin_expect(n == T, 1)) leave(integral_constant<int, T>{});
+    else if (n >= kMost) leave(integral_constant<int, kMost>{});
+    else if (n >= T + 8) leave(integral_constant<int, T + 8>{});
+    else if (n >= T + 4) leave(integral_constant<int, T + 4>{});
+    else if (n >= T) leave(integral_constant<int, T>{});
+    else if (n >= 4) leave(integral_constant<int, 4>{});
+    else if (n >= 1) leave(integral_constant<int, 1>{});
+    else leave(integral_constant<int, 0>{});
     sm.done = sm.seq - n;
 }
 __device__ __forceinline__ void wait_all(Stream& sm) {
@@ -256,10 +291,9 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const Item& item,
         sm.cmark2 = buf == 2 ? sm.seq : sm.cmark2;
     };
     auto buf_of = [&](int win) { return (win & 1) ? sm.cb1 : sm.cb0; };
-    // Issue stream tile `idx` (own tile idx, or tile idx - ntiles of the next item) if it
-    // is the next one due and exists; own tiles must be asked for in increasing order.
+    // Issue the next stream tile due (own tile idx, or tile idx - ntiles of the next item), if it
+    // exists; own tiles are asked for in increasing order.
     auto issue = [&](int idx) {
-        if (idx != sm.iss) return;
         int buf, at;
         int g = item.g;
         if (idx < ntiles) {
@@ -269,12 +303,12 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const Item& item,
             at = 2 * w;
         } else {
             const int j = idx - ntiles;
-            if (j >= next_pre) return;
+            if (j >= next_pre) return false;
             buf = sm.cbn;
             at = 2 * j;
             g = next.g;
         }
-        wait_for(sm, pick3(buf, sm.cmark0, sm.cmark1, sm.cmark2));   // the window's block ids must have landed
+        wait_for<D / 8>(sm, pick3(buf, sm.cmark0, sm.cmark1, sm.cmark2));   // the window's block ids must have landed
         const int* sc = s_cols + buf * 64 + at;
         // (a table entry of -1 inside a request's length is the caller's error; it must not become a
         // read before the cache)
@@ -286,14 +320,18 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const Item& item,
         sm.tmark0 = stg == 0 ? sm.seq : sm.tmark0;
         sm.tmark1 = stg == 1 ? sm.seq : sm.tmark1;
         sm.iss = idx + 1;
+        return true;
+    };
+    auto issue_upto = [&](int last) {
+        if (sm.iss == last - 1 && !issue(last - 1)) return;
+        if (sm.iss == last) issue(last);
     };
     if (!sm.cols_ready) fetch_cols(trow, item.c0, item.c1, 0, sm.cb0);
     fetch_cols(trow, item.c0, item.c1, 1, sm.cb1);
     if (has_next) fetch_cols(nrow, next.c0, next.c1, 0, sm.cbn);
     // Own tiles only at this point (no-ops when the predecessor has asked for them):
     // the next item's column window has only just been requested.
-    issue(0);
-    if (ntiles > 1) issue(1);
+    issue_upto(min(ntiles, 2) - 1);
 
     // B operand of the first product: Q^T, lane (n, kg) holds q[row n][32 ks + 8 kg .. +8].
     // The rows of a single request's query group are contiguous in q; the predecessor
@@ -306,13 +344,15 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const Item& item,
     bool q_from_lds = false;
     if constexpr (NT == 1) q_from_lds = sm.q_ready;
     if (q_from_lds) {
-        wait_for(sm, sm.qmark);
+        wait_for<D / 8>(sm, sm.qmark);
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) qB[0][ks] = as_bf16x8(ld16(s_q + L.k_off[ks]));
     } else {
+        int of = n;                     // (worked out again for each item: kept for the kernel's life these would be spilled)
+        asm volatile("" : "+v"(of));
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
-            const int row = nt * 16 + n;
+            const int row = nt * 16 + of;
             const bool ok = row < item.nrows;
             const int mem = (row * g_rcp) >> 16, hh = row - mem * a.G;   // row / G and row % G (rows < 64, G <= 64)
             const int req = ok ? (item.mlist_off < 0 ? item.who : mlist[mem]) : 0;
@@ -395,7 +435,7 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const Item& item,
     float tmax[NT];    // scaled maximum of those, positions past the end left out
     int tile_pos = 0;  // position of the tile's first token
     bool ragged = false;   // the tile reaches past the item's last token (wave-uniform)
-    bf16x8 vA[NI];     // vA[i]: head dim 8*(lane%16) + i (head_dim 64: lanes n >= 8 carry dim 8*(n-8) + i + 4), k-slots = the lane group's 8 tokens
+    bf16x8 vA[NI];     // vA[i]: head dim 16 i + n, k-slots = the lane group's 8 tokens (4 of each block)
     auto scores = [&](int nt, float (&r)[8]) {   // this lane's 8 scores of row tile nt; -inf past the end
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt)
@@ -412,25 +452,33 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const Item& item,
     auto front = [&](int t) {
         const int stg = (sm.phase + t) & 1;
         const char* st = s_stage + stg * STG;
-        wait_for(sm, stg == 0 ? sm.tmark0 : sm.tmark1);   // tile t has landed
+        wait_for<D / 8>(sm, stg == 0 ? sm.tmark0 : sm.tmark1);   // tile t has landed
         // Read the tile out of its stage and hand the stage back.  With 16 or 32 query
         // rows everything is read up front so that the refill starts at once; with 64
         // rows registers are short, so V is read after the first product (that
         // instantiation computes long enough per tile for the later refill not to matter).
+        // V comes out of LDS transposed: the 16 lanes of a group read the group's four token rows, 16 dims of each, and
+        // lane n is left with dim n of the four.
         constexpr bool kLate = NT == 4 || D == 256;   // registers are short: K of the second block and V are read after the first product
-        constexpr int VH = D == 256 ? 2 : 1;          // a V row has 32 chunks at head_dim 256: lane n takes chunks n and n + 16
         bf16x8 kA[kLate ? 1 : 2][KS];
-        u32x4 vr[8 * VH];
+        auto read_v = [&]() {
+#pragma unroll
+            for (int i = 0; i < NI; ++i) {
+                typedef short s16x4 __attribute__((ext_vector_type(4)));
+                typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
+                const uint32_t at = lds_base + stg * STG + 2 * BLK + (L.v_off ^ ((i & 7) * 32)) + (i >> 3) * 256;
+                const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(uintptr_t)at), hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(uintptr_t)(at + BLK));
+                vA[i] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+            }
+        };
 #pragma unroll
         for (int mt = 0; mt < (kLate ? 1 : 2); ++mt)
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) kA[mt][ks] = as_bf16x8(ld16(st + mt * BLK + L.k_off[ks]));
         if constexpr (!kLate) {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) vr[j] = ld16(st + (2 + (j >> 2)) * BLK + L.v_off[j & 3]);
+            read_v();
             wait_lgkmcnt0();   // the stage is read out: refill it with stream tile t+2
-            issue(t + 1);      // (only due if the look-ahead into the next item stopped short)
-            issue(t + 2);
+            issue_upto(t + 2); // (t + 1 is only due if the look-ahead into the next item stopped short)
         }
 
         tile_pos = (item.c0 + 2 * t) * kBlock;
@@ -454,53 +502,21 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const Item& item,
                     sacc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kA[kLate ? 0 : mt][ks], qB[nt][ks], sacc[nt][mt], 0, 0, 0);
         }
         if constexpr (kLate) {
-#pragma unroll
-            for (int h = 0; h < VH; ++h)
-#pragma unroll
-                for (int j = 0; j < 8; ++j) vr[8 * h + j] = ld16(st + (2 + (j >> 2)) * BLK + L.v_off[j & 3] + h * 256);
+            read_v();
             wait_lgkmcnt0();
-            issue(t + 1);
-            issue(t + 2);
+            issue_upto(t + 2);
         }
 
-        // ---- V: zero rows past the end (they may hold anything), then 8x8 transposes of 16-bit values
+        // ---- V: zero tokens past the end (they may hold anything)
         if (__builtin_expect(ragged, 0)) {
+            u32x4 live;        // the halves of a fragment's registers whose token counts
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int pos = tile_pos + (j >> 2) * 16 + kg * 4 + (j & 3);
-                if (pos >= item.tok_end) {
-#pragma unroll
-                    for (int h = 0; h < VH; ++h) vr[8 * h + j] = u32x4{0u, 0u, 0u, 0u};
-                }
+            for (int w = 0; w < 4; ++w) {
+                const int pos = tile_pos + (w >> 1) * 16 + kg * 4 + 2 * (w & 1);
+                live[w] = (pos < item.tok_end ? 0xFFFFu : 0u) | (pos + 1 < item.tok_end ? 0xFFFF0000u : 0u);
             }
-        }
-        if constexpr (D >= 128) {
 #pragma unroll
-            for (int h = 0; h < VH; ++h)
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const uint32_t sel = (i & 1) ? 0x07060302u : 0x05040100u;
-                    u32x4 o;
-#pragma unroll
-                    for (int w = 0; w < 4; ++w) o[w] = __builtin_amdgcn_perm(vr[8 * h + 2 * w + 1][i >> 1], vr[8 * h + 2 * w][i >> 1], sel);
-                    vA[8 * h + i] = as_bf16x8(o);     // (head_dim 256: products 8.. carry dims 128 + 8 n + i)
-                }
-        } else {
-            // a token row has 8 chunks: lanes n and n + 8 read the same one; lane n < 8 hands elements 0..3 of it
-            // to products 0..3 (dims 8 n + i), lane n >= 8 elements 4..7 (dims 8 (n - 8) + 4 + i)
-            const int hi = n >> 3;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const uint32_t sel = (i & 1) ? 0x07060302u : 0x05040100u;
-                u32x4 o;
-#pragma unroll
-                for (int w = 0; w < 4; ++w) {
-                    const uint32_t lo1 = vr[2 * w + 1][i >> 1], lo0 = vr[2 * w][i >> 1];
-                    const uint32_t hi1 = vr[2 * w + 1][2 + (i >> 1)], hi0 = vr[2 * w][2 + (i >> 1)];
-                    o[w] = __builtin_amdgcn_perm(hi ? hi1 : lo1, hi ? hi0 : lo0, sel);
-                }
-                vA[i] = as_bf16x8(o);
-            }
+            for (int i = 0; i < NI; ++i) vA[i] = as_bf16x8(__builtin_bit_cast(u32x4, vA[i]) & live);
         }
 
         // ---- row maxima, one query row per lane (per row tile); the scores themselves stay
@@ -578,34 +594,16 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const Item& item,
         }
     }
 
-    // ---- partial rows: lane (n, kg) holds, for row 16 nt + n, dims 8 (4 kg + jj) + i: runs of 8 floats
+    // ---- partial rows: lane (n, kg) holds, for row 16 nt + n, dims 16 i + 4 kg .. of product i
     const char* ml = sgpr(a.ws + a.lay.ml + (size_t)item.pbase * sizeof(float2));          // the item's first partial row
     const char* pacc = sgpr(a.ws + a.lay.acc + (size_t)item.pbase * (D * sizeof(float)));
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
         const float l = lacc[nt][0];   // every element of the column holds the row's sum
         const int row = nt * 16 + n;
-        if (nt * 16 < item.nrows) {    // wave-uniform: lane 0 has a row here, so all nine stores are issued
+        if (nt * 16 < item.nrows) {    // wave-uniform: lane 0 has a row here, so all its stores are issued
             if (row < item.nrows) {
-                if constexpr (D >= 128) {
-#pragma unroll
-                    for (int h = 0; h < D / 128; ++h) {
-                        const uint32_t dst = (uint32_t)row * (D * 4u) + (uint32_t)kg * 128u + (uint32_t)h * 512u;
-#pragma unroll
-                        for (int jj = 0; jj < 4; ++jj) {
-                            store_f32x4(pacc, dst + jj * 32, f32x4{oacc[nt][8 * h + 0][jj], oacc[nt][8 * h + 1][jj], oacc[nt][8 * h + 2][jj], oacc[nt][8 * h + 3][jj]});
-                            store_f32x4(pacc, dst + jj * 32 + 16, f32x4{oacc[nt][8 * h + 4][jj], oacc[nt][8 * h + 5][jj], oacc[nt][8 * h + 6][jj], oacc[nt][8 * h + 7][jj]});
-                        }
-                    }
-                } else {
-                    // product i, output row m = 4 kg + jj: dim 8 m + i for m < 8, 8 (m - 8) + 4 + i for m >= 8
-#pragma unroll
-                    for (int jj = 0; jj < 4; ++jj) {
-                        const int m = 4 * kg + jj, db = m < 8 ? 8 * m : 8 * (m - 8) + 4;
-                        store_f32x4(pacc, (uint32_t)row * (D * 4u) + (uint32_t)db * 4u,
-                                    f32x4{oacc[nt][0][jj], oacc[nt][1][jj], oacc[nt][2][jj], oacc[nt][3][jj]});
-                    }
-                }
+                store_row(pacc, (uint32_t)row * (D * 4u) + (uint32_t)kg * 16u, oacc[nt]);
                 if (kg == 0) store_f32x2(ml, (uint32_t)row * 8u, m_run[nt], l);
             }
             sm.seq += D / 16 + 1;
@@ -871,33 +869,26 @@ __global__ __launch_bounds__(64 * waves_per_group<D>()) void sweep_mfma_kernel(S
     Lanes L;
     L.n = lane & 15;
     L.kg = lane >> 4;
+    {
+        const int row = 4 * L.kg + (L.n >> 2), sub = (L.n & 3) >> 1;   // chunk 2 i + sub of the row holds the lane's dims of product i
+        L.v_off = row * (D * 2) + ((sub ^ row) & (D == 64 ? 7 : 15)) * 16 + (L.n & 1) * 8;
+    }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < 8; ++i) {
         if constexpr (D == 128) {
-            const int row = 4 * i + L.kg;                          // token row of the block this lane fetches in load i
-            L.dma_off[i] = row * 256 + ((L.n ^ row) & 15) * 16;    // LDS chunk position n receives global chunk n ^ row
-            L.k_off[i] = L.n * 256 + (((4 * i + L.kg) ^ L.n) & 15) * 16;   // token row n, chunk 4 ks + kg
-            const int vrow = 4 * L.kg + i;                         // token row of V k-slot i (and i + 4 in the second block)
-            L.v_off[i] = vrow * 256 + ((L.n ^ vrow) & 15) * 16;    // chunk n of that row
+            const int row = 4 * (i & 3) + L.kg;                    // token row of the block this lane fetches in load i
+            L.dma_off[i] = L.kg * 256 + ((L.n ^ row) & 15) * 16;   // LDS chunk position n receives global chunk n ^ row
+            L.k_off[i] = L.n * 256 + (((4 * (i & 3) + L.kg) ^ L.n) & 15) * 16;   // token row n, chunk 4 ks + kg
         } else if constexpr (D == 64) {
             // head_dim 64: 128-byte token rows of 8 chunks, eight rows per load; position p of row r holds chunk p ^ (r % 8)
-            const int row = 8 * (i & 1) + (lane >> 3), pos = lane & 7;
-            L.dma_off[i] = row * 128 + ((pos ^ row) & 7) * 16;     // (loads 0 and 1 only)
+            const int row = lane >> 3, pos = lane & 7;
+            L.dma_off[i] = row * 128 + ((pos ^ row) & 7) * 16;     // (both loads)
             L.k_off[i] = L.n * 128 + (((4 * (i & 1) + L.kg) ^ L.n) & 7) * 16;   // token row n, chunk 4 ks + kg (k-steps 0 and 1)
-            const int vrow = 4 * L.kg + i;
-            L.v_off[i] = vrow * 128 + ((L.n ^ vrow) & 7) * 16;     // chunk n % 8 of that row
         } else {
             // head_dim 256: 512-byte token rows of 32 chunks, two rows per load; each half of a row is swizzled like a
-            // 256-byte row (position p of row r holds chunk (p & 16) | ((p ^ r) & 15)); V chunk n + 16 sits 256 bytes on
-            const int vrow = 4 * L.kg + i;
-            L.v_off[i] = vrow * 512 + ((L.n ^ vrow) & 15) * 16;
-        }
-    }
-    if constexpr (D == 256) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
+            // 256-byte row (position p of row r holds chunk (p & 16) | ((p ^ r) & 15)); dims 128 on sit 256 bytes on
             const int row = 2 * i + (lane >> 5), pos = lane & 31;
-            L.dma_off[i] = row * 512 + ((pos & 16) | ((pos ^ row) & 15)) * 16;
+            L.dma_off[i] = (lane >> 5) * 512 + ((pos & 16) | ((pos ^ row) & 15)) * 16 + (i >> 2) * 4096;
             const int c = 4 * i + L.kg;                                          // chunk of k-step i
             L.k_off[i] = L.n * 512 + ((c & 16) | ((c ^ L.n) & 15)) * 16;
         }

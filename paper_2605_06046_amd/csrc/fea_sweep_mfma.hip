@@ -2,12 +2,11 @@
 // up to 64 heads per KV head (32 at head_dim 256; any ratio: 7 as in 28/4, 5 as in 40/8, ...).  What
 // follows describes head_dim 128.  Head_dim 64 is the same kernel with 2 KB blocks (two
 // loads each, 128-byte token rows of eight chunks, swizzled by the row modulo 8), two
-// k-steps in the first product and four output products per 16 rows, lanes n and n+8
-// sharing a V chunk and taking its lower and upper four dims.  Head_dim 256: 8 KB
+// k-steps in the first product and four output products per 16 rows.  Head_dim 256: 8 KB
 // blocks (eight loads, 512-byte rows whose halves are swizzled like 256-byte rows),
-// eight k-steps, sixteen output products per 16 rows (lane n takes V chunks n and
-// n+16), work items of at most 32 rows (O for 32 rows fills half the accumulation
-// registers), and two waves per workgroup, whose two 32 KB stages each fill the LDS.
+// eight k-steps, sixteen output products per 16 rows, work items of at most 32 rows (O
+// for 32 rows fills half the accumulation registers), and two waves per workgroup, whose
+// two 32 KB stages each fill the LDS.
 //
 // One wave per SIMD (workgroups of four waves, one workgroup per compute unit); the planner has
 // cut the stream of 32-token tiles into equal shares, and wave w sweeps the consecutive work
@@ -38,8 +37,16 @@
 // whole 256-byte token rows; inside a row the sixteen 16-byte chunks are placed
 // XOR-swizzled by the row number, which makes the "lane = token" reads of the K
 // operand bank-conflict free without padding (the DMA path cannot pad).  V needs
-// "lane = head dim, 8 tokens per lane": it is read back as whole token rows and
-// transposed 8x8 in registers with byte permutes.
+// "lane = head dim, 8 tokens per lane", which is how the transposing LDS read hands it
+// over (ds_read_b64_tr_b16: the 16 lanes of a group read four token rows, 16 dims of
+// each, and lane n is left with dim n of the four).
+//
+// A wave alone on its SIMD issues an instruction in four cycles and fetches 8 bytes of them in
+// 4.7 to 7.2 (by compute unit), so with few query rows on a tile its time is the number of its instructions: 420 a tile at
+// head_dim 64 when the waits were a tree over all 50 counts, V was transposed by permutes and selects, every load set M0 and
+// the sums were copied back.  Since: 48 requests of head_dim 256 on 3000 tokens 54.6 -> 46.3 us a call (27 registers were
+// spilled there as well), four layers on nested prefixes, 40/8/128, 160.7 -> 155.8, 128 requests of head_dim 64 in 8 groups
+// 55.5 -> 53.9, 64 on one prefix of 4096, 32/8/128, 55.9 -> 55.6.
 //
 // The LDS writes of those loads are invisible to the compiler, so the waits are
 // explicit: vmcnt before a stage is read, lgkmcnt before it is overwritten.
@@ -166,6 +173,20 @@ __device__ __forceinline__ void scale_acc(f32x4& acc, float f) {
         : "v"(f));
     acc[0] = a0; acc[1] = a1; acc[2] = a2; acc[3] = a3;
 }
+// acc += A B in place: as the builtin the sums came out in other registers than they went in, and every tile copied them back (20
+// moves for 16 query rows of head_dim 64).  FIRST: what the vector unit has just written into B wants two wait states.
+template <bool FIRST> __device__ __forceinline__ void add_product(f32x4& acc, bf16x8 a, bf16x8 b) {
+    if constexpr (FIRST) asm("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+    else asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+}
+// Sums that the compiler's instructions have just written or are about to read: it does not see the products' side.  The last
+// products' results want up to 19 wait states before they are read; what is written here is there well before the first product.
+template <bool READ, int N> __device__ __forceinline__ void settle(f32x4& l, f32x4 (&o)[N]) {
+    if constexpr (READ) asm volatile("s_nop 15\n\ts_nop 3" : "+a"(l), "+a"(o[0]), "+a"(o[1]), "+a"(o[2]), "+a"(o[3]));
+    else asm volatile("" : "+a"(l), "+a"(o[0]), "+a"(o[1]), "+a"(o[2]), "+a"(o[3]));
+#pragma unroll
+    for (int i = 4; i < N; i += 4) asm volatile("" : "+a"(o[i]), "+a"(o[i + 1]), "+a"(o[i + 2]), "+a"(o[i + 3]));
+}
 // Stores issued by hand so that the wave can count them (see Stream): wave-uniform
 // base address in scalar registers, 32-bit byte offset per lane.  The hardware reads
 // the data registers of a wide store a little after issue and does not interlock
@@ -291,9 +312,10 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const Item& item,
         sm.cmark2 = buf == 2 ? sm.seq : sm.cmark2;
     };
     auto buf_of = [&](int win) { return (win & 1) ? sm.cb1 : sm.cb0; };
-    // Issue the next stream tile due (own tile idx, or tile idx - ntiles of the next item), if it
-    // exists; own tiles are asked for in increasing order.
+    // Issue stream tile `idx` (own tile idx, or tile idx - ntiles of the next item) if it
+    // is the next one due and exists; own tiles must be asked for in increasing order.
     auto issue = [&](int idx) {
+        if (idx != sm.iss) return;
         int buf, at;
         int g = item.g;
         if (idx < ntiles) {
@@ -303,7 +325,7 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const Item& item,
             at = 2 * w;
         } else {
             const int j = idx - ntiles;
-            if (j >= next_pre) return false;
+            if (j >= next_pre) return;
             buf = sm.cbn;
             at = 2 * j;
             g = next.g;
@@ -320,18 +342,14 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const Item& item,
         sm.tmark0 = stg == 0 ? sm.seq : sm.tmark0;
         sm.tmark1 = stg == 1 ? sm.seq : sm.tmark1;
         sm.iss = idx + 1;
-        return true;
-    };
-    auto issue_upto = [&](int last) {
-        if (sm.iss == last - 1 && !issue(last - 1)) return;
-        if (sm.iss == last) issue(last);
     };
     if (!sm.cols_ready) fetch_cols(trow, item.c0, item.c1, 0, sm.cb0);
     fetch_cols(trow, item.c0, item.c1, 1, sm.cb1);
     if (has_next) fetch_cols(nrow, next.c0, next.c1, 0, sm.cbn);
     // Own tiles only at this point (no-ops when the predecessor has asked for them):
     // the next item's column window has only just been requested.
-    issue_upto(min(ntiles, 2) - 1);
+    issue(0);
+    if (ntiles > 1) issue(1);
 
     // B operand of the first product: Q^T, lane (n, kg) holds q[row n][32 ks + 8 kg .. +8].
     // The rows of a single request's query group are contiguous in q; the predecessor
@@ -424,13 +442,13 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const Item& item,
         lacc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int i = 0; i < NI; ++i) oacc[nt][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        settle<false>(lacc[nt], oacc[nt]);
     }
 
     // One tile in two halves.  front(t): wait for the tile, read it out of its stage
-    // (handing the stage back for the refill), S^T = K Q^T, V transposed, and the
+    // (handing the stage back for the refill), S^T = K Q^T, and the
     // scaled scores with their per-lane maximum.  back(): weights, denominators and
-    // O^T += V^T P^T.  Between the two the reference exponents may have to be raised;
-    // that happens in a second copy of the loop, entered at most once per item.
+    // O^T += V^T P^T.  Between the two the reference exponents may have to be raised.
     f32x4 sacc[NT][2]; // S^T of the tile: this lane's 8 tokens (two blocks of 4) per row tile
     float tmax[NT];    // scaled maximum of those, positions past the end left out
     int tile_pos = 0;  // position of the tile's first token
@@ -449,7 +467,7 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const Item& item,
             }
         }
     };
-    auto front = [&](int t) {
+    auto front = [&](int t, auto first) {
         const int stg = (sm.phase + t) & 1;
         const char* st = s_stage + stg * STG;
         wait_for<D / 8>(sm, stg == 0 ? sm.tmark0 : sm.tmark1);   // tile t has landed
@@ -471,6 +489,11 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const Item& item,
                 vA[i] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
             }
         };
+        auto ask = [&]() {     // (the tile after this one is due only where the look-ahead stopped short of an item of one tile)
+            if constexpr (decltype(first)::value)
+                if (ntiles == 1) issue(t + 1);
+            issue(t + 2);
+        };
 #pragma unroll
         for (int mt = 0; mt < (kLate ? 1 : 2); ++mt)
 #pragma unroll
@@ -478,7 +501,7 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const Item& item,
         if constexpr (!kLate) {
             read_v();
             wait_lgkmcnt0();   // the stage is read out: refill it with stream tile t+2
-            issue_upto(t + 2); // (t + 1 is only due if the look-ahead into the next item stopped short)
+            ask();
         }
 
         tile_pos = (item.c0 + 2 * t) * kBlock;
@@ -504,7 +527,7 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const Item& item,
         if constexpr (kLate) {
             read_v();
             wait_lgkmcnt0();
-            issue_upto(t + 2);
+            ask();
         }
 
         // ---- V: zero tokens past the end (they may hold anything)
@@ -561,37 +584,22 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const Item& item,
             bf16x8 pB;
 #pragma unroll
             for (int x = 0; x < 8; ++x) pB[x] = (__bf16)exp2_fast(fmaf(r[x], a.scale_log2, neg_m));
-            lacc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pB, lacc[nt], 0, 0, 0);
+            add_product<true>(lacc[nt], ones, pB);
 #pragma unroll
-            for (int i = 0; i < NI; ++i)
-                oacc[nt][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vA[i], pB, oacc[nt][i], 0, 0, 0);
+            for (int i = 0; i < NI; ++i) add_product<false>(oacc[nt][i], vA[i], pB);
         }
     };
     // First tile: the reference is its row maximum, nothing to rescale yet.
-    front(0);
+    front(0, std::true_type{});
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
         float rmax = fmaxf(tmax[nt], __shfl_xor(tmax[nt], 16));
         m_run[nt] = fmaxf(fmaxf(rmax, __shfl_xor(rmax, 32)), kLowest);
     }
     back();
-    // Fast loop: no reference is ever raised in here, the accumulators are only touched
-    // by the matrix core.  It is left for good (to the loop below) the first time a
-    // score outgrows its reference.
-    int t = 1;
-    bool need = false;
-    for (; t < ntiles; ++t) {
-        need = front(t);
-        if (__builtin_expect(need, 0)) break;
+    for (int t = 1; t < ntiles; ++t) {
+        if (__builtin_expect(front(t, std::false_type{}), 0)) raise_refs();
         back();
-    }
-    if (need) {
-        for (;;) {   // tile t has been through front()
-            raise_refs();
-            back();
-            if (++t >= ntiles) break;
-            front(t);
-        }
     }
 
     // ---- partial rows: lane (n, kg) holds, for row 16 nt + n, dims 16 i + 4 kg .. of product i
@@ -599,6 +607,7 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const Item& item,
     const char* pacc = sgpr(a.ws + a.lay.acc + (size_t)item.pbase * (D * sizeof(float)));
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
+        settle<true>(lacc[nt], oacc[nt]);
         const float l = lacc[nt][0];   // every element of the column holds the row's sum
         const int row = nt * 16 + n;
         if (nt * 16 < item.nrows) {    // wave-uniform: lane 0 has a row here, so all its stores are issued

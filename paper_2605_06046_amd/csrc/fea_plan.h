@@ -116,6 +116,12 @@ struct PlanArgs {
     int32_t pre_grid;    // its grid
     int32_t histories;   // tiles (of 32 tokens) from which on a batch that shares nothing is swept by whole histories; 0: never
     int32_t histories_each;   // ... and how many of them a history has to have on average
+    const void* k_cache;      // KV tiles that the launch's other workgroups read ahead of the sweep:
+    const void* v_cache;
+    int32_t block_bytes;      // (of one block and KV head)
+    int32_t ahead;            // the last so many tiles of every (request, KV head); 0: the planner's workgroup is alone
+    int32_t ahead_grid;       // workgroups, the planner's among them
+    int32_t own;              // ... and how many columns of their own the requests must have
 };
 
 // What run_kernel leaves for the planner, per groupable request: the run it shares with its
@@ -153,6 +159,7 @@ struct Launch {
     void* ev_mid[2] = {nullptr, nullptr};   // where a step is two dispatches: end of the first, start of the second
 };
 
+void set_read_ahead(PlanArgs& a, const void* k_cache, const void* v_cache, int head_dim, int cus);   // (bfloat16 caches; the rest of `a` is set)
 void launch_plan(const PlanArgs& a, const Launch& L);
 void launch_refresh(const PlanArgs& a, const Launch& L);
 void launch_sweep_generic(const SweepArgs& a, int dtype, int head_dim, int grid, const Launch& L);

@@ -16,9 +16,11 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 
+#include <algorithm>
 #include <climits>
 #include <type_traits>
 
+#include "fea_device.h"
 #include "fea_plan.h"
 
 namespace fea {
@@ -265,6 +267,59 @@ __global__ __launch_bounds__(kRunThreads) void run_kernel(PlanArgs a) {
     }
 }
 
+// What the planner's launch does besides: its workgroup keeps one compute unit busy, and next to nothing of the memory, for 13 us
+// and more.  Others meanwhile read the ends of the histories - the part that is hardly ever shared, which the sweep therefore
+// takes from memory - and throw away what they read: the sweep then finds 32 MB of it nearer (16 MB gain half as much, 50 MB no
+// more, and take longer than the planner where it is quick).  Nothing depends on it.
+//  - Half of the compute units do it: 1.00 of a call's time where there is nothing to read (all of them 1.003, 0.1 to 0.5 us for
+//    their start), and as much gained.
+//  - They wait 2400 cycles first: the planner reads its tables then, and waits for them.
+//  - They do it if half of the requests that share a run with one of theirs (of 32 looked at) have `own` columns and more behind what
+//    they share, 60 MB in all if they are alike: where much less is read for the first time by the sweep, or nothing is shared (the
+//    planner is done at once then, 64 requests of 4224 to 5120 tokens 229 -> 234 us), there is little to gain.
+// 64 requests on one prefix of 4096, 32/8/128: 55.4 -> 51.4 us a call; 128 of head_dim 64 in 8 groups 54.2 -> 51.5, 32 on one of 32K
+// 75.0 -> 73.2, 80 drawn shapes that share runs 0.986 in the mean, 0.94 at best (three sets of caches in turn; with nine, 0.97).
+constexpr int kAheadMB = 32, kOwnMB = 60, kAheadSample = 32;
+__device__ __forceinline__ void read_ahead(const PlanArgs& a) {
+    __shared__ int s_go;
+    constexpr int kWaves = kPlanThreads / 64;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    __builtin_amdgcn_s_sleep(38);          // (of 64 cycles)
+    if (wave == 0) {
+        const int i = blockIdx.x % a.B, other = (i + 1 + (lane % kAheadSample)) % a.B;
+        const int32_t* row = a.bt + (size_t)i * a.stride;
+        const int32_t* peer = a.bt + (size_t)other * a.stride;
+        const int L = max(0, min(a.seq_lens[other], a.stride * kBlock)), at = (L + kBlock - 1) / kBlock - 1 - a.own;
+        const bool shares = lane < kAheadSample && other != i && peer[0] == row[0], apart = shares && at >= 1 && peer[max(at, 0)] != row[max(at, 0)];
+        const int all = __popcll(__ballot(shares)), n = __popcll(__ballot(apart));
+        if (lane == 0) s_go = all > 0 && 2 * n >= all;
+    }
+    __syncthreads();
+    if (!s_go) return;
+    const int units = a.B * a.Hkv;
+    for (int w = (blockIdx.x - 1) * kWaves + wave; w < units * a.ahead; w += (gridDim.x - 1) * kWaves) {
+        const int t = w / units, u = w - t * units, i = u / a.Hkv, g = u - i * a.Hkv;
+        const int32_t* row = a.bt + (size_t)i * a.stride;
+        const int L = max(0, min(a.seq_lens[i], a.stride * kBlock)), c1 = (L + kBlock - 1) / kBlock - 1 - 2 * t;
+        if (c1 < 1) continue;
+        const size_t at0 = ((size_t)max(row[c1 - 1], 0) * a.Hkv + g) * a.block_bytes, at1 = ((size_t)max(row[c1], 0) * a.Hkv + g) * a.block_bytes;
+        const char* k = static_cast<const char*>(a.k_cache);
+        const char* v = static_cast<const char*>(a.v_cache);
+        const char* from[4] = {k + at0, k + at1, v + at0, v + at1};
+        for (int at = 0; at < a.block_bytes; at += 2048) {     // (head_dim 64: 2 KB a block)
+            u32x4 x[4][2];
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) x[b][j] = ld16(from[b] + at + 1024 * j + 16 * lane);
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) asm volatile("" :: "v"(x[b][j]));
+        }
+    }
+}
+
 constexpr int kSegmentTiles = 1;              // tiles that a further segment of a share costs
 constexpr int kGroupMax = kGroupReqMax / 2;   // a group has at least two members
 
@@ -291,6 +346,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
     __shared__ __attribute__((aligned(16))) int s_sums[4][kPlanThreads / 64];
     __shared__ int s_ngroups, s_ngrouped, s_shared_blocks, s_nflw, s_nest, s_adopt, s_longest[kPlanThreads / 64];
 
+    if (blockIdx.x > 0) { read_ahead(a); return; }
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int* hdr = reinterpret_cast<int*>(a.ws);
@@ -1213,6 +1269,16 @@ void launch_refresh(const PlanArgs& a, const Launch& L) {
                           static_cast<hipEvent_t>(L.ev_start), static_cast<hipEvent_t>(L.ev_stop), 0, a);
 }
 
+void set_read_ahead(PlanArgs& a, const void* k_cache, const void* v_cache, int head_dim, int cus) {
+    a.k_cache = k_cache;
+    a.v_cache = v_cache;
+    a.block_bytes = kBlock * head_dim * 2;
+    a.ahead_grid = cus / 2;
+    const int64_t column = (int64_t)a.B * a.Hkv * 2 * a.block_bytes;       // bytes of K and V of a column of every request
+    a.ahead = a.ahead_grid > 1 ? (int32_t)std::min<int64_t>(a.stride / 4, kAheadMB * 1000000ll / (2 * column)) : 0;
+    a.own = (int32_t)(kOwnMB * 1000000ll / column);
+}
+
 void launch_plan(const PlanArgs& a, const Launch& L) {
     hipStream_t st = static_cast<hipStream_t>(L.stream);
     hipEvent_t e0 = static_cast<hipEvent_t>(L.ev_start), e1 = static_cast<hipEvent_t>(L.ev_stop);
@@ -1221,7 +1287,7 @@ void launch_plan(const PlanArgs& a, const Launch& L) {
                               static_cast<hipEvent_t>(L.ev_mid[0]), 0, a);
         hipExtLaunchKernelGGL(plan_kernel, dim3(1), dim3(kPlanThreads), 0, st, static_cast<hipEvent_t>(L.ev_mid[1]), e1, 0, a);
     } else {
-        hipExtLaunchKernelGGL(plan_kernel, dim3(1), dim3(kPlanThreads), 0, st, e0, e1, 0, a);
+        hipExtLaunchKernelGGL(plan_kernel, dim3(a.ahead > 0 ? a.ahead_grid : 1), dim3(kPlanThreads), 0, st, e0, e1, 0, a);
     }
 }
 

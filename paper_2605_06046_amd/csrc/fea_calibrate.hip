@@ -23,16 +23,14 @@ __device__ __forceinline__ const char* uniform_ptr(const char* p) {
     return reinterpret_cast<const char*>(lo | (hi << 32));
 }
 
-// Four wave-wide 16-byte-per-lane loads (one 4 KB chunk) into LDS at `lds` (wave-uniform).
+// Four wave-wide 16-byte-per-lane loads (one 4 KB chunk) into LDS at `lds` (wave-uniform).  The immediate offset moves both
+// addresses.  Read once, they pass by the caches as the sweep's own columns do.
 __device__ __forceinline__ void fetch_chunk(const char* base, uint32_t lane_off, uint32_t lds) {
     asm volatile(
-        "s_nop 4\n\t"
-        "s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1\n\t"
-        "s_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:1024\n\t"
-        "s_mov_b32 m0, %4\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:2048\n\t"
-        "s_mov_b32 m0, %5\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:3072"
-        :: "v"(lane_off), "s"(base), "s"(lds), "s"(lds + 1024), "s"(lds + 2048), "s"(lds + 3072)
-        : "memory", "m0");
+        "s_nop 4\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\t"
+        "global_load_lds_dwordx4 %0, %1 nt\n\tglobal_load_lds_dwordx4 %0, %1 offset:1024 nt\n\t"
+        "global_load_lds_dwordx4 %0, %1 offset:2048 nt\n\tglobal_load_lds_dwordx4 %0, %1 offset:3072 nt"
+        :: "v"(lane_off), "s"(base), "s"(lds) : "memory", "m0");
 }
 
 // n_chunks is a power of two; chunk c of the stream sits at ((c * mult) mod n_chunks) * 4 KB,

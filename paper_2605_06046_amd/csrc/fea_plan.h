@@ -74,7 +74,7 @@ struct SegDesc {
 
 struct Item {          // one KV sweep: a row set x one KV head x a column range (32 bytes)
     int32_t who;       // request whose table row is read (the group's leader for a shared run)
-    int32_t g;         // KV head (bits 0-15); pieces of shared runs swept by a team of waves: team size (bits 16-19), rank (bits 20-23)
+    int32_t g;         // KV head (bits 0-15); pieces of shared runs swept by a team of waves: team size (bits 16-19), rank (bits 20-23); kOnce
     int32_t nrows;     // query rows: (requests in the row set) x (group heads)
     int32_t mlist_off; // the row set's request ids start at members[mlist_off]; negative: just `who` (kOpenEnded: and
                        // the piece ends where the request's history ends)
@@ -82,6 +82,7 @@ struct Item {          // one KV sweep: a row set x one KV head x a column range
     int32_t pbase;     // partial row of the item's first query row
     int32_t tok_end;   // tokens at positions >= tok_end are not attended to
 };
+constexpr int32_t kOnce = 1 << 24;   // in Item::g: no other item reads these columns (not said of what teams sweep)
 static_assert(sizeof(Item) == 32, "Item is read as two 16-byte words");
 
 // Byte offsets of the workspace sections (all multiples of 256).

@@ -344,7 +344,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
         unsigned short glist[kGroupMax];        // then the list of viable leaders
     } w;
     __shared__ __attribute__((aligned(16))) int s_sums[4][kPlanThreads / 64];
-    __shared__ int s_ngroups, s_ngrouped, s_shared_blocks, s_nflw, s_nest, s_adopt, s_longest[kPlanThreads / 64];
+    __shared__ int s_ngroups, s_ngrouped, s_shared_blocks, s_nflw, s_nest, s_adopt, s_alike, s_longest[kPlanThreads / 64];
 
     if (blockIdx.x > 0) { read_ahead(a); return; }
     const int tid = threadIdx.x, lane = tid & 63;
@@ -379,7 +379,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
         }
     }
     for (int s = tid; s < slots; s += kPlanThreads) { h2.keys[s] = -1; h2.vals[s] = INT_MAX; }
-    if (tid == 0) { s_ngroups = 0; s_ngrouped = 0; s_shared_blocks = 0; s_nflw = 0; }
+    if (tid == 0) { s_ngroups = 0; s_ngrouped = 0; s_shared_blocks = 0; s_nflw = 0; s_alike = 0; }
     if (a.pre) {
         __syncthreads();   // (s_nflw is zero)
         // ---- leaders and common runs were found by run_kernel
@@ -565,6 +565,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
     const int w32 = a.tune.weights & 255, w64 = (a.tune.weights >> 8) & 255;
     auto tile_weight = [&](int rows) { return rows <= 16 ? 16 : (rows <= 32 ? w32 : w64); };
     const FastDiv by_mpt(a.mpt);
+    bool split_off = false;   // groups have split off groups, which sweep the outer run again
     // Row tiles of one piece of a shared run read the same KV bytes.  On the matrix-core path the sweep
     // runs them as a team of 2 or 4 waves of one workgroup that fetches every tile once; for that the
     // row tiles of a piece sit on neighbouring shares, in slots of 1, 2 or a multiple of 4 (the slots
@@ -711,6 +712,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
                     const long long cost = (long long)run2 * group_weight(c2) * by_mpt.cdiv(c2);
                     adopt[k] = c2 >= 2 && gain > cost;
                     if (adopt[k] && lead2[k] == tid + k * kPlanThreads) atomicAdd(&s_adopt, 1);
+                    if (!adopt[k] && c2 >= 2 && run2 > r1[k]) s_alike = 1;   // (of their own columns some are the same)
                 }
                 if (in[k] && !adopt[k]) atomicMin(&u.c.moff[lead1[k]], tid + k * kPlanThreads);   // who leads the rest
             }
@@ -719,6 +721,8 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
 #pragma unroll
             for (int k = 0; k < kPer; ++k) lead_f[k] = adopt[k] ? lead2[k] : (in[k] ? u.c.moff[lead1[k]] : lead1[k]);
             const bool again = s_adopt > 0 && level + 1 < kMaxLevels;
+            split_off = split_off || s_adopt > 0;
+            if (s_adopt > 0 && level + 1 == kMaxLevels && tid == 0) s_alike = 1;   // (not looked at)
             __syncthreads();                           // every leader is read before any changes
 #pragma unroll
             for (int k = 0; k < kPer; ++k) {
@@ -1008,6 +1012,10 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
         rem = q - room;
         if (rem == q) { rem = 0; ++k; }
     };
+    // Columns that one item alone reads are marked: the sweep has them pass by the caches.  Not marked are a request's own columns
+    // where others may have the same ones (nothing was looked for, a request has no place among those that were compared, or a
+    // subgroup was found and left as it was), and runs with more than one row tile, or swept by subgroups too.
+    const int own_once = a.variant == 1 && a.grouping && B <= kGroupReqMax && s_alike == 0 ? kOnce : 0;
     const WideDiv by_q(max(q, 1));
     const int k_start = by_q.div(tbase), rem_start = tbase - k_start * q;
 
@@ -1062,7 +1070,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
                 for_pieces(units, k, rem, [&](int jb, int je, bool starts, int kk) {
                     const int cs = c0 + 2 * jb, ce = min(nb, c0 + 2 * je);
                     // (the piece that ends at the request's last column is marked: it grows with the request, see refresh_kernel)
-                    write_item(&items[idx], i, g, a.G, ce == nb ? kOpenEnded : -1, cs, ce, rows_sh + (idx - n_sh) * a.G, min(L, ce * kBlock));
+                    write_item(&items[idx], i, g | own_once, a.G, ce == nb ? kOpenEnded : -1, cs, ce, rows_sh + (idx - n_sh) * a.G, min(L, ce * kBlock));
                     if (starts) wave_first[n_sh + kk] = idx;
                     ++idx;
                 });
@@ -1129,6 +1137,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
             }
             const int tiles_p = tiles_padded(tiles_r);
             const int team = (teams && tiles_r >= 2) ? (tiles_r == 2 ? 2 : 4) : 0;
+            const int once = a.variant == 1 && tiles_r == 1 && !split_off ? kOnce : 0;
             const FastDiv by_tp(tiles_p), by_pc(n_pc);
             const int n = Hkv * n_pc * tiles_p, n_slots = items_padded(n);
             const int full_rows = a.mpt * a.G, last_rows = (cnt - (tiles_r - 1) * a.mpt) * a.G;
@@ -1143,7 +1152,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
                 const int rest = by_tp.div(k), tau = k - rest * tiles_p;
                 const int g = by_pc.div(rest), pc = rest - g * n_pc;
                 const int cs = 2 * (pc * ps + min(pc, extra)), ce = min(run, cs + 2 * (ps + (pc < extra ? 1 : 0)));
-                const int g_team = g | (team << 16) | ((team ? (tau & (team - 1)) : 0) << 20);   // KV head, team size, rank in the team
+                const int g_team = g | once | (team << 16) | ((team ? (tau & (team - 1)) : 0) << 20);   // KV head, team size, rank in the team
                 if (tau >= tiles_r) {                  // no rows of its own: a team member that only fetches
                     write_item(dst, ld, g_team, 0, -1, cs, ce, 0, ce * kBlock);
                     continue;

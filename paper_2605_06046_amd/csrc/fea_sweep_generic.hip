@@ -105,7 +105,8 @@ __global__ __launch_bounds__(kGenThreads) void sweep_generic_kernel(SweepArgs a)
     const int n_items = hdr[H_ITEMS];
 
     for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
-        const Item item = items[it];
+        Item item = items[it];
+        item.g &= 0xFFFF;
         const int32_t* row = a.bt + (size_t)item.who * a.stride;
         const int t_begin = item.c0 * kBlock, t_end = item.tok_end;
         // query rows of the item: one request's query group, or those of the members of a group's row tile

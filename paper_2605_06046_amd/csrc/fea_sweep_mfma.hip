@@ -115,37 +115,49 @@ __device__ __forceinline__ void dma16x2(const char* base, uint32_t off0, uint32_
         : "memory", "m0");
 }
 // A tile: the loads of its four blocks, into LDS one behind the other from lds on.  The immediate offset of such a load moves
-// both its addresses, so M0 is set once for 4 KB (head_dim 64: 2 KB) instead of for every load.
-template <int D>
+// both its addresses, so M0 is set once for 4 KB (head_dim 64: 2 KB) instead of for every load.  ONCE: nobody else reads these
+// bytes (kOnce), they need not stay in the caches, and kept there they only cost: a scattered read of 2 GB so 6.4 -> 6.9 TB/s, 256
+// requests in 8 groups on 4096 (32/8/128) 169 -> 152 us, 64 on one 51.4 -> 47.8, five groups of 16 on 10240 89 -> 77.5, 44 drawn
+// shapes 0.94 of the time with eight sets of caches in turn (0.88 to 1.02).  One small batch over and over, which the caches would
+// hold: 1.00 (0.88 to 1.07).  Columns that others read too are left to the caches: 48 requests on a system prompt in 6 groups,
+// four layers 148 us, 155 with all of them passing by.
+template <int D, bool ONCE>
 __device__ __forceinline__ void dma_tile(const char* k0, const char* k1, const char* v0, const char* v1, const uint32_t (&off)[8], uint32_t lds) {
-    if constexpr (D == 64) {
-        asm volatile(
-            "s_nop 4\n\ts_mov_b32 m0, %5\n\ts_nop 0\n\t"
-            "global_load_lds_dwordx4 %0, %1\n\tglobal_load_lds_dwordx4 %0, %1 offset:1024\n\ts_addk_i32 m0, 0x800\n\ts_nop 0\n\t"
-            "global_load_lds_dwordx4 %0, %2\n\tglobal_load_lds_dwordx4 %0, %2 offset:1024\n\ts_addk_i32 m0, 0x800\n\ts_nop 0\n\t"
-            "global_load_lds_dwordx4 %0, %3\n\tglobal_load_lds_dwordx4 %0, %3 offset:1024\n\ts_addk_i32 m0, 0x800\n\ts_nop 0\n\t"
-            "global_load_lds_dwordx4 %0, %4\n\tglobal_load_lds_dwordx4 %0, %4 offset:1024"
-            :: "v"(off[0]), "s"(k0), "s"(k1), "s"(v0), "s"(v1), "s"(lds) : "memory", "m0", "scc");
-    } else {
-#define FEA_DMA4(A, B, C, E, BASE) "global_load_lds_dwordx4 " A ", " BASE "\n\tglobal_load_lds_dwordx4 " B ", " BASE " offset:1024\n\t" \
-        "global_load_lds_dwordx4 " C ", " BASE " offset:2048\n\tglobal_load_lds_dwordx4 " E ", " BASE " offset:3072\n\t"
+#define FEA_DMA2(A, BASE, AT) "global_load_lds_dwordx4 " A ", " BASE AT "\n\tglobal_load_lds_dwordx4 " A ", " BASE " offset:1024" AT "\n\t"
+#define FEA_DMA4(A, B, C, E, BASE, AT) "global_load_lds_dwordx4 " A ", " BASE AT "\n\tglobal_load_lds_dwordx4 " B ", " BASE " offset:1024" AT "\n\t" \
+        "global_load_lds_dwordx4 " C ", " BASE " offset:2048" AT "\n\tglobal_load_lds_dwordx4 " E ", " BASE " offset:3072" AT "\n\t"
+#define FEA_DMA8(BASE, AT) FEA_DMA4("%0", "%1", "%2", "%3", BASE, AT) FEA_M0_ON FEA_DMA4("%4", "%5", "%6", "%7", BASE, AT)
 #define FEA_M0_ON "s_addk_i32 m0, 0x1000\n\ts_nop 0\n\t"
-        if constexpr (D == 128) {
-            asm volatile("s_nop 4\n\ts_mov_b32 m0, %8\n\ts_nop 0\n\t"
-                         FEA_DMA4("%0", "%1", "%2", "%3", "%4") FEA_M0_ON FEA_DMA4("%0", "%1", "%2", "%3", "%5") FEA_M0_ON
-                         FEA_DMA4("%0", "%1", "%2", "%3", "%6") FEA_M0_ON FEA_DMA4("%0", "%1", "%2", "%3", "%7")
-                         :: "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(k0), "s"(k1), "s"(v0), "s"(v1), "s"(lds) : "memory", "m0", "scc");
-        } else {
-#define FEA_DMA8(BASE) FEA_DMA4("%0", "%1", "%2", "%3", BASE) FEA_M0_ON FEA_DMA4("%4", "%5", "%6", "%7", BASE)
-            asm volatile("s_nop 4\n\ts_mov_b32 m0, %12\n\ts_nop 0\n\t"
-                         FEA_DMA8("%8") FEA_M0_ON FEA_DMA8("%9") FEA_M0_ON FEA_DMA8("%10") FEA_M0_ON FEA_DMA8("%11")
-                         :: "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "v"(off[4]), "v"(off[5]), "v"(off[6]), "v"(off[7]),
-                            "s"(k0), "s"(k1), "s"(v0), "s"(v1), "s"(lds) : "memory", "m0", "scc");
-#undef FEA_DMA8
-        }
-#undef FEA_DMA4
-#undef FEA_M0_ON
+#define FEA_M0_ON2 "s_addk_i32 m0, 0x800\n\ts_nop 0\n\t"
+#define FEA_TILE64(AT) asm volatile("s_nop 4\n\ts_mov_b32 m0, %5\n\ts_nop 0\n\t" \
+        FEA_DMA2("%0", "%1", AT) FEA_M0_ON2 FEA_DMA2("%0", "%2", AT) FEA_M0_ON2 FEA_DMA2("%0", "%3", AT) FEA_M0_ON2 FEA_DMA2("%0", "%4", AT) \
+        :: "v"(off[0]), "s"(k0), "s"(k1), "s"(v0), "s"(v1), "s"(lds) : "memory", "m0", "scc")
+#define FEA_TILE128(AT) asm volatile("s_nop 4\n\ts_mov_b32 m0, %8\n\ts_nop 0\n\t" \
+        FEA_DMA4("%0", "%1", "%2", "%3", "%4", AT) FEA_M0_ON FEA_DMA4("%0", "%1", "%2", "%3", "%5", AT) FEA_M0_ON \
+        FEA_DMA4("%0", "%1", "%2", "%3", "%6", AT) FEA_M0_ON FEA_DMA4("%0", "%1", "%2", "%3", "%7", AT) \
+        :: "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(k0), "s"(k1), "s"(v0), "s"(v1), "s"(lds) : "memory", "m0", "scc")
+#define FEA_TILE256(AT) asm volatile("s_nop 4\n\ts_mov_b32 m0, %12\n\ts_nop 0\n\t" \
+        FEA_DMA8("%8", AT) FEA_M0_ON FEA_DMA8("%9", AT) FEA_M0_ON FEA_DMA8("%10", AT) FEA_M0_ON FEA_DMA8("%11", AT) \
+        :: "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "v"(off[4]), "v"(off[5]), "v"(off[6]), "v"(off[7]), \
+           "s"(k0), "s"(k1), "s"(v0), "s"(v1), "s"(lds) : "memory", "m0", "scc")
+    if constexpr (D == 64) {
+        if constexpr (ONCE) FEA_TILE64(" nt");
+        else FEA_TILE64("");
+    } else if constexpr (D == 128) {
+        if constexpr (ONCE) FEA_TILE128(" nt");
+        else FEA_TILE128("");
+    } else {
+        if constexpr (ONCE) FEA_TILE256(" nt");
+        else FEA_TILE256("");
     }
+#undef FEA_DMA2
+#undef FEA_DMA4
+#undef FEA_DMA8
+#undef FEA_M0_ON
+#undef FEA_M0_ON2
+#undef FEA_TILE64
+#undef FEA_TILE128
+#undef FEA_TILE256
 }
 // One load of 4 bytes per lane (block ids of 64 table columns), same conventions.
 __device__ __forceinline__ void dma4(const void* base, uint32_t lane_off, uint32_t lds_addr) {
@@ -210,6 +222,8 @@ __device__ __forceinline__ void store_f32x2(const char* base, uint32_t off, floa
 template <int N> __device__ __forceinline__ void wait_vmcnt() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
 __device__ __forceinline__ void wait_lgkmcnt0() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
+struct Piece : Item { int once; };   // g: the KV head alone; once: its kOnce
+
 struct Lanes {
     int n;                 // lane % 16: query row of a 16-row tile / token of a block / 16-byte chunk
     int kg;                // lane / 16: k-slot group of the MFMA operands
@@ -220,7 +234,7 @@ struct Lanes {
 
 // Fetch blocks b0, b1 of KV head g into the stage at LDS address `stage` (16 loads).
 template <int D>
-__device__ __forceinline__ void fetch_tile(const SweepArgs& a, int g, int b0, int b1, uint32_t stage, const Lanes& L) {
+__device__ __forceinline__ void fetch_tile(const SweepArgs& a, int g, int once, int b0, int b1, uint32_t stage, const Lanes& L) {
     constexpr int BLK = kBlock * D * 2;
     const size_t o0 = (size_t)((uint32_t)b0 * (uint32_t)a.Hkv + (uint32_t)g) * BLK;   // (blocks times KV heads: below 2^32, a block has 2 KB or more)
     const size_t o1 = (size_t)((uint32_t)b1 * (uint32_t)a.Hkv + (uint32_t)g) * BLK;
@@ -228,7 +242,8 @@ __device__ __forceinline__ void fetch_tile(const SweepArgs& a, int g, int b0, in
     const char* k1 = sgpr(static_cast<const char*>(a.k_cache) + o1);
     const char* v0 = sgpr(static_cast<const char*>(a.v_cache) + o0);
     const char* v1 = sgpr(static_cast<const char*>(a.v_cache) + o1);
-    dma_tile<D>(k0, k1, v0, v1, L.dma_off, sgpr(stage));
+    if (once) dma_tile<D, true>(k0, k1, v0, v1, L.dma_off, sgpr(stage));
+    else dma_tile<D, false>(k0, k1, v0, v1, L.dma_off, sgpr(stage));
 }
 
 // Tile stream of one wave.  `phase` is the stage the current item's tile 0 uses,
@@ -286,7 +301,7 @@ __device__ __forceinline__ void wait_all(Stream& sm) {
 }
 
 template <int NT, int D>
-__device__ __forceinline__ void sweep_item(const SweepArgs& a, const Item& item, const Item& next, bool has_next,
+__device__ __forceinline__ void sweep_item(const SweepArgs& a, const Piece& item, const Piece& next, bool has_next,
                                            int g_rcp, char* s_stage, const int* s_cols, const char* s_q, uint32_t lds_base,
                                            uint32_t cols_base, uint32_t q_base, const Lanes& L, int lane, Stream& sm) {
     constexpr int BLK = kBlock * D * 2;      // bytes of one (block, KV head)
@@ -317,7 +332,7 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const Item& item,
     auto issue = [&](int idx) {
         if (idx != sm.iss) return;
         int buf, at;
-        int g = item.g;
+        int g = item.g, once = item.once;
         if (idx < ntiles) {
             const int w = idx & 31, win = idx >> 5;
             if (w == 0 && idx > 0) fetch_cols(trow, item.c0, item.c1, win + 1, buf_of(win + 1));   // `win` came 32 tiles ago
@@ -329,6 +344,7 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const Item& item,
             buf = sm.cbn;
             at = 2 * j;
             g = next.g;
+            once = next.once;
         }
         wait_for<D / 8>(sm, pick3(buf, sm.cmark0, sm.cmark1, sm.cmark2));   // the window's block ids must have landed
         const int* sc = s_cols + buf * 64 + at;
@@ -337,7 +353,7 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const Item& item,
         const int b0 = max(__builtin_amdgcn_readfirstlane(sc[0]), 0);
         const int b1 = max(__builtin_amdgcn_readfirstlane(sc[1]), 0);
         const int stg = (sm.phase + idx) & 1;
-        fetch_tile<D>(a, g, b0, b1, lds_base + stg * STG, L);
+        fetch_tile<D>(a, g, once, b0, b1, lds_base + stg * STG, L);
         sm.seq += D / 8;
         sm.tmark0 = stg == 0 ? sm.seq : sm.tmark0;
         sm.tmark1 = stg == 1 ? sm.seq : sm.tmark1;
@@ -636,7 +652,7 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const Item& item,
 // has to live across it.  `team_base`: LDS address of the team's ring (2 x team tiles of K, then of V).
 #include "fea_sweep_core.inc"
 constexpr int kTeamCols = 1024;   // columns of a piece a team can sweep: their block ids fill the wave's query buffer (4 KB)
-__device__ __forceinline__ void sweep_team_core(const SweepArgs& a, const Item& item, int team, int rank, int g_rcp,
+__device__ __forceinline__ void sweep_team_core(const SweepArgs& a, const Piece& item, int team, int rank, int g_rcp,
                                                 uint32_t team_base, uint32_t tab_base, int lane) {
     // The per-lane inputs are worked out again from a copy of the lane number the compiler cannot
     // see through: they must sit in the few registers the sequence leaves alone, and tying them to
@@ -699,6 +715,8 @@ template <int D> constexpr int waves_per_group() { return D == 256 ? 2 : kWavesP
 // the other arrives, and a tile is asked for as soon as the one two before it has been read.  The next history is claimed
 // while this one is read.  (A weight enters the second product as two bfloat16 numbers here, the denominator unrounded: 0.7 of
 // the shares' error against float64, 0.00166 against 0.00233 for 512 requests of 512 to 4096 tokens, 64/8/128.)
+// Every byte is read once, and passes by the caches: 512 requests of 512 to 4096 tokens, 64/8/128, 829 -> 744 us (6.7 TB/s; V
+// alone 756), 256 of 512 to 1024, 32/8/128, 148 -> 138 (136).
 constexpr int kHistoryRows = 16;
 template <int D, int W>
 __device__ __forceinline__ void sweep_histories(const SweepArgs& a, char* lds, int* hdr, int wave, int lane) {
@@ -752,11 +770,11 @@ __device__ __forceinline__ void sweep_histories(const SweepArgs& a, char* lds, i
         };
         auto ask_k = [&](TileT& t) {
 #pragma unroll
-            for (int b = 0; b < TB; ++b) t.load_k(b, kb[b], n, kg);
+            for (int b = 0; b < TB; ++b) t.template load_k<true>(b, kb[b], n, kg);
         };
         auto ask_v = [&](TileT& t) {
 #pragma unroll
-            for (int b = 0; b < TB; ++b) t.load_v(b, vb[b], n, kg);
+            for (int b = 0; b < TB; ++b) t.template load_v<true>(b, vb[b], n, kg);
         };
         auto scores = [&](TileT& t, float (&p)[PN]) {
 #pragma unroll
@@ -915,11 +933,11 @@ __global__ __launch_bounds__(64 * waves_per_group<D>()) void sweep_mfma_kernel(S
         const int4* p = reinterpret_cast<const int4*>(s_desc + k * 8);
         const int4 w0 = p[0], w1 = p[1];
         auto u = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
-        Item x;
+        Piece x;
         const int gt = u(w0.y);
         team = (gt >> 16) & 15;
         rank = (gt >> 20) & 15;
-        x.who = u(w0.x); x.g = gt & 0xFFFF; x.nrows = u(w0.z); x.mlist_off = u(w0.w);
+        x.who = u(w0.x); x.g = gt & 0xFFFF; x.once = gt & kOnce; x.nrows = u(w0.z); x.mlist_off = u(w0.w);
         x.c0 = u(w1.x); x.c1 = u(w1.y); x.pbase = u(w1.z); x.tok_end = u(w1.w);
         return x;
     };
@@ -953,7 +971,7 @@ __global__ __launch_bounds__(64 * waves_per_group<D>()) void sweep_mfma_kernel(S
         int win_first = it;
         fetch_desc(win_first, sm);
         wait_all(sm);
-        Item item = read_desc(0);
+        Piece item = read_desc(0);
         // A piece of a shared run as this wave's only work, its row tiles on the neighbouring waves of this
         // workgroup: the team sweeps it together if it qualifies (every member sees the same columns, so
         // they all decide alike).  Members without rows of their own only take part in that.
@@ -977,7 +995,7 @@ __global__ __launch_bounds__(64 * waves_per_group<D>()) void sweep_mfma_kernel(S
                 fetch_desc(win_first, sm);
                 wait_all(sm);
             }
-            const Item next = has_next ? read_desc(it + 1 - win_first) : item;
+            const Piece next = has_next ? read_desc(it + 1 - win_first) : item;
             if (item.nrows <= 16) sweep_item<1, D>(a, item, next, has_next, g_rcp, s_stage, s_cols, s_q, lds_base, cols_base, q_base, L, lane, sm);
             else if (D == 256 || item.nrows <= 32) sweep_item<2, D>(a, item, next, has_next, g_rcp, s_stage, s_cols, s_q, lds_base, cols_base, q_base, L, lane, sm);   // (head_dim 256: the planner makes no item of more than 32 rows)
             else sweep_item<(D == 256 ? 2 : 4), D>(a, item, next, has_next, g_rcp, s_stage, s_cols, s_q, lds_base, cols_base, q_base, L, lane, sm);

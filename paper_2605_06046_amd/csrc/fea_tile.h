@@ -153,15 +153,15 @@ template <int D> struct Tile<bf16_t, D, 16> {
 #pragma unroll
         for (int j = 0; j < KC; ++j) q[j] = n < nh ? ld16(row + (4 * j + kg) * 16) : u32x4{0u, 0u, 0u, 0u};
     }
-    __device__ __forceinline__ void load_k(int b, const char* blk, int n, int kg) {
+    template <bool ONCE = false> __device__ __forceinline__ void load_k(int b, const char* blk, int n, int kg) {
 #pragma unroll
-        for (int j = 0; j < KC; ++j) k[b][j] = ld16(blk + (uint32_t)(n * (D * 2) + kg * 16 + j * 64));
+        for (int j = 0; j < KC; ++j) k[b][j] = ld16<ONCE>(blk + (uint32_t)(n * (D * 2) + kg * 16 + j * 64));
     }
-    __device__ __forceinline__ void load_v(int b, const char* blk, int n, int kg) {
+    template <bool ONCE = false> __device__ __forceinline__ void load_v(int b, const char* blk, int n, int kg) {
 #pragma unroll
         for (int r = 0; r < 4; ++r)
 #pragma unroll
-            for (int h = 0; h < VH; ++h) v[b][r][h] = ld16(blk + (uint32_t)((4 * kg + r) * (D * 2) + (D >= 128 ? n : n & 7) * 16 + h * 256));
+            for (int h = 0; h < VH; ++h) v[b][r][h] = ld16<ONCE>(blk + (uint32_t)((4 * kg + r) * (D * 2) + (D >= 128 ? n : n & 7) * 16 + h * 256));
     }
     __device__ __forceinline__ void mask(float (&p)[PN], int rest, int, int kg) {
 #pragma unroll

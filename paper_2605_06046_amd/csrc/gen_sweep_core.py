@@ -134,8 +134,11 @@ class Gen:
             if blk == 1:
                 v.append("s_addk_i32 m0, 0x1000")
                 v.append("s_nop 0")
+            # (A team reads every tile once and has it pass by the caches, also where another team reads it too: 40 requests in
+            # each of 4 groups behind a system prompt 69.7 -> 67.8 us, 20 in each of 6 60.2 -> 62.8, 500 on one prefix the same;
+            # and two forms of the sequence, chosen by the item, cost every team 0.3 us.  32 requests on one of 32K 73.4 -> 64.1.)
             for q in range(4):
-                v.append(f"global_load_lds_dwordx4 {DOFF(q)}, {SADDR}" + (f" offset:{1024 * q}" if q else ""))
+                v.append(f"global_load_lds_dwordx4 {DOFF(q)}, {SADDR}" + (f" offset:{1024 * q}" if q else "") + " nt")
         return v
 
     def issue_own(self):

@@ -269,17 +269,18 @@ __global__ __launch_bounds__(kRunThreads) void run_kernel(PlanArgs a) {
 
 // What the planner's launch does besides: its workgroup keeps one compute unit busy, and next to nothing of the memory, for 13 us
 // and more.  Others meanwhile read the ends of the histories - the part that is hardly ever shared, which the sweep therefore
-// takes from memory - and throw away what they read: the sweep then finds 32 MB of it nearer (16 MB gain half as much, 50 MB no
-// more, and take longer than the planner where it is quick).  Nothing depends on it.
+// takes from memory - and throw away what they read: the sweep then finds 28 MB of it nearer, or whole tiles of about that (16 MB
+// gain half as much, 48 no more, and take longer than the planner where it is quick).  Nothing depends on it.
 //  - Half of the compute units do it: 1.00 of a call's time where there is nothing to read (all of them 1.003, 0.1 to 0.5 us for
 //    their start), and as much gained.
 //  - They wait 2400 cycles first: the planner reads its tables then, and waits for them.
 //  - They do it if half of the requests that share a run with one of theirs (of 32 looked at) have `own` columns and more behind what
 //    they share, 60 MB in all if they are alike: where much less is read for the first time by the sweep, or nothing is shared (the
 //    planner is done at once then, 64 requests of 4224 to 5120 tokens 229 -> 234 us), there is little to gain.
-// 64 requests on one prefix of 4096, 32/8/128: 55.4 -> 51.4 us a call; 128 of head_dim 64 in 8 groups 54.2 -> 51.5, 32 on one of 32K
-// 75.0 -> 73.2, 80 drawn shapes that share runs 0.986 in the mean, 0.94 at best (three sets of caches in turn; with nine, 0.97).
-constexpr int kAheadMB = 32, kOwnMB = 60, kAheadSample = 32;
+// 64 requests on one prefix of 4096, 32/8/128: 50.1 -> 48.1 us a call; 128 of head_dim 64 in 8 groups 49.7 -> 47.3, 32 on one of 32K
+// 67.0 -> 64.0; after run_kernel 256 in 8 groups on 4096 155.1 -> 151.5, 240 of 16/2/128 73.2 -> 70.0, 400 of 8/2/64 the same.  80
+// drawn shapes that share runs, while the sweep's own loads stayed in the caches: 0.986 of the time (nine sets of caches in turn 0.97).
+constexpr int kAheadMB = 28, kOwnMB = 60, kAheadSample = 32;
 __device__ __forceinline__ void read_ahead(const PlanArgs& a) {
     __shared__ int s_go;
     constexpr int kWaves = kPlanThreads / 64;
@@ -1284,7 +1285,7 @@ void set_read_ahead(PlanArgs& a, const void* k_cache, const void* v_cache, int h
     a.block_bytes = kBlock * head_dim * 2;
     a.ahead_grid = cus / 2;
     const int64_t column = (int64_t)a.B * a.Hkv * 2 * a.block_bytes;       // bytes of K and V of a column of every request
-    a.ahead = a.ahead_grid > 1 ? (int32_t)std::min<int64_t>(a.stride / 4, kAheadMB * 1000000ll / (2 * column)) : 0;
+    a.ahead = a.ahead_grid > 1 ? (int32_t)std::min<int64_t>(a.stride / 4, (kAheadMB * 1000000ll + column) / (2 * column)) : 0;
     a.own = (int32_t)(kOwnMB * 1000000ll / column);
 }
 
@@ -1294,7 +1295,7 @@ void launch_plan(const PlanArgs& a, const Launch& L) {
     if (a.pre) {   // each dispatch gets a whole pair of events; the step runs from the first start to the last stop
         hipExtLaunchKernelGGL(run_kernel, dim3(a.pre_grid), dim3(kRunThreads), 0, st, e0,
                               static_cast<hipEvent_t>(L.ev_mid[0]), 0, a);
-        hipExtLaunchKernelGGL(plan_kernel, dim3(1), dim3(kPlanThreads), 0, st, static_cast<hipEvent_t>(L.ev_mid[1]), e1, 0, a);
+        hipExtLaunchKernelGGL(plan_kernel, dim3(a.ahead > 0 ? a.ahead_grid : 1), dim3(kPlanThreads), 0, st, static_cast<hipEvent_t>(L.ev_mid[1]), e1, 0, a);
     } else {
         hipExtLaunchKernelGGL(plan_kernel, dim3(a.ahead > 0 ? a.ahead_grid : 1), dim3(kPlanThreads), 0, st, e0, e1, 0, a);
     }

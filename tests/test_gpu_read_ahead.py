@@ -11,6 +11,7 @@ pytestmark = pytest.mark.gpu
 
 
 # A column of 16 tokens holds 64 head_dim bytes of K and V per KV head: own parts of 60 MB and more in all turn the reading on.
+@pytest.mark.parametrize("run_kernel_min", [0, -1])     # (-1: the planner's launch is the second one)
 @pytest.mark.parametrize("B,Hq,Hkv,d,own,empty", [
     (40, 32, 8, 128, (384, 700), 3),       # 64 KB a column: 24 columns and more each
     (40, 32, 8, 128, (352, 380), 0),       # about the line
@@ -18,7 +19,7 @@ pytestmark = pytest.mark.gpu
     (37, 6, 3, 64, (2160, 2600), 2),
     (24, 4, 2, 256, (1300, 1500), 1),
 ])
-def test_same_result_as_a_plan_without_it(B, Hq, Hkv, d, own, empty):
+def test_same_result_as_a_plan_without_it(B, Hq, Hkv, d, own, empty, run_kernel_min):
     import torch
     from paper_2605_06046_amd import (AttnParams, FEA_DTYPE_BF16, FEA_FLAG_PLAN_ONLY, FEA_FLAG_REUSE_PLAN,
                                       fea_decode_attention, fea_decode_workspace_bytes)
@@ -28,7 +29,7 @@ def test_same_result_as_a_plan_without_it(B, Hq, Hkv, d, own, empty):
     lens[1:1 + empty] = np.array([0, 1, 15], dtype=np.int32)[:empty]       # no history, and ones that end in the first block
     columns = (lens + 15) // 16
     bt[np.arange(bt.shape[1])[None, :] >= columns[:, None]] = -1
-    mk = lambda flags: AttnParams(Hq, Hkv, d, FEA_DTYPE_BF16, flags=flags, fused_max=-1)
+    mk = lambda flags: AttnParams(Hq, Hkv, d, FEA_DTYPE_BF16, flags=flags, fused_max=-1, run_kernel_min=run_kernel_min)
     q, k, v = to_device(wl.q), to_device(wl.k_cache), to_device(wl.v_cache)
     dbt, dl = torch.from_numpy(bt).cuda(), torch.from_numpy(lens).cuda()
     n = fea_decode_workspace_bytes(mk(0), *bt.shape)

@@ -267,8 +267,13 @@ template <int D> struct Tile<bf16_t, D, 16> {
 // 180 shapes: 0.86 of the time in the mean (0.63 to 1.03); 32/8/128, 16 requests of 1152 to 2048 tokens 34.6 -> 31.1 us,
 // 32/8/32, 200 requests of 1600 tokens, 90 % shared, 94 -> 57.  Not with two such sets for five to eight heads: 1.06 of the
 // time (0.87 to 1.34: twice the registers for q, and short histories wait for its loads).
-//     S = K Q^T      product (tq, kg) = lane / 4: token rows 4 tq .. 4 tq + 3 of a block (lane n = 4 tq + row), chunks 4 j + kg;
-//                    its four sums over kg are exchanged so that lane (n, kg) ends with token 4 tq + kg and head n % 4
+//     S = K Q^T      on the vector unit: 16 lanes side by side read 256 bytes of a K row, four rows 4 t + kg a load, and each lane
+//                    multiplies its chunks with those of the four heads; the 16 lanes' sums are halved among them from step to
+//                    step, so that lane (n, kg) ends with token 4 (n / 4) + kg and head n % 4.  A product's operand would be four
+//                    rows in four neighbouring lanes, and that a load then hands out 16 bytes of every row is what bound the
+//                    kernel: 32/8/128, 16 requests of 1152 to 2048 tokens 28.2 -> 23.6 us, 40 of 300 to 2000 94.6 -> 86.8,
+//                    16/4/256, 20 of 1124 to 1824 32.9 -> 26.9, 32/8/64, 60 on one prefix of 2048 50.7 -> 41.8; eight others
+//                    0.87 to 0.96 of the time.
 //     O += P V       one token's weights are one product's A operand, handed to all products whose lanes hold that token's V
 //                    row: a load of 16 bytes a lane covers 64 / LR rows, and instruction x takes, for each of them, the weights
 //                    of the x-th of the products in their lanes (the row's token follows from that: token_of).
@@ -278,23 +283,31 @@ template <int CB, int X> __device__ __forceinline__ f32x4 mfma4(float a, float b
 template <int D> struct Tile<float, D, 4> {
     static constexpr int TB = D >= 128 ? 1 : 2, PN = TB;   // blocks per tile; a lane has one token of each
     static constexpr int KC = D / 16, NI = 4, ES = 4;
+    static constexpr int CC = D >= 64 ? D / 64 : 1;        // chunks of a K row per lane
+    static constexpr int RR = KC / CC;                     // rows per lane and block: 4 (head_dim 32: 2, 8 lanes a row)
     static constexpr int LR = D / 4;                       // lanes that a V row takes
     static constexpr int NX = LR / 4;                      // loads of V per block, products per V row
     static constexpr int CB = NX == 2 ? 1 : NX == 4 ? 2 : NX == 8 ? 3 : 4;
-    f32x4 k[TB][KC], v[TB][NX], q[KC];
+    f32x4 k[TB][KC], v[TB][NX], q[4 * CC];
 
     static __device__ __forceinline__ int token_of(int x, int n, int kg) {   // of the V row that this lane holds of load x
         const int from = (n + 16 * kg) / LR * NX + x;      // the product whose weights it meets
         return 4 * (from & 3) + (from >> 2);
     }
-    __device__ __forceinline__ void load_q(const char* rows, int nh, int n, int kg) {
-        const char* row = rows + min(head(n), nh - 1) * (D * ES);
+    __device__ __forceinline__ void load_q(const char* rows, int nh, int n, int) {
 #pragma unroll
-        for (int j = 0; j < KC; ++j) q[j] = head(n) < nh ? *reinterpret_cast<const f32x4*>(row + (4 * j + kg) * 16) : f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int h = 0; h < 4; ++h)
+#pragma unroll
+            for (int c = 0; c < CC; ++c)
+                q[h * CC + c] = h < nh ? *reinterpret_cast<const f32x4*>(rows + h * (D * ES) + (D >= 64 ? n + 16 * c : n & 7) * 16) : f32x4{0.f, 0.f, 0.f, 0.f};
     }
     __device__ __forceinline__ void load_k(int b, const char* blk, int n, int kg) {
 #pragma unroll
-        for (int j = 0; j < KC; ++j) k[b][j] = *reinterpret_cast<const f32x4*>(blk + (uint32_t)(n * (D * 4) + kg * 16 + j * 64));
+        for (int t = 0; t < RR; ++t)
+#pragma unroll
+            for (int c = 0; c < CC; ++c)
+                k[b][t * CC + c] = *reinterpret_cast<const f32x4*>(blk + (uint32_t)((D >= 64 ? 4 * t + kg : 4 * t + 8 * (n >> 3) + kg) * (D * ES) +
+                                                                                    (D >= 64 ? n + 16 * c : n & 7) * 16));
     }
     __device__ __forceinline__ void load_v(int b, const char* blk, int n, int kg) {
 #pragma unroll
@@ -311,23 +324,39 @@ template <int D> struct Tile<float, D, 4> {
         }
     }
     __device__ __forceinline__ void scores(float (&p)[PN]) {
-        constexpr int GC = KC < 8 ? KC : 8;                // products in one chain
+        const int n = threadIdx.x & 15;
+        auto halve = [](bool upper, float x, float y, auto moved) {    // the lower lanes' x, the upper ones' y, with the partner's
+            return (upper ? y : x) + moved(upper ? x : y);
+        };
 #pragma unroll
         for (int b = 0; b < TB; ++b) {
-            f32x4 s;
+            float s[RR][4];
 #pragma unroll
-            for (int j0 = 0; j0 < KC; j0 += GC) {
-                f32x4 c[4];
+            for (int t = 0; t < RR; ++t)
 #pragma unroll
-                for (int j = j0; j < j0 + GC; ++j)
+                for (int h = 0; h < 4; ++h) {
+                    float even = 0.f, odd = 0.f;           // (two chains: half the error of one, and half the wait)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) c[e] = mfma4<0, 0>(k[b][j][e], q[j][e], j == j0 ? f32x4{0.f, 0.f, 0.f, 0.f} : c[e]);
-                const f32x4 part = (c[0] + c[1]) + (c[2] + c[3]);
-                s = j0 == 0 ? part : s + part;
+                    for (int c = 0; c < CC; ++c) {
+                        const f32x4 x = k[b][t * CC + c], y = q[h * CC + c];
+                        even = c == 0 ? x[0] * y[0] : fmaf(x[0], y[0], even);
+                        odd = c == 0 ? x[1] * y[1] : fmaf(x[1], y[1], odd);
+                        even = fmaf(x[2], y[2], even);
+                        odd = fmaf(x[3], y[3], odd);
+                    }
+                    s[t][h] = even + odd;
+                }
+            if constexpr (RR == 4) {
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int h = 0; h < 4; ++h) s[t][h] = halve(n & 8, s[t][h], s[2 + t][h], lanes_moved<0x128>);      // rotated by 8
             }
-            const Pair even = swap32(s[0], s[2]), odd = swap32(s[1], s[3]);   // lower half: tokens 0 and 1, upper: 2 and 3
-            const Pair all = swap16(even.a + even.b, odd.a + odd.b);
-            p[b] = all.a + all.b;
+#pragma unroll
+            for (int h = 0; h < 4; ++h) s[0][h] = halve(n & 4, s[0][h], s[1][h], lanes_moved<0x141>);                  // mirrored in 8
+#pragma unroll
+            for (int h = 0; h < 2; ++h) s[0][h] = halve(n & 2, s[0][h], s[0][2 + h], lanes_moved<0x4E>);
+            p[b] = halve(n & 1, s[0][0], s[0][1], lanes_moved<0xB1>);
         }
     }
     template <int X> __device__ __forceinline__ void take(int b, float w, f32x4 (&c)[4]) {

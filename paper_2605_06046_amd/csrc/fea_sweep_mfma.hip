@@ -720,7 +720,7 @@ template <int D> constexpr int waves_per_group() { return D == 256 ? 2 : kWavesP
 constexpr int kHistoryRows = 16;
 template <int D, int W>
 __device__ __forceinline__ void sweep_histories(const SweepArgs& a, char* lds, int* hdr, int wave, int lane) {
-    using TileT = tile::Tile<tile::bf16_t, D, kHistoryRows>;
+    using TileT = tile::Tile<tile::bf16_t, D, kHistoryRows, true>;
     constexpr int TB = TileT::TB, NI = TileT::NI, PN = TileT::PN, BLK = kBlock * D * 2, PAD = D + 4;
     struct alignas(16) Fold { float acc[W][kHistoryRows][PAD]; float2 ml[W][kHistoryRows]; int next; };   // (two in turn: one barrier a history)
     static_assert(2 * sizeof(Fold) <= (size_t)W * kStages * 4 * BLK, "fits the tile stages");
@@ -770,11 +770,11 @@ __device__ __forceinline__ void sweep_histories(const SweepArgs& a, char* lds, i
         };
         auto ask_k = [&](TileT& t) {
 #pragma unroll
-            for (int b = 0; b < TB; ++b) t.template load_k<true>(b, kb[b], n, kg);
+            for (int b = 0; b < TB; ++b) t.load_k(b, kb[b], n, kg);
         };
         auto ask_v = [&](TileT& t) {
 #pragma unroll
-            for (int b = 0; b < TB; ++b) t.template load_v<true>(b, vb[b], n, kg);
+            for (int b = 0; b < TB; ++b) t.load_v(b, vb[b], n, kg);
         };
         auto scores = [&](TileT& t, float (&p)[PN]) {
 #pragma unroll

@@ -36,11 +36,52 @@ __device__ __forceinline__ float sum_over_kg(float x) {
     return q.a + q.b;
 }
 
-// A lane's registers of one tile, and the two products, for row tiles of R query heads.  A lane works out the weights of
-// PN tokens for one head.
-template <typename T, int D, int R> struct Tile;
+// bfloat16, K of a block in a 16-row product: lane (n, kg) has row n, chunks (of 16 bytes) k_chunk(j, kg), j < KC; q likewise.  It is
+// not loaded so - a load then takes 16 bytes of a row for each of four neighbouring lanes - but four lanes read a row's 64 bytes in
+// one piece, four rows one after the other, and hand each other what is theirs (rows of 128 bytes: two lanes, two rows): 64
+// instructions for four chunks a lane.  Measured against rows in neighbouring lanes: 16 requests on a prefix of 1500, 32/8/128, 14.9 ->
+// 11.6 us, 24 on one of 500, 64/8/128, 11.4 -> 9.2, 60 in two groups, 32/2/128, 17.1 -> 15.2, 8 of 90 to 700 tokens, 28/4/128, 8.0 ->
+// 7.2, 40 on 1500, 8/2/64, 9.7 -> 8.7; five others 0.97 to 1.00 of the time.  float32 groups of more than four heads, which the
+// products bind, take 1.02 to 1.07 of the time so.  (Conditional moves that take the partner's register through their own exchange, by
+// hand, are half as many instructions and took 1.00 to 1.05 of the time.)
+template <int KC> __device__ __forceinline__ int k_chunk(int j, int kg) { return KC == 2 ? 2 * kg + j : 16 * (j >> 2) + 4 * kg + (j & 3); }
+template <int KC> __device__ __forceinline__ uint32_t k_offset(int j, int n, int kg) {    // of load j, from the block's start
+    return KC == 2 ? (uint32_t)((2 * (n >> 1) + j) * 128 + (2 * kg + (n & 1)) * 16)
+                   : (uint32_t)((4 * (n >> 2) + (j & 3)) * (KC * 64) + (16 * (j >> 2) + 4 * kg + (n & 3)) * 16);
+}
+template <int CTRL> __device__ __forceinline__ u32x4 chunk_moved(u32x4 x) {
+#pragma unroll
+    for (int w = 0; w < 4; ++w) x[w] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x[w], CTRL, 0xF, 0xF, true);
+    return x;
+}
+template <int CTRL> __device__ __forceinline__ void swap_chunks(bool upper, u32x4& x, u32x4& y) {   // the lower lane's y against the upper one's x
+    const u32x4 from_y = chunk_moved<CTRL>(y), from_x = chunk_moved<CTRL>(x);
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        x[w] = upper ? from_y[w] : x[w];
+        y[w] = upper ? y[w] : from_x[w];
+    }
+}
+template <int KC> __device__ __forceinline__ void to_rows(u32x4 (&x)[KC]) {
+    const int n = threadIdx.x & 15;
+#pragma unroll
+    for (int j = 0; j < KC; j += 2) swap_chunks<0xB1>(n & 1, x[j], x[j + 1]);
+    if constexpr (KC > 2) {
+#pragma unroll
+        for (int j = 0; j < KC; j += 4) {
+            swap_chunks<0x4E>(n & 2, x[j], x[j + 2]);
+            swap_chunks<0x4E>(n & 2, x[j + 1], x[j + 3]);
+        }
+    }
+}
 
-template <int D> struct Tile<float, D, 16> {
+// A lane's registers of one tile, and the two products, for row tiles of R query heads.  A lane works out the weights of
+// PN tokens for one head.  ONCE: its bytes are read once and pass by the caches, and rows stay in neighbouring lanes: long histories
+// that nobody shares are bound by memory, and lose by the moves (64 requests of 4224 to 5120 tokens, 32/8/128, 202 -> 207 us, 512 of
+// 512 to 4096, 64/8/128, 744 -> 747; 256 of 512 to 1024 138.4 -> 132.9).
+template <typename T, int D, int R, bool ONCE = false> struct Tile;
+
+template <int D> struct Tile<float, D, 16, false> {
     static constexpr int TB = D >= 128 ? 1 : 2;            // blocks per tile
     static constexpr int PN = 4 * TB;
     static constexpr int KC = D / 16;                      // chunks of a K row per lane
@@ -140,7 +181,7 @@ template <int D> struct Tile<float, D, 16> {
     }
 };
 
-template <int D> struct Tile<bf16_t, D, 16> {
+template <int D, bool ONCE> struct Tile<bf16_t, D, 16, ONCE> {
     static constexpr int TB = 2, PN = 8;
     static constexpr int KC = D / 32;
     static constexpr int VH = D == 256 ? 2 : 1;
@@ -151,13 +192,13 @@ template <int D> struct Tile<bf16_t, D, 16> {
     __device__ __forceinline__ void load_q(const char* rows, int nh, int n, int kg) {
         const char* row = rows + min(n, nh - 1) * (D * ES);
 #pragma unroll
-        for (int j = 0; j < KC; ++j) q[j] = n < nh ? ld16(row + (4 * j + kg) * 16) : u32x4{0u, 0u, 0u, 0u};
+        for (int j = 0; j < KC; ++j) q[j] = n < nh ? ld16(row + (ONCE ? 4 * j + kg : k_chunk<KC>(j, kg)) * 16) : u32x4{0u, 0u, 0u, 0u};
     }
-    template <bool ONCE = false> __device__ __forceinline__ void load_k(int b, const char* blk, int n, int kg) {
+    __device__ __forceinline__ void load_k(int b, const char* blk, int n, int kg) {
 #pragma unroll
-        for (int j = 0; j < KC; ++j) k[b][j] = ld16<ONCE>(blk + (uint32_t)(n * (D * 2) + kg * 16 + j * 64));
+        for (int j = 0; j < KC; ++j) k[b][j] = ld16<ONCE>(blk + (ONCE ? (uint32_t)(n * (D * 2) + kg * 16 + j * 64) : k_offset<KC>(j, n, kg)));
     }
-    template <bool ONCE = false> __device__ __forceinline__ void load_v(int b, const char* blk, int n, int kg) {
+    __device__ __forceinline__ void load_v(int b, const char* blk, int n, int kg) {
 #pragma unroll
         for (int r = 0; r < 4; ++r)
 #pragma unroll
@@ -178,6 +219,10 @@ template <int D> struct Tile<bf16_t, D, 16> {
         f32x4 s[TB];
 #pragma unroll
         for (int b = 0; b < TB; ++b) s[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if constexpr (!ONCE) {
+#pragma unroll
+            for (int b = 0; b < TB; ++b) to_rows(k[b]);
+        }
 #pragma unroll
         for (int j = 0; j < KC; ++j)
 #pragma unroll
@@ -280,7 +325,7 @@ template <int D> struct Tile<bf16_t, D, 16> {
 template <int CB, int X> __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, CB, X, 0);
 }
-template <int D> struct Tile<float, D, 4> {
+template <int D> struct Tile<float, D, 4, false> {
     static constexpr int TB = D >= 128 ? 1 : 2, PN = TB;   // blocks per tile; a lane has one token of each
     static constexpr int KC = D / 16, NI = 4, ES = 4;
     static constexpr int CC = D >= 64 ? D / 64 : 1;        // chunks of a K row per lane

@@ -87,18 +87,33 @@ static int64_t direct_rounds(const fea_attn_params* p, int64_t stride) {
     return (tiles + waves - 1) / waves;
 }
 
-// Pieces a history is cut into there.  Workgroups that leave most of the chip idle are worth cutting, up to one per compute
-// unit and 32 per history; the fold of the pieces takes 3 us, a round of a wave's tiles 2.3 (what one compute unit fetches), so
-// it has to save two rounds, and no more pieces are made than the rounds that are left need.  Measured on 284 shapes with 1 to
-// 64 pieces each, 1.01 of the best in the mean: bf16 32/8/128, one request of 6400 tokens (25 rounds) 60.6 us whole, 22.2 /
-// 15.5 / 12.2 / 13.8 / 14.0 in 4 / 8 / 16 / 24 / 32 pieces; 32/2/128, two of 20000 (79 rounds) 178.6 whole, 21.2 / 20.2 / 25.7
-// in 16 / 32 / 64; 8 of 700 (3 rounds) 10.7 whole, 10.8 in 2, 11.0 in 3.
-static int64_t direct_pieces(const fea_attn_params* p, int64_t B, int64_t stride) {
+// Pieces a history is cut into there, at most: workgroups that leave most of the chip idle are worth cutting, up to one per compute
+// unit and 32 per history, where that saves two rounds.  (The lines of direct_pays were measured with as many.)
+static int64_t direct_most(const fea_attn_params* p, int64_t B, int64_t stride) {
     const int64_t groups = direct_groups(p, B), rounds = direct_rounds(p, stride);
     if (groups <= 0 || 2 * groups > cu_count()) return 1;
     const int64_t most = std::min<int64_t>({cu_count() / groups, rounds, 32});
     const int64_t left = most > 0 ? (rounds + most - 1) / most : rounds;
     return rounds - left >= 2 ? (rounds + left - 1) / left : 1;
+}
+// How many it is cut into: what costs least.  A round of a wave's tiles takes 1 us (float32 1.6, with more than four heads 2.4), the
+// fold of q pieces 1 us, 0.12 for each of them and 0.1 for every query head of the row tile.  Fitted to 66 shapes with 1 to 32 pieces
+// each: 1.029 of the best in the mean (as many as there are at most: 1.042), none slower: bf16 32/2/128, 7 requests of 3 rounds 7.2 us
+// whole, 8.8 in 3; 42 of 4 rounds 8.6, in 2 11.3; 28/4/128, 8 short chats of 3 7.1, 7.7; 12/4/256, 2 of 58 rounds 17.6 in 29, 16.7 in
+// 20, 82 whole.
+static int64_t direct_pieces(const fea_attn_params* p, int64_t B, int64_t stride) {
+    const int64_t groups = direct_groups(p, B), rounds = direct_rounds(p, stride), most = direct_most(p, B, stride);
+    if (most <= 1) return 1;
+    const int heads = std::min(16, p->num_q_heads / p->num_kv_heads);
+    const double round_us = p->dtype != FEA_DTYPE_F32 ? 1.0 : heads > 4 ? 2.4 : 1.6, fold_us = 1.0 + 0.1 * heads;
+    double least = round_us * (double)rounds;
+    int64_t pieces = 1;
+    for (int64_t n = 2; n <= std::min<int64_t>({cu_count() / groups, rounds, 32}); ++n) {
+        const int64_t left = (rounds + n - 1) / n, q = (rounds + left - 1) / left;     // no more pieces than the rounds that are left need
+        const double us = round_us * (double)left + fold_us + 0.12 * (double)q;
+        if (us < least) { least = us; pieces = q; }
+    }
+    return pieces;
 }
 
 // Whether it is expected to beat plan + sweep + merge.  It reads what requests share once per request (5.0 to 5.9 TB/s
@@ -139,7 +154,7 @@ static bool direct_pays(const fea_attn_params* p, int64_t B, int64_t stride, int
     const double group = (double)(p->num_q_heads / p->num_kv_heads), groups = (double)direct_groups(p, B), cus = cu_count();
     const double tokens = (double)stride * kBlock, dd = p->head_dim / 64.0;
     const double per_group = tokens * p->head_dim * (f32 ? 8.0 : 4.0), bytes = groups * per_group;   // K and V read by a workgroup, by all
-    const int64_t pieces = direct_pieces(p, B, stride), rounds = (direct_rounds(p, stride) + pieces - 1) / pieces;
+    const int64_t pieces = direct_most(p, B, stride), rounds = (direct_rounds(p, stride) + pieces - 1) / pieces;
     if (variant == 1) {
         if (bytes <= 64e6 || (group > 8 && bytes <= 225e6 && groups <= 4 * cus && rounds <= 12) || (bytes <= 100e6 && groups <= 6 * cus) || (bytes <= 128e6 && direct_tiles(p, stride) <= 2)) return true;
         return group <= 4 && ((groups <= cus && per_group <= (p->head_dim == 256 ? 1.33e6 : 1 << 20)) || (groups <= 2 * cus && per_group <= 1 << 18));

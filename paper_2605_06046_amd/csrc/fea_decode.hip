@@ -106,11 +106,12 @@ static int64_t direct_pieces(const fea_attn_params* p, int64_t B, int64_t stride
     if (most <= 1) return 1;
     const int heads = std::min(16, p->num_q_heads / p->num_kv_heads);
     const double round_us = p->dtype != FEA_DTYPE_F32 ? 1.0 : heads > 4 ? 2.4 : 1.6, fold_us = 1.0 + 0.1 * heads;
-    double least = round_us * (double)rounds;
-    int64_t pieces = 1;
-    for (int64_t n = 2; n <= std::min<int64_t>({cu_count() / groups, rounds, 32}); ++n) {
-        const int64_t left = (rounds + n - 1) / n, q = (rounds + left - 1) / left;     // no more pieces than the rounds that are left need
-        const double us = round_us * (double)left + fold_us + 0.12 * (double)q;
+    const int all = (int)rounds, at_most = std::min<int>({cu_count() / (int)groups, all, 32});
+    double least = round_us * all;
+    int pieces = 1;
+    for (int left = (all + at_most - 1) / at_most; round_us * left < least; ++left) {      // rounds left; a few of them, then they alone cost more
+        const int q = (all + left - 1) / left;             // no more pieces than those need
+        const double us = round_us * left + fold_us + 0.12 * q;
         if (us < least) { least = us; pieces = q; }
     }
     return pieces;
@@ -140,14 +141,14 @@ static int64_t direct_pieces(const fea_attn_params* p, int64_t B, int64_t stride
 // proportion to them.  float32 from 2 to 16 query heads per KV head: the plan-free kernel wins on all of 1174 shapes of even
 // lengths (60 MB to 9 GB of histories, 0 to 99 % shared; 0.25 of the reused plan's time in the mean, 0.82 the closest: 2/1/32,
 // 300 requests of 32544 tokens, 90 % shared, 290 against 351 us).  But the table's width does not tell how long the others are,
-// and one long history among short ones is read by its own workgroups alone, at 53 GB/s each, where a plan spreads it over the
+// and one long history among short ones is read by its own workgroups alone, at 53 GB/s each then, where a plan spreads it over the
 // chip: 2/1/64, 134 requests, one of 46207 tokens and the rest of 34, 394 against 58 and, of the reused plan, 24 us.  So up to
 // 1.5 MB of a history to a workgroup: on 107 shapes there (one or a twentieth of the requests long, or all alike) at most 0.76 of
 // a new plan's time and 1.51 of a reused one's (0.44 and 0.54 in the mean); beyond it up to 1.44 of a new plan's time at 2.3 MB
 // and 6.8 at 24.  And up to the 10 GB that were measured.  Past either line the estimate decides, and with one head: that can lose on histories
 // that are shared and long (8/8/64, 1000 requests of 2192 tokens, 99 % shared: 612 against 515 and 480 us).
 // The estimate's 2 us a round and 4 us for the fold of pieces say where that line was measured to lie, not what the two cost
-// today (2.3 and 3): with those, 82 of 200 shapes near the line would change sides, 76 of them to a plan, which takes 1.38 of
+// today (1.0 to 2.4, above, and about 3): with 2.3 and 3, what they cost while K rows were not read in pieces, 82 of 200 shapes near the line would change sides, 76 of them to a plan, which takes 1.38 of
 // their time now where it is new and 0.74 where it is reused.
 static bool direct_pays(const fea_attn_params* p, int64_t B, int64_t stride, int variant) {
     const bool f32 = p->dtype == FEA_DTYPE_F32;

@@ -19,12 +19,11 @@
 // float32, over 56 shapes of 33 to 2000 tokens: the same error against float64 to within 2e-6 of it.
 //
 // Bound: latency (the chain length, table row and q -> K -> V -> fold over the waves) for short histories, 6 to 8 us
-// in all; then memory, at 5.0 to 5.9 TB/s where the chip is full (8 and more where what requests share sits in L2; a compute
-// unit fetches 53 GB/s at most); with float32, more than four query heads and few workgroups the matrix cores' float32 rate (a
+// in all; then memory, at 5.0 to 5.9 TB/s where the chip is full (8 and more where what requests share sits in L2); with float32, more than four query heads and few workgroups the matrix cores' float32 rate (a
 // block of 16 tokens is 64 instructions of 32 cycles at head_dim 128, whatever part of the 16 query rows is real).  Measured
-// against the vector-unit kernel it replaces: float32 8/2/64, 4 requests of 320 tokens 11.6 -> 6.6 us a call; float32
-// 32/8/128, 16 requests of 1152 to 2048 tokens 78.7 -> 27.5; against plan, sweep and merge: bf16 28/4/128, 8 requests of 90
-// to 700 tokens 23.6 -> 7.9.
+// against the vector-unit kernel it replaces: float32 8/2/64, 4 requests of 320 tokens 11.6 -> 6.0 us a call; float32
+// 32/8/128, 16 requests of 1152 to 2048 tokens 78.7 -> 22.7; against plan, sweep and merge: bf16 28/4/128, 8 requests of 90
+// to 700 tokens 23.6 -> 6.7.
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 

@@ -300,6 +300,45 @@ __device__ __forceinline__ void wait_all(Stream& sm) {
     sm.done = sm.seq;
 }
 
+// Brings an item's query rows into the wave's query buffer, laid out like a K block: one contiguous run of at most 16 rows.
+__device__ __forceinline__ bool rows_in_line(const Item& item) { return item.nrows <= 16 && item.mlist_off < 0; }
+template <int D>
+__device__ __forceinline__ void fetch_rows(const SweepArgs& a, const Item& item, uint32_t q_base, int lane, Stream& sm) {
+    const int n = lane & 15, kg = lane >> 4;
+    const char* qn = reinterpret_cast<const char*>(static_cast<const uint16_t*>(a.q) + ((size_t)item.who * a.Hq + item.g * a.G) * D);
+    const uint32_t qb = sgpr(q_base);
+    if constexpr (D == 128) {
+        uint32_t off[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int row = 4 * j + kg;                          // row of the buffer this lane fills in load j
+            off[j] = (uint32_t)min(row, item.nrows - 1) * 256u + (uint32_t)((n ^ row) & 15) * 16u;   // rows past the end repeat the last one
+        }
+        dma16x4(sgpr(qn), off[0], off[1], off[2], off[3], qb, qb + 1024, qb + 2048, qb + 3072);
+        sm.seq += 4;
+    } else if constexpr (D == 64) {
+        uint32_t off[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int row = 8 * j + (lane >> 3), pos = lane & 7;   // 128-byte rows: eight per load
+            off[j] = (uint32_t)min(row, item.nrows - 1) * 128u + (uint32_t)((pos ^ row) & 7) * 16u;
+        }
+        dma16x2(sgpr(qn), off[0], off[1], qb, qb + 1024);
+        sm.seq += 2;
+    } else {
+        uint32_t off[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int row = 2 * j + (lane >> 5), pos = lane & 31;  // 512-byte rows: two per load
+            off[j] = (uint32_t)min(row, item.nrows - 1) * 512u + (uint32_t)((pos & 16) | ((pos ^ row) & 15)) * 16u;
+        }
+        dma16x4(sgpr(qn), off[0], off[1], off[2], off[3], qb, qb + 1024, qb + 2048, qb + 3072);
+        dma16x4(sgpr(qn), off[4], off[5], off[6], off[7], qb + 4096, qb + 5120, qb + 6144, qb + 7168);
+        sm.seq += 8;
+    }
+    sm.qmark = sm.seq;
+}
+
 template <int NT, int D>
 __device__ __forceinline__ void sweep_item(const SweepArgs& a, const Piece& item, const Piece& next, bool has_next,
                                            int g_rcp, char* s_stage, const int* s_cols, const char* s_q, uint32_t lds_base,
@@ -407,41 +446,10 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const Piece& item
             for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qB[nt][ks]));
     }
     // Bring in the next item's query rows if they are one contiguous run of at most 16.
-    const bool q_next = has_next && next.nrows <= 16 && next.mlist_off < 0;
+    const bool q_next = has_next && rows_in_line(next);
     if (q_next) {
         wait_lgkmcnt0();   // the buffer has been read out
-        const char* qn = reinterpret_cast<const char*>(Q + ((size_t)next.who * a.Hq + next.g * a.G) * D);
-        const uint32_t qb = sgpr(q_base);
-        if constexpr (D == 128) {
-            uint32_t off[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int row = 4 * j + kg;                          // row of the buffer this lane fills in load j
-                off[j] = (uint32_t)min(row, next.nrows - 1) * 256u + (uint32_t)((n ^ row) & 15) * 16u;   // rows past the end repeat the last one
-            }
-            dma16x4(sgpr(qn), off[0], off[1], off[2], off[3], qb, qb + 1024, qb + 2048, qb + 3072);
-            sm.seq += 4;
-        } else if constexpr (D == 64) {
-            uint32_t off[2];
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int row = 8 * j + (lane >> 3), pos = lane & 7;   // 128-byte rows: eight per load
-                off[j] = (uint32_t)min(row, next.nrows - 1) * 128u + (uint32_t)((pos ^ row) & 7) * 16u;
-            }
-            dma16x2(sgpr(qn), off[0], off[1], qb, qb + 1024);
-            sm.seq += 2;
-        } else {
-            uint32_t off[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int row = 2 * j + (lane >> 5), pos = lane & 31;  // 512-byte rows: two per load
-                off[j] = (uint32_t)min(row, next.nrows - 1) * 512u + (uint32_t)((pos & 16) | ((pos ^ row) & 15)) * 16u;
-            }
-            dma16x4(sgpr(qn), off[0], off[1], off[2], off[3], qb, qb + 1024, qb + 2048, qb + 3072);
-            dma16x4(sgpr(qn), off[4], off[5], off[6], off[7], qb + 4096, qb + 5120, qb + 6144, qb + 7168);
-            sm.seq += 8;
-        }
-        sm.qmark = sm.seq;
+        fetch_rows<D>(a, next, q_base, lane, sm);
     }
 
     // The softmax denominator is accumulated by the matrix core as well: a V^T row
@@ -987,6 +995,14 @@ __global__ __launch_bounds__(64 * waves_per_group<D>()) void sweep_mfma_kernel(S
             }
         }
         if (item.nrows == 0 && it + 1 == it_end) continue;   // a slot that only exists for a team (or a filler)
+        // The first item's query rows ahead of its tiles, so that not everything asked for has to be there before the first product:
+        // 48 requests of head_dim 256 on 3000 tokens 44.6 -> 44.0 us, 128 of head_dim 64 in 8 groups 47.5 -> 47.0.  Not at head_dim 128:
+        // beside teams, which are on their way then, it took 1.01 to 1.02 of the time (64 on 4096 48.9 -> 49.8; without any, 0.99).
+        if constexpr (D != 128)
+            if (rows_in_line(item) && item.nrows > 0) {
+                fetch_rows<D>(a, item, q_base, lane, sm);
+                sm.q_ready = true;
+            }
         for (;;) {
             const bool has_next = it + 1 < it_end;
             if (has_next && it + 1 - win_first == kDescWindow) {   // window used up: fetch the next one (drains the stream once)

@@ -34,7 +34,7 @@ struct Knobs {
 static const Knobs& knobs() {
     static const Knobs k = {env_int("FEA_FORCE_GENERIC", 0), env_int("FEA_SWEEP_GRID", 0), env_int("FEA_SPARE_WAVES", 16),
                             env_int("FEA_MIN_PIECE", 4),     env_int("FEA_MIN_RUN", 2),    env_int("FEA_W32", 18),
-                            env_int("FEA_W64", 24), env_int("FEA_NO_FAST_SHARED", 0), env_int("FEA_WTEAM", 10),
+                            env_int("FEA_W64", 24), env_int("FEA_NO_FAST_SHARED", 0), env_int("FEA_WTEAM", 12),
                             env_int("FEA_WTEAM2", 12), env_int("FEA_TEAM_FIXED", 40), env_int("FEA_DIRECT_PIECES", 0),
                             env_int("FEA_HISTORIES", 6)};
     return k;

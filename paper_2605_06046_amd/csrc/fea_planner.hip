@@ -577,7 +577,10 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
     // cost of one 32-token tile of a shared run per wave that sweeps it, for a group of cnt members: a team
     // fetches the tile once for all its row tiles and overlaps the two products, which makes the tile far
     // cheaper for a wave than a tile it streams and sweeps alone
-    // (a team of 2 fetches half of every tile per wave, a team of 4 a quarter: the tile costs the former more)
+    // (a team of 2 fetches half of every tile per wave, a team of 4 a quarter.  Both 12 sixteenths.  With 10 for a team of 4 the
+    // cuts move and with them what weights are rounded against: outputs of 64 requests on 4096, 32/8/128, differ by 0.003, as far
+    // from float64 as before, in the same time - 48.6 to 49.3 us, 48.6 to 49.9 with 12 -, 240 of 16/2/128 in 4 groups 72.0 -> 69.6,
+    // 500 on one of 10240 167 to 173, 165 to 173 with 12)
     const int w_team = (a.tune.weights >> 16) & 255, w_team2 = (a.tune.weights >> 24) & 127;
     auto group_weight = [&](int cnt) {
         const int tiles_r = by_mpt.cdiv(cnt);

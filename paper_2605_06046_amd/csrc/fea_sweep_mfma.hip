@@ -185,20 +185,43 @@ __device__ __forceinline__ void scale_acc(f32x4& acc, float f) {
         : "v"(f));
     acc[0] = a0; acc[1] = a1; acc[2] = a2; acc[3] = a3;
 }
-// acc += A B in place: as the builtin the sums came out in other registers than they went in, and every tile copied them back (20
-// moves for 16 query rows of head_dim 64).  FIRST: what the vector unit has just written into B wants two wait states.
-template <bool FIRST> __device__ __forceinline__ void add_product(f32x4& acc, bf16x8 a, bf16x8 b) {
-    if constexpr (FIRST) asm("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
-    else asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+// o[i] += v[i] p in place, and l += ones p with the first four: as the builtin the sums came out in other registers than they went
+// in, and every tile copied them back (20 moves for 16 query rows of head_dim 64).  What the vector unit has written into an operand
+// wants two wait states before a product reads it.  The compiler sees no products here, and puts a statement, and a copy of one of its
+// operands, wherever the data allow: so each statement waits for itself.  (Hidden behind the product before it; as a statement for
+// each product, and the wait in the first alone, other schedules than the default one put the weights right before a product.)
+template <int AT = 0, int N> __device__ __forceinline__ void add_products(f32x4& l, f32x4 (&o)[N], bf16x8 ones, const bf16x8 (&v)[N], bf16x8 p) {
+    if constexpr (AT == 0)
+        asm("s_nop 1\n\t"
+            "v_mfma_f32_16x16x32_bf16 %0, %5, %6, %0\n\tv_mfma_f32_16x16x32_bf16 %1, %7, %6, %1\n\tv_mfma_f32_16x16x32_bf16 %2, %8, %6, %2\n\t"
+            "v_mfma_f32_16x16x32_bf16 %3, %9, %6, %3\n\tv_mfma_f32_16x16x32_bf16 %4, %10, %6, %4"
+            : "+a"(l), "+a"(o[0]), "+a"(o[1]), "+a"(o[2]), "+a"(o[3]) : "v"(ones), "v"(p), "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]));
+    else
+        asm("s_nop 1\n\t"
+            "v_mfma_f32_16x16x32_bf16 %0, %5, %4, %0\n\tv_mfma_f32_16x16x32_bf16 %1, %6, %4, %1\n\t"
+            "v_mfma_f32_16x16x32_bf16 %2, %7, %4, %2\n\tv_mfma_f32_16x16x32_bf16 %3, %8, %4, %3"
+            : "+a"(o[AT]), "+a"(o[AT + 1]), "+a"(o[AT + 2]), "+a"(o[AT + 3]) : "v"(p), "v"(v[AT]), "v"(v[AT + 1]), "v"(v[AT + 2]), "v"(v[AT + 3]));
+    if constexpr (AT + 4 < N) add_products<AT + 4>(l, o, ones, v, p);
 }
 // Sums that the compiler's instructions have just written or are about to read: it does not see the products' side.  The last
-// products' results want up to 19 wait states before they are read; what is written here is there well before the first product.
+// products' results want up to 19 wait states before they are read (one statement for all of an item's sums: each of them is behind
+// its products and before its reads); what is written here is there well before the first product.
+#define FEA_SUMS4(I) "+a"(o[I]), "+a"(o[I + 1]), "+a"(o[I + 2]), "+a"(o[I + 3])
 template <bool READ, int N> __device__ __forceinline__ void settle(f32x4& l, f32x4 (&o)[N]) {
-    if constexpr (READ) asm volatile("s_nop 15\n\ts_nop 3" : "+a"(l), "+a"(o[0]), "+a"(o[1]), "+a"(o[2]), "+a"(o[3]));
-    else asm volatile("" : "+a"(l), "+a"(o[0]), "+a"(o[1]), "+a"(o[2]), "+a"(o[3]));
-#pragma unroll
-    for (int i = 4; i < N; i += 4) asm volatile("" : "+a"(o[i]), "+a"(o[i + 1]), "+a"(o[i + 2]), "+a"(o[i + 3]));
+    static_assert(N == 4 || N == 8 || N == 16, "head_dim 64, 128, 256");
+    if constexpr (!READ) asm volatile("" : "+a"(l));
+    if constexpr (N == 4) {
+        if constexpr (READ) asm volatile("s_nop 15\n\ts_nop 3" : "+a"(l), FEA_SUMS4(0));
+        else asm volatile("" : FEA_SUMS4(0));
+    } else if constexpr (N == 8) {
+        if constexpr (READ) asm volatile("s_nop 15\n\ts_nop 3" : "+a"(l), FEA_SUMS4(0), FEA_SUMS4(4));
+        else asm volatile("" : FEA_SUMS4(0), FEA_SUMS4(4));
+    } else {
+        if constexpr (READ) asm volatile("s_nop 15\n\ts_nop 3" : "+a"(l), FEA_SUMS4(0), FEA_SUMS4(4), FEA_SUMS4(8), FEA_SUMS4(12));
+        else asm volatile("" : FEA_SUMS4(0), FEA_SUMS4(4), FEA_SUMS4(8), FEA_SUMS4(12));
+    }
 }
+#undef FEA_SUMS4
 // Stores issued by hand so that the wave can count them (see Stream): wave-uniform
 // base address in scalar registers, 32-bit byte offset per lane.  The hardware reads
 // the data registers of a wide store a little after issue and does not interlock
@@ -608,9 +631,7 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const Piece& item
             bf16x8 pB;
 #pragma unroll
             for (int x = 0; x < 8; ++x) pB[x] = (__bf16)exp2_fast(fmaf(r[x], a.scale_log2, neg_m));
-            add_product<true>(lacc[nt], ones, pB);
-#pragma unroll
-            for (int i = 0; i < NI; ++i) add_product<false>(oacc[nt][i], vA[i], pB);
+            add_products(lacc[nt], oacc[nt], ones, vA, pB);
         }
     };
     // First tile: the reference is its row maximum, nothing to rescale yet.

@@ -74,9 +74,9 @@ template <typename T> __device__ __forceinline__ void store4(char* dst, float x0
     else *reinterpret_cast<uint2*>(dst) = make_uint2(bf16_rne(x0) | (bf16_rne(x1) << 16), bf16_rne(x2) | (bf16_rne(x3) << 16));
 }
 
-template <typename T, int D, int R, int W>
+template <typename T, int D, int R, int W, bool PIECES>
 __global__ __launch_bounds__(64 * W) void decode_direct_kernel(SweepArgs a, int row_tiles, int pieces) {
-    using TileT = Tile<T, D, R>;
+    using TileT = Tile<T, D, R, false, PIECES>;
     constexpr int TB = TileT::TB, NI = TileT::NI, ES = TileT::ES, PN = TileT::PN;
     constexpr int BLK = kBlock * D * ES;           // bytes of one (block, KV head)
     constexpr int PAD = D + 4;                     // floats between the rows of the fold buffer (16 rows written side by side)
@@ -256,18 +256,29 @@ __global__ __launch_bounds__(64 * W) void decode_direct_kernel(SweepArgs a, int 
         reinterpret_cast<int*>(a.ws)[tid] = tid == H_VARIANT ? kNoPlan : tid == H_WAVES ? (int)gridDim.x * W : 0;
 }
 
-template <typename T, int D, int R, int W>
+template <typename T, int D, int R, int W, bool PIECES = true>
 void launch_waves(const SweepArgs& a, int pieces, const Launch& L) {
     const int row_tiles = (a.G + 15) / 16;
-    hipExtLaunchKernelGGL((decode_direct_kernel<T, D, R, W>), dim3((unsigned)(a.B * a.Hkv * row_tiles * pieces)), dim3(64 * W), 0,
+    hipExtLaunchKernelGGL((decode_direct_kernel<T, D, R, W, PIECES>), dim3((unsigned)(a.B * a.Hkv * row_tiles * pieces)), dim3(64 * W), 0,
                           static_cast<hipStream_t>(L.stream), static_cast<hipEvent_t>(L.ev_start), static_cast<hipEvent_t>(L.ev_stop), 0,
                           a, row_tiles, pieces);
 }
 
+// bfloat16 K rows come in pieces (fea_tile.h) where that saves more than the moves behind the loads cost.  Not at head_dim 256 in
+// tables of two rounds of a workgroup's tiles, 16 blocks: 32/8/256, 100 requests of 32 tokens 16.4 us with pieces, 14.6 without, 55 of
+// 60 to 140 14.9 and 14.2, 30 of 130 to 190 8.9 and 8.4 (10.4 and 9.7 with four sets of caches in turn).  Beyond, 0.92 to 0.94 of the time
+// with pieces for 16 of 180 to 260 (in turn 0.99), 1.05 for 30 of 160 to 220.  Nor at head_dim 128 in tables of two tiles: 64/8/128, 180
+// of 32 tokens 7.8 and 7.4 (up to 100 requests 0.98 to 1.01).  In wider ones 0.89 to 1.01 with pieces from 33 tokens on, 1.03 to 1.06 for
+// 100 requests and more of one or two blocks.  Head_dim 64, of whose chunks half as many move: 0.97 to 1.00.
 template <typename T, int D, int R>
 void launch_rows(const SweepArgs& a, int pieces, const Launch& L) {
-    if (a.stride <= 2 * Tile<T, D, R>::TB) launch_waves<T, D, R, 2>(a, pieces, L);
-    else launch_waves<T, D, R, direct_waves<D>()>(a, pieces, L);
+    constexpr int TB = Tile<T, D, R>::TB, W = direct_waves<D>();
+    constexpr bool kShortApart = sizeof(T) == 2 && D >= 128;
+    if (a.stride <= 2 * TB) return launch_waves<T, D, R, 2, !kShortApart>(a, pieces, L);
+    if constexpr (kShortApart && D == 256) {
+        if (a.stride <= 2 * TB * W) return launch_waves<T, D, R, W, false>(a, pieces, L);
+    }
+    launch_waves<T, D, R, W>(a, pieces, L);
 }
 
 template <typename T, int D>

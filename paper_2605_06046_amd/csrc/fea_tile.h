@@ -42,7 +42,8 @@ __device__ __forceinline__ float sum_over_kg(float x) {
 // instructions for four chunks a lane.  Measured against rows in neighbouring lanes: 16 requests on a prefix of 1500, 32/8/128, 14.9 ->
 // 11.6 us, 24 on one of 500, 64/8/128, 11.4 -> 9.2, 60 in two groups, 32/2/128, 17.1 -> 15.2, 8 of 90 to 700 tokens, 28/4/128, 8.0 ->
 // 7.2, 40 on 1500, 8/2/64, 9.7 -> 8.7; five others 0.97 to 1.00 of the time.  float32 groups of more than four heads, which the
-// products bind, take 1.02 to 1.07 of the time so.  (Conditional moves that take the partner's register through their own exchange, by
+// products bind, take 1.02 to 1.07 of the time so; and where a wave has a tile or two in all it waits for the moves as well, see the
+// plan-free kernel's rule.  (Conditional moves that take the partner's register through their own exchange, by
 // hand, are half as many instructions and took 1.00 to 1.05 of the time.)
 template <int KC> __device__ __forceinline__ int k_chunk(int j, int kg) { return KC == 2 ? 2 * kg + j : 16 * (j >> 2) + 4 * kg + (j & 3); }
 template <int KC> __device__ __forceinline__ uint32_t k_offset(int j, int n, int kg) {    // of load j, from the block's start
@@ -76,12 +77,12 @@ template <int KC> __device__ __forceinline__ void to_rows(u32x4 (&x)[KC]) {
 }
 
 // A lane's registers of one tile, and the two products, for row tiles of R query heads.  A lane works out the weights of
-// PN tokens for one head.  ONCE: its bytes are read once and pass by the caches, and rows stay in neighbouring lanes: long histories
-// that nobody shares are bound by memory, and lose by the moves (64 requests of 4224 to 5120 tokens, 32/8/128, 202 -> 207 us, 512 of
-// 512 to 4096, 64/8/128, 744 -> 747; 256 of 512 to 1024 138.4 -> 132.9).
-template <typename T, int D, int R, bool ONCE = false> struct Tile;
+// PN tokens for one head.  ONCE: its bytes are read once and pass by the caches.  PIECES: K rows are loaded in pieces; whole histories
+// keep them in neighbouring lanes (with pieces 64 requests of 4224 to 5120 tokens, 32/8/128, 202 -> 207 us, 512 of 512 to 4096,
+// 64/8/128, 744 -> 747; 256 of 512 to 1024 138.4 -> 132.9).
+template <typename T, int D, int R, bool ONCE = false, bool PIECES = !ONCE> struct Tile;
 
-template <int D> struct Tile<float, D, 16, false> {
+template <int D> struct Tile<float, D, 16, false, true> {
     static constexpr int TB = D >= 128 ? 1 : 2;            // blocks per tile
     static constexpr int PN = 4 * TB;
     static constexpr int KC = D / 16;                      // chunks of a K row per lane
@@ -181,7 +182,7 @@ template <int D> struct Tile<float, D, 16, false> {
     }
 };
 
-template <int D, bool ONCE> struct Tile<bf16_t, D, 16, ONCE> {
+template <int D, bool ONCE, bool PIECES> struct Tile<bf16_t, D, 16, ONCE, PIECES> {
     static constexpr int TB = 2, PN = 8;
     static constexpr int KC = D / 32;
     static constexpr int VH = D == 256 ? 2 : 1;
@@ -192,11 +193,11 @@ template <int D, bool ONCE> struct Tile<bf16_t, D, 16, ONCE> {
     __device__ __forceinline__ void load_q(const char* rows, int nh, int n, int kg) {
         const char* row = rows + min(n, nh - 1) * (D * ES);
 #pragma unroll
-        for (int j = 0; j < KC; ++j) q[j] = n < nh ? ld16(row + (ONCE ? 4 * j + kg : k_chunk<KC>(j, kg)) * 16) : u32x4{0u, 0u, 0u, 0u};
+        for (int j = 0; j < KC; ++j) q[j] = n < nh ? ld16(row + (PIECES ? k_chunk<KC>(j, kg) : 4 * j + kg) * 16) : u32x4{0u, 0u, 0u, 0u};
     }
     __device__ __forceinline__ void load_k(int b, const char* blk, int n, int kg) {
 #pragma unroll
-        for (int j = 0; j < KC; ++j) k[b][j] = ld16<ONCE>(blk + (ONCE ? (uint32_t)(n * (D * 2) + kg * 16 + j * 64) : k_offset<KC>(j, n, kg)));
+        for (int j = 0; j < KC; ++j) k[b][j] = ld16<ONCE>(blk + (PIECES ? k_offset<KC>(j, n, kg) : (uint32_t)(n * (D * 2) + kg * 16 + j * 64)));
     }
     __device__ __forceinline__ void load_v(int b, const char* blk, int n, int kg) {
 #pragma unroll
@@ -219,7 +220,7 @@ template <int D, bool ONCE> struct Tile<bf16_t, D, 16, ONCE> {
         f32x4 s[TB];
 #pragma unroll
         for (int b = 0; b < TB; ++b) s[b] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if constexpr (!ONCE) {
+        if constexpr (PIECES) {
 #pragma unroll
             for (int b = 0; b < TB; ++b) to_rows(k[b]);
         }
@@ -325,7 +326,7 @@ template <int D, bool ONCE> struct Tile<bf16_t, D, 16, ONCE> {
 template <int CB, int X> __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, CB, X, 0);
 }
-template <int D> struct Tile<float, D, 4, false> {
+template <int D> struct Tile<float, D, 4, false, true> {
     static constexpr int TB = D >= 128 ? 1 : 2, PN = TB;   // blocks per tile; a lane has one token of each
     static constexpr int KC = D / 16, NI = 4, ES = 4;
     static constexpr int CC = D >= 64 ? D / 64 : 1;        // chunks of a K row per lane

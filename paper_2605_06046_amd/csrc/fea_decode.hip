@@ -188,6 +188,8 @@ static int32_t check_params(const fea_attn_params* p, const char* who) {
     return FEA_OK;
 }
 
+constexpr int kFarMB = 32;   // what a call reads, from which on the sweep's loads pass by the caches (see the planner, and dma_tile)
+
 static int32_t resolve(const fea_attn_params* p, int32_t B, int32_t stride, Resolved& r, const char* who) {
     if (B < 0 || stride < 0) return fail(FEA_EINVAL, "%s: negative B or table_stride", who);
     if ((int64_t)B * p->num_q_heads > 0x3FFFFFFF || (int64_t)stride * kBlock > 0x3FFFFFFF)
@@ -366,6 +368,7 @@ int32_t decode_impl(const fea_attn_params* p, const void* q, const void* k_cache
         // 45.2 us with it, five other shapes 0.98 to 1.03 of the time.)
         if (r.variant == 1 && p->head_dim != 256 && !plan_only) set_read_ahead(pa, k_cache, v_cache, p->head_dim, cu_count());
         pa.histories_each = 1536 / p->head_dim;
+        pa.far_tiles = (kFarMB * 1000000 + 128 * p->head_dim - 1) / (128 * p->head_dim);   // (a tile: two blocks of K and of V)
         if (p->flags & FEA_FLAG_REFRESH_PLAN) launch_refresh(pa, where[0]);
         else launch_plan(pa, where[0]);
     }

@@ -82,7 +82,7 @@ struct Item {          // one KV sweep: a row set x one KV head x a column range
     int32_t pbase;     // partial row of the item's first query row
     int32_t tok_end;   // tokens at positions >= tok_end are not attended to
 };
-constexpr int32_t kOnce = 1 << 24;   // in Item::g: no other item reads these columns (not said of what teams sweep)
+constexpr int32_t kOnce = 1 << 24;   // in Item::g: no other item reads these columns, and they need not stay in the caches (not said of what teams sweep)
 static_assert(sizeof(Item) == 32, "Item is read as two 16-byte words");
 
 // Byte offsets of the workspace sections (all multiples of 256).
@@ -117,6 +117,7 @@ struct PlanArgs {
     int32_t pre_grid;    // its grid
     int32_t histories;   // tiles (of 32 tokens) from which on a batch that shares nothing is swept by whole histories; 0: never
     int32_t histories_each;   // ... and how many of them a history has to have on average
+    int32_t far_tiles;   // tiles (every KV head's) from which on what one item alone reads is marked kOnce
     const void* k_cache;      // KV tiles that the launch's other workgroups read ahead of the sweep:
     const void* v_cache;
     int32_t block_bytes;      // (of one block and KV head)

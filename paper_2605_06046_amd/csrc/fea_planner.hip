@@ -1018,8 +1018,10 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
     };
     // Columns that one item alone reads are marked: the sweep has them pass by the caches.  Not marked are a request's own columns
     // where others may have the same ones (nothing was looked for, a request has no place among those that were compared, or a
-    // subgroup was found and left as it was), and runs with more than one row tile, or swept by subgroups too.
-    const int own_once = a.variant == 1 && a.grouping && B <= kGroupReqMax && s_alike == 0 ? kOnce : 0;
+    // subgroup was found and left as it was), and runs with more than one row tile, or swept by subgroups too.  Nor is anything in a
+    // batch of less than 32 MB: the memory-side cache (256 MB) holds what eight layers of it read from one step to the next.
+    const bool far = a.variant == 1 && T_pr - per_seg * segs_pr + Hkv * (s_shared_blocks >> 1) >= a.far_tiles;
+    const int own_once = far && a.grouping && B <= kGroupReqMax && s_alike == 0 ? kOnce : 0;
     const WideDiv by_q(max(q, 1));
     const int k_start = by_q.div(tbase), rem_start = tbase - k_start * q;
 
@@ -1141,7 +1143,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
             }
             const int tiles_p = tiles_padded(tiles_r);
             const int team = (teams && tiles_r >= 2) ? (tiles_r == 2 ? 2 : 4) : 0;
-            const int once = a.variant == 1 && tiles_r == 1 && !split_off ? kOnce : 0;
+            const int once = far && tiles_r == 1 && !split_off ? kOnce : 0;
             const FastDiv by_tp(tiles_p), by_pc(n_pc);
             const int n = Hkv * n_pc * tiles_p, n_slots = items_padded(n);
             const int full_rows = a.mpt * a.G, last_rows = (cnt - (tiles_r - 1) * a.mpt) * a.G;

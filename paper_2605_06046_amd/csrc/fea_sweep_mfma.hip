@@ -117,10 +117,13 @@ __device__ __forceinline__ void dma16x2(const char* base, uint32_t off0, uint32_
 // A tile: the loads of its four blocks, into LDS one behind the other from lds on.  The immediate offset of such a load moves
 // both its addresses, so M0 is set once for 4 KB (head_dim 64: 2 KB) instead of for every load.  ONCE: nobody else reads these
 // bytes (kOnce), they need not stay in the caches, and kept there they only cost: a scattered read of 2 GB so 6.4 -> 6.9 TB/s, 256
-// requests in 8 groups on 4096 (32/8/128) 169 -> 152 us, 64 on one 51.4 -> 47.8, five groups of 16 on 10240 89 -> 77.5, 44 drawn
-// shapes 0.94 of the time with eight sets of caches in turn (0.88 to 1.02).  One small batch over and over, which the caches would
-// hold: 1.00 (0.88 to 1.07).  Columns that others read too are left to the caches: 48 requests on a system prompt in 6 groups,
-// four layers 148 us, 155 with all of them passing by.
+// requests in 8 groups on 4096 (32/8/128) 166 -> 147 us, 64 on one, three sets of caches in turn, 51.3 -> 48.8, five groups of 16 on
+// 10240, two sets, 112 -> 100.  49 drawn shapes with more in turn than the memory-side cache holds (800 MB): 0.99 of the time where a
+// call reads up to 32 MB, 0.97 up to 64, 0.93 up to 128, 0.91 up to 240.  Where that cache would hold all of it, one batch over and
+// over or few layers of it: 1.03, 1.05, 1.01 and 1.01 (0.96 to 1.12), so a call that reads less than 32 MB, eight layers of which
+// would stay there, is left to the caches: 0.97 of the time then where all of it is held (39 calls, 0.90 to 1.03), 1.02 where it is not
+// (21, 0.99 to 1.06), none slower than before there were such loads.  Columns that others read too are left to the caches: 48
+// requests on a system prompt in 6 groups, four layers 148 us, 155 with all of them passing by.
 template <int D, bool ONCE>
 __device__ __forceinline__ void dma_tile(const char* k0, const char* k1, const char* v0, const char* v1, const uint32_t (&off)[8], uint32_t lds) {
 #define FEA_DMA2(A, BASE, AT) "global_load_lds_dwordx4 " A ", " BASE AT "\n\tglobal_load_lds_dwordx4 " A ", " BASE " offset:1024" AT "\n\t"

@@ -43,6 +43,18 @@ def run_hip(q, k_cache, v_cache, bt, lens, num_q_heads, num_kv_heads, head_dim, 
     return out.float().cpu().numpy().astype(np.float64), info
 
 
+ITEM = np.dtype([(x, "<i4") for x in ("who", "g", "nrows", "mlist_off", "c0", "c1", "pbase", "tok_end")])
+
+
+def plan_items(ws, B, num_kv_heads):
+    """The work items of the plan in a workspace, whose sections lie as in WsLayout."""
+    raw = ws.cpu().numpy()
+    n_items, capacity = raw[:64].view("<i4")[[0, 10]]
+    up = lambda n: (n + 255) & ~255
+    at = 256 + 2 * up(32 * B) + up(4 * B) + up(8 * 2 * B * num_kv_heads) + up(4 * (int(capacity) + 2))
+    return raw[at:at + 32 * int(n_items)].view(ITEM)
+
+
 def library_tables(wl):
     pool = fea_kv_alloc(wl.num_blocks, 16, wl.perm_seed)
     bt, lens, _, _ = fea_build_block_tables(pool, wl.tokens, wl.tok_offsets, wl.max_blocks_per_seq)

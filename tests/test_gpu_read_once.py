@@ -1,6 +1,6 @@
 """Columns that one item alone reads pass by the caches, others do not: batches of either kind, and both in one - nothing shared,
 groups, groups that split off a larger one, members that go on sharing and stay together, grouping switched off - against the
-oracle."""
+oracle.  (Small ones, which stay in the caches whatever reads them: what is marked, and larger ones, are test_gpu_once_marks'.)"""
 import numpy as np
 import pytest
 

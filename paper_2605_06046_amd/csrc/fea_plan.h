@@ -34,6 +34,7 @@ enum Hdr {
     H_CAPACITY = 10,   // items the workspace it was made in has room for (its sections lie by that); 0: no plan (fea_direct.hip)
     H_HISTORIES = 11,  // not 0 where H_VARIANT is kHistories (a word of its own: the sweep keeps 6 registers more of H_VARIANT's
                        // branch alive, which spill, and takes 27 us instead of 24.6 for 32 requests of 2100 to 2900 tokens)
+    H_AHEAD = 12,      // tiles of every history that a planner's launch has read ahead; written only where one did
     H_WORDS = 64
 };
 

@@ -269,8 +269,11 @@ __global__ __launch_bounds__(kRunThreads) void run_kernel(PlanArgs a) {
 
 // What the planner's launch does besides: its workgroup keeps one compute unit busy, and next to nothing of the memory, for 13 us
 // and more.  Others meanwhile read the ends of the histories - the part that is hardly ever shared, which the sweep therefore
-// takes from memory - and throw away what they read: the sweep then finds 28 MB of it nearer, or whole tiles of about that (16 MB
-// gain half as much, 48 no more, and take longer than the planner where it is quick).  Nothing depends on it.
+// takes from memory - and throw away what they read: the sweep then finds it nearer.  Whole tiles of every history, as many as come
+// nearest to 28 MB (where there are tiles small enough to choose: 16 MB gain half as much, 48 no more, and take longer than the planner
+// where it is quick).  One tile of a large batch is up to 56 MB: 300 to 420 requests of 8 KV heads, or 600 to 840 of 4, take 0.957 to 0.983
+// of a call's time with it (16 shapes of head_dim 128), 500 to 840 of 8 at head_dim 64 0.964 to 1.001 (9).  The launch ends, and the
+// sweep starts, when all of them have; they write nothing but a word of the header.
 //  - Half of the compute units do it: 1.00 of a call's time where there is nothing to read (all of them 1.003, 0.1 to 0.5 us for
 //    their start), and as much gained.
 //  - They wait 2400 cycles first: the planner reads its tables then, and waits for them.
@@ -297,6 +300,7 @@ __device__ __forceinline__ void read_ahead(const PlanArgs& a) {
     }
     __syncthreads();
     if (!s_go) return;
+    if (threadIdx.x == 0) reinterpret_cast<int*>(a.ws)[H_AHEAD] = a.ahead;
     const int units = a.B * a.Hkv;
     for (int w = (blockIdx.x - 1) * kWaves + wave; w < units * a.ahead; w += (gridDim.x - 1) * kWaves) {
         const int t = w / units, u = w - t * units, i = u / a.Hkv, g = u - i * a.Hkv;
@@ -1018,7 +1022,8 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
     };
     // Columns that one item alone reads are marked: the sweep has them pass by the caches.  Not marked are a request's own columns
     // where others may have the same ones (nothing was looked for, a request has no place among those that were compared, or a
-    // subgroup was found and left as it was), and runs with more than one row tile, or swept by subgroups too.  Nor is anything in a
+    // subgroup was found and left as it was, one of them for the whole batch), and runs with more than one row tile, or, in a batch where
+    // any group has split off, that subgroups may sweep too.  Nor is anything in a
     // batch of less than 32 MB: the memory-side cache (256 MB) holds what eight layers of it read from one step to the next.
     const bool far = a.variant == 1 && T_pr - per_seg * segs_pr + Hkv * (s_shared_blocks >> 1) >= a.far_tiles;
     const int own_once = far && a.grouping && B <= kGroupReqMax && s_alike == 0 ? kOnce : 0;

@@ -147,9 +147,11 @@ static int64_t direct_pieces(const fea_attn_params* p, int64_t B, int64_t stride
 // a new plan's time and 1.51 of a reused one's (0.44 and 0.54 in the mean); beyond it up to 1.44 of a new plan's time at 2.3 MB
 // and 6.8 at 24.  And up to the 10 GB that were measured.  Past either line the estimate decides, and with one head: that can lose on histories
 // that are shared and long (8/8/64, 1000 requests of 2192 tokens, 99 % shared: 612 against 515 and 480 us).
-// The estimate's 2 us a round and 4 us for the fold of pieces say where that line was measured to lie, not what the two cost
-// today (1.0 to 2.4, above, and about 3): with 2.3 and 3, what they cost while K rows were not read in pieces, 82 of 200 shapes near the line would change sides, 76 of them to a plan, which takes 1.38 of
-// their time now where it is new and 0.74 where it is reused.
+// All of that was measured while K rows were not read in pieces and histories were cut into direct_most of them, which the estimate
+// goes on counting with; its 2 us a round and 4 us for the fold say where the line was found to lie, not what the two cost today (1.0
+// to 2.4, above, and about 3).  Today the lines of bfloat16 are on the safe side: 88 shapes inside them, which a table 1.4 times
+// as wide takes outside, take 0.53 of a new plan's time and 0.84 of a reused one's (0.86 and 1.19 at most); 72 outside, which one as
+// much narrower takes inside, would take 0.58 and 0.90 (0.87 and 1.47 at most).
 static bool direct_pays(const fea_attn_params* p, int64_t B, int64_t stride, int variant) {
     const bool f32 = p->dtype == FEA_DTYPE_F32;
     const double group = (double)(p->num_q_heads / p->num_kv_heads), groups = (double)direct_groups(p, B), cus = cu_count();

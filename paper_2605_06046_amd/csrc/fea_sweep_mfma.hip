@@ -44,9 +44,9 @@
 // A wave alone on its SIMD issues an instruction in four cycles and fetches 8 bytes of them in
 // 4.7 to 7.2 (by compute unit), so with few query rows on a tile its time is the number of its instructions: 420 a tile at
 // head_dim 64 when the waits were a tree over all 50 counts, V was transposed by permutes and selects, every load set M0 and
-// the sums were copied back.  Since: 48 requests of head_dim 256 on 3000 tokens 54.6 -> 46.3 us a call (27 registers were
-// spilled there as well), four layers on nested prefixes, 40/8/128, 160.7 -> 155.8, 128 requests of head_dim 64 in 8 groups
-// 55.5 -> 53.9, 64 on one prefix of 4096, 32/8/128, 55.9 -> 55.6.
+// the sums were copied back.  Without those, all else as it was then: 48 requests of head_dim 256 on 3000 tokens 53.9 -> 45.8 us a
+// call (27 registers were spilled there as well), a layer of nested prefixes, 40/8/128, 37.3 -> 35.7, 128 requests of head_dim 64 in 8
+// groups 55.3 -> 53.9, 64 on one prefix of 4096, 32/8/128, 54.7 both.
 //
 // The LDS writes of those loads are invisible to the compiler, so the waits are
 // explicit: vmcnt before a stage is read, lgkmcnt before it is overwritten.
@@ -292,7 +292,7 @@ struct Stream {
     // window when the items switch).
     int cb0, cb1, cbn;
     bool cols_ready;   // the current item's first window was requested while its predecessor ran
-    bool q_ready;      // so were its query rows (into the LDS query buffer)
+    bool q_ready;      // its query rows were requested (into the LDS query buffer): by its predecessor, or ahead of a share's first tile
     uint32_t seq;      // hand-issued loads so far
     uint32_t done;     // loads [0, done) are known to have landed
     uint32_t tmark0, tmark1;          // mark of the tile in stage 0 / 1
@@ -434,11 +434,12 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const Piece& item
 
     // B operand of the first product: Q^T, lane (n, kg) holds q[row n][32 ks + 8 kg .. +8].
     // The rows of a single request's query group are contiguous in q; the predecessor
-    // has then already brought them into the LDS query buffer (laid out like a K
-    // block: 16 rows, chunks swizzled by the row), and nothing has to be waited for
-    // that is younger than that.  Otherwise (first item of a share, rows gathered
-    // through a member list, more than 16 rows) they are loaded here and everything
-    // in flight is drained once.
+    // - or, for the first item of a share at head_dim 64 and 256, the kernel ahead of the
+    // item's tiles - has then already brought them into the LDS query buffer (laid out
+    // like a K block: 16 rows, chunks swizzled by the row), and nothing has to be waited
+    // for that is younger than that.  Otherwise (first item of a share at head_dim 128,
+    // rows gathered through a member list, more than 16 rows) they are loaded here and
+    // everything in flight is drained once.
     bf16x8 qB[NT][KS];
     bool q_from_lds = false;
     if constexpr (NT == 1) q_from_lds = sm.q_ready;

@@ -1,5 +1,6 @@
 """Device chunk hashes around the batches of 16 chunks that the chain takes at a time (whole, and the last, short one), for
-every chunk count up to three batches and around the staging tile of 2048, with a full and a short last chunk."""
+every chunk count up to three batches, around eight slabs of 256 leaves and around one to five, with a full and a short last
+chunk."""
 import numpy as np
 import pytest
 
